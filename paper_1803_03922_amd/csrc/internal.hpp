@@ -284,10 +284,12 @@ __device__ __forceinline__ int64_t wave_append(bool want, unsigned long long *co
 __device__ __forceinline__ bool bit_test(const uint32_t *bm, uint32_t v) {
   return (bm[v >> 5] >> (v & 31)) & 1u;
 }
-// Test-and-set: true iff this call changed the bit from 0 to 1.
+// Test-and-set: true iff this call changed the bit from 0 to 1. The test before
+// the atomic is a plain cached read: a stale word can only lack a bit (bits
+// are set, never cleared, while a kernel claims), and then the atomic decides.
 __device__ __forceinline__ bool bit_claim(uint32_t *bm, uint32_t v) {
   const uint32_t b = 1u << (v & 31);
-  if (__hip_atomic_load(&bm[v >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & b) return false;
+  if (bm[v >> 5] & b) return false;
   return !(atomicOr(&bm[v >> 5], b) & b);
 }
 
