@@ -2,28 +2,37 @@
 //
 // Mode 1 is the paper's degree-separated direction-optimized BFS at p = 1
 // (Section IV): the normal frontier is a compacted queue, the delegate
-// frontier a bitmask (Section IV-A). Each level runs
-//   previsit  - normal queue: nn/nd workloads, normal frontier bitmap;
-//               delegate mask: frontier list, dd/dn workloads, bottom-up
-//               candidate list (Section IV, "previsit");
-//   decision  - per kernel dd, dn, nd: FV vs BV = |U|(q+s)/q with factor0 /
-//               factor1 (Section IV-B); nn is always top-down;
-//   visits    - top-down: normal queue over nn (+nd), delegate list over dd
-//               and/or dn with merge-path style load balance over the
-//               frontier's prefix sum; bottom-up: dn via the nd rows of the nd
-//               source list, dd and nd via the delegate rows of unvisited
-//               delegates, each stopping at the first frontier parent;
-//   close     - Fd = Cd & ~Vd, Vd = Cd, clear the normal frontier bitmap.
+// frontier a bitmask (Section IV-A). A level is up to four phases:
+//   previsit  - delegate mask: Fd = Cd & ~Vd, Vd = Cd, dd/dn workloads of the
+//               frontier; normal queue: nn/nd workloads, normal frontier
+//               bitmap, and the nn top-down visit (nn is always forward and
+//               its claims change none of the decision's inputs);
+//   list      - (levels with a forward dd or dn visit) the frontier delegates
+//               with the prefix sum of their forward row lengths;
+//   forward   - top-down nd from the normal queue, dd and dn from that list,
+//               balanced over edges;
+//   backward  - bottom-up dn over the nd source list, dd and nd over the
+//               unvisited delegates, each stopping at the first frontier parent.
+// The direction decision (Section IV-B: FV vs BV = |U|(q+s)/q with factor0 /
+// factor1, per kernel dd, dn, nd) falls between previsit and the rest. Every
+// block makes it for itself from the level's counters, so it costs neither a
+// launch nor a barrier.
 // Exactly-once discovery comes from atomic test-and-set on the claimed
 // bitmaps (normals: Vn; delegates: Cd = visited or found this level), so
 // queues hold no duplicates and depth/parent are written once per vertex.
-// The normal previsit and the nn top-down visit share one pass over the
-// queue: nn is always top-down, and its claims change none of the decision's
-// inputs (those come from the frontier and from running counts).
 //
 // Mode 0 is plain top-down BFS over the plain CSR (the paper's "BFS" beside
-// "DOBFS", Section VI-C), with the same load-balanced expansion.
+// "DOBFS", Section VI-C): a list phase (degrees of the queue's rows) and an
+// expansion balanced over edges.
+//
+// Two drivers run the same phases:
+//   one launch   - a grid small enough to be resident at once runs all levels,
+//                  its phases separated by a grid barrier (small graphs, where
+//                  dispatch would cost more than the work);
+//   level by level - a kernel per phase, the host one level ahead.
+#include <algorithm>
 #include <cmath>
+#include <condition_variable>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -34,76 +43,144 @@ namespace dsbfs {
 
 void msbfs_release(Workspace *ws);
 
-void level_graphs_release(Workspace *ws);
-
 Workspace::~Workspace() {
   msbfs_release(this);
-  level_graphs_release(this);
-  if (hctr && !borrowed) (void)hipHostFree(hctr);
   if (hstat && !borrowed) (void)hipHostFree(hstat);
   for (hipEvent_t e : events) (void)hipEventDestroy(e);
-  for (hipEvent_t e : lev_ev)
-    if (e) (void)hipEventDestroy(e);
 }
 
 namespace {
 
-constexpr int kBS = 256;
-constexpr int kNW = kBS / kWave;
+constexpr int kSegs = 256;  // segments of a forward list (one block each)
 
-// Search state of degree-separated DOBFS on the device. One small kernel per
-// level (k_decide) makes the direction decision and writes the level's plan
-// here; every other kernel of the level reads its flag and returns at once
-// when it has no work, so the levels run back to back without a host round
-// trip (the host only learns, a level or two later, that the search ended).
-struct DevCtl {
-  double f0[4], f1[4];     // direction-switch factors (dd, dn, nd, nn)
-  uint64_t forced_seed;
-  int32_t forced;
-  int32_t done;            // the frontier is empty: every later kernel returns
-  int32_t level;           // level in progress
-  int32_t level1;          // depth this level writes (level + 1)
-  int32_t dir[4];          // current direction per kernel (0 forward, 1 backward)
-  int32_t nn_do;           // nn under the direction decision (else always forward)
-  int32_t nn_td, nn_bu;    // plan of this level for nn (nn_do only)
-  int32_t cand_state;      // -1: the next bottom-up normal pass scans the whole nd source list
-  int32_t nc_pending;      // the previous pass compacted a candidate list of unknown length
-  int32_t mark_fn;         // this level marks the normal frontier bitmap
-  int32_t nd_td, dd_td, dn_td, dn_bu, dd_bu, nd_bu;  // plan of this level
-  int32_t bulk_fn, clear_fn, cin_sel, cout_sel;
-  int64_t nwords;
-  int64_t rem[4];          // unvisited: delegates with a dd edge, with a dn edge, nd-list
-                           // normals, normals with an nn edge
-  int64_t nc;              // candidates of the next bottom-up normal pass
-  int64_t qn, fdn;         // frontier sizes of this level
-  unsigned long long deg_sum;                         // sum of frontier degrees so far
-  unsigned long long units[DSBFS_NUM_KERNELS][6];     // work units per kernel so far
+// Per-level counters of a search (device). Three copies rotate: level L adds
+// into ctr[L % 3], reads the queue lengths the previous level left in
+// ctr[(L + 2) % 3] and clears ctr[(L + 1) % 3].
+//
+// Sums are kept in kCtrCopies parts, each word on a 128-byte line of its own:
+// device-scope atomics on one line are served one after the other (12.6 ns
+// each), and 2048 blocks adding four counts to one line at the end of a large
+// level cost it about 100 us. A block adds to part blockIdx % kCtrCopies.
+constexpr int kCtrCopies = 8;
+struct alignas(128) CtrLine {
+  unsigned long long v;
+  unsigned long long pad[15];
+};
+enum { kFvNn, kQNn, kFvNd, kQNd, kFdn, kFvDd, kQDd, kFvDn, kQDn, kPrevSums,
+       kClDn = kPrevSums,  // delegates with a dn edge claimed by this level
+       kNumSums };
+struct LevelCtr {
+  // Tails of the next normal queue (bits 0..31: the queue length of the next
+  // level) and of the next bottom-up normal candidate list (bits 32..63), in
+  // one word: the bottom-up normal pass appends to both and reserves both
+  // with one atomic. Neither count reaches 2^31, so no carry crosses.
+  CtrLine qn_nc;
+  CtrLine sum[kNumSums][kCtrCopies];
 };
 
-// What the host learns of each level, written by k_decide into pinned host
-// memory (a ring of 4 slots, slot = level & 3).
+// A level's counts, summed over the parts.
+struct LevelCounts {
+  unsigned long long v[kNumSums];
+};
+
+// State of a search between levels.
+struct LevelState {
+  int32_t level;
+  int32_t done;        // the frontier is empty: every later kernel returns
+  int32_t dir[4];      // current direction per kernel dd, dn, nd, nn (0 forward, 1 backward)
+  int32_t cand_state;  // -1: the next bottom-up normal pass scans the whole nd source list
+  int32_t nc_pending;  // the previous pass compacted a candidate list of unknown length
+  int32_t marked;      // the previous level marked its normal frontier bitmap
+  int32_t pad;
+  int64_t rem[4];      // unvisited: delegates with a dd edge, with a dn edge, nd-list
+                       // normals, normals with an nn edge
+  int64_t nc;          // candidates of the next bottom-up normal pass
+};
+
+// Totals over the levels so far that the decision keeps (statistics only).
+struct LevelTotals {
+  unsigned long long deg_sum;                    // sum of frontier degrees
+  unsigned long long kept;                       // bottom-up candidates kept
+  unsigned long long units0[DSBFS_NUM_KERNELS];  // queue / list entries per kernel
+  int64_t launches[DSBFS_NUM_KERNELS];           // visits that had work
+};
+
+// What a level does after its previsit.
+struct Plan {
+  int32_t nd_td, dd_td, dn_td, dn_bu, dd_bu, nd_bu, nn_td, nn_bu;
+  int32_t cin_sel, cout_sel;  // bottom-up candidate list read (-1: all) and written
+  int64_t nc, qn;
+};
+
+// What the host learns of each level (a ring of 4 slots, slot = level & 3):
+// written by the level's last kernel into pinned host memory, seq last.
 struct LevelStatus {
   int32_t done, level;
-  int32_t plan[10];  // nd_td, dd_td, dn_td, dn_bu (runs), dd_bu, nd_bu, bulk_fn, mark_fn,
-                     // nn_td (separate pass), nn_bu
   dsbfs_level_stats rec;
+  int32_t pad;
+  int32_t seq;       // level + 1 once the rest is written
 };
 constexpr int kStatusSlots = 4;
 
-// Whether this level marks the normal frontier bitmap Fn. Fn is read only by
-// a bottom-up nd visit (which needs an unvisited delegate with a dn edge left
-// after this level's frontier: rem[1] - q_dn > 0) and, with nn_do, by a
-// bottom-up nn visit. The delegate previsit runs first, so q_dn is known to
-// the normal previsit and to the decision alike.
-__device__ __forceinline__ int level_marks_fn(const DevCtl *c, int64_t q_dn) {
-  return c->mark_fn && (c->rem[1] - q_dn > 0 || (c->nn_do && c->rem[3] > 0));
-}
+// Grid barrier: arrivals per group of blocks, groups complete, and one release
+// word per group, each on its own 128-byte line.
+constexpr int kBarGroups = 8;
+struct GridBar {
+  CtrLine arrive[kBarGroups], top, release[kBarGroups];
+  CtrLine err;  // 1: a wait exceeded its bound; every block leaves
+};
 
-// Bytes of one of the two tile arrays of the delegate-frontier prefix sum.
-inline size_t dtiles_half(int64_t d) {
-  const size_t nb = size_t((d + kBS * 8 - 1) / (kBS * 8)) + 1;
-  return (nb * 8 + 255) / 256 * 256;
-}
+// Control block of a search (device memory).
+struct SearchCtl {
+  GridBar bar;
+  LevelState st[2];  // level L reads st[L & 1], its last kernel writes the other
+  LevelCtr ctr[3];
+  LevelTotals tot;
+  unsigned long long units[DSBFS_NUM_KERNELS][4];  // work units per kernel so far
+  int64_t seg_len[kSegs];   // edges of each segment of the forward list
+  int32_t seg_cnt[kSegs];   // its entries
+  int32_t levels;           // one launch: levels with a non-empty frontier
+  int32_t pad;
+};
+
+// Arguments of every kernel of a search.
+struct Search {
+  // graph (see Graph)
+  const uint64_t *noff, *doff;
+  const uint16_t *nlen;
+  const int32_t *ncol;
+  const uint32_t *nnoff;
+  const int32_t *nncol, *dcol, *vid_of, *ndsrc, *nds_col, *nnsrc;
+  const int64_t *nds_off;
+  const int2 *nds_first, *dd_first;
+  const uint32_t *ddm, *dnm;
+  const int64_t *poff;
+  const int32_t *pcol, *did;
+  int32_t n, d, nwords, dwords;
+  int64_t n_ndsrc, n_nnsrc;
+  // results
+  int32_t *depth, *parent;
+  // scratch (see Workspace)
+  uint32_t *Vn, *Fn0, *Fn1, *Vd, *Fd, *Cd;
+  int32_t *Q0, *Q1, *C0, *C1, *dlist;
+  int64_t *dscan;
+  SearchCtl *ctl;
+  LevelStatus *hs;
+  // options
+  double f0[4], f1[4];
+  uint64_t forced_seed;
+  int32_t forced, nn_do;
+  int32_t count;  // statistics are wanted: keep work units and every workload sum
+  int32_t source, mode;
+
+  __device__ __forceinline__ uint32_t *fn(int p) const { return p ? Fn1 : Fn0; }
+  __device__ __forceinline__ int32_t *q(int p) const { return p ? Q1 : Q0; }
+  __device__ __forceinline__ int32_t *cand(int p) const { return p ? C1 : C0; }
+  __device__ __forceinline__ void put(int32_t v, int32_t p, int32_t dep) const {
+    depth[v] = dep;
+    if (parent) parent[v] = p;
+  }
+};
 
 __host__ __device__ inline uint64_t mix64(uint64_t z) {
   z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ULL;
@@ -118,159 +195,102 @@ __host__ __device__ inline double bv_estimate(int64_t U, int64_t q, int64_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// init
+// block scratch and small helpers
 // ---------------------------------------------------------------------------
-__global__ void k_init(int32_t *depth, int32_t *parent, int32_t n, uint32_t *Vn, uint32_t *Fn,
-                       int32_t nwords, uint32_t *Vd, uint32_t *Fd, uint32_t *Cd, int32_t dwords) {
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  const int64_t t0 = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  for (int64_t v = t0; v < n; v += stride) {
-    depth[v] = -1;
-    if (parent) parent[v] = -1;
-  }
-  for (int64_t w = t0; w < nwords; w += stride) {
-    Vn[w] = 0;
-    Fn[w] = 0;
-  }
-  for (int64_t w = t0; w < dwords; w += stride) {
-    Vd[w] = 0;
-    Fd[w] = 0;
-    Cd[w] = 0;
-  }
-}
-
-// Seeds the source: a delegate enters the delegate frontier mask, a normal
-// vertex the normal queue. prev's queue tail becomes the level-0 queue
-// length (no bottom-up candidates yet).
-__global__ void k_seed(int32_t s, const int32_t *did, int32_t *depth, int32_t *parent,
-                       uint32_t *Vn, uint32_t *Vd, uint32_t *Fd, uint32_t *Cd, int32_t *Q,
-                       LevelCtr *prev, int mode) {
-  depth[s] = 0;
-  if (parent) parent[s] = s;
-  const int32_t k = mode == 1 ? did[s] : -1;
-  if (k >= 0) {
-    Vd[k >> 5] |= 1u << (k & 31);
-    Fd[k >> 5] |= 1u << (k & 31);
-    Cd[k >> 5] |= 1u << (k & 31);
-    prev->qn_nc = 0;
-  } else {
-    Vn[s >> 5] |= 1u << (s & 31);
-    Q[0] = s;
-    prev->qn_nc = 1;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// previsit
-// ---------------------------------------------------------------------------
-// All per-level kernels are grid-stride loops over a bounded grid (a few
-// workgroups per CU) and publish counters and queue entries once per block:
-// device-scope atomics on one address serialize chip-wide, so one per wave
-// over a multi-million-entry frontier would dominate the level.
-constexpr int kQCap = 1536;  // LDS append buffer entries per queue per block
-
-// Exclusive scan over the block of one int per thread; *total = block sum.
-__device__ __forceinline__ int block_excl_scan_i32(int v, int *sh, int *total) {
-  const int w = threadIdx.x / kWave, l = lane_id();
-  const int incl = wave_incl_scan(v);
-  if (l == kWave - 1) sh[w] = incl;
-  __syncthreads();
-  int before = 0, all = 0;
-  for (int i = 0; i < kNW; ++i) {
-    const int t = sh[i];
-    before += i < w ? t : 0;
-    all += t;
-  }
-  *total = all;
-  __syncthreads();
-  return before + incl - v;
-}
-
-// One thread per mask word: frontier delegates -> dlist, with their dd/dn
-// workloads. Positions come from a block scan plus one global atomic per block.
-__global__ void __launch_bounds__(kBS) k_prev_deleg(const uint32_t *Fd, int32_t dwords,
-                                                    const uint64_t *doff, int32_t *dlist,
-                                                    LevelCtr *cur, const DevCtl *c) {
-  if (c->done) return;
-  // The frontier list feeds only the forward dd/dn visit. Under the
-  // heuristic schedule, once dd and dn both go backward with no switch back
-  // (factor1 = 0) none can follow: the list is not written.
-  const bool want_list = !(c->forced == 0 && c->dir[0] == 1 && c->dir[1] == 1 &&
-                           c->f1[0] == 0.0 && c->f1[1] == 0.0);
-  __shared__ int shf[kNW];
-  __shared__ unsigned long long base;
-  __shared__ unsigned long long sh[4 * kNW];
-  unsigned long long fv_dd = 0, q_dd = 0, fv_dn = 0, q_dn = 0;
-  for (int64_t w0 = int64_t(blockIdx.x) * blockDim.x; w0 < dwords;
-       w0 += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t w = w0 + threadIdx.x;
-    uint32_t f = w < dwords ? Fd[w] : 0u;
-    int tf;
-    const int ef = block_excl_scan_i32(__popc(f), shf, &tf);
-    if (threadIdx.x == 0) base = tf ? atomicAdd(&cur->nd_list, (unsigned long long)tf) : 0ull;
-    __syncthreads();
-    unsigned long long pf = base + ef;
-    while (f) {
-      const int b = __ffs(f) - 1;
-      f &= f - 1;
-      const int32_t k = int32_t(w * 32 + b);
-      if (want_list) dlist[pf] = k;
-      ++pf;
-      const uint64_t x0 = doff[k], x1 = doff[k + 1];
-      const int64_t dd = row_first(x0), dn = row_start(x1) - row_start(x0) - dd;
-      fv_dd += dd;
-      q_dd += dd > 0;
-      fv_dn += dn;
-      q_dn += dn > 0;
-    }
-    __syncthreads();
-  }
-  block_add4(&cur->fv_dd, fv_dd, q_dd, fv_dn, q_dn, sh);
-}
-
-// Unclaimed delegates (not visited and not claimed earlier in this level)
-// with an edge in a subgraph scanned bottom-up this level (dd part if dd_bu,
-// dn part if nd_bu) -> dcand, ascending.
-__global__ void __launch_bounds__(kBS) k_dcand(const uint32_t *Cd, const uint32_t *ddm,
-                                               const uint32_t *dnm, int32_t dwords,
-                                               const DevCtl *ctl, int32_t *dcand, LevelCtr *cur) {
-  if (ctl->done || !(ctl->dd_bu || ctl->nd_bu)) return;
-  const int dd_bu = ctl->dd_bu, nd_bu = ctl->nd_bu;
-  __shared__ int shc[kNW];
-  __shared__ unsigned long long base;
-  for (int64_t w0 = int64_t(blockIdx.x) * blockDim.x; w0 < dwords;
-       w0 += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t w = w0 + threadIdx.x;
-    uint32_t c = 0;
-    if (w < dwords) c = ~Cd[w] & ((dd_bu ? ddm[w] : 0u) | (nd_bu ? dnm[w] : 0u));
-    int tc;
-    const int ec = block_excl_scan_i32(__popc(c), shc, &tc);
-    if (threadIdx.x == 0) base = tc ? atomicAdd(&cur->nd_cand, (unsigned long long)tc) : 0ull;
-    __syncthreads();
-    unsigned long long pc = base + ec;
-    while (c) {
-      const int b = __ffs(c) - 1;
-      c &= c - 1;
-      dcand[pc++] = int32_t(w * 32 + b);
-    }
-    __syncthreads();
-  }
-}
-
-// ---------------------------------------------------------------------------
-// visits
-// ---------------------------------------------------------------------------
-struct Out {
-  int32_t *depth;
-  int32_t *parent;
-  int32_t level1;  // depth written by this level (L + 1)
-  __device__ __forceinline__ void put(int32_t v, int32_t p) const {
-    depth[v] = level1;
-    if (parent) parent[v] = p;
-  }
+// LDS of one wave: the 64 rows it walks together.
+struct WaveRows {
+  int32_t excl[kWave];  // exclusive prefix of the row lengths
+  int32_t aux[kWave];   // parent vertex (forward), first hit (backward), mask word
+  int64_t beg[kWave];   // row starts
+  int64_t mid[kWave];   // where the row's second part starts
 };
 
-// Largest index lo in [0, 64) with ex[lo] <= e (ex non-decreasing, ex[0] = 0).
+template <int NW> struct Scratch {
+  // entries of each append buffer (four waves: eight blocks fit a compute unit's 160 KB)
+  static constexpr int kCap = NW <= 4 ? 1408 : 3072;
+  WaveRows w[NW];
+  int32_t buf[2 * kCap];  // queue and candidate buffers, or one buffer per wave
+  int qcount, ccount;
+  unsigned long long qbase, cbase;
+  unsigned long long red[16];
+  int64_t sh[NW];
+  int64_t seg[kSegs + 1];  // prefix of the forward list's segments
+  unsigned long long units[DSBFS_NUM_KERNELS * 4];
+  LevelCounts now;
+  LevelState st, ns;
+  Plan plan;
+  int64_t qn, nc_prev, q_dn;
+  int mark, ok;
+};
+
+// Wave totals through DPP scans; the value is the same in every lane.
+__device__ __forceinline__ uint32_t wave_total(uint32_t x) {
+  return uint32_t(lane_read(wave_incl_scan(int32_t(x)), kWave - 1));
+}
+__device__ __forceinline__ unsigned long long wave_total(unsigned long long x) {
+  // low and high parts separately: 64 values below 2^24 sum below 2^30
+  const uint32_t lo = wave_total(uint32_t(x & 0xffffffull));
+  const uint32_t hi = wave_total(uint32_t(x >> 24));
+  return (static_cast<unsigned long long>(hi) << 24) + lo;
+}
+
+__device__ __forceinline__ unsigned long long ctr_load(const unsigned long long *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Adds a thread's counts to word j.. of the block's sums (LDS), one LDS atomic a wave.
+template <class T> __device__ __forceinline__ void block_acc(unsigned long long *dst, T x) {
+  const T t = wave_total(x);
+  if (lane_id() == 0 && t) atomicAdd(dst, static_cast<unsigned long long>(t));
+}
+
+// Work units of a kernel (only kept when statistics are wanted): into the
+// block's sums, which go to memory once per launch.
+template <int NW>
+__device__ __forceinline__ void count_units(const Search &a, Scratch<NW> &S, int k, uint32_t x0,
+                                            uint32_t x1, uint32_t x2, uint32_t x3) {
+  if (!a.count) return;
+  block_acc(&S.units[k * 4 + 0], x0);
+  block_acc(&S.units[k * 4 + 1], x1);
+  block_acc(&S.units[k * 4 + 2], x2);
+  block_acc(&S.units[k * 4 + 3], x3);
+}
+
+template <int NW> __device__ __forceinline__ void units_open(const Search &a, Scratch<NW> &S) {
+  for (int i = threadIdx.x; i < DSBFS_NUM_KERNELS * 4; i += blockDim.x) S.units[i] = 0;
+  for (int i = threadIdx.x; i < 16; i += blockDim.x) S.red[i] = 0;
+  __syncthreads();
+}
+template <int NW> __device__ __forceinline__ void units_close(const Search &a, Scratch<NW> &S) {
+  __syncthreads();
+  if (!a.count) return;
+  for (int i = threadIdx.x; i < DSBFS_NUM_KERNELS * 4; i += blockDim.x)
+    if (S.units[i]) atomicAdd(&a.ctl->units[i / 4][i % 4], S.units[i]);
+}
+
+// Adds the block's sums red[k0 .. k1) to the level's counters and clears them
+// (block-uniform).
+template <int NW>
+__device__ __forceinline__ void red_flush(Scratch<NW> &S, LevelCtr &c, int k0, int k1) {
+  __syncthreads();
+  const int k = k0 + int(threadIdx.x);
+  if (k < k1) {
+    const unsigned long long t = S.red[k];
+    if (t) atomicAdd(&c.sum[k][blockIdx.x % kCtrCopies].v, t);
+    S.red[k] = 0;
+  }
+  __syncthreads();
+}
+
+// Clears a level's counters (by block 0).
+__device__ __forceinline__ void ctr_clear(LevelCtr &c) {
+  if (blockIdx.x != 0) return;
+  for (int i = threadIdx.x; i < kNumSums * kCtrCopies; i += blockDim.x)
+    c.sum[i / kCtrCopies][i % kCtrCopies].v = 0;
+  if (threadIdx.x == 0) c.qn_nc.v = 0;
+}
+
+// Largest index lo in [0, 64) with ex[lo] <= e (ex non-decreasing, ex[0] <= e).
 __device__ __forceinline__ int owner64(const int32_t *ex, int32_t e) {
   int lo = 0;
 #pragma unroll
@@ -281,211 +301,950 @@ __device__ __forceinline__ int owner64(const int32_t *ex, int32_t e) {
   return lo;
 }
 
-// Wave-balanced top-down expansion of one part of the rows of the normal
-// queue: each wave owns 64 queue entries per step; their part lengths are
-// prefix-summed across the wave and the wave walks the concatenated edge
-// range 64 edges at a time, so lanes stay busy whatever the mix of degrees
-// (all are <= TH). `part` 0 = nn (claims normals, enqueues them), 1 = nd
-// (claims delegates in Cd).
-template <int part>
-__device__ __forceinline__ void expand_normal_rows(int32_t u, int32_t len, int64_t beg,
-                                                   int32_t (&s_excl)[kWave],
-                                                   int32_t (&s_u)[kWave],
-                                                   int64_t (&s_beg)[kWave], const int32_t *ncol,
-                                                   const int32_t *vid_of, const Out &out,
-                                                   uint32_t *Vn, uint32_t *Cd, BlockAppend &qa,
-                                                   unsigned long long &edges,
-                                                   unsigned long long &claimed) {
-  const int l = lane_id();
-  const int32_t incl = wave_incl_scan(len);
-  const int32_t T = lane_read(incl, kWave - 1);
-  wave_sync();
-  s_excl[l] = incl - len;
-  s_u[l] = u;
-  s_beg[l] = beg;
-  wave_sync();
-  if (l == 0) edges += T;
-  for (int32_t e0 = 0; e0 < T; e0 += kWave) {
-    const int32_t e = e0 + l;
-    bool won = false;
-    int32_t v = 0;
-    if (e < T) {
-      const int lo = owner64(s_excl, e);
-      v = ncol[s_beg[lo] + (e - s_excl[lo])];
-      if (part == 0) {
-        won = bit_claim(Vn, uint32_t(v));
-        if (won) {
-          out.put(v, s_u[lo]);
-          ++claimed;
-        }
-      } else if (bit_claim(Cd, uint32_t(v))) {
-        out.put(vid_of[v], s_u[lo]);
-        ++claimed;
+// Position of the r-th (from 0) set bit of x, r < popcount(x).
+__device__ __forceinline__ int nth_bit(uint32_t x, int r) {
+  int pos = 0;
+#pragma unroll
+  for (int s = 16; s > 0; s >>= 1) {
+    const int c = __popc(x & ((1u << s) - 1u));
+    if (r >= c) {
+      r -= c;
+      x >>= s;
+      pos += s;
+    }
+  }
+  return pos;
+}
+
+// Append buffer of one wave in LDS: a full buffer goes out with one atomic on
+// the list's counter (device-scope atomics on one address serialize across
+// the chip, 12.6 ns each, so waves never do one per step).
+struct WaveAppend {
+  int32_t *buf;
+  int cap;  // at least 2 * kWave
+  unsigned long long *gcount;  // bits 0..31 count this list
+  int32_t *gout;
+  int cnt;
+
+  __device__ __forceinline__ void push(bool want, int32_t v) {
+    const uint64_t m = __ballot(want);
+    if (m == 0) return;
+    if (want) buf[cnt + int(lanes_below(m))] = v;
+    cnt += __popcll(m);
+    if (cnt > cap - kWave) flush();
+  }
+  __device__ void flush() {
+    if (cnt == 0) return;
+    wave_sync();
+    unsigned long long b = 0;
+    if (lane_id() == 0) b = atomicAdd(gcount, (unsigned long long)cnt) & 0xffffffffull;
+    b = lane_read(b, 0);
+    for (int i = lane_id(); i < cnt; i += kWave) gout[b + i] = buf[i];
+    wave_sync();
+    cnt = 0;
+  }
+};
+
+// The block's two append buffers as one buffer per wave.
+template <int NW>
+__device__ __forceinline__ WaveAppend wave_append_buf(Scratch<NW> &S, unsigned long long *gcount,
+                                                      int32_t *gout) {
+  constexpr int per = 2 * Scratch<NW>::kCap / NW;
+  return WaveAppend{S.buf + (threadIdx.x / kWave) * per, per, gcount, gout, 0};
+}
+
+// ---------------------------------------------------------------------------
+// grid barrier (one-launch searches)
+// ---------------------------------------------------------------------------
+// Two levels: a block counts its arrival on its group's line, the group's last
+// arrival counts on `top`, the last of those releases every group. Blocks poll
+// their own group's line with relaxed loads; every block fences on both sides
+// (agent scope), so plain stores before the barrier are visible after it.
+// Counters only grow (k_init zeroes them), so nothing is reset between
+// barriers. Measured, empty: 1.9 us for 16 blocks, 2.5 for 64, 3.4 for 128,
+// 5.2 for 256, 9 for 512: the fences of each block are served one after the
+// other, which is why a one-launch search runs few, wide blocks.
+// A wait is bounded: past the bound every block leaves (returns false) and the
+// host runs the search level by level instead.
+constexpr long long kBarTicks = 20000000;  // 0.2 s of the 100 MHz wall clock
+
+__device__ bool grid_sync(GridBar &b, unsigned long long epoch, int *ok) {
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned G = gridDim.x, grp = blockIdx.x % kBarGroups;
+    const unsigned gsize = G / kBarGroups + (grp < G % kBarGroups ? 1u : 0u);
+    const unsigned ngrp = G < kBarGroups ? G : kBarGroups;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    const unsigned long long t = __hip_atomic_fetch_add(
+        &b.arrive[grp].v, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (t + 1 == epoch * gsize) {
+      // the group's arrivals happen before this one's count on top
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
+      const unsigned long long u = __hip_atomic_fetch_add(
+          &b.top.v, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (u + 1 == epoch * ngrp) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
+        for (unsigned i = 0; i < ngrp; ++i)
+          __hip_atomic_store(&b.release[i].v, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
-    if (part == 0) qa.push(won, v);
+    const long long t0 = wall_clock64();
+    int good = 1;
+    while (ctr_load(&b.release[grp].v) < epoch) {
+      if (ctr_load(&b.err.v)) {
+        good = 0;
+        break;
+      }
+      if (wall_clock64() - t0 > kBarTicks) {
+        __hip_atomic_store(&b.err.v, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        good = 0;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    *ok = good;
+  }
+  __syncthreads();
+  return *ok != 0;
+}
+
+// ---------------------------------------------------------------------------
+// init
+// ---------------------------------------------------------------------------
+// Fills the outputs, clears bitmaps and the control block, and seeds the
+// source: a delegate is claimed (the first previsit moves it to the frontier
+// mask), a normal vertex enters the queue. The counters of "level -1" hold the
+// level-0 queue length. Bound by the output fill: 6.5 TB/s at 67M vertices.
+__global__ void k_init(Search a, LevelState init) {
+  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+  const int64_t t0 = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int32_t s = a.source;
+  const int32_t k = a.mode == 1 ? a.did[s] : -1;
+  for (int64_t v = t0; v < a.n; v += stride) {
+    a.depth[v] = v == s ? 0 : -1;
+    if (a.parent) a.parent[v] = v == s ? s : -1;
+  }
+  for (int64_t w = t0; w < a.nwords; w += stride) {
+    a.Vn[w] = k < 0 && w == (s >> 5) ? 1u << (s & 31) : 0u;
+    a.Fn0[w] = 0;
+    a.Fn1[w] = 0;
+  }
+  for (int64_t w = t0; w < a.dwords; w += stride) {
+    a.Vd[w] = 0;
+    a.Fd[w] = 0;
+    a.Cd[w] = k >= 0 && w == (k >> 5) ? 1u << (k & 31) : 0u;
+  }
+  if (blockIdx.x == 0) {
+    unsigned long long *c = reinterpret_cast<unsigned long long *>(a.ctl);
+    for (int i = threadIdx.x; i < int(sizeof(SearchCtl) / 8); i += blockDim.x) c[i] = 0;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      a.ctl->st[0] = init;
+      LevelCtr &before = a.ctl->ctr[2];
+      before.qn_nc.v = k < 0 ? 1u : 0u;
+      before.sum[kClDn][0].v = k >= 0 && bit_test(a.dnm, uint32_t(k)) ? 1u : 0u;
+      if (k < 0) a.Q0[0] = s;
+    }
   }
 }
 
-// One pass over the normal queue: previsit (nn/nd workloads and counts of
-// the frontier, normal frontier bitmap Fn) fused with the nn top-down visit.
-// Fn is only read by a bottom-up nd visit; mark_fn = 0 when none can happen
-// (no unvisited delegate has a dn edge).
-__global__ void __launch_bounds__(kBS) k_normal_level(const int32_t *Q, const LevelCtr *prev,
-                                                      const uint64_t *noff, const uint16_t *nlen,
-                                                      const int32_t *ncol, const uint32_t *nnoff,
-                                                      const int32_t *nncol,
-                                                      Out out, uint32_t *Vn, uint32_t *Fn,
-                                                      const DevCtl *c, int32_t *Qnext,
-                                                      LevelCtr *cur) {
-  if (c->done) return;
-  const int64_t qn = lc_qn(prev);
-  // blocks past the queue have nothing to add (a short queue leaves most of
-  // the grid idle: skip its LDS set-up and block reductions)
+// ---------------------------------------------------------------------------
+// decision
+// ---------------------------------------------------------------------------
+// Opens level L in the block: the queue length and candidate count the
+// previous level left, and whether this level marks the normal frontier
+// bitmap Fn. Fn is read only by a bottom-up nd visit (which needs an unvisited
+// delegate with a dn edge left after this level's frontier) and, with nn_do,
+// by a bottom-up nn visit.
+template <int NW>
+__device__ __forceinline__ void level_open(const Search &a, Scratch<NW> &S, int L) {
+  const LevelCtr &prev = a.ctl->ctr[(L + 2) % 3];
+  // the first wave: lanes 0..7 the parts of the claim count, lane 8 the tails
+  if (threadIdx.x < kWave) {
+    const int l = lane_id();
+    unsigned long long x = 0;
+    if (l < kCtrCopies) x = ctr_load(&prev.sum[kClDn][l].v);
+    else if (l == kCtrCopies) x = ctr_load(&prev.qn_nc.v);
+    const uint32_t claimed = wave_total(l < kCtrCopies ? uint32_t(x) : 0u);
+    const unsigned long long t = lane_read(x, kCtrCopies);
+    if (l == 0) {
+      S.q_dn = int64_t(claimed);
+      S.qn = int64_t(t & 0xffffffffull);
+      S.nc_prev = int64_t(t >> 32);
+      S.mark = S.st.rem[1] - S.q_dn > 0 || (a.nn_do && S.st.rem[3] > 0);
+    }
+  }
+  __syncthreads();
+}
+
+// Direction decision of Section IV-B for dd, dn, nd (indices 0, 1, 2) from
+// the level's previsit counts c, in FP64 with the same expression as the
+// oracle's replay, the bookkeeping of the remaining counts, and the plan of
+// the rest of the level. One thread, on its own copies; rec (may be NULL) gets
+// the level's record.
+__device__ __forceinline__ void decide_level(const Search &a, LevelState &t, const LevelCounts &c,
+                                             int64_t qn, int64_t nc_prev, int mark, Plan &p,
+                                             LevelStatus *rec) {
+  const int32_t L = t.level;
+  const int64_t fdn = int64_t(c.v[kFdn]);
+  if (t.nc_pending) {
+    // length of the candidate list the previous bottom-up normal pass compacted
+    t.nc = nc_prev;
+    t.nc_pending = 0;
+  }
+  t.level = L + 1;
+  t.marked = 0;
+  if (rec) {
+    rec->level = L;
+    rec->done = 0;
+  }
+  if (qn == 0 && fdn == 0) {
+    t.done = 1;
+    if (rec) rec->done = 1;
+    return;
+  }
+  t.marked = mark;
+  const int64_t q[3] = {int64_t(c.v[kQDd]), int64_t(c.v[kQDn]), int64_t(c.v[kQNd])};
+  const int64_t FV[3] = {int64_t(c.v[kFvDd]), int64_t(c.v[kFvDn]), int64_t(c.v[kFvNd])};
+  const int64_t q_nn = int64_t(c.v[kQNn]), fv_nn = int64_t(c.v[kFvNn]);
+  t.rem[0] -= q[0];
+  t.rem[1] -= q[1];
+  t.rem[2] -= q[2];
+  t.rem[3] -= q_nn;
+  const int64_t U[3] = {t.rem[0], t.rem[2], t.rem[1]};
+  const int64_t R[3] = {t.rem[0], t.rem[1], t.rem[2]};
+  auto choose = [&](int k, int64_t qk, int64_t fvk, double bvk) {
+    int d = t.dir[k];
+    if (a.forced == 1) d = 0;
+    else if (a.forced == 2) d = L >= 1 ? 1 : 0;
+    else if (a.forced == 3)
+      d = int(mix64(a.forced_seed + uint64_t(L) * 3 + k + (k == 3 ? 0x5bd1e995ull : 0)) & 1);
+    else if (qk > 0) {
+      if (d == 0 && double(fvk) > a.f0[k] * bvk) d = 1;
+      else if (d == 1 && double(fvk) < a.f1[k] * bvk) d = 0;
+    }
+    t.dir[k] = d;
+  };
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const double bv = bv_estimate(U[k], q[k], R[k]);
+    choose(k, q[k], FV[k], bv);
+    if (rec) {
+      rec->rec.q[k] = q[k];
+      rec->rec.s[k] = R[k];
+      rec->rec.U[k] = U[k];
+      rec->rec.FV[k] = FV[k];
+      rec->rec.BV[k] = bv;
+      rec->rec.dir[k] = t.dir[k];
+    }
+  }
+  // nn (nn_do only): U = s = unvisited normals with an nn edge (symmetric)
+  const double bv_nn = a.nn_do ? bv_estimate(t.rem[3], q_nn, t.rem[3]) : 0.0;
+  if (a.nn_do) choose(3, q_nn, fv_nn, bv_nn);
+  p.qn = qn;
+  p.nn_td = a.nn_do && t.dir[3] == 0 && q_nn > 0;
+  p.nn_bu = a.nn_do && t.dir[3] == 1 && q_nn > 0 && t.rem[3] > 0;
+  // without nn_do, nn went top-down inside the previsit already
+  p.dd_td = t.dir[0] == 0 && q[0] > 0;
+  p.dn_td = t.dir[1] == 0 && q[1] > 0;
+  p.nd_td = t.dir[2] == 0 && q[2] > 0;
+  p.dd_bu = t.dir[0] == 1 && q[0] > 0 && U[0] > 0;
+  p.dn_bu = t.dir[1] == 1 && q[1] > 0 && U[1] > 0 && t.nc > 0;
+  p.nd_bu = t.dir[2] == 1 && q[2] > 0 && U[2] > 0;
+  p.nc = t.nc;
+  if (p.dn_bu) {
+    p.cin_sel = t.cand_state;
+    p.cout_sel = t.cand_state < 0 ? 0 : (t.cand_state ^ 1);
+    t.cand_state = p.cout_sel;
+    t.nc_pending = 1;
+  }
+  if (rec) {
+    rec->rec.U_nn = a.nn_do ? t.rem[3] : 0;
+    rec->rec.s_nn = rec->rec.U_nn;
+    rec->rec.BV_nn = bv_nn;
+    rec->rec.dir_nn = a.nn_do ? t.dir[3] : 0;
+    rec->rec.FV_nn = fv_nn;
+    rec->rec.q_nn = q_nn;
+    rec->rec.frontier_normal = qn;
+    rec->rec.frontier_delegate = fdn;
+  }
+}
+
+// Adds level st's contribution to the totals (one thread of one block, after
+// the decision; only when statistics are wanted).
+__device__ inline void account_level(const Search &a, const LevelState &st, const LevelState &ns,
+                                     const LevelCounts &c, int64_t qn, int64_t nc_prev,
+                                     const Plan &p, LevelTotals &t) {
+  const int64_t fdn = int64_t(c.v[kFdn]);
+  t.units0[DSBFS_K_PREV_NORMAL] += qn;
+  t.units0[DSBFS_K_PREV_DELEG] += fdn;
+  ++t.launches[DSBFS_K_PREV_NORMAL];
+  if (a.d > 0) ++t.launches[DSBFS_K_PREV_DELEG];
+  t.deg_sum += c.v[kFvNn] + c.v[kFvNd] + c.v[kFvDd] + c.v[kFvDn];
+  if (st.nc_pending) t.kept += nc_prev;
+  if (ns.done) return;
+  ++t.launches[DSBFS_K_CLOSE];
+  if (ns.marked) t.units0[DSBFS_K_CLOSE] += a.nwords;
+  if (p.nd_td) t.units0[DSBFS_K_TD_NORMAL] += qn;
+  if (p.nn_td) t.units0[DSBFS_K_TD_NN] += qn;
+  if (p.dd_td || p.dn_td) t.units0[DSBFS_K_TD_DELEG] += fdn;
+  t.launches[DSBFS_K_TD_NORMAL] += p.nd_td;
+  t.launches[DSBFS_K_TD_DELEG] += p.dd_td || p.dn_td;
+  t.launches[DSBFS_K_BU_NORMAL] += p.dn_bu;
+  t.launches[DSBFS_K_BU_DELEG] += p.dd_bu || p.nd_bu;
+  t.launches[DSBFS_K_TD_NN] += p.nn_td;
+  t.launches[DSBFS_K_BU_NN] += p.nn_bu;
+}
+
+// The decision of level L, made by every block for itself (S.ns, S.plan).
+// level_open has run for L.
+template <int NW>
+__device__ __forceinline__ void level_plan(const Search &a, Scratch<NW> &S, int L,
+                                           LevelStatus *rec = nullptr) {
+  const LevelCtr &c = a.ctl->ctr[L % 3];
+  // the first wave, eight lanes a sum: nine sums in two rounds of loads
+  static_assert(kPrevSums <= 2 * kWave / kCtrCopies, "two rounds");
+  if (threadIdx.x < kWave) {
+    const int l = lane_id(), part = l % kCtrCopies;
+    unsigned long long x[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int k = r * (kWave / kCtrCopies) + l / kCtrCopies;
+      x[r] = k < kPrevSums ? ctr_load(&c.sum[k][part].v) : 0ull;
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int k = r * (kWave / kCtrCopies) + l / kCtrCopies;
+      unsigned long long t = x[r];
+      for (int o = 1; o < kCtrCopies; o <<= 1) t += __shfl_xor(t, o, kWave);
+      if (part == 0 && k < kPrevSums) S.now.v[k] = t;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const LevelCounts now = S.now;
+    LevelState t = S.st;
+    Plan p{};
+    decide_level(a, t, now, S.qn, S.nc_prev, S.mark, p, rec);
+    S.ns = t;
+    S.plan = p;
+  }
+  __syncthreads();
+}
+
+// ---------------------------------------------------------------------------
+// previsit
+// ---------------------------------------------------------------------------
+// Mask words of one wave step of the delegate passes: a power of two, small
+// enough that every wave of the grid has a step when there are that many words.
+__device__ __forceinline__ int mask_step(int32_t words, int64_t nwaves) {
+  int c = kWave;
+  while (c > 2 && int64_t(words) < c * nwaves) c >>= 1;
+  return c;
+}
+
+// Delegates claimed by the previous level become the frontier mask, with their
+// dd/dn counts. Workloads (degree sums) need the row offsets of every frontier
+// delegate; they are read only while a decision can still depend on them or
+// statistics want them: under the heuristic schedule with factor1 = 0 a kernel
+// that went backward never switches back. A wave enumerates the set bits of
+// its words 64 at a time, one delegate per lane, so the offset reads are
+// coalesced and dense whatever the density of the mask (one thread per word,
+// walking its bits alone, took 54 us at 1.7M frontier delegates of RMAT 26).
+template <int NW> __device__ void prev_deleg(const Search &a, Scratch<NW> &S) {
+  const bool need_fv = a.count || a.forced != 0 || S.st.dir[0] == 0 || S.st.dir[1] == 0 ||
+                       a.f1[0] != 0.0 || a.f1[1] != 0.0;
+  const int l = lane_id();
+  const int64_t nwaves = int64_t(gridDim.x) * (blockDim.x / kWave);
+  const int64_t wid = int64_t(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave;
+  const int cw = mask_step(a.dwords, nwaves);
+  WaveRows &R = S.w[threadIdx.x / kWave];
+  uint32_t cnt = 0, q_dd = 0, q_dn = 0;
+  unsigned long long fv_dd = 0, fv_dn = 0;
+  for (int64_t w0 = wid * cw; w0 < a.dwords; w0 += nwaves * cw) {
+    const int64_t w = w0 + l;
+    uint32_t f = 0;
+    if (l < cw && w < a.dwords) {
+      const uint32_t cd = a.Cd[w];
+      f = cd & ~a.Vd[w];
+      a.Fd[w] = f;
+      if (f) {
+        a.Vd[w] = cd;
+        cnt += __popc(f);
+        q_dd += __popc(f & a.ddm[w]);
+        q_dn += __popc(f & a.dnm[w]);
+      }
+    }
+    if (!need_fv) continue;
+    const int32_t c = __popc(f);
+    const int32_t incl = wave_incl_scan(c);
+    const int32_t T = lane_read(incl, kWave - 1);
+    if (T == 0) continue;
+    wave_sync();
+    R.excl[l] = incl - c;
+    R.aux[l] = int32_t(f);
+    wave_sync();
+    for (int32_t i = l; i < T; i += kWave) {
+      const int o = owner64(R.excl, i);
+      const int64_t k = (w0 + o) * 32 + nth_bit(uint32_t(R.aux[o]), i - R.excl[o]);
+      const uint64_t x0 = a.doff[k], x1 = a.doff[k + 1];
+      const int64_t dd = row_first(x0);
+      fv_dd += dd;
+      fv_dn += row_start(x1) - row_start(x0) - dd;
+    }
+  }
+  block_acc(&S.red[kFdn], cnt);
+  block_acc(&S.red[kQDd], q_dd);
+  block_acc(&S.red[kQDn], q_dn);
+  if (need_fv) {
+    block_acc(&S.red[kFvDd], fv_dd);
+    block_acc(&S.red[kFvDn], fv_dn);
+  }
+}
+
+// Forward expansion of one part of the rows of up to 64 normal vertices, one
+// per lane (u: vertex, len: part length, beg: its start): the lengths are
+// prefix-summed across the wave, which walks the concatenated entries 64 at a
+// time, so lanes stay busy whatever the mix of degrees (all are <= TH). Four
+// steps of a long walk go together: their column loads, then their tests,
+// then their atomics are in flight at once, since a step alone waits for
+// three dependent round trips. to_normal: nn (claims normals, enqueues them),
+// else nd (claims delegates in Cd).
+template <bool to_normal, int U>
+__device__ __forceinline__ void expand_step(const Search &a, const WaveRows &R,
+                                            const int32_t *col, int32_t e0, int32_t T,
+                                            int32_t dep, WaveAppend &qa, uint32_t &claimed,
+                                            uint32_t &with_dn) {
+  const int l = lane_id();
+  int32_t v[U];
+  int o[U];
+  uint32_t wd[U], old[U];
+  uint32_t *const bm = to_normal ? a.Vn : a.Cd;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int32_t e = min(e0 + u * kWave + l, T - 1);
+    o[u] = owner64(R.excl, e);
+    v[u] = col[R.beg[o[u]] + (e - R.excl[o[u]])];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) wd[u] = bm[uint32_t(v[u]) >> 5];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t b = 1u << (v[u] & 31);
+    old[u] = b;
+    // a stale word can only lack a bit: the atomic decides
+    if (e0 + u * kWave + l < T && !(wd[u] & b)) old[u] = atomicOr(&bm[uint32_t(v[u]) >> 5], b);
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const bool won = !(old[u] & (1u << (v[u] & 31)));
+    if (won) {
+      ++claimed;
+      if (to_normal) {
+        a.put(v[u], R.aux[o[u]], dep);
+      } else {
+        a.put(a.vid_of[v[u]], R.aux[o[u]], dep);
+        with_dn += bit_test(a.dnm, uint32_t(v[u]));
+      }
+    }
+    if (to_normal) qa.push(won, v[u]);
+  }
+}
+
+template <bool to_normal>
+__device__ __forceinline__ void expand_rows(const Search &a, WaveRows &R, const int32_t *col,
+                                            int32_t u, int32_t len, int64_t beg, int32_t dep,
+                                            WaveAppend &qa, uint32_t &edges, uint32_t &claimed,
+                                            uint32_t &with_dn) {
+  const int l = lane_id();
+  const int32_t incl = wave_incl_scan(len);
+  const int32_t T = lane_read(incl, kWave - 1);
+  if (T == 0) return;
+  wave_sync();
+  R.excl[l] = incl - len;
+  R.aux[l] = u;
+  R.beg[l] = beg;
+  wave_sync();
+  if (l == 0) edges += uint32_t(T);
+  int32_t e0 = 0;
+  for (; T - e0 > 2 * kWave; e0 += 4 * kWave)
+    expand_step<to_normal, 4>(a, R, col, e0, T, dep, qa, claimed, with_dn);
+  for (; e0 < T; e0 += kWave)
+    expand_step<to_normal, 1>(a, R, col, e0, T, dep, qa, claimed, with_dn);
+}
+
+// The nn part of row u: its length and, when `start` is set, where it begins
+// (in the compact nn copy if there is one, else in the full rows).
+__device__ __forceinline__ void nn_part(const Search &a, int32_t u, bool start, int32_t &nn,
+                                        int64_t &nd, int64_t &beg) {
+  // part lengths from 2 bytes per vertex; the start only for rows with nn
+  // edges (most normal rows of a scale-free graph have none)
+  const uint32_t lw = a.nlen[u];
+  if (lw == kLenWide) {
+    const uint64_t w0 = a.noff[u], w1 = a.noff[u + 1];
+    nn = int32_t(row_first(w0));
+    nd = row_start(w1) - row_start(w0) - nn;
+    beg = a.nnoff ? int64_t(a.nnoff[u]) : row_start(w0);
+  } else {
+    nn = int32_t(lw & 0xFFu);
+    nd = int64_t(lw >> 8);
+    if (nn > 0 && start) beg = a.nnoff ? int64_t(a.nnoff[u]) : row_start(a.noff[u]);
+  }
+}
+
+// One pass over the normal queue: previsit (nn/nd workloads and counts of the
+// frontier, normal frontier bitmap Fn) fused with the nn top-down visit. With
+// nn under the direction decision (nn_do) it only counts and marks.
+template <int NW> __device__ void prev_normal(const Search &a, Scratch<NW> &S, int L) {
+  const int64_t qn = S.qn;
   if (int64_t(blockIdx.x) * blockDim.x >= qn) return;
-  const int mark_fn = level_marks_fn(c, int64_t(cur->q_dn));
-  // with nn under the direction decision this pass only counts (and marks
-  // Fn); nn is expanded after the decision, forward or backward
-  const int expand = !c->nn_do;
-  out.level1 = c->level1;
-  __shared__ int32_t s_excl[kNW][kWave];
-  __shared__ int32_t s_u[kNW][kWave];
-  __shared__ int64_t s_beg[kNW][kWave];
-  __shared__ int32_t qbuf[kQCap];
-  __shared__ int qcount;
-  __shared__ unsigned long long qbase;
-  __shared__ unsigned long long sh[4 * kNW];
-  BlockAppend qa{qbuf, &qcount, &qbase, kQCap, &cur->qn_nc, Qnext};
-  qa.init();
-  const int w = threadIdx.x / kWave;
-  unsigned long long fv_nn = 0, q_nn = 0, fv_nd = 0, q_nd = 0, edges = 0, claimed = 0;
+  const int mark = S.mark, expand = !a.nn_do;
+  const int32_t *const Q = a.q(L & 1);
+  uint32_t *const Fn = a.fn(L & 1);
+  WaveRows &R = S.w[threadIdx.x / kWave];
+  WaveAppend qa = wave_append_buf(S, &a.ctl->ctr[L % 3].qn_nc.v, a.q((L + 1) & 1));
+  uint32_t q_nn = 0, q_nd = 0, edges = 0, claimed = 0, none = 0;
+  unsigned long long fv_nn = 0, fv_nd = 0;
   for (int64_t b0 = int64_t(blockIdx.x) * blockDim.x; b0 < qn;
        b0 += int64_t(gridDim.x) * blockDim.x) {
     const int64_t i = b0 + threadIdx.x;
     int32_t u = 0, nn = 0;
     int64_t beg = 0;
     if (i < qn) {
+      int64_t nd = 0;
       u = Q[i];
-      // part lengths from 2 bytes per vertex; where the nn part starts only
-      // for rows with nn edges (most normal rows have none), from the compact
-      // nn copy when there is one
-      const uint32_t lw = nlen[u];
-      int64_t nd;
-      if (lw == kLenWide) {
-        const uint64_t w0 = noff[u], w1 = noff[u + 1];
-        nn = int32_t(row_first(w0));
-        nd = row_start(w1) - row_start(w0) - nn;
-        beg = nnoff ? int64_t(nnoff[u]) : row_start(w0);
-      } else {
-        nn = int32_t(lw & 0xFFu);
-        nd = int64_t(lw >> 8);
-        if (nn > 0 && expand) beg = nnoff ? int64_t(nnoff[u]) : row_start(noff[u]);
-      }
+      nn_part(a, u, expand, nn, nd, beg);
       fv_nn += nn;
       q_nn += nn > 0;
       fv_nd += nd;
       q_nd += nd > 0;
     }
     // queues filled by the bottom-up pass are in ascending order: mark word by word
-    if (mark_fn) wave_bit_set(Fn, uint32_t(u), i < qn, true);
-    expand_normal_rows<0>(u, expand ? nn : 0, beg, s_excl[w], s_u[w], s_beg[w],
-                          nnoff ? nncol : ncol, nullptr, out, Vn, nullptr, qa, edges, claimed);
-    qa.maybe_flush(kBS * 2);
+    if (mark) wave_bit_set(Fn, uint32_t(u), i < qn, true);
+    if (expand)
+      expand_rows<true>(a, R, a.nnoff ? a.nncol : a.ncol, u, nn, beg, L + 1, qa, edges, claimed,
+                        none);
   }
   qa.flush();
-  block_add4(&cur->fv_nn, fv_nn, q_nn, fv_nd, q_nd, sh);
-  // units: queue entries (counted on the host), nn edges, normals claimed
-  block_add4(cur->units[DSBFS_K_PREV_NORMAL], 0, edges, claimed, 0, sh);
+  block_acc(&S.red[kQNd], q_nd);
+  // the other sums only where a decision or the statistics read them
+  if (a.count || a.forced != 0 || S.st.dir[2] == 0 || a.f1[2] != 0.0)
+    block_acc(&S.red[kFvNd], fv_nd);
+  if (a.count || a.nn_do) {
+    block_acc(&S.red[kFvNn], fv_nn);
+    block_acc(&S.red[kQNn], q_nn);
+  }
+  // units: queue entries (counted by the decision), nn edges, normals claimed
+  count_units(a, S, DSBFS_K_PREV_NORMAL, 0, edges, claimed, 0);
 }
 
-// Top-down nn from the normal queue, after the direction decision (nn_do,
-// levels where nn goes forward): the expansion k_normal_level fuses into the
-// previsit otherwise.
-__global__ void __launch_bounds__(kBS) k_td_nn(const int32_t *Q, const DevCtl *c,
-                                               const uint64_t *noff, const uint16_t *nlen,
-                                               const int32_t *ncol, const uint32_t *nnoff,
-                                               const int32_t *nncol, Out out, uint32_t *Vn,
-                                               int32_t *Qnext, LevelCtr *cur) {
-  if (c->done || !c->nn_td) return;
-  const int64_t qn = c->qn;
-  if (int64_t(blockIdx.x) * blockDim.x >= qn) return;
-  out.level1 = c->level1;
-  __shared__ int32_t s_excl[kNW][kWave];
-  __shared__ int32_t s_u[kNW][kWave];
-  __shared__ int64_t s_beg[kNW][kWave];
-  __shared__ int32_t qbuf[kQCap];
-  __shared__ int qcount;
-  __shared__ unsigned long long qbase;
-  __shared__ unsigned long long sh[4 * kNW];
-  BlockAppend qa{qbuf, &qcount, &qbase, kQCap, &cur->qn_nc, Qnext};
-  qa.init();
-  const int w = threadIdx.x / kWave;
-  unsigned long long edges = 0, claimed = 0;
+// Previsit of level L: kDeleg and kNormal parts, and kClear: the frontier
+// bitmap that the previous level marked (two alternate by level, so clearing
+// one does not wait for the marking of the other) and the counters of level
+// L + 1.
+enum { kDeleg = 1, kNormal = 2, kClear = 4, kNn = 8, kCommit = 16 };
+template <int NW, int parts> __device__ __forceinline__ void previsit(const Search &a,
+                                                                      Scratch<NW> &S, int L) {
+  if (parts & kClear) {
+    if (S.st.marked) {
+      uint32_t *const F = a.fn((L + 1) & 1);
+      for (int64_t w = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; w < a.nwords;
+           w += int64_t(gridDim.x) * blockDim.x)
+        F[w] = 0;
+    }
+    ctr_clear(a.ctl->ctr[(L + 1) % 3]);
+  }
+  if (parts & kDeleg) prev_deleg(a, S);
+  if (parts & kNormal) prev_normal(a, S, L);
+  if (parts & (kDeleg | kNormal)) red_flush(S, a.ctl->ctr[L % 3], 0, kPrevSums);
+}
+
+// ---------------------------------------------------------------------------
+// edge-balanced expansion of a list of rows
+// ---------------------------------------------------------------------------
+// The list is cut into segments, one per listing block: segment b's entries
+// start at b * stride of the list, dscan holds each entry's exclusive prefix
+// within its segment, seg_len its total. Totals meet in the expansion, where
+// every block scans the (at most kSegs) segment lengths in LDS: the list needs
+// no device-wide scan (three kernels before).
+
+// Exclusive scan of x over the block; *total = sum.
+template <int NW>
+__device__ __forceinline__ int64_t block_scan(Scratch<NW> &S, int64_t x, int64_t *total) {
+  const int w = threadIdx.x / kWave, nw = blockDim.x / kWave;
+  const int64_t incl = wave_incl_scan(x);
+  if (lane_id() == kWave - 1) S.sh[w] = incl;
+  __syncthreads();
+  int64_t before = 0, all = 0;
+  for (int i = 0; i < nw; ++i) {
+    const int64_t t = S.sh[i];
+    before += i < w ? t : 0;
+    all += t;
+  }
+  *total = all;
+  __syncthreads();
+  return before + incl - x;
+}
+
+__device__ __forceinline__ int list_segs() { return min(int(gridDim.x), kSegs); }
+
+// Entries of a segment of mode 0's list: an even share of the queue, but no
+// less than kMinSeg, so that a wave's share of a short queue lies in one
+// segment (a wave takes the segments of its share one after the other).
+constexpr int64_t kMinSeg = 1024;
+__device__ __forceinline__ int64_t plain_seg(int64_t qn, int ns) {
+  return max((qn + ns - 1) / ns, kMinSeg);
+}
+
+// Frontier delegates with the lengths of their forward parts (dd if dd_td, dn
+// if dn_td). Segment b lists the delegates of its share of the mask words.
+template <int NW> __device__ void list_deleg(const Search &a, Scratch<NW> &S) {
+  const int ns = list_segs();
+  if (int(blockIdx.x) >= ns) return;
+  const int dd_td = S.plan.dd_td, dn_td = S.plan.dn_td;
+  const int64_t per = (int64_t(a.dwords) + ns - 1) / ns;
+  const int64_t wb = blockIdx.x * per, we = min(wb + per, int64_t(a.dwords));
+  const int64_t out0 = wb * 32;
+  int64_t done = 0, sum = 0;
+  for (int64_t w0 = wb; w0 < we; w0 += blockDim.x) {
+    const int64_t w = w0 + threadIdx.x;
+    const uint32_t f = w < we ? a.Fd[w] : 0u;
+    int64_t len = 0;
+    for (uint32_t g = f; g; g &= g - 1) {
+      const int64_t k = w * 32 + __ffs(g) - 1;
+      const uint64_t x0 = a.doff[k], x1 = a.doff[k + 1];
+      const int64_t dd = row_first(x0), dn = row_start(x1) - row_start(x0) - dd;
+      len += (dd_td ? dd : 0) + (dn_td ? dn : 0);
+    }
+    int64_t all, alln;
+    int64_t at = sum + block_scan(S, len, &all);
+    int64_t pos = out0 + done + block_scan(S, int64_t(__popc(f)), &alln);
+    for (uint32_t g = f; g; g &= g - 1) {
+      const int64_t k = w * 32 + __ffs(g) - 1;
+      const uint64_t x0 = a.doff[k], x1 = a.doff[k + 1];
+      const int64_t dd = row_first(x0), dn = row_start(x1) - row_start(x0) - dd;
+      a.dlist[pos] = int32_t(k);
+      a.dscan[pos] = at;
+      ++pos;
+      at += (dd_td ? dd : 0) + (dn_td ? dn : 0);
+    }
+    sum += all;
+    done += alln;
+  }
+  if (threadIdx.x == 0) {
+    a.ctl->seg_len[blockIdx.x] = sum;
+    a.ctl->seg_cnt[blockIdx.x] = int32_t(done);
+  }
+}
+
+// Mode 0: the whole queue, with the degrees of its rows.
+template <int NW> __device__ void list_plain(const Search &a, Scratch<NW> &S, int L) {
+  const int ns = list_segs();
+  if (int(blockIdx.x) >= ns) return;
+  const int32_t *const Q = a.q(L & 1);
+  const int64_t per = plain_seg(S.qn, ns);
+  const int64_t b = min(blockIdx.x * per, S.qn), e = min(b + per, S.qn);
+  int64_t sum = 0;
+  for (int64_t i0 = b; i0 < e; i0 += blockDim.x) {
+    const int64_t i = i0 + threadIdx.x;
+    int64_t len = 0;
+    if (i < e) {
+      const int32_t u = Q[i];
+      len = a.poff[u + 1] - a.poff[u];
+    }
+    int64_t all;
+    const int64_t at = sum + block_scan(S, len, &all);
+    if (i < e) a.dscan[i] = at;
+    sum += all;
+  }
+  if (threadIdx.x == 0) {
+    a.ctl->seg_len[blockIdx.x] = sum;
+    a.ctl->seg_cnt[blockIdx.x] = int32_t(e - b);
+  }
+}
+
+// Largest i in [0, cnt) with p[i] <= x (p non-decreasing, p[0] <= x), for a
+// whole wave: 64 probes a round.
+__device__ __forceinline__ int64_t wave_search(const int64_t *p, int64_t cnt, int64_t x) {
+  int64_t lo = 0, len = cnt;
+  while (len > 1) {
+    const int64_t step = (len + kWave - 1) / kWave;
+    const int64_t at = int64_t(lane_id()) * step;
+    const uint64_t m = __ballot(at < len && p[lo + min(at, len - 1)] <= x);
+    const int64_t j = (63 - __builtin_clzll(m)) * step;  // lane 0 always holds
+    lo += j;
+    len = min(step, len - j);
+  }
+  return lo;
+}
+
+// One step of the expansion: the entries [e0, lim) of the window in R, U * 64
+// of them at most (plain: claims normals; else dd entries claim delegates, dn
+// entries normals). R.beg[o] + e is entry e's column, R.mid[o] where row o's
+// dn part begins.
+template <bool plain, int U>
+__device__ __forceinline__ void list_step(const Search &a, const WaveRows &R, int64_t ew,
+                                          int64_t e0, int64_t lim, int32_t dep, WaveAppend &qa,
+                                          uint32_t &cl_n, uint32_t &cl_d, uint32_t &with_dn) {
+  const int l = lane_id();
+  int32_t x[U];
+  int o[U];
+  bool ok[U], dd[U];
+  uint32_t wd[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t e = e0 + u * kWave + l;
+    ok[u] = e < lim;
+    const int64_t ec = ok[u] ? e : lim - 1;
+    o[u] = owner64(R.excl, int32_t(ec - ew));
+    dd[u] = !plain && ec < R.mid[o[u]];
+    x[u] = (plain ? a.pcol : a.dcol)[R.beg[o[u]] + ec];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) wd[u] = (dd[u] ? a.Cd : a.Vn)[uint32_t(x[u]) >> 5];
+  if (plain) {
+    // columns by neighbour degree: no two lanes share a word by design
+    uint32_t old[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t b = 1u << (x[u] & 31);
+      old[u] = b;
+      if (ok[u] && !(wd[u] & b)) old[u] = atomicOr(&a.Vn[uint32_t(x[u]) >> 5], b);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool won = !(old[u] & (1u << (x[u] & 31)));
+      if (won) {
+        a.put(x[u], R.aux[o[u]], dep);
+        ++cl_n;
+      }
+      qa.push(won, x[u]);
+    }
+    return;
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    // claims: the word read above first (most edges lead to vertices already
+    // claimed), then one atomic per run of lanes sharing a bitmap word (dn
+    // parts are ascending)
+    const bool want = ok[u] && !((wd[u] >> (x[u] & 31)) & 1u);
+    if (__ballot(want && dd[u])) {
+      if (wave_bit_claim(a.Cd, uint32_t(x[u]), ok[u] && dd[u], want && dd[u])) {
+        a.put(a.vid_of[x[u]], R.aux[o[u]], dep);
+        with_dn += bit_test(a.dnm, uint32_t(x[u]));
+        ++cl_d;
+      }
+    }
+    if (__ballot(want && !dd[u])) {
+      const bool won = wave_bit_claim(a.Vn, uint32_t(x[u]), ok[u] && !dd[u], want && !dd[u]);
+      if (won) {
+        a.put(x[u], R.aux[o[u]], dep);
+        ++cl_n;
+      }
+      qa.push(won, x[u]);
+    }
+  }
+}
+
+// Top-down over the listed rows, balanced over edges: every wave takes one
+// contiguous share of the concatenated rows. It finds the first row by search
+// and then stages 64 rows at a time in LDS (prefix, first column, parent); a
+// step finds its entries' rows there. Steps of four column loads, tests and
+// atomics in flight, as in the normal expansion: a step alone is a chain of
+// round trips.
+template <bool plain, int NW>
+__device__ void expand_list(const Search &a, Scratch<NW> &S, int L, uint32_t &with_dn) {
+  const int ns = list_segs();
+  const int l = lane_id(), w = threadIdx.x / kWave, nw = blockDim.x / kWave;
+  // exclusive prefix of the segment lengths
+  {
+    int64_t run = 0;
+    for (int i0 = 0; i0 < ns; i0 += blockDim.x) {
+      const int i = i0 + threadIdx.x;
+      int64_t all;
+      const int64_t at = run + block_scan(S, i < ns ? a.ctl->seg_len[i] : 0, &all);
+      if (i < ns) S.seg[i] = at;
+      run += all;
+    }
+    if (threadIdx.x == 0) S.seg[ns] = run;
+    __syncthreads();
+  }
+  const int64_t E = S.seg[ns];
+  const int64_t nwaves = int64_t(gridDim.x) * nw;
+  const int64_t share = ((E + nwaves - 1) / nwaves + kWave - 1) / kWave * kWave;
+  const int64_t eb = (int64_t(blockIdx.x) * nw + w) * share, ee = min(E, eb + share);
+  const int32_t *const list = plain ? a.q(L & 1) : a.dlist;
+  const int64_t stride = plain ? plain_seg(S.qn, ns) : (int64_t(a.dwords) + ns - 1) / ns * 32;
+  WaveRows &R = S.w[w];
+  WaveAppend qa = wave_append_buf(S, &a.ctl->ctr[L % 3].qn_nc.v, a.q((L + 1) & 1));
+  const int dd_td = !plain && S.plan.dd_td;
+  uint32_t cl_n = 0, cl_d = 0;
+  for (int64_t e = eb; e < ee;) {
+    // segment of e (the last one starting at or before it; empty ones share
+    // their start with the next)
+    int sg = 0;
+    for (int step = kSegs / 2; step > 0; step >>= 1)
+      if (sg + step < ns && S.seg[sg + step] <= e) sg += step;
+    const int64_t s0 = S.seg[sg], s1 = S.seg[sg + 1];
+    const int64_t lim = min(ee, s1) - s0;
+    const int64_t base = sg * stride, cnt = a.ctl->seg_cnt[sg];
+    int64_t own = wave_search(a.dscan + base, cnt, e - s0);
+    for (int64_t ew = e - s0; ew < lim;) {
+      const int64_t i = own + l;
+      const bool in = i < cnt;
+      int32_t u = 0;
+      int64_t pre = 0, beg = 0, mid = 0;
+      if (in) {
+        u = list[base + i];
+        pre = a.dscan[base + i];
+        if (plain) {
+          beg = a.poff[u] - pre;
+        } else {
+          const uint64_t x0 = a.doff[u];
+          const int64_t dd = row_first(x0);
+          beg = row_start(x0) + (dd_td ? 0 : dd) - pre;
+          mid = dd_td ? pre + dd : 0;
+          u = a.vid_of[u];
+        }
+      }
+      const int64_t wend = own + kWave < cnt ? a.dscan[base + own + kWave] : s1 - s0;
+      const int64_t stop = min(lim, wend);
+      wave_sync();
+      // a row that began before ew has a negative prefix (rows are shorter
+      // than 2^24 entries, 64 of them sum below 2^31)
+      R.excl[l] = in ? int32_t(pre - ew) : INT32_MAX;
+      R.aux[l] = u;
+      R.beg[l] = beg;
+      R.mid[l] = mid;
+      wave_sync();
+      int64_t p = ew;
+      for (; stop - p > 2 * kWave; p += 4 * kWave)
+        list_step<plain, 4>(a, R, ew, p, stop, L + 1, qa, cl_n, cl_d, with_dn);
+      for (; p < stop; p += kWave)
+        list_step<plain, 1>(a, R, ew, p, stop, L + 1, qa, cl_n, cl_d, with_dn);
+      ew = stop;
+      own += kWave;
+    }
+    e = s0 + lim;
+  }
+  qa.flush();
+  const uint32_t edges = l == 0 && eb < ee ? uint32_t(ee - eb) : 0u;
+  if (plain) {
+    // units: queue entries (counted by the caller), edges, claimed
+    count_units(a, S, DSBFS_K_PLAIN, 0, edges, cl_n, 0);
+  } else {
+    // units: -, edges, normals claimed, delegates claimed
+    count_units(a, S, DSBFS_K_TD_DELEG, 0, edges, cl_n, cl_d);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// forward visits of the normal queue
+// ---------------------------------------------------------------------------
+// Top-down nd (levels where nd goes forward), and nn when it is under the
+// direction decision and goes forward.
+template <int NW, int parts>
+__device__ void td_normal(const Search &a, Scratch<NW> &S, int L, uint32_t &with_dn) {
+  const int64_t qn = S.plan.qn;
+  const int nd_td = (parts & kNormal) && S.plan.nd_td, nn_td = (parts & kNn) && S.plan.nn_td;
+  if (!nd_td && !nn_td) return;
+  const int32_t *const Q = a.q(L & 1);
+  WaveRows &R = S.w[threadIdx.x / kWave];
+  WaveAppend qa = wave_append_buf(S, &a.ctl->ctr[L % 3].qn_nc.v, a.q((L + 1) & 1));
+  uint32_t nd_e = 0, nd_c = 0, nn_e = 0, nn_c = 0, none = 0;
   for (int64_t b0 = int64_t(blockIdx.x) * blockDim.x; b0 < qn;
        b0 += int64_t(gridDim.x) * blockDim.x) {
     const int64_t i = b0 + threadIdx.x;
-    int32_t u = 0, nn = 0;
-    int64_t beg = 0;
-    if (i < qn) {
-      u = Q[i];
-      const uint32_t lw = nlen[u];
-      if (lw == kLenWide) {
-        const uint64_t w0 = noff[u];
-        nn = int32_t(row_first(w0));
-        beg = nnoff ? int64_t(nnoff[u]) : row_start(w0);
-      } else {
-        nn = int32_t(lw & 0xFFu);
-        if (nn > 0) beg = nnoff ? int64_t(nnoff[u]) : row_start(noff[u]);
+    const int32_t u = i < qn ? Q[i] : 0;
+    if (nd_td) {
+      int32_t len = 0;
+      int64_t beg = 0;
+      if (i < qn) {
+        const uint64_t w0 = a.noff[u], w1 = a.noff[u + 1];
+        beg = row_start(w0) + row_first(w0);
+        len = int32_t(row_start(w1) - beg);
       }
+      expand_rows<false>(a, R, a.ncol, u, len, beg, L + 1, qa, nd_e, nd_c, with_dn);
     }
-    expand_normal_rows<0>(u, nn, beg, s_excl[w], s_u[w], s_beg[w], nnoff ? nncol : ncol, nullptr,
-                          out, Vn, nullptr, qa, edges, claimed);
-    qa.maybe_flush(kBS * 2);
+    if (nn_td) {
+      int32_t nn = 0;
+      int64_t nd = 0, beg = 0;
+      if (i < qn) nn_part(a, u, true, nn, nd, beg);
+      expand_rows<true>(a, R, a.nnoff ? a.nncol : a.ncol, u, nn, beg, L + 1, qa, nn_e, nn_c,
+                        none);
+    }
   }
   qa.flush();
-  // units: queue entries (counted by the decision), nn edges, normals claimed
-  block_add4(cur->units[DSBFS_K_TD_NN], 0, edges, claimed, 0, sh);
+  // units: -, edges, -, delegates claimed / -, edges, normals claimed, -
+  if (nd_td) count_units(a, S, DSBFS_K_TD_NORMAL, 0, nd_e, 0, nd_c);
+  if (nn_td) count_units(a, S, DSBFS_K_TD_NN, 0, nn_e, nn_c, 0);
+}
+
+// Forward visits of level L, of the parts asked for.
+template <int NW, int parts>
+__device__ __forceinline__ void forward(const Search &a, Scratch<NW> &S, int L) {
+  uint32_t with_dn = 0;
+  if (parts & (kNormal | kNn)) td_normal<NW, parts>(a, S, L, with_dn);
+  __syncthreads();
+  if ((parts & kDeleg) && (S.plan.dd_td || S.plan.dn_td)) expand_list<false>(a, S, L, with_dn);
+  block_acc(&S.red[kClDn], with_dn);
+  red_flush(S, a.ctl->ctr[L % 3], kClDn, kClDn + 1);
+}
+
+// ---------------------------------------------------------------------------
+// bottom-up visits
+// ---------------------------------------------------------------------------
+// Walks the concatenated rows of a wave's 64 candidates (R.excl, R.beg set,
+// lane l's row has len entries), 64 entries per step, until every row has a
+// hit or ends: R.aux[l] gets the first hit of row l (an index into the
+// concatenation), kNone if there is none. hit(o, q) tests entry q of row o.
+constexpr int32_t kNone = 0x7fffffff;
+template <class F>
+__device__ __forceinline__ void walk_rows(WaveRows &R, int32_t T, int32_t len, uint32_t &edges,
+                                          F &&hit) {
+  const int l = lane_id();
+  uint64_t remaining = __ballot(len > 0);
+  for (int32_t e0 = 0; e0 < T && remaining; e0 += kWave) {
+    const int32_t e = e0 + l;
+    if (e < T) {
+      const int o = owner64(R.excl, e);
+      // a row whose parent an earlier step found is not read further: a scan
+      // stops at its first frontier neighbour (Section IV-B)
+      if (R.aux[o] == kNone) {
+        ++edges;
+        if (hit(o, R.beg[o] + (e - R.excl[o]))) atomicMin(&R.aux[o], e);
+      }
+    }
+    wave_sync();
+    remaining = __ballot(len > 0 && R.aux[l] == kNone);
+  }
 }
 
 // Bottom-up nn (nn_do, levels where nn goes backward): every normal vertex
 // with an nn edge that is still unvisited scans its nn part (ascending IDs)
-// for a vertex of the level's normal frontier (bitmap Fn, marked by the
-// previsit), stopping at the first; the rows of a wave's 64 candidates are
-// walked together, 64 entries per step, as in k_bu_normal. A candidate is
-// one lane's and no other kernel claims normals while this one runs, so
+// for a vertex of the level's normal frontier Fn, stopping at the first. A
+// candidate is one lane's and no other visit claims normals meanwhile, so
 // claims set bits without reading them back.
-__global__ void __launch_bounds__(kBS) k_bu_nn(const DevCtl *c, const int32_t *nnsrc,
-                                               int64_t nsrc, const uint64_t *noff,
-                                               const uint16_t *nlen, const int32_t *ncol,
-                                               const uint32_t *Fn, Out out, uint32_t *Vn,
-                                               int32_t *Qnext, LevelCtr *cur) {
-  if (c->done || !c->nn_bu) return;
-  out.level1 = c->level1;
-  __shared__ int32_t s_excl[kNW][kWave];
-  __shared__ int32_t s_found[kNW][kWave];
-  __shared__ int64_t s_beg[kNW][kWave];
-  __shared__ int32_t qbuf[kQCap];
-  __shared__ int qcount;
-  __shared__ unsigned long long qbase;
-  __shared__ unsigned long long sh[4 * kNW];
-  BlockAppend qa{qbuf, &qcount, &qbase, kQCap, &cur->qn_nc, Qnext};
-  qa.init();
-  const int w = threadIdx.x / kWave, l = lane_id();
-  constexpr int32_t kNone = 0x7fffffff;
-  unsigned long long reads = 0, scanned = 0, edges = 0, claimed = 0;
-  for (int64_t b0 = int64_t(blockIdx.x) * blockDim.x; b0 < nsrc;
+template <int NW> __device__ void bu_nn(const Search &a, Scratch<NW> &S, int L) {
+  const uint32_t *const Fn = a.fn(L & 1);
+  WaveRows &R = S.w[threadIdx.x / kWave];
+  WaveAppend qa = wave_append_buf(S, &a.ctl->ctr[L % 3].qn_nc.v, a.q((L + 1) & 1));
+  const int l = lane_id();
+  uint32_t reads = 0, scanned = 0, edges = 0, claimed = 0;
+  for (int64_t b0 = int64_t(blockIdx.x) * blockDim.x; b0 < a.n_nnsrc;
        b0 += int64_t(gridDim.x) * blockDim.x) {
     const int64_t i = b0 + threadIdx.x;
-    const bool ok = i < nsrc;
+    const bool ok = i < a.n_nnsrc;
     int32_t v = 0, len = 0;
     int64_t beg = 0;
     if (ok) {
-      v = nnsrc[i];
+      v = a.nnsrc[i];
       ++reads;
-      if (!bit_test(Vn, uint32_t(v))) {
+      if (!bit_test(a.Vn, uint32_t(v))) {
         ++scanned;
-        const uint32_t lw = nlen[v];
-        const uint64_t w0 = noff[v];
+        const uint32_t lw = a.nlen[v];
+        const uint64_t w0 = a.noff[v];
         beg = row_start(w0);
         len = lw == kLenWide ? int32_t(row_first(w0)) : int32_t(lw & 0xFFu);
       }
@@ -493,192 +1252,49 @@ __global__ void __launch_bounds__(kBS) k_bu_nn(const DevCtl *c, const int32_t *n
     const int32_t incl = wave_incl_scan(len);
     const int32_t T = lane_read(incl, kWave - 1);
     wave_sync();
-    s_excl[w][l] = incl - len;
-    s_beg[w][l] = beg;
-    s_found[w][l] = kNone;
+    R.excl[l] = incl - len;
+    R.beg[l] = beg;
+    R.aux[l] = kNone;
     wave_sync();
-    uint64_t remaining = __ballot(len > 0);
-    for (int32_t e0 = 0; e0 < T && remaining; e0 += kWave) {
-      const int32_t e = e0 + l;
-      if (e < T) {
-        const int lo = owner64(s_excl[w], e);
-        if (s_found[w][lo] == kNone) {
-          const int32_t x = ncol[s_beg[w][lo] + (e - s_excl[w][lo])];
-          ++edges;
-          if (bit_test(Fn, uint32_t(x))) atomicMin(&s_found[w][lo], e);
-        }
-      }
-      wave_sync();
-      remaining = __ballot(len > 0 && s_found[w][l] == kNone);
-    }
-    const int32_t fe = s_found[w][l];
+    walk_rows(R, T, len, edges,
+              [&](int, int64_t q) { return bit_test(Fn, uint32_t(a.ncol[q])); });
+    const int32_t fe = R.aux[l];
     const bool won = ok && len > 0 && fe != kNone;
-    wave_bit_set(Vn, uint32_t(v), ok, won);
+    wave_bit_set(a.Vn, uint32_t(v), ok, won);
     if (won) {
-      out.put(v, ncol[beg + (fe - (incl - len))]);
+      a.put(v, a.ncol[beg + (fe - (incl - len))], L + 1);
       ++claimed;
     }
     qa.push(won, v);
-    qa.maybe_flush(kBS);
   }
   qa.flush();
   // units: list entries read, unvisited scanned, edges inspected, claimed
-  block_add4(cur->units[DSBFS_K_BU_NN], reads, scanned, edges, claimed, sh);
-}
-
-// Top-down nd from the normal queue (only on levels where nd goes forward).
-__global__ void __launch_bounds__(kBS) k_td_nd(const int32_t *Q, const DevCtl *c,
-                                               const uint64_t *noff, const int32_t *ncol,
-                                               const int32_t *vid_of, Out out, uint32_t *Cd,
-                                               LevelCtr *cur) {
-  if (c->done || !c->nd_td) return;
-  const int64_t qn = c->qn;
-  out.level1 = c->level1;
-  __shared__ int32_t s_excl[kNW][kWave];
-  __shared__ int32_t s_u[kNW][kWave];
-  __shared__ int64_t s_beg[kNW][kWave];
-  __shared__ unsigned long long sh[4 * kNW];
-  const int w = threadIdx.x / kWave;
-  BlockAppend none{nullptr, nullptr, nullptr, 0, nullptr, nullptr};
-  unsigned long long edges = 0, claimed = 0;
-  for (int64_t b0 = int64_t(blockIdx.x) * blockDim.x; b0 < qn;
-       b0 += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t i = b0 + threadIdx.x;
-    int32_t u = 0, len = 0;
-    int64_t beg = 0;
-    if (i < qn) {
-      u = Q[i];
-      const uint64_t w0 = noff[u], w1 = noff[u + 1];
-      beg = row_start(w0) + row_first(w0);
-      len = int32_t(row_start(w1) - beg);
-    }
-    expand_normal_rows<1>(u, len, beg, s_excl[w], s_u[w], s_beg[w], ncol, vid_of, out, nullptr,
-                          Cd, none, edges, claimed);
-  }
-  // units: -, edges, -, delegates claimed
-  block_add4(cur->units[DSBFS_K_TD_NORMAL], 0, edges, 0, claimed, sh);
-}
-
-// Largest idx in [0, cnt) with pre[idx] <= e (pre non-decreasing, pre[0] = 0).
-__device__ __forceinline__ int64_t seg_search(const int64_t *pre, int64_t cnt, int64_t e) {
-  int64_t lo = 0, hi = cnt - 1;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi + 1) >> 1;
-    if (pre[mid] <= e) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
-
-// Top-down from the delegate frontier over dd and/or dn. Delegate degrees span
-// a wide range, so the work is balanced over edges: the frontier's selected
-// row parts, concatenated, are cut into one contiguous range per block, and a
-// block takes 256 consecutive edges per step, one per lane. Lanes of a wave
-// mostly share a row, so the row lookups broadcast and the column reads
-// coalesce. Each wave finds the row of its first edge once by binary search
-// in the prefix sum of the part lengths and walks forward from there.
-__global__ void __launch_bounds__(kBS) k_td_deleg(const int32_t *dlist, const int64_t *dscan,
-                                                  const LevelCtr *curc, const uint64_t *doff,
-                                                  const int32_t *dcol, const int32_t *vid_of,
-                                                  const DevCtl *c, Out out, uint32_t *Vn,
-                                                  uint32_t *Cd, int32_t *Qnext, LevelCtr *cur) {
-  if (c->done || !(c->dd_td || c->dn_td)) return;
-  const int dd_td = c->dd_td;
-  out.level1 = c->level1;
-  __shared__ int32_t qbuf[kQCap];
-  __shared__ int qcount;
-  __shared__ unsigned long long qbase;
-  __shared__ unsigned long long sh[4 * kNW];
-  BlockAppend qa{qbuf, &qcount, &qbase, kQCap, &cur->qn_nc, Qnext};
-  qa.init();
-  const int64_t nd = int64_t(curc->nd_list);
-  const int64_t E = dscan[nd];
-  const int w = threadIdx.x / kWave;
-  unsigned long long cl_n = 0, cl_d = 0, edges = 0;
-  // block range [bs, be), a multiple of the block width long
-  const int64_t per = (E + gridDim.x - 1) / gridDim.x;
-  const int64_t bchunk = (per + kBS - 1) / kBS * kBS;
-  const int64_t bs = int64_t(blockIdx.x) * bchunk, be = min(bs + bchunk, E);
-  int64_t idx = 0;  // row of the wave's first edge in the current step
-  if (bs + w * kWave < be) idx = seg_search(dscan, nd, bs + w * kWave);
-  for (int64_t b0 = bs; b0 < be; b0 += kBS) {
-    const int64_t e = b0 + threadIdx.x;
-    const bool valid = e < be;
-    int64_t my = idx;
-    int32_t x = 0, pk = 0;
-    bool is_dd = false;
-    if (valid) {
-      while (dscan[my + 1] <= e) ++my;
-      const int32_t k = dlist[my];
-      const int64_t j = e - dscan[my];
-      const uint64_t w0 = doff[k];
-      const int64_t beg = row_start(w0), dd = row_first(w0);
-      is_dd = dd_td && j < dd;
-      x = dcol[dd_td ? beg + j : beg + dd + j];
-      pk = vid_of[k];
-      ++edges;
-    }
-    // the next step's first edge lies at or after this step's last one
-    idx = lane_read(my, kWave - 1);
-    // claims: a cheap visited test first (most edges lead to vertices already
-    // claimed), then one atomic per run of lanes sharing a bitmap word
-    const bool want_d = valid && is_dd && !bit_test(Cd, uint32_t(x));
-    const bool want_n = valid && !is_dd && !bit_test(Vn, uint32_t(x));
-    const bool won_d = wave_bit_claim(Cd, uint32_t(x), valid && is_dd, want_d);
-    const bool won_n = wave_bit_claim(Vn, uint32_t(x), valid && !is_dd, want_n);
-    if (won_d) {
-      out.put(vid_of[x], pk);
-      ++cl_d;
-    }
-    if (won_n) {
-      out.put(x, pk);
-      ++cl_n;
-    }
-    qa.push(won_n, x);
-    qa.maybe_flush(kBS);
-  }
-  qa.flush();
-  // units: -, edges, normals claimed, delegates claimed
-  block_add4(cur->units[DSBFS_K_TD_DELEG], 0, edges, cl_n, cl_d, sh);
+  count_units(a, S, DSBFS_K_BU_NN, reads, scanned, edges, claimed);
 }
 
 // Bottom-up dn (destination: normal vertices). Candidates are positions in
 // the nd source list; row p of the source-list-ordered nd copy holds the
 // delegate neighbours of ndsrc[p]. Each wave takes 64 candidates, drops the
-// visited ones, and walks the concatenation of the remaining rows 64 entries
-// at a time (consecutive candidates have consecutive rows, so the first pass
-// over the whole list streams them); the first entry of a row found in the
-// frontier mask Fd is kept with an LDS atomicMin, and the wave stops as soon
-// as every remaining candidate has one. Candidates still unvisited are
-// compacted (as positions) for the next bottom-up level.
-__global__ void __launch_bounds__(kBS) k_bu_normal(const DevCtl *c, int32_t *c0, int32_t *c1,
-                                                   const int32_t *ndsrc, const int64_t *nds_off,
-                                                   const int32_t *nds_col, const int2 *nds_first,
-                                                   const int32_t *vid_of, const uint32_t *Fd,
-                                                   Out out, uint32_t *Vn, int32_t *Qnext,
-                                                   LevelCtr *cur) {
-  if (c->done || !c->dn_bu) return;
+// visited ones, and walks the concatenation of the remaining rows
+// (consecutive candidates have consecutive rows, so the first pass over the
+// whole list streams them). Candidates still unvisited are compacted (as
+// positions) for the next bottom-up level.
+template <int NW> __device__ void bu_normal(const Search &a, Scratch<NW> &S, int L) {
   // first pass: every position of the nd source list (dense); later passes:
   // the positions the previous pass left unvisited
-  const int dense = c->cin_sel < 0;
-  const int32_t *cin = c->cin_sel == 0 ? c0 : c1;
-  int32_t *cout = c->cout_sel == 0 ? c0 : c1;
-  const int64_t nc = c->nc;
-  out.level1 = c->level1;
-  __shared__ int32_t s_excl[kNW][kWave];
-  __shared__ int32_t s_found[kNW][kWave];
-  __shared__ int64_t s_beg[kNW][kWave];
-  __shared__ int32_t qbuf[kQCap], cbuf[kQCap];
-  __shared__ int qcount, ccount;
-  __shared__ unsigned long long qbase, cbase;
-  __shared__ unsigned long long sh[4 * kNW];
-  BlockAppend qa{qbuf, &qcount, &qbase, kQCap, &cur->qn_nc, Qnext};
-  BlockAppend ca{cbuf, &ccount, &cbase, kQCap, &cur->qn_nc, cout, 32};
+  const int dense = S.plan.cin_sel < 0;
+  const int32_t *const cin = a.cand(S.plan.cin_sel);
+  const int64_t nc = S.plan.nc;
+  constexpr int cap = Scratch<NW>::kCap;
+  unsigned long long *const tails = &a.ctl->ctr[L % 3].qn_nc.v;
+  BlockAppend qa{S.buf, &S.qcount, &S.qbase, cap, tails, a.q((L + 1) & 1)};
+  BlockAppend ca{S.buf + cap, &S.ccount, &S.cbase, cap, tails, a.cand(S.plan.cout_sel), 32};
   qa.init();
   ca.init();
-  const int w = threadIdx.x / kWave, l = lane_id();
-  constexpr int32_t kNone = 0x7fffffff;
-  unsigned long long reads = 0, scanned = 0, edges = 0, claimed = 0;
+  __syncthreads();
+  WaveRows &R = S.w[threadIdx.x / kWave];
+  const int l = lane_id();
+  uint32_t reads = 0, scanned = 0, edges = 0, claimed = 0;
   for (int64_t b0 = int64_t(blockIdx.x) * blockDim.x; b0 < nc;
        b0 += int64_t(gridDim.x) * blockDim.x) {
     const int64_t i = b0 + threadIdx.x;
@@ -687,7 +1303,7 @@ __global__ void __launch_bounds__(kBS) k_bu_normal(const DevCtl *c, int32_t *c0,
     int64_t beg = 0;
     bool visited = true;
     int32_t hit0 = -1;  // delegate found at the first entry of the row
-    int32_t pk0 = 0;  // vertex of the row's first delegate (its parent if it is a hit)
+    int32_t pk0 = 0;    // vertex of the row's first delegate (its parent if it is a hit)
     if (ok) {
       pos = dense ? int32_t(i) : cin[i];
       // The loads are ordered to keep the chain of dependent accesses short:
@@ -695,499 +1311,436 @@ __global__ void __launch_bounds__(kBS) k_bu_normal(const DevCtl *c, int32_t *c0,
       // first entry (rows in the list are never empty) does not wait for the
       // visited test, and the parent candidate is fetched beside the
       // frontier test.
-      v = ndsrc[pos];
+      v = a.ndsrc[pos];
       // Rows start with their highest-degree delegate, the likeliest to be in
       // the frontier: a hit there skips the wave's walk for this row. The
       // first entry and its vertex come from a dense array (8 bytes per
       // candidate, read in list order); its frontier bit is tested whether
       // or not the candidate turns out to be visited, so that the loads
       // overlap the visited test instead of following it.
-      const int2 f = nds_first[pos];
+      const int2 f = a.nds_first[pos];
       const int32_t k0 = f.x;
       pk0 = f.y;
-      const bool f0 = bit_test(Fd, uint32_t(k0));
+      const bool f0 = bit_test(a.Fd, uint32_t(k0));
       ++reads;
-      visited = bit_test(Vn, uint32_t(v));
+      visited = bit_test(a.Vn, uint32_t(v));
       hit0 = (!visited && f0) ? k0 : -1;
       scanned += !visited;
       edges += !visited;
       if (!visited && !f0) {
         // a miss: the rest of the row is walked below
-        beg = nds_off[pos] + 1;
-        len = int32_t(nds_off[pos + 1] - beg);
+        beg = a.nds_off[pos] + 1;
+        len = int32_t(a.nds_off[pos + 1] - beg);
       }
     }
     const int32_t incl = wave_incl_scan(len);
     const int32_t T = lane_read(incl, kWave - 1);
     wave_sync();
-    s_excl[w][l] = incl - len;
-    s_beg[w][l] = beg;
-    s_found[w][l] = kNone;
+    R.excl[l] = incl - len;
+    R.beg[l] = beg;
+    R.aux[l] = kNone;
     wave_sync();
-    uint64_t remaining = __ballot(len > 0);
-    for (int32_t e0 = 0; e0 < T && remaining; e0 += kWave) {
-      const int32_t e = e0 + l;
-      if (e < T) {
-        const int lo = owner64(s_excl[w], e);
-        // a row whose parent an earlier step found is not read further: a
-        // scan stops at its first frontier neighbour (Section IV-B)
-        if (s_found[w][lo] == kNone) {
-          const int32_t x = nds_col[s_beg[w][lo] + (e - s_excl[w][lo])];
-          ++edges;
-          if (bit_test(Fd, uint32_t(x))) atomicMin(&s_found[w][lo], e);
-        }
-      }
-      wave_sync();
-      remaining = __ballot(len > 0 && s_found[w][l] == kNone);
-    }
-    const int32_t fe = s_found[w][l];
+    walk_rows(R, T, len, edges,
+              [&](int, int64_t q) { return bit_test(a.Fd, uint32_t(a.nds_col[q])); });
+    const int32_t fe = R.aux[l];
     const bool found = hit0 >= 0 || (len > 0 && fe != kNone);
-    // A vertex is the candidate of one lane only, and no other kernel claims
-    // normal vertices while this one runs (the level's nn visit is complete),
-    // so a found candidate is this lane's: its bit is set without waiting for
+    // A vertex is the candidate of one lane only, and no other visit claims
+    // normal vertices meanwhile (the level's forward visits are complete), so
+    // a found candidate is this lane's: its bit is set without waiting for
     // the atomic's old value. Candidates are ascending: set word by word.
     const bool won = ok && found;
-    wave_bit_set(Vn, uint32_t(v), ok, won);
+    wave_bit_set(a.Vn, uint32_t(v), ok, won);
     if (won) {
-      out.put(v, hit0 >= 0 ? pk0 : vid_of[nds_col[beg + (fe - (incl - len))]]);
+      a.put(v, hit0 >= 0 ? pk0 : a.vid_of[a.nds_col[beg + (fe - (incl - len))]], L + 1);
       ++claimed;
     }
     qa.push(won, v);
     ca.push(ok && !visited && !found, pos);
     __syncthreads();
-    if (qcount > kQCap - kBS || ccount > kQCap - kBS) flush_pair(qa, ca);
+    if (S.qcount > cap - int(blockDim.x) || S.ccount > cap - int(blockDim.x)) flush_pair(qa, ca);
   }
   flush_pair(qa, ca);
   // units: list entries read, unvisited scanned, edges inspected, claimed
-  block_add4(cur->units[DSBFS_K_BU_NORMAL], reads, scanned, edges, claimed, sh);
+  count_units(a, S, DSBFS_K_BU_NORMAL, reads, scanned, edges, claimed);
 }
 
-// Bottom-up dd and/or nd (destination: delegates). One unvisited delegate
-// per lane: it first tests the first entry of its scanned range (dd parts
-// start with their highest-degree neighbour, the likeliest to be in the
-// frontier); the rows that miss are then walked together, 64 entries per step
-// over their concatenation (prefix sums across the wave), until each has a
-// hit or ends. dd entries are tested against Fd, dn entries against the
-// normal frontier bitmap Fn. Candidates are ascending, so claims go word by
-// word.
-__global__ void __launch_bounds__(kBS) k_bu_deleg(const int32_t *dcand, const LevelCtr *curc,
-                                                  const uint64_t *doff, const int32_t *dcol,
-                                                  const int2 *dd_first, const uint32_t *Fd,
-                                                  const uint32_t *Fn,
-                                                  const int32_t *vid_of, const DevCtl *c,
-                                                  Out out, uint32_t *Cd, LevelCtr *cur) {
-  if (c->done || !(c->dd_bu || c->nd_bu)) return;
-  const int dd_bu = c->dd_bu, nd_bu = c->nd_bu;
-  out.level1 = c->level1;
-  __shared__ int32_t s_excl[kNW][kWave];
-  __shared__ int32_t s_found[kNW][kWave];
-  __shared__ int64_t s_beg[kNW][kWave];
-  __shared__ int64_t s_mid[kNW][kWave];
-  __shared__ unsigned long long sh[4 * kNW];
-  const int64_t nc = int64_t(curc->nd_cand);
-  const int w = threadIdx.x / kWave, l = lane_id();
-  constexpr int32_t kNone = 0x7fffffff;
-  unsigned long long cands = 0, edges = 0, claimed = 0;
-  for (int64_t b0 = int64_t(blockIdx.x) * blockDim.x; b0 < nc;
-       b0 += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t i = b0 + threadIdx.x;
-    const bool ok = i < nc;
-    int32_t k = 0, len = 0, vk = 0, px = 0;
-    int64_t p = 0, mid = 0, hit = -1;
-    if (ok) {
-      k = dcand[i];
-      const uint64_t w0 = doff[k], w1 = doff[k + 1];
-      vk = vid_of[k];                    // fetched beside the row bounds,
-      const int2 f = dd_first[k];        // as is the dense first dd entry
-      const int64_t beg = row_start(w0);
-      mid = beg + row_first(w0);
-      p = dd_bu ? beg : mid;
-      const int64_t hi = nd_bu ? row_start(w1) : mid;
-      if (p < hi) {
-        ++cands;
-        const bool in_dd = p < mid;
-        const int32_t x = in_dd ? f.x : dcol[p];
-        ++edges;
-        px = in_dd ? f.y : x;  // the parent if this entry is a hit
-        if (in_dd ? bit_test(Fd, uint32_t(x)) : bit_test(Fn, uint32_t(x))) hit = p;
-        else ++p;
-        // delegate degrees are below 2^24, so 64 rows sum below 2^31
-        if (hit < 0) len = int32_t(hi - p);
-      }
+// Bottom-up dd and/or nd (destination: delegates): unclaimed delegates with
+// an edge in a subgraph scanned bottom-up this level. A wave takes a few mask
+// words and enumerates their candidates 64 at a time, one per lane, so no
+// candidate list is written. Each lane first tests the first entry of its
+// scanned range (dd parts start with their highest-degree neighbour, the
+// likeliest to be in the frontier); the rows that miss are then walked
+// together. dd entries are tested against Fd, dn entries against the normal
+// frontier bitmap Fn. The words are this wave's alone: claims are collected in
+// LDS and the word stored once.
+template <int NW> __device__ void bu_deleg(const Search &a, Scratch<NW> &S, int L,
+                                           uint32_t &with_dn) {
+  const int dd_bu = S.plan.dd_bu, nd_bu = S.plan.nd_bu;
+  const uint32_t *const Fn = a.fn(L & 1);
+  const int l = lane_id();
+  const int64_t nwaves = int64_t(gridDim.x) * (blockDim.x / kWave);
+  const int64_t wid = int64_t(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave;
+  const int cw = min(mask_step(a.dwords, nwaves), 16);
+  WaveRows &R = S.w[threadIdx.x / kWave];
+  // this wave's part of the append buffers: mask words and their prefix, and
+  // the bits claimed
+  int32_t *const wpre = S.buf + (threadIdx.x / kWave) * (3 * kWave);
+  int32_t *const wbits = wpre + kWave;
+  unsigned int *const wgot = reinterpret_cast<unsigned int *>(wpre + 2 * kWave);
+  uint32_t cands = 0, edges = 0, claimed = 0;
+  for (int64_t w0 = wid * cw; w0 < a.dwords; w0 += nwaves * cw) {
+    const int64_t w = w0 + l;
+    uint32_t c = 0, cd = 0, dnm = 0;
+    if (l < cw && w < a.dwords) {
+      cd = a.Cd[w];
+      dnm = a.dnm[w];
+      c = ~cd & ((dd_bu ? a.ddm[w] : 0u) | (nd_bu ? dnm : 0u));
     }
-    const bool probe_hit = hit >= 0;
-    const int32_t incl = wave_incl_scan(len);
-    const int32_t T = lane_read(incl, kWave - 1);
-    if (T > 0) {
-      wave_sync();
-      s_excl[w][l] = incl - len;
-      s_beg[w][l] = p;
-      s_mid[w][l] = mid;
-      s_found[w][l] = kNone;
-      wave_sync();
-      uint64_t remaining = __ballot(len > 0);
-      for (int32_t e0 = 0; e0 < T && remaining; e0 += kWave) {
-        const int32_t e = e0 + l;
-        if (e < T) {
-          const int lo = owner64(s_excl[w], e);
-          if (s_found[w][lo] == kNone) {
-            const int64_t q = s_beg[w][lo] + (e - s_excl[w][lo]);
-            const int32_t x = dcol[q];
-            ++edges;
-            if (q < s_mid[w][lo] ? bit_test(Fd, uint32_t(x)) : bit_test(Fn, uint32_t(x)))
-              atomicMin(&s_found[w][lo], e);
-          }
+    const int32_t pc = __popc(c);
+    const int32_t pincl = wave_incl_scan(pc);
+    const int32_t total = lane_read(pincl, kWave - 1);
+    if (total == 0) continue;
+    wave_sync();
+    wpre[l] = pincl - pc;
+    wbits[l] = int32_t(c);
+    wgot[l] = 0;
+    wave_sync();
+    for (int32_t i0 = 0; i0 < total; i0 += kWave) {
+      const int32_t i = i0 + l;
+      const bool ok = i < total;
+      int32_t k = 0, len = 0, vk = 0, px = 0;
+      int64_t p = 0, mid = 0, hit = -1;
+      int wo = 0, bit = 0;
+      if (ok) {
+        wo = owner64(wpre, i);
+        bit = nth_bit(uint32_t(wbits[wo]), i - wpre[wo]);
+        k = int32_t((w0 + wo) * 32 + bit);
+        const uint64_t x0 = a.doff[k], x1 = a.doff[k + 1];
+        vk = a.vid_of[k];             // fetched beside the row bounds,
+        const int2 f = a.dd_first[k];  // as is the dense first dd entry
+        const int64_t beg = row_start(x0);
+        mid = beg + row_first(x0);
+        p = dd_bu ? beg : mid;
+        const int64_t hi = nd_bu ? row_start(x1) : mid;
+        if (p < hi) {
+          ++cands;
+          const bool in_dd = p < mid;
+          const int32_t x = in_dd ? f.x : a.dcol[p];
+          ++edges;
+          px = in_dd ? f.y : x;  // the parent if this entry is a hit
+          if (in_dd ? bit_test(a.Fd, uint32_t(x)) : bit_test(Fn, uint32_t(x))) hit = p;
+          else ++p;
+          // delegate degrees are below 2^24, so 64 rows sum below 2^31
+          if (hit < 0) len = int32_t(hi - p);
         }
+      }
+      const bool probe_hit = hit >= 0;
+      const int32_t incl = wave_incl_scan(len);
+      const int32_t T = lane_read(incl, kWave - 1);
+      if (T > 0) {
         wave_sync();
-        remaining = __ballot(len > 0 && s_found[w][l] == kNone);
+        R.excl[l] = incl - len;
+        R.beg[l] = p;
+        R.mid[l] = mid;
+        R.aux[l] = kNone;
+        wave_sync();
+        walk_rows(R, T, len, edges, [&](int o, int64_t q) {
+          const uint32_t x = uint32_t(a.dcol[q]);
+          return q < R.mid[o] ? bit_test(a.Fd, x) : bit_test(Fn, x);
+        });
+        const int32_t fe = R.aux[l];
+        if (len > 0 && fe != kNone) hit = p + (fe - (incl - len));
       }
-      const int32_t fe = s_found[w][l];
-      if (len > 0 && fe != kNone) hit = p + (fe - (incl - len));
-      wave_sync();
+      if (ok && hit >= 0) {
+        atomicOr(&wgot[wo], 1u << bit);
+        int32_t par = px;
+        if (!probe_hit) {
+          const int32_t x = a.dcol[hit];
+          par = hit < mid ? a.vid_of[x] : x;
+        }
+        a.put(vk, par, L + 1);
+        ++claimed;
+      }
     }
-    // each candidate delegate is one lane's, and no other kernel claims
-    // delegates while this one runs: set the bit without reading it back
-    const bool won = ok && hit >= 0;
-    wave_bit_set(Cd, uint32_t(k), ok, won);
-    if (won) {
-      int32_t par = px;
-      if (!probe_hit) {
-        const int32_t x = dcol[hit];
-        par = hit < mid ? vid_of[x] : x;
-      }
-      out.put(vk, par);
-      ++claimed;
+    wave_sync();
+    const uint32_t got = wgot[l];
+    if (got) {
+      a.Cd[w] = cd | got;
+      with_dn += __popc(got & dnm);
     }
   }
   // units: candidates scanned, edges inspected, claimed
-  block_add4(cur->units[DSBFS_K_BU_DELEG], cands, edges, claimed, 0, sh);
+  count_units(a, S, DSBFS_K_BU_DELEG, cands, edges, claimed, 0);
 }
 
-// Level close: the next delegate frontier is what was claimed this level
-// (Fd = Cd & ~Vd, Vd = Cd); the normal frontier bitmap is cleared either
-// word by word under this level's queue (small levels) or, when the host has
-// cleared it in bulk, not at all (clear_fn = 0).
-__global__ void k_close(uint32_t *Vd, uint32_t *Fd, const uint32_t *Cd, int32_t dwords,
-                        uint32_t *Fn, int64_t nwords, const int32_t *Q, DevCtl *c,
-                        LevelCtr *next) {
-  if (c->done) return;
-  const int clear_fn = c->clear_fn, bulk_fn = c->bulk_fn;
-  const int64_t qn = c->qn;
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  const int64_t t0 = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  for (int64_t w = t0; w < dwords; w += stride) {
-    const uint32_t cw = Cd[w];
-    Fd[w] = cw & ~Vd[w];
-    Vd[w] = cw;
-  }
-  if (bulk_fn) {
-    for (int64_t w = t0; w < nwords; w += stride) Fn[w] = 0;
-  } else if (clear_fn) {
-    for (int64_t i = t0; i < qn; i += stride) Fn[Q[i] >> 5] = 0;
-  }
-  // Open the next level: clear its counters (this level's "previous" ones,
-  // which nothing reads after the decision) and fix its depth and whether it
-  // marks the normal frontier bitmap (only read by a bottom-up nd visit,
-  // impossible once no unvisited delegate has a dn edge).
-  if (blockIdx.x == 0) {
-    unsigned long long *w = reinterpret_cast<unsigned long long *>(next);
-    for (int i = threadIdx.x; i < int(sizeof(LevelCtr) / 8); i += blockDim.x) w[i] = 0;
-    if (threadIdx.x == 0) {
-      c->level += 1;
-      c->level1 = c->level + 1;
-      c->mark_fn = c->rem[1] > 0 || (c->nn_do && c->rem[3] > 0);
-    }
+// Bottom-up dn and dd/nd of level L, of the parts asked for. They touch
+// different bitmaps (Vn and the queues; Cd), so one phase runs both.
+template <int NW, int parts>
+__device__ __forceinline__ void backward(const Search &a, Scratch<NW> &S, int L) {
+  uint32_t with_dn = 0;
+  if ((parts & kNormal) && S.plan.dn_bu) bu_normal(a, S, L);
+  __syncthreads();
+  if ((parts & kDeleg) && (S.plan.dd_bu || S.plan.nd_bu)) {
+    bu_deleg(a, S, L, with_dn);
+    block_acc(&S.red[kClDn], with_dn);
+    red_flush(S, a.ctl->ctr[L % 3], kClDn, kClDn + 1);
   }
 }
-
 // ---------------------------------------------------------------------------
-// level control on the device
+// level by level: one kernel per phase
 // ---------------------------------------------------------------------------
-__global__ void k_ctl_init(DevCtl *c, DevCtl init) { *c = init; }
+// Every per-level kernel is a grid-stride loop over a bounded grid (8
+// workgroups per CU), reads the level's state and returns at once when its
+// plan has no work. Host launches run one level ahead of the device.
+constexpr int kBS = 256;
+constexpr int kNW = kBS / kWave;
 
-// The decision itself (one thread), into the level's status record.
-__device__ void decide_level(DevCtl *__restrict__ c, const LevelCtr *__restrict__ cur,
-                             const LevelCtr *__restrict__ prev, LevelStatus *st) {
-  const int32_t L = c->level;
-  const int64_t qn = lc_qn(prev), fdn = int64_t(cur->nd_list);
-  c->units[DSBFS_K_PREV_NORMAL][0] += qn;
-  c->units[DSBFS_K_PREV_DELEG][0] += fdn;
-  c->deg_sum += cur->fv_nn + cur->fv_nd + cur->fv_dd + cur->fv_dn;
-  if (c->nc_pending) {
-    // length of the candidate list the previous bottom-up normal pass compacted
-    c->nc = lc_nc(prev);
-    c->units[DSBFS_K_BU_NORMAL][4] += lc_nc(prev);
-    c->nc_pending = 0;
-  }
-  if (qn == 0 && fdn == 0) {
-    c->done = 1;
-    st->level = L;
-    st->done = 1;
+// Loads the state of level L into the block; false if the search has ended.
+template <int NW>
+__device__ __forceinline__ bool level_enter(const Search &a, Scratch<NW> &S, int L) {
+  const uint32_t *from = reinterpret_cast<const uint32_t *>(&a.ctl->st[L & 1]);
+  uint32_t *to = reinterpret_cast<uint32_t *>(&S.st);
+  for (int i = threadIdx.x; i < int(sizeof(LevelState) / 4); i += blockDim.x) to[i] = from[i];
+  units_open(a, S);
+  if (S.st.done) return false;
+  level_open(a, S, L);
+  return true;
+}
+
+template <int parts>
+__global__ void __launch_bounds__(kBS, 8) k_previsit(Search a, int L) {
+  __shared__ Scratch<kNW> S;
+  if (!level_enter(a, S, L)) return;
+  previsit<kNW, parts>(a, S, L);
+  units_close(a, S);
+}
+
+__global__ void __launch_bounds__(kBS, 8) k_list(Search a, int L) {
+  __shared__ Scratch<kNW> S;
+  if (!level_enter(a, S, L)) return;
+  level_plan(a, S, L);
+  if (S.plan.dd_td || S.plan.dn_td) list_deleg(a, S);
+}
+
+template <int parts>
+__global__ void __launch_bounds__(kBS, 8) k_forward(Search a, int L) {
+  __shared__ Scratch<kNW> S;
+  if (!level_enter(a, S, L)) return;
+  level_plan(a, S, L);
+  if (S.ns.done) return;
+  forward<kNW, parts>(a, S, L);
+  units_close(a, S);
+}
+
+__global__ void __launch_bounds__(kBS, 8) k_bu_nn(Search a, int L) {
+  __shared__ Scratch<kNW> S;
+  if (!level_enter(a, S, L)) return;
+  level_plan(a, S, L);
+  if (!S.plan.nn_bu) return;
+  bu_nn(a, S, L);
+  units_close(a, S);
+}
+
+// Publishes a level's record to the host: the record, then its sequence number.
+template <int NW>
+__device__ void publish(const Search &a, const LevelStatus &rec, int L) {
+  __syncthreads();
+  LevelStatus *const to = a.hs + (L & (kStatusSlots - 1));
+  const uint32_t *f = reinterpret_cast<const uint32_t *>(&rec);
+  uint32_t *t = reinterpret_cast<uint32_t *>(to);
+  for (int i = threadIdx.x; i < int(offsetof(LevelStatus, seq) / 4); i += blockDim.x) t[i] = f[i];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0)
+    __hip_atomic_store(&to->seq, L + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The level's last kernel: bottom-up visits; with kCommit, block 0 also
+// commits the state of the next level and publishes this level's record.
+template <int parts>
+__global__ void __launch_bounds__(kBS, 8) k_backward(Search a, int L) {
+  __shared__ Scratch<kNW> S;
+  LevelStatus &rec = *reinterpret_cast<LevelStatus *>(S.seg);  // segments are not used here
+  const bool commit = (parts & kCommit) && blockIdx.x == 0;
+  if (!level_enter(a, S, L)) {
+    // levels launched behind the last one: the end stays visible to both slots
+    if (commit && threadIdx.x == 0) a.ctl->st[(L + 1) & 1].done = 1;
     return;
   }
-  const int64_t q[3] = {int64_t(cur->q_dd), int64_t(cur->q_dn), int64_t(cur->q_nd)};
-  const int64_t FV[3] = {int64_t(cur->fv_dd), int64_t(cur->fv_dn), int64_t(cur->fv_nd)};
-  // what the normal previsit of this level did (before the counts move on)
-  c->mark_fn = level_marks_fn(c, q[1]);
-  c->rem[0] -= q[0];
-  c->rem[1] -= q[1];
-  c->rem[2] -= q[2];
-  const int64_t q_nn = int64_t(cur->q_nn), fv_nn = int64_t(cur->fv_nn);
-  c->rem[3] -= q_nn;
-  const int64_t U[3] = {c->rem[0], c->rem[2], c->rem[1]};
-  const int64_t S[3] = {c->rem[0], c->rem[1], c->rem[2]};
-  double BV[3];
-  auto choose = [&](int k, int64_t qk, int64_t fvk, double bvk) {
-    int d = c->dir[k];
-    if (c->forced == 1) d = 0;
-    else if (c->forced == 2) d = L >= 1 ? 1 : 0;
-    else if (c->forced == 3)
-      d = int(mix64(c->forced_seed + uint64_t(L) * 3 + k + (k == 3 ? 0x5bd1e995ull : 0)) & 1);
-    else if (qk > 0) {
-      if (d == 0 && double(fvk) > c->f0[k] * bvk) d = 1;
-      else if (d == 1 && double(fvk) < c->f1[k] * bvk) d = 0;
+  level_plan(a, S, L, commit ? &rec : nullptr);
+  if (commit) {
+    if (threadIdx.x == 0) {
+      a.ctl->st[(L + 1) & 1] = S.ns;
+      if (a.count) account_level(a, S.st, S.ns, S.now, S.qn, S.nc_prev, S.plan, a.ctl->tot);
     }
-    c->dir[k] = d;
-  };
-  for (int k = 0; k < 3; ++k) {
-    BV[k] = bv_estimate(U[k], q[k], S[k]);
-    choose(k, q[k], FV[k], BV[k]);
-    st->rec.q[k] = q[k];
-    st->rec.s[k] = S[k];
-    st->rec.U[k] = U[k];
-    st->rec.FV[k] = FV[k];
-    st->rec.BV[k] = BV[k];
-    st->rec.dir[k] = c->dir[k];
+    publish<kNW>(a, rec, L);
   }
-  // nn (nn_do only): U = s = unvisited normals with an nn edge (symmetric)
-  const double BV_nn = c->nn_do ? bv_estimate(c->rem[3], q_nn, c->rem[3]) : 0.0;
-  if (c->nn_do) choose(3, q_nn, fv_nn, BV_nn);
-  st->rec.U_nn = c->nn_do ? c->rem[3] : 0;
-  st->rec.s_nn = st->rec.U_nn;
-  st->rec.BV_nn = BV_nn;
-  st->rec.dir_nn = c->nn_do ? c->dir[3] : 0;
-  st->rec.FV_nn = fv_nn;
-  st->rec.q_nn = q_nn;
-  st->rec.frontier_normal = qn;
-  st->rec.frontier_delegate = fdn;
-  const int nn_td = c->nn_do && c->dir[3] == 0 && q_nn > 0;
-  const int nn_bu = c->nn_do && c->dir[3] == 1 && q_nn > 0 && c->rem[3] > 0;
-  // without nn_do, nn went top-down inside k_normal_level already
-  const int dd_td = c->dir[0] == 0 && q[0] > 0, dn_td = c->dir[1] == 0 && q[1] > 0;
-  const int nd_td = c->dir[2] == 0 && q[2] > 0;
-  const int dd_bu = c->dir[0] == 1 && q[0] > 0 && U[0] > 0;
-  const int dn_bu = c->dir[1] == 1 && q[1] > 0 && U[1] > 0 && c->nc > 0;
-  const int nd_bu = c->dir[2] == 1 && q[2] > 0 && U[2] > 0;
-  // large levels clear the normal frontier bitmap with one streaming fill
-  // instead of one scattered store per queue entry
-  const int bulk_fn = c->mark_fn && qn * 16 > c->nwords;
-  c->nd_td = nd_td;
-  c->dd_td = dd_td;
-  c->dn_td = dn_td;
-  c->dn_bu = dn_bu;
-  c->dd_bu = dd_bu;
-  c->nd_bu = nd_bu;
-  c->nn_td = nn_td;
-  c->nn_bu = nn_bu;
-  c->bulk_fn = bulk_fn;
-  c->clear_fn = c->mark_fn && !bulk_fn;
-  c->qn = qn;
-  c->fdn = fdn;
-  if (dn_bu) {
-    c->cin_sel = c->cand_state;
-    c->cout_sel = c->cand_state < 0 ? 0 : (c->cand_state ^ 1);
-    c->cand_state = c->cout_sel;
-    c->nc_pending = 1;
-  }
-  if (nd_td) c->units[DSBFS_K_TD_NORMAL][0] += qn;
-  if (nn_td) c->units[DSBFS_K_TD_NN][0] += qn;
-  if (dd_td || dn_td) c->units[DSBFS_K_TD_DELEG][0] += fdn;
-  c->units[DSBFS_K_CLOSE][0] += bulk_fn ? c->nwords / 4 : qn;
-  const int plan[10] = {nd_td, dd_td, dn_td, dn_bu, dd_bu, nd_bu, bulk_fn, c->mark_fn, nn_td,
-                        nn_bu};
-  for (int i = 0; i < 10; ++i) st->plan[i] = plan[i];
-  st->level = L;
-  st->done = 0;
+  if (S.ns.done) return;
+  backward<kNW, parts>(a, S, L);
+  units_close(a, S);
 }
 
-// Direction decision of Section IV-B for dd, dn, nd (indices 0, 1, 2) from
-// this level's previsit counts, in FP64 with the same expression as the
-// oracle's replay, and the plan of the rest of the level. One wave: the work
-// units are summed by 36 lanes, the decision is made by lane 0 into an LDS
-// record, and the record goes to pinned host memory one word per lane.
-__global__ void k_decide(DevCtl *c, const LevelCtr *cur, const LevelCtr *prev,
-                         LevelStatus *hs) {
-  if (c->done) return;
-  __shared__ LevelStatus rec;
-  __shared__ int32_t slot;
-  const int t = threadIdx.x;
-  // the previous level's kernels are complete: their work units
-  if (t < DSBFS_NUM_KERNELS * 4) c->units[t / 4][t % 4] += prev->units[t / 4][t % 4];
-  __syncthreads();
-  if (t == 0) {
-    decide_level(c, cur, prev, &rec);
-    slot = rec.level & (kStatusSlots - 1);
+// Mode 0, one level: the queue's degrees, then the expansion.
+template <int NW> __device__ __forceinline__ bool plain_open(const Search &a, Scratch<NW> &S, int L) {
+  if (threadIdx.x == 0) {
+    S.qn = int64_t(ctr_load(&a.ctl->ctr[(L + 2) % 3].qn_nc.v) & 0xffffffffull);
+    S.plan = Plan{};
   }
   __syncthreads();
-  const uint32_t *from = reinterpret_cast<const uint32_t *>(&rec);
-  uint32_t *to = reinterpret_cast<uint32_t *>(hs + slot);
-  for (int i = t; i < int(sizeof(LevelStatus) / 4); i += blockDim.x) to[i] = from[i];
+  return S.qn > 0;
+}
+__global__ void __launch_bounds__(kBS, 8) k_plain_list(Search a, int L) {
+  __shared__ Scratch<kNW> S;
+  ctr_clear(a.ctl->ctr[(L + 1) % 3]);
+  if (plain_open(a, S, L)) list_plain(a, S, L);
 }
 
-// Exclusive prefix sum of the top-down row lengths of the frontier delegates
-// (count on the device): tile sums, a scan of the tile sums in one block, and
-// the per-tile scans. Grids cover every delegate; tiles past the count return.
-constexpr int kScanItems = 8, kScanTile = kBS * kScanItems;
-
-__device__ __forceinline__ int64_t block_excl_scan_i64(int64_t v, int64_t *sh, int64_t *total) {
-  const int w = threadIdx.x / kWave, l = lane_id(), nw = blockDim.x / kWave;
-  const int64_t incl = wave_incl_scan(v);
-  if (l == kWave - 1) sh[w] = incl;
-  __syncthreads();
-  int64_t before = 0, all = 0;
-  for (int i = 0; i < nw; ++i) {
-    before += i < w ? sh[i] : 0;
-    all += sh[i];
-  }
-  *total = all;
-  __syncthreads();
-  return before + incl - v;
-}
-
-// First pass: the top-down length of each frontier delegate's row (dd part
-// if dd goes forward, dn part if dn does) and the sum of each tile.
-__global__ void __launch_bounds__(kBS) k_dscan_reduce(const int32_t *dlist, const uint64_t *doff,
-                                                      const LevelCtr *cur, const DevCtl *c,
-                                                      int32_t *len, int64_t *bsum) {
-  if (c->done || !(c->dd_td || c->dn_td)) return;
-  __shared__ int64_t sh[kNW];
-  const int dd_td = c->dd_td, dn_td = c->dn_td;
-  const int64_t N = int64_t(cur->nd_list);
-  const int64_t base = int64_t(blockIdx.x) * kScanTile;
-  if (base >= N) return;
-  int64_t x = 0;
-  for (int k = 0; k < kScanItems; ++k) {
-    const int64_t i = base + int64_t(threadIdx.x) * kScanItems + k;
-    if (i < N) {
-      const int32_t kd = dlist[i];
-      const uint64_t w0 = doff[kd], w1 = doff[kd + 1];
-      const int64_t dd = row_first(w0), dn = row_start(w1) - row_start(w0) - dd;
-      const int32_t l = int32_t((dd_td ? dd : 0) + (dn_td ? dn : 0));
-      len[i] = l;
-      x += l;
-    }
-  }
-  int64_t tot;
-  (void)block_excl_scan_i64(x, sh, &tot);
-  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
-}
-
-__global__ void __launch_bounds__(1024) k_dscan_top(const int64_t *bsum, int64_t *bscan,
-                                                    int64_t *out, const LevelCtr *cur,
-                                                    const DevCtl *c) {
-  if (c->done || !(c->dd_td || c->dn_td)) return;
-  __shared__ int64_t sh[1024 / kWave];
-  const int64_t N = int64_t(cur->nd_list);
-  const int64_t nb = (N + kScanTile - 1) / kScanTile;
-  int64_t carry = 0;
-  for (int64_t i0 = 0; i0 < nb; i0 += blockDim.x) {
-    const int64_t i = i0 + threadIdx.x;
-    const int64_t x = i < nb ? bsum[i] : 0;
-    int64_t tot;
-    const int64_t ex = block_excl_scan_i64(x, sh, &tot);
-    if (i < nb) bscan[i] = carry + ex;
-    carry += tot;
-  }
-  if (threadIdx.x == 0) out[N] = carry;
-}
-
-__global__ void __launch_bounds__(kBS) k_dscan_down(const int32_t *len, int64_t *out,
-                                                    const LevelCtr *cur, const DevCtl *c,
-                                                    const int64_t *bscan) {
-  if (c->done || !(c->dd_td || c->dn_td)) return;
-  __shared__ int64_t sh[kNW];
-  const int64_t N = int64_t(cur->nd_list);
-  const int64_t base = int64_t(blockIdx.x) * kScanTile;
-  if (base >= N) return;
-  const int64_t t0 = base + int64_t(threadIdx.x) * kScanItems;
-  int64_t x = 0;
-  for (int k = 0; k < kScanItems; ++k)
-    if (t0 + k < N) x += len[t0 + k];
-  int64_t tot;
-  int64_t run = bscan[blockIdx.x] + block_excl_scan_i64(x, sh, &tot);
-  for (int k = 0; k < kScanItems; ++k)
-    if (t0 + k < N) {
-      out[t0 + k] = run;
-      run += len[t0 + k];
-    }
-}
-
-// ---------------------------------------------------------------------------
-// plain top-down (mode 0)
-// ---------------------------------------------------------------------------
-// Runs of consecutive edges per thread in the plain top-down expansion.
-constexpr int kRun = 4;
-
-__global__ void k_plain_len(const int32_t *Q, const LevelCtr *prev, const int64_t *poff,
-                            int32_t *len) {
-  const int64_t qn = lc_qn(prev);
-  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < qn;
-       i += int64_t(gridDim.x) * blockDim.x) {
-    const int32_t u = Q[i];
-    len[i] = int32_t(poff[u + 1] - poff[u]);
-  }
-}
-
-__global__ void __launch_bounds__(kBS) k_plain_expand(const int32_t *Q, const LevelCtr *prev,
-                                                      const int64_t *scan, const int64_t *poff,
-                                                      const int32_t *pcol, Out out, uint32_t *Vn,
-                                                      int32_t *Qnext, LevelCtr *cur) {
-  __shared__ int32_t qbuf[kQCap];
-  __shared__ int qcount;
-  __shared__ unsigned long long qbase;
-  __shared__ unsigned long long sh[4 * kNW];
-  BlockAppend qa{qbuf, &qcount, &qbase, kQCap, &cur->qn_nc, Qnext};
-  qa.init();
-  const int64_t qn = lc_qn(prev);
-  const int64_t E = scan[qn];
-  const int64_t nruns = (E + kRun - 1) / kRun;
-  unsigned long long claimed = 0;
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  for (int64_t r0 = int64_t(blockIdx.x) * blockDim.x; r0 < nruns; r0 += stride) {
-    const int64_t r = r0 + threadIdx.x;
-    int64_t e = r * kRun;
-    const int64_t eend = min(e + kRun, E);
-    int64_t idx = r < nruns ? seg_search(scan, qn, e) : 0;
-    for (int t = 0; t < kRun; ++t, ++e) {
-      bool won = false;
-      int32_t v = 0;
-      if (r < nruns && e < eend) {
-        while (scan[idx + 1] <= e) ++idx;
-        const int32_t u = Q[idx];
-        v = pcol[poff[u] + (e - scan[idx])];
-        won = bit_claim(Vn, uint32_t(v));
-        if (won) {
-          out.put(v, u);
-          ++claimed;
-        }
+__global__ void __launch_bounds__(kBS, 8) k_plain_expand(Search a, int L) {
+  __shared__ Scratch<kNW> S;
+  LevelStatus &rec = *reinterpret_cast<LevelStatus *>(S.seg);  // before the segments
+  units_open(a, S);
+  const bool work = plain_open(a, S, L);
+  if (blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < int(sizeof(LevelStatus) / 4); i += blockDim.x)
+      reinterpret_cast<uint32_t *>(&rec)[i] = 0;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      rec.done = !work;
+      rec.level = L;
+      rec.rec.frontier_normal = S.qn;
+      if (a.count && work) {
+        a.ctl->tot.units0[DSBFS_K_PLAIN] += S.qn;
+        ++a.ctl->tot.launches[DSBFS_K_PLAIN];
       }
-      qa.push(won, v);
     }
-    qa.maybe_flush(kBS * kRun + kBS);
+    publish<kNW>(a, rec, L);
+    __syncthreads();
   }
-  qa.flush();
-  unsigned long long entries = 0, edges = 0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    entries = (unsigned long long)qn;
-    edges = (unsigned long long)E;
-  }
-  // units: queue entries, edges, claimed
-  block_add4(cur->units[DSBFS_K_PLAIN], entries, edges, claimed, 0, sh);
+  if (!work) return;
+  uint32_t none = 0;
+  expand_list<true>(a, S, L, none);
+  units_close(a, S);
 }
 
+// ---------------------------------------------------------------------------
+// one launch: all levels of a search in one resident grid
+// ---------------------------------------------------------------------------
+// For graphs whose levels are a few microseconds of work: a kernel boundary
+// costs 4.5 us (12 kernels and a 13 us graph hand-over per level before:
+// search_rmat22's 642 us were 380 us of dispatch), a grid barrier of 64 wide
+// blocks 2.5 us and there are two or three per level. Every block follows the
+// search's state by itself, so a level needs no other exchange than its
+// counters.
+constexpr int kWideNW = 16;
+
+// How block 0 left: 1 done, -1 a barrier wait exceeded its bound.
+__device__ __forceinline__ void one_launch_end(const Search &a, int levels, bool ok) {
+  if (blockIdx.x != 0) return;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    a.ctl->levels = levels;
+    a.hs->level = levels;
+    __threadfence_system();
+    __hip_atomic_store(&a.hs->seq, ok ? 1 : -1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
+__global__ void __launch_bounds__(1024) k_search(Search a) {
+  __shared__ Scratch<kWideNW> S;
+  GridBar &bar = a.ctl->bar;
+  unsigned long long ep = 0;
+  if (threadIdx.x == 0) S.st = a.ctl->st[0];
+  units_open(a, S);
+  int L = 0;
+  bool ok = true;
+  for (;; ++L) {
+    level_open(a, S, L);
+    previsit<kWideNW, kDeleg | kNormal | kClear>(a, S, L);
+    if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+    level_plan(a, S, L);
+    if (a.count && blockIdx.x == 0 && threadIdx.x == 0)
+      account_level(a, S.st, S.ns, S.now, S.qn, S.nc_prev, S.plan, a.ctl->tot);
+    if (S.ns.done) break;
+    const Plan &p = S.plan;
+    if (p.dd_td || p.dn_td) {
+      list_deleg(a, S);
+      if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+    }
+    if (p.dd_td || p.dn_td || p.nd_td || p.nn_td) {
+      forward<kWideNW, kDeleg | kNormal | kNn>(a, S, L);
+      if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+    }
+    if (p.nn_bu) {
+      bu_nn(a, S, L);
+      if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+    }
+    if (p.dn_bu || p.dd_bu || p.nd_bu) {
+      backward<kWideNW, kDeleg | kNormal>(a, S, L);
+      if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) S.st = S.ns;
+    __syncthreads();
+  }
+  units_close(a, S);
+  one_launch_end(a, L, ok);
+}
+
+__global__ void __launch_bounds__(1024) k_plain_search(Search a) {
+  __shared__ Scratch<kWideNW> S;
+  GridBar &bar = a.ctl->bar;
+  unsigned long long ep = 0;
+  units_open(a, S);
+  int L = 0;
+  bool ok = true;
+  for (;; ++L) {
+    if (!plain_open(a, S, L)) break;
+    ctr_clear(a.ctl->ctr[(L + 1) % 3]);
+    if (a.count && blockIdx.x == 0 && threadIdx.x == 0) {
+      a.ctl->tot.units0[DSBFS_K_PLAIN] += S.qn;
+      ++a.ctl->tot.launches[DSBFS_K_PLAIN];
+    }
+    list_plain(a, S, L);
+    if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+    uint32_t none = 0;
+    expand_list<true>(a, S, L, none);
+    if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+  }
+  units_close(a, S);
+  one_launch_end(a, L, ok);
+}
 
 // Number of resident waves worth of blocks for grid-stride kernels.
 int stride_grid() { return 256 * 8; }
+
+// Shape of a one-launch search (blocks = 0: level by level instead). A barrier
+// costs more the more blocks there are, a level's work less, so the grid grows
+// with the graph; plain top-down searches read every edge, about four times
+// the work per vertex. Measured (us a search, RMAT edge factor 16, parents;
+// 32x256 / 64x256 / 64x512 / 128x512 / 256x512 / 256x1024 / level by level):
+//   n = 2^12   152 /  155 /  159 / 169 / 190 / 200 / 225
+//   n = 2^16   141 /  133 /  135 / 142 / 166 / 184 / 203
+//   n = 2^18   371 /  272 /  220 / 221 / 249 / 266 / 290
+//   n = 2^20   597 /  386 /  296 / 259 / 278 / 306 / 366
+//   n = 2^22  2027 / 1115 /  718 / 490 / 421 / 437 / 501
+//   n = 2^23  4484 / 2375 / 1468 / 914 / 695 / 654 / 733
+//   n = 2^26     - /    - /    - /   - / 3102 / 2628 / 2535
+// plain, n = 2^16  264 / 206 / 181 / 186 / 224 / 292 / 284
+// plain, n = 2^20 3728 / 2058 / 1457 / 1030 / 903 / 943 / 957
+struct OneLaunch {
+  int blocks, threads;
+};
+
+OneLaunch one_launch_shape(const Graph *g, int mode) {
+  const int64_t w = int64_t(g->n) * (mode == 0 ? 4 : 1);
+  if (w <= (1 << 15)) return {32, 256};
+  if (w <= (1 << 17)) return {64, 256};
+  if (w <= 3 << 17) return {64, 512};
+  if (w <= 3 << 19) return {128, 512};
+  if (w <= 3 << 21) return {256, 512};
+  if (w <= 3 << 22) return {256, 1024};
+  return {0, 0};
+}
 
 }  // namespace
 
@@ -1209,20 +1762,13 @@ Workspace *workspace_create(const Graph *g, int32_t max_lanes) {
     ws->q0.alloc(al, size_t(n) * 4, s);
     ws->q1.alloc(al, size_t(n) * 4, s);
     ws->dlist.alloc(al, size_t(d) * 4, s);
-    ws->dcand.alloc(al, size_t(d) * 4, s);
     ws->dlen.alloc(al, size_t(std::max(n, d)) * 4, s);
     ws->dscan.alloc(al, size_t(std::max(n, d) + 1) * 8, s);
     ws->c0.alloc(al, size_t(g->st.n_ndsrc) * 4, s);
     ws->c1.alloc(al, size_t(g->st.n_ndsrc) * 4, s);
-    ws->ctr.alloc(al, 2 * sizeof(LevelCtr), s);
-    ws->scan_tmp.alloc(al, scan_tmp_bytes(std::max(n, d)), s);
-    HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&ws->hctr), 2 * sizeof(LevelCtr),
-                         hipHostMallocDefault));
-    ws->dctl.alloc(al, sizeof(DevCtl), s);
-    ws->dtiles.alloc(al, 2 * dtiles_half(d), s);
+    ws->ctl.alloc(al, sizeof(SearchCtl), s);
     HIPCHK(hipHostMalloc(&ws->hstat, kStatusSlots * sizeof(LevelStatus), hipHostMallocDefault));
     std::memset(ws->hstat, 0, kStatusSlots * sizeof(LevelStatus));
-    for (hipEvent_t &e : ws->lev_ev) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     return ws;
   } catch (...) {
     delete ws;
@@ -1251,18 +1797,59 @@ static dsbfs_run_opts default_opts() {
 
 void run_opts_default(dsbfs_run_opts *o) { *o = default_opts(); }
 
+// Blocks of grids that wait for their own blocks (one-launch searches, the
+// persistent multi-source kernel) may not be resident in part beside each
+// other: two such grids could hold the compute units each needs to complete.
+// Each takes its blocks' worth of compute units from its device's gate before
+// the launch and returns them once the launch has completed.
+namespace {
+struct ResidentGate {
+  std::mutex mu;
+  std::condition_variable cv;
+  int used = 0;
+};
+ResidentGate &resident_gate() {
+  static ResidentGate gates[64];
+  int dev = 0;
+  HIPCHK(hipGetDevice(&dev));
+  if (dev < 0 || dev >= 64) fail(DSBFS_ERR_INVALID_ARG, "device index out of range");
+  return gates[dev];
+}
+constexpr int kGateUnits = 256;  // compute units
+}  // namespace
 
-// Per-kernel launch counts, unit totals and (optionally) HIP-event timing.
+ResidentLease::ResidentLease(int blocks, bool wait) {
+  ResidentGate &g = resident_gate();
+  std::unique_lock<std::mutex> lk(g.mu);
+  const int want = std::min(blocks, kGateUnits);
+  if (wait) g.cv.wait(lk, [&] { return g.used + want <= kGateUnits; });
+  if (g.used + want > kGateUnits) return;
+  g.used += want;
+  units = want;
+  gate = &g;
+}
+
+ResidentLease::~ResidentLease() {
+  if (!gate) return;
+  ResidentGate &g = *static_cast<ResidentGate *>(gate);
+  {
+    std::lock_guard<std::mutex> lk(g.mu);
+    g.used -= units;
+  }
+  g.cv.notify_all();
+}
+
+namespace {
+
+// Per-kernel HIP-event timing of a profiled search.
 struct Prof {
   bool on = false;
   hipStream_t s = nullptr;
   Workspace *ws = nullptr;
   size_t next = 0;
   struct Span { int k, b, e, level; };
-  int level = -1;  // level whose kernels are being launched (-1: init)
   std::vector<Span> spans;
-  int64_t launches[DSBFS_NUM_KERNELS] = {};
-  double units[DSBFS_NUM_KERNELS][6] = {};
+  int64_t launches_seen[DSBFS_NUM_KERNELS] = {};
 
   hipEvent_t ev() {
     if (next == ws->events.size()) {
@@ -1272,252 +1859,244 @@ struct Prof {
     }
     return ws->events[next++];
   }
-  int begin() {
-    if (!on) return -1;
-    const int i = int(next);
+  template <class F> void timed(int k, int level, F &&f) {
+    if (!on) {
+      f();
+      return;
+    }
+    const int b = int(next);
     HIPCHK(hipEventRecord(ev(), s));
-    return i;
-  }
-  void end(int k, int b) {
-    ++launches[k];
-    if (!on) return;
-    const int i = int(next);
+    f();
+    const int e = int(next);
     HIPCHK(hipEventRecord(ev(), s));
-    spans.push_back({k, b, i, level});
-  }
-  void add_level(const LevelCtr &c) {
-    for (int k = 0; k < DSBFS_NUM_KERNELS; ++k)
-      for (int j = 0; j < 4; ++j) units[k][j] += double(c.units[k][j]);
+    spans.push_back({k, b, e, level});
   }
 };
 
-namespace {
+Search search_args(const Graph *g, Workspace *ws, const dsbfs_run_opts &o, int32_t source,
+                   int32_t *depth, int32_t *parent, bool count) {
+  Search a{};
+  a.noff = g->noff.as<uint64_t>();
+  a.doff = g->doff.as<uint64_t>();
+  a.nlen = g->nlen.as<uint16_t>();
+  a.ncol = g->ncol.as<int32_t>();
+  a.nnoff = g->nnoff.as<uint32_t>();
+  a.nncol = g->nncol.as<int32_t>();
+  a.dcol = g->dcol.as<int32_t>();
+  a.vid_of = g->vid_of.as<int32_t>();
+  a.ndsrc = g->ndsrc.as<int32_t>();
+  a.nds_col = g->nds_col.as<int32_t>();
+  a.nnsrc = g->nnsrc.as<int32_t>();
+  a.nds_off = g->nds_off.as<int64_t>();
+  a.nds_first = g->nds_first.as<int2>();
+  a.dd_first = g->dd_first.as<int2>();
+  a.ddm = g->ddsrc_mask.as<uint32_t>();
+  a.dnm = g->dnsrc_mask.as<uint32_t>();
+  a.poff = g->poff.as<int64_t>();
+  a.pcol = g->pcol.as<int32_t>();
+  a.did = g->did.as<int32_t>();
+  a.n = g->n;
+  a.d = g->d;
+  a.nwords = g->nwords();
+  a.dwords = g->dwords();
+  a.n_ndsrc = g->st.n_ndsrc;
+  a.n_nnsrc = g->st.n_nnsrc;
+  a.depth = depth;
+  a.parent = parent;
+  a.Vn = ws->Vn.as<uint32_t>();
+  // two normal frontier bitmaps alternate by level; the second lies in dlen,
+  // which single-source searches do not use otherwise
+  a.Fn0 = ws->Fn.as<uint32_t>();
+  a.Fn1 = ws->dlen.as<uint32_t>();
+  a.Vd = ws->Vd.as<uint32_t>();
+  a.Fd = ws->Fd.as<uint32_t>();
+  a.Cd = ws->Cd.as<uint32_t>();
+  a.Q0 = ws->q0.as<int32_t>();
+  a.Q1 = ws->q1.as<int32_t>();
+  a.C0 = ws->c0.as<int32_t>();
+  a.C1 = ws->c1.as<int32_t>();
+  a.dlist = ws->dlist.as<int32_t>();
+  a.dscan = ws->dscan.as<int64_t>();
+  a.ctl = ws->ctl.as<SearchCtl>();
+  a.hs = static_cast<LevelStatus *>(ws->hstat);
+  for (int k = 0; k < 3; ++k) {
+    a.f0[k] = o.factor0[k];
+    a.f1[k] = o.factor1[k];
+  }
+  a.f0[3] = o.factor0_nn;
+  a.f1[3] = o.factor1_nn;
+  a.forced_seed = o.forced_seed;
+  a.forced = o.forced;
+  a.nn_do = o.nn_do;
+  a.count = count;
+  a.source = source;
+  a.mode = o.mode;
+  return a;
+}
 
-// The kernels of one level of degree-separated DOBFS (queue parity p: the
-// level reads Q[p] and ctr[p ^ 1], writes Q[p ^ 1] and ctr[p]). Every kernel
-// reads the plan from the control block, so the same sequence serves every
-// level and can be captured once.
-struct LevelLaunch {
-  const Graph *g;
-  Workspace *ws;
-  Out out;
-  DevCtl *c;
-  LevelCtr *ctr;
-  int32_t *Q[2], *C[2];
-  uint32_t *Vn, *Fn, *Vd, *Fd, *Cd;
-  LevelStatus *hs;
-  int64_t *bsum, *bscan;
-  bool nn_do;  // nn under the direction decision: its own forward and backward passes
+LevelState first_state(const Graph *g) {
+  LevelState t{};
+  t.cand_state = -1;
+  t.rem[0] = g->st.n_ddsrc;
+  t.rem[1] = g->st.n_dnsrc;
+  t.rem[2] = g->st.n_ndsrc;
+  t.rem[3] = g->st.n_nnsrc;
+  t.nc = g->st.n_ndsrc;
+  return t;
+}
 
-  // skip: kernels left out because they cannot have work (captured level
-  // variants): bit 0 the forward nd visit, bit 1 the forward dd/dn visit and
-  // its prefix sum. Direct launches pass 0.
-  void enqueue(int p, hipStream_t s, Prof *P, int skip = 0) const {
-    const int32_t n = g->n, d = g->d;
-    LevelCtr *cur = ctr + p, *prev = ctr + (p ^ 1);
-    const int SG = stride_grid();
-    auto begin = [&]() { return P ? P->begin() : -1; };
-    auto end = [&](int k, int b) {
-      if (P) P->end(k, b);
-    };
-    // the delegate previsit first: the normal previsit reads its frontier
-    // count (whether Fn is needed this level)
-    int b = -1;
-    if (d > 0) {
-      b = begin();
-      hipLaunchKernelGGL(k_prev_deleg, dim3(grid_for(g->dwords(), kBS, 4096)), dim3(kBS), 0, s,
-                         Fd, g->dwords(), g->doff.as<uint64_t>(), ws->dlist.as<int32_t>(), cur,
-                         static_cast<const DevCtl *>(c));
-      HIPCHK(hipGetLastError());
-      end(DSBFS_K_PREV_DELEG, b);
-    }
-    b = begin();
-    hipLaunchKernelGGL(k_normal_level, dim3(SG), dim3(kBS), 0, s, Q[p], prev,
-                       g->noff.as<uint64_t>(), g->nlen.as<uint16_t>(), g->ncol.as<int32_t>(),
-                       static_cast<const uint32_t *>(g->nnoff.as<uint32_t>()),
-                       static_cast<const int32_t *>(g->nncol.as<int32_t>()), out, Vn, Fn,
-                       static_cast<const DevCtl *>(c), Q[p ^ 1], cur);
+// The kernels of level L, level by level. skip: forward kernels that cannot
+// have work (bit 0 all of them, bit 1 the delegate list).
+void launch_level(const Search &a, int L, int skip, hipStream_t s) {
+  const dim3 G(stride_grid()), B(kBS);
+  if (a.mode == 0) {
+    hipLaunchKernelGGL(k_plain_list, dim3(kSegs), B, 0, s, a, L);
+    hipLaunchKernelGGL(k_plain_expand, G, B, 0, s, a, L);
     HIPCHK(hipGetLastError());
-    end(DSBFS_K_PREV_NORMAL, b);
-    hipLaunchKernelGGL(k_decide, dim3(1), dim3(kWave), 0, s, c, static_cast<const LevelCtr *>(cur),
-                       static_cast<const LevelCtr *>(prev), hs);
-    HIPCHK(hipGetLastError());
-    if (nn_do) {
-      b = begin();
-      hipLaunchKernelGGL(k_td_nn, dim3(SG), dim3(kBS), 0, s, static_cast<const int32_t *>(Q[p]),
-                         static_cast<const DevCtl *>(c), g->noff.as<uint64_t>(),
-                         g->nlen.as<uint16_t>(), g->ncol.as<int32_t>(),
-                         static_cast<const uint32_t *>(g->nnoff.as<uint32_t>()),
-                         static_cast<const int32_t *>(g->nncol.as<int32_t>()), out, Vn, Q[p ^ 1],
-                         cur);
-      HIPCHK(hipGetLastError());
-      end(DSBFS_K_TD_NN, b);
+    return;
+  }
+  hipLaunchKernelGGL((k_previsit<kDeleg | kNormal | kClear>), G, B, 0, s, a, L);
+  if (!(skip & 3) && a.d > 0) hipLaunchKernelGGL(k_list, dim3(kSegs), B, 0, s, a, L);
+  if (!(skip & 1) && (a.d > 0 || a.nn_do))
+    hipLaunchKernelGGL((k_forward<kDeleg | kNormal | kNn>), G, B, 0, s, a, L);
+  if (a.nn_do && a.n_nnsrc > 0) hipLaunchKernelGGL(k_bu_nn, G, B, 0, s, a, L);
+  hipLaunchKernelGGL((k_backward<kDeleg | kNormal | kCommit>), G, B, 0, s, a, L);
+  HIPCHK(hipGetLastError());
+}
+
+// The same level with a kernel per visit, each timed (profile = 1).
+void launch_level_profiled(const Search &a, int L, Prof &P) {
+  const dim3 G(stride_grid()), B(kBS);
+  hipStream_t s = P.s;
+  if (a.mode == 0) {
+    P.timed(DSBFS_K_PLAIN, L, [&] { launch_level(a, L, 0, s); });
+    return;
+  }
+  if (a.d > 0)
+    P.timed(DSBFS_K_PREV_DELEG, L,
+            [&] { hipLaunchKernelGGL((k_previsit<kDeleg>), G, B, 0, s, a, L); });
+  P.timed(DSBFS_K_CLOSE, L, [&] { hipLaunchKernelGGL((k_previsit<kClear>), G, B, 0, s, a, L); });
+  P.timed(DSBFS_K_PREV_NORMAL, L,
+          [&] { hipLaunchKernelGGL((k_previsit<kNormal>), G, B, 0, s, a, L); });
+  if (a.nn_do)
+    P.timed(DSBFS_K_TD_NN, L, [&] { hipLaunchKernelGGL((k_forward<kNn>), G, B, 0, s, a, L); });
+  if (a.d > 0) {
+    P.timed(DSBFS_K_TD_NORMAL, L,
+            [&] { hipLaunchKernelGGL((k_forward<kNormal>), G, B, 0, s, a, L); });
+    P.timed(DSBFS_K_TD_DELEG, L, [&] {
+      hipLaunchKernelGGL(k_list, dim3(kSegs), B, 0, s, a, L);
+      hipLaunchKernelGGL((k_forward<kDeleg>), G, B, 0, s, a, L);
+    });
+  }
+  if (a.nn_do && a.n_nnsrc > 0)
+    P.timed(DSBFS_K_BU_NN, L, [&] { hipLaunchKernelGGL(k_bu_nn, G, B, 0, s, a, L); });
+  P.timed(DSBFS_K_BU_NORMAL, L,
+          [&] { hipLaunchKernelGGL((k_backward<kNormal>), G, B, 0, s, a, L); });
+  P.timed(DSBFS_K_BU_DELEG, L,
+          [&] { hipLaunchKernelGGL((k_backward<kDeleg | kCommit>), G, B, 0, s, a, L); });
+  HIPCHK(hipGetLastError());
+}
+
+// Waits until the device has published level L's record (pinned memory).
+const LevelStatus &await_status(Workspace *ws, int L, hipStream_t s) {
+  LevelStatus *st = static_cast<LevelStatus *>(ws->hstat) + (L & (kStatusSlots - 1));
+  for (int64_t spin = 1;; ++spin) {
+    if (__atomic_load_n(&st->seq, __ATOMIC_ACQUIRE) == L + 1) return *st;
+    if (spin % 4096 == 0) {
+      // the stream running dry (or failing) without the record is an error
+      const hipError_t e = hipStreamQuery(s);
+      if (e == hipErrorNotReady) continue;
+      HIPCHK(e);
+      if (__atomic_load_n(&st->seq, __ATOMIC_ACQUIRE) == L + 1) return *st;
+      fail(DSBFS_ERR_DEVICE, "search ended without a level record");
     }
-    if (d > 0 && !(skip & 1)) {
-      b = begin();
-      hipLaunchKernelGGL(k_td_nd, dim3(SG), dim3(kBS), 0, s, static_cast<const int32_t *>(Q[p]),
-                         static_cast<const DevCtl *>(c), g->noff.as<uint64_t>(),
-                         g->ncol.as<int32_t>(), g->vid_of.as<int32_t>(), out, Cd, cur);
-      HIPCHK(hipGetLastError());
-      end(DSBFS_K_TD_NORMAL, b);
-    }
-    if (d > 0 && !(skip & 2)) {
-      b = begin();
-      const unsigned nb = unsigned((int64_t(d) + kScanTile - 1) / kScanTile);
-      hipLaunchKernelGGL(k_dscan_reduce, dim3(nb), dim3(kBS), 0, s,
-                         static_cast<const int32_t *>(ws->dlist.as<int32_t>()),
-                         g->doff.as<uint64_t>(), static_cast<const LevelCtr *>(cur),
-                         static_cast<const DevCtl *>(c), ws->dlen.as<int32_t>(), bsum);
-      hipLaunchKernelGGL(k_dscan_top, dim3(1), dim3(1024), 0, s, static_cast<const int64_t *>(bsum),
-                         bscan, ws->dscan.as<int64_t>(), static_cast<const LevelCtr *>(cur),
-                         static_cast<const DevCtl *>(c));
-      hipLaunchKernelGGL(k_dscan_down, dim3(nb), dim3(kBS), 0, s, ws->dlen.as<int32_t>(),
-                         ws->dscan.as<int64_t>(), static_cast<const LevelCtr *>(cur),
-                         static_cast<const DevCtl *>(c), static_cast<const int64_t *>(bscan));
-      hipLaunchKernelGGL(k_td_deleg, dim3(SG), dim3(kBS), 0, s, ws->dlist.as<int32_t>(),
-                         ws->dscan.as<int64_t>(), static_cast<const LevelCtr *>(cur),
-                         g->doff.as<uint64_t>(), g->dcol.as<int32_t>(), g->vid_of.as<int32_t>(),
-                         static_cast<const DevCtl *>(c), out, Vn, Cd, Q[p ^ 1], cur);
-      HIPCHK(hipGetLastError());
-      end(DSBFS_K_TD_DELEG, b);
-    }
-    // bottom-up nn (nn_do): after every forward visit of the level, before
-    // the bottom-up dn visit (which then sees its claims as visited)
-    if (nn_do && g->st.n_nnsrc > 0) {
-      b = begin();
-      hipLaunchKernelGGL(k_bu_nn, dim3(SG), dim3(kBS), 0, s, static_cast<const DevCtl *>(c),
-                         g->nnsrc.as<int32_t>(), g->st.n_nnsrc, g->noff.as<uint64_t>(),
-                         g->nlen.as<uint16_t>(), g->ncol.as<int32_t>(),
-                         static_cast<const uint32_t *>(Fn), out, Vn, Q[p ^ 1], cur);
-      HIPCHK(hipGetLastError());
-      end(DSBFS_K_BU_NN, b);
-    }
-    if (d > 0) {
-      if (g->st.n_ndsrc > 0 && !(skip & 4)) {
-        b = begin();
-        hipLaunchKernelGGL(k_bu_normal, dim3(SG), dim3(kBS), 0, s, static_cast<const DevCtl *>(c),
-                           C[0], C[1], g->ndsrc.as<int32_t>(), g->nds_off.as<int64_t>(),
-                           g->nds_col.as<int32_t>(), g->nds_first.as<int2>(),
-                           g->vid_of.as<int32_t>(), static_cast<const uint32_t *>(Fd), out, Vn,
-                           Q[p ^ 1], cur);
-        HIPCHK(hipGetLastError());
-        end(DSBFS_K_BU_NORMAL, b);
+  }
+}
+
+void launch_init(const Search &a, const LevelState &st, hipStream_t s) {
+  hipLaunchKernelGGL(k_init, dim3(grid_for(std::max(a.n, 1), kBS, 4096)), dim3(kBS), 0, s, a, st);
+  HIPCHK(hipGetLastError());
+}
+
+// Level by level; seen gets the records of the levels with a frontier.
+void run_levels(const Graph *g, Workspace *ws, const Search &a, const dsbfs_run_opts &o, Prof &P,
+                std::vector<LevelStatus> &seen, hipStream_t s) {
+  LevelStatus *hs = static_cast<LevelStatus *>(ws->hstat);
+  if (!ws->borrowed)
+    for (int i = 0; i < kStatusSlots; ++i) hs[i].seq = 0;
+  P.timed(DSBFS_K_INIT, -1, [&] { launch_init(a, first_state(g), s); });
+  if (P.on || ws->borrowed) {
+    // a synchronization per level, so that only visits with work keep their
+    // spans; the allocation-free search copies the record from device memory
+    for (int32_t L = 0;; ++L) {
+      const size_t sp0 = P.spans.size();
+      if (P.on) launch_level_profiled(a, L, P);
+      else launch_level(a, L, 0, s);
+      LevelStatus st;
+      if (ws->borrowed)
+        HIPCHK(hipMemcpyAsync(&st, hs + (L & (kStatusSlots - 1)), sizeof(LevelStatus),
+                              hipMemcpyDeviceToHost, s));
+      HIPCHK(hipStreamSynchronize(s));
+      if (!ws->borrowed) st = hs[L & (kStatusSlots - 1)];
+      if (st.seq != L + 1) fail(DSBFS_ERR_DEVICE, "search ended without a level record");
+      if (P.on) {
+        LevelTotals tot;
+        HIPCHK(hipMemcpy(&tot, &a.ctl->tot, sizeof(tot), hipMemcpyDeviceToHost));
+        std::vector<Prof::Span> keep;
+        for (size_t i = sp0; i < P.spans.size(); ++i)
+          if (tot.launches[P.spans[i].k] > P.launches_seen[P.spans[i].k]) keep.push_back(P.spans[i]);
+        for (int k = 0; k < DSBFS_NUM_KERNELS; ++k) P.launches_seen[k] = tot.launches[k];
+        P.spans.resize(sp0);
+        P.spans.insert(P.spans.end(), keep.begin(), keep.end());
       }
-      if (!(skip & 8)) {
-      b = begin();
-      hipLaunchKernelGGL(k_dcand, dim3(grid_for(g->dwords(), kBS, 4096)), dim3(kBS), 0, s,
-                         static_cast<const uint32_t *>(Cd), g->ddsrc_mask.as<uint32_t>(),
-                         g->dnsrc_mask.as<uint32_t>(), g->dwords(), static_cast<const DevCtl *>(c),
-                         ws->dcand.as<int32_t>(), cur);
-      hipLaunchKernelGGL(k_bu_deleg, dim3(SG), dim3(kBS), 0, s, ws->dcand.as<int32_t>(),
-                         static_cast<const LevelCtr *>(cur), g->doff.as<uint64_t>(),
-                         g->dcol.as<int32_t>(), g->dd_first.as<int2>(),
-                         static_cast<const uint32_t *>(Fd), static_cast<const uint32_t *>(Fn),
-                         g->vid_of.as<int32_t>(), static_cast<const DevCtl *>(c), out, Cd, cur);
-      HIPCHK(hipGetLastError());
-      end(DSBFS_K_BU_DELEG, b);
-      }
+      if (st.done) break;
+      seen.push_back(st);
     }
-    b = begin();
-    hipLaunchKernelGGL(k_close, dim3(grid_for(std::max<int64_t>(n, g->dwords()), kBS, 4096)),
-                       dim3(kBS), 0, s, Vd, Fd, static_cast<const uint32_t *>(Cd), g->dwords(), Fn,
-                       int64_t(g->nwords()), static_cast<const int32_t *>(Q[p]), c, prev);
-    HIPCHK(hipGetLastError());
-    end(DSBFS_K_CLOSE, b);
+    return;
   }
-};
-
-LevelLaunch level_launch(const Graph *g, Workspace *ws, const Out &out, bool nn_do) {
-  LevelLaunch ll{};
-  ll.nn_do = nn_do;
-  ll.g = g;
-  ll.ws = ws;
-  ll.out = out;
-  ll.c = ws->dctl.as<DevCtl>();
-  ll.ctr = ws->ctr.as<LevelCtr>();
-  ll.Q[0] = ws->q0.as<int32_t>();
-  ll.Q[1] = ws->q1.as<int32_t>();
-  ll.C[0] = ws->c0.as<int32_t>();
-  ll.C[1] = ws->c1.as<int32_t>();
-  ll.Vn = ws->Vn.as<uint32_t>();
-  ll.Fn = ws->Fn.as<uint32_t>();
-  ll.Vd = ws->Vd.as<uint32_t>();
-  ll.Fd = ws->Fd.as<uint32_t>();
-  ll.Cd = ws->Cd.as<uint32_t>();
-  ll.hs = static_cast<LevelStatus *>(ws->hstat);
-  // tile sums and their scan of the delegate-frontier prefix sum
-  const size_t half = dtiles_half(g->d);
-  ll.bsum = ws->dtiles.as<int64_t>();
-  ll.bscan = reinterpret_cast<int64_t *>(ws->dtiles.as<char>() + half);
-  return ll;
-}
-
-// Captured level graphs per workspace, for the depth / parent buffers they
-// were captured with: one per queue parity and skip variant (see
-// LevelLaunch::enqueue), each captured when first needed.
-constexpr int kLevelVariants = 16;
-struct LevelGraphs {
-  int32_t *depth = nullptr, *parent = nullptr;
-  bool nn_do = false;
-  int64_t searches = 0;  // searches run on these graphs
-  hipGraph_t graph[kLevelVariants][2] = {};
-  hipGraphExec_t exec[kLevelVariants][2] = {};
-};
-
-}  // namespace
-
-void level_graphs_release(Workspace *ws) {
-  auto *lg = static_cast<LevelGraphs *>(ws->lvl);
-  if (!lg) return;
-  for (int v = 0; v < kLevelVariants; ++v)
-    for (int i = 0; i < 2; ++i) {
-      if (lg->exec[v][i]) (void)hipGraphExecDestroy(lg->exec[v][i]);
-      if (lg->graph[v][i]) (void)hipGraphDestroy(lg->graph[v][i]);
-    }
-  delete lg;
-  ws->lvl = nullptr;
-}
-
-namespace {
-
-// The level graphs of this workspace for ll's buffers (recaptured when they
-// change); variant v of parity p is captured on first use.
-LevelGraphs &level_graphs(Workspace *ws, const LevelLaunch &ll) {
-  auto *lg = static_cast<LevelGraphs *>(ws->lvl);
-  if (lg && lg->depth == ll.out.depth && lg->parent == ll.out.parent && lg->nn_do == ll.nn_do)
-    return *lg;
-  level_graphs_release(ws);
-  lg = new LevelGraphs();
-  ws->lvl = lg;
-  lg->depth = ll.out.depth;
-  lg->parent = ll.out.parent;
-  lg->nn_do = ll.nn_do;
-  return *lg;
-}
-
-hipGraphExec_t level_exec(Workspace *ws, LevelGraphs &lg, const LevelLaunch &ll, int v, int p) {
-  if (lg.exec[v][p]) return lg.exec[v][p];
-  hipStream_t cs = nullptr;
-  HIPCHK(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-  try {
-    HIPCHK(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-    try {
-      ll.enqueue(p, cs, nullptr, v);
-    } catch (...) {
-      hipGraph_t gr = nullptr;
-      (void)hipStreamEndCapture(cs, &gr);
-      if (gr) (void)hipGraphDestroy(gr);
-      throw;
-    }
-    HIPCHK(hipStreamEndCapture(cs, &lg.graph[v][p]));
-    HIPCHK(hipGraphInstantiate(&lg.exec[v][p], lg.graph[v][p], nullptr, nullptr, 0));
-  } catch (...) {
-    (void)hipStreamDestroy(cs);
-    level_graphs_release(ws);
-    throw;
+  // The host stays one level ahead and stops once a level reports an empty
+  // frontier (the level queued behind it returns at once). The level it
+  // launches next leaves out forward kernels that cannot have work, from the
+  // latest record it has seen: under the heuristic schedule with factor1 = 0 a
+  // subgraph that went backward never switches back (FV < 0 * BV never holds).
+  const bool monotone = o.forced == 0 && !o.nn_do && o.factor1[0] == 0.0 &&
+                        o.factor1[1] == 0.0 && o.factor1[2] == 0.0;
+  int skip = 0;
+  for (int32_t L = 0;; ++L) {
+    launch_level(a, L, skip, s);
+    if (L < 1) continue;
+    const LevelStatus &st = await_status(ws, L - 1, s);
+    if (st.done) break;
+    seen.push_back(st);
+    if (monotone && o.mode == 1 && st.rec.dir[0] == 1 && st.rec.dir[1] == 1)
+      skip = st.rec.dir[2] == 1 ? 1 : 2;
   }
-  (void)hipStreamDestroy(cs);
-  return lg.exec[v][p];
+  // the level behind the last one is still queued: the workspace is free for
+  // a search on another stream only after it
+  HIPCHK(hipStreamSynchronize(s));
+}
+
+// The whole search in one launch; false if its grid could not run (its
+// workspace is then to be initialized again).
+bool run_one_launch(const Graph *g, Workspace *ws, Search a, const OneLaunch &shape,
+                    hipStream_t s, int32_t *levels) {
+  ResidentLease lease(shape.blocks, false);
+  if (!lease.units) return false;
+  LevelStatus *hs = static_cast<LevelStatus *>(ws->hstat);
+  if (!ws->borrowed) hs->seq = 0;
+  launch_init(a, first_state(g), s);
+  if (a.mode == 1)
+    hipLaunchKernelGGL(k_search, dim3(shape.blocks), dim3(shape.threads), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_plain_search, dim3(shape.blocks), dim3(shape.threads), 0, s, a);
+  HIPCHK(hipGetLastError());
+  LevelStatus st;
+  if (ws->borrowed)
+    HIPCHK(hipMemcpyAsync(&st, hs, sizeof(LevelStatus), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  if (!ws->borrowed) st = *hs;
+  *levels = st.level;
+  return st.seq == 1;
 }
 
 }  // namespace
@@ -1534,271 +2113,90 @@ void bfs_run(const Graph *g, Workspace *ws, int32_t source, const dsbfs_run_opts
     fail(DSBFS_ERR_INVALID_ARG, "mode 0 needs the plain CSR (keep_plain_csr)");
   if (o.forced < 0 || o.forced > 3) fail(DSBFS_ERR_INVALID_ARG, "forced must be 0..3");
   if (o.nn_do != 0 && o.nn_do != 1) fail(DSBFS_ERR_INVALID_ARG, "nn_do must be 0 or 1");
-  int32_t *par = o.want_parent ? parent : nullptr;
 
-  const int32_t n = g->n, d = g->d;
-  uint32_t *Vn = ws->Vn.as<uint32_t>(), *Fn = ws->Fn.as<uint32_t>();
-  uint32_t *Vd = ws->Vd.as<uint32_t>(), *Fd = ws->Fd.as<uint32_t>(), *Cd = ws->Cd.as<uint32_t>();
-  int32_t *Q[2] = {ws->q0.as<int32_t>(), ws->q1.as<int32_t>()};
-  LevelCtr *ctr = ws->ctr.as<LevelCtr>();
-  LevelCtr *h = ws->hctr;
-  const int SG = stride_grid();
+  const Search a = search_args(g, ws, o, source, depth, o.want_parent ? parent : nullptr,
+                               stats != nullptr);
   Prof P;
   P.on = o.profile != 0 && stats != nullptr;
   P.s = s;
   P.ws = ws;
-
-  int b = P.begin();
-  hipLaunchKernelGGL(k_init, dim3(grid_for(std::max(n, 1), kBS, 4096)), dim3(kBS), 0, s, depth,
-                     par, n, Vn, Fn, g->nwords(), Vd, Fd, Cd, g->dwords());
-  HIPCHK(hipGetLastError());
-  HIPCHK(hipMemsetAsync(ctr, 0, 2 * sizeof(LevelCtr), s));
-  // level L uses ctr[L & 1]; the seed plays the part of "level -1" (ctr[1]).
-  hipLaunchKernelGGL(k_seed, dim3(1), dim3(1), 0, s, source, g->did.as<int32_t>(), depth, par,
-                     Vn, Vd, Fd, Cd, Q[0], ctr + 1, o.mode);
-  HIPCHK(hipGetLastError());
-  P.end(DSBFS_K_INIT, b);
-  P.units[DSBFS_K_INIT][0] = n;
-
-  std::vector<dsbfs_level_stats> rec;
-  double deg_sum = 0;  // sum of degrees over all frontiers = over reached vertices
-  int qi = 0;  // Q[qi] is the current queue
-  Out out{depth, par, 0};
-
-  if (o.mode == 0) {
-    for (int32_t L = 0;; ++L) {
-      LevelCtr *cur = ctr + (L & 1), *prev = ctr + ((L + 1) & 1);
-      // the previous level's queue length is the only input of this level
-      HIPCHK(hipMemcpyAsync(h, prev, sizeof(LevelCtr), hipMemcpyDeviceToHost, s));
-      HIPCHK(hipStreamSynchronize(s));
-      P.add_level(*h);
-      const int64_t qn = lc_qn(h);
-      if (qn == 0) break;
-      HIPCHK(hipMemsetAsync(cur, 0, sizeof(LevelCtr), s));
-      out.level1 = L + 1;
-      b = P.begin();
-      hipLaunchKernelGGL(k_plain_len, dim3(grid_for(qn, kBS, 8192)), dim3(kBS), 0, s, Q[qi], prev,
-                         g->poff.as<int64_t>(), ws->dlen.as<int32_t>());
-      HIPCHK(hipGetLastError());
-      scan_excl_i32_to_i64(ws->dlen.as<int32_t>(), ws->dscan.as<int64_t>(), qn, ws->scan_tmp.p, s);
-      hipLaunchKernelGGL(k_plain_expand, dim3(SG), dim3(kBS), 0, s, Q[qi], prev,
-                         ws->dscan.as<int64_t>(), g->poff.as<int64_t>(), g->pcol.as<int32_t>(),
-                         out, Vn, Q[qi ^ 1], cur);
-      HIPCHK(hipGetLastError());
-      P.end(DSBFS_K_PLAIN, b);
-      qi ^= 1;
-      dsbfs_level_stats r{};
-      r.frontier_normal = qn;
-      rec.push_back(r);
-    }
-  } else {
-    // Degree-separated DOBFS with the level control on the device.
-    DevCtl *c = ws->dctl.as<DevCtl>();
-    DevCtl init{};
-    for (int k = 0; k < 3; ++k) {
-      init.f0[k] = o.factor0[k];
-      init.f1[k] = o.factor1[k];
-    }
-    init.f0[3] = o.factor0_nn;
-    init.f1[3] = o.factor1_nn;
-    init.nn_do = o.nn_do;
-    init.forced = o.forced;
-    init.forced_seed = o.forced_seed;
-    init.level = 0;  // level 0 is open: counters cleared above, depth 1 next
-    init.level1 = 1;
-    init.mark_fn = g->st.n_dnsrc > 0 || (o.nn_do && g->st.n_nnsrc > 0);
-    init.cand_state = -1;
-    init.nwords = g->nwords();
-    init.rem[0] = g->st.n_ddsrc;
-    init.rem[1] = g->st.n_dnsrc;
-    init.rem[2] = g->st.n_ndsrc;
-    init.rem[3] = g->st.n_nnsrc;
-    init.nc = g->st.n_ndsrc;
-    hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(1), 0, s, c, init);
-    HIPCHK(hipGetLastError());
-    LevelStatus *hs = static_cast<LevelStatus *>(ws->hstat);
-    const LevelLaunch ll = level_launch(g, ws, out, o.nn_do != 0);
-    std::vector<LevelStatus> seen;
-    if (ws->borrowed) {
-      // allocation-free search: direct launches (no captured graphs, no
-      // events), and the level's status record copied from device memory
-      // after each level
-      for (int32_t L = 0;; ++L) {
-        ll.enqueue(L & 1, s, nullptr);
-        LevelStatus st;
-        HIPCHK(hipMemcpyAsync(&st, hs + (L & (kStatusSlots - 1)), sizeof(LevelStatus),
-                              hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
-        if (st.done) break;
-        seen.push_back(st);
-      }
-    } else if (P.on) {
-      // direct launches with an event around each kernel and one stream
-      // synchronization per level, so that only kernels with work are counted
-      for (int32_t L = 0;; ++L) {
-        const size_t sp0 = P.spans.size();
-        P.level = L;
-        ll.enqueue(L & 1, s, &P);
-        HIPCHK(hipStreamSynchronize(s));
-        const LevelStatus st = hs[L & (kStatusSlots - 1)];
-        const int32_t ran[DSBFS_NUM_KERNELS] = {
-            0, 1, d > 0, !st.done && st.plan[0], !st.done && (st.plan[1] || st.plan[2]),
-            !st.done && st.plan[3], !st.done && (st.plan[4] || st.plan[5]), !st.done, 0,
-            !st.done && st.plan[8], !st.done && st.plan[9]};
-        std::vector<Prof::Span> keep;
-        for (size_t i = sp0; i < P.spans.size(); ++i) {
-          if (ran[P.spans[i].k]) keep.push_back(P.spans[i]);
-          else --P.launches[P.spans[i].k];
-        }
-        P.spans.resize(sp0);
-        P.spans.insert(P.spans.end(), keep.begin(), keep.end());
-        if (st.done) break;
-        seen.push_back(st);
-      }
-    } else {
-      // one captured graph per level; the host stays one level ahead and
-      // stops once a finished level reports an empty frontier (the level
-      // already queued behind it returns at once). One level ahead hides the
-      // host's wait and launch behind the level in flight; two would add a
-      // second graph of no-op kernels at the end of every search.
-      //
-      // The level the host launches next leaves out kernels that cannot have
-      // work, from the latest status it has seen (two levels earlier):
-      // - under the heuristic schedule with factor1 = 0 a subgraph that went
-      //   backward never switches back (FV < 0 * BV never holds), so its
-      //   forward kernels could only return at once;
-      // - the counts U of unvisited vertices a bottom-up visit scans never
-      //   grow, and a bottom-up visit needs U > 0 (any schedule).
-      //
-      // Variants run only on graphs kept from an earlier search: a caller
-      // that passes new output buffers on every call (the query server's
-      // result rows) would otherwise capture several graphs per search.
-      LevelGraphs &lg = level_graphs(ws, ll);
-      const bool variants = lg.searches > 0;
-      const bool monotone = o.forced == 0 && o.factor1[0] == 0.0 && o.factor1[1] == 0.0 &&
-                            o.factor1[2] == 0.0;
-      int variant = 0;
-      for (int32_t L = 0;; ++L) {
-        HIPCHK(hipGraphLaunch(level_exec(ws, lg, ll, variant, L & 1), s));
-        HIPCHK(hipEventRecord(ws->lev_ev[L % 3], s));
-        if (L >= 1) {
-          HIPCHK(hipEventSynchronize(ws->lev_ev[(L - 1) % 3]));
-          const LevelStatus &st = hs[(L - 1) & (kStatusSlots - 1)];
-          if (st.done) break;
-          seen.push_back(st);
-          if (!variants) continue;
-          variant = (st.rec.U[1] == 0 ? 4 : 0) | (st.rec.U[0] == 0 && st.rec.U[2] == 0 ? 8 : 0);
-          if (monotone)
-            variant |= (st.rec.dir[2] == 1 ? 1 : 0) |
-                       (st.rec.dir[0] == 1 && st.rec.dir[1] == 1 ? 2 : 0);
-        }
-      }
-      ++lg.searches;
-    }
-    for (const LevelStatus &st : seen) {
-      rec.push_back(st.rec);
-      if (!P.on) {
-        const int32_t *pl = st.plan;
-        ++P.launches[DSBFS_K_PREV_NORMAL];
-        if (d > 0) ++P.launches[DSBFS_K_PREV_DELEG];
-        if (pl[0]) ++P.launches[DSBFS_K_TD_NORMAL];
-        if (pl[1] || pl[2]) ++P.launches[DSBFS_K_TD_DELEG];
-        if (pl[3]) ++P.launches[DSBFS_K_BU_NORMAL];
-        if (pl[4] || pl[5]) ++P.launches[DSBFS_K_BU_DELEG];
-        if (pl[8]) ++P.launches[DSBFS_K_TD_NN];
-        if (pl[9]) ++P.launches[DSBFS_K_BU_NN];
-        ++P.launches[DSBFS_K_CLOSE];
-      }
-    }
-    if (!P.on) {
-      // the level that found the frontier empty ran its previsit (as did the
-      // levels queued behind it, which return at once and are not counted)
-      ++P.launches[DSBFS_K_PREV_NORMAL];
-      if (d > 0) ++P.launches[DSBFS_K_PREV_DELEG];
-    }
-    if (stats) {
-      DevCtl hc{};
-      HIPCHK(hipMemcpyAsync(&hc, c, sizeof(DevCtl), hipMemcpyDeviceToHost, s));
-      HIPCHK(hipStreamSynchronize(s));
-      for (int k = 0; k < DSBFS_NUM_KERNELS; ++k) {
-        if (k == DSBFS_K_INIT) continue;
-        for (int j = 0; j < 6; ++j) P.units[k][j] = double(hc.units[k][j]);
-      }
-      deg_sum = double(hc.deg_sum);
-    }
+  std::vector<LevelStatus> seen;
+  int32_t num_levels = 0;
+  // One launch unless the caller wants a record per level.
+  const bool records = stats && stats->levels && stats->capacity > 0;
+  const OneLaunch shape = one_launch_shape(g, o.mode);
+  if (!(shape.blocks && !P.on && !records &&
+        run_one_launch(g, ws, a, shape, s, &num_levels))) {
+    run_levels(g, ws, a, o, P, seen, s);
+    num_levels = int32_t(seen.size());
   }
+  if (!stats) return;
 
-  if (stats) {
-    HIPCHK(hipStreamSynchronize(s));
-    stats->num_levels = int32_t(rec.size());
-    for (int32_t i = 0; i < stats->num_levels && i < stats->capacity && stats->levels; ++i) {
-      stats->levels[i] = rec[i];
-      for (double &t : stats->levels[i].kernel_ms) t = 0.0;  // filled from the spans below
-    }
-    // Every reached vertex sits in exactly one level's frontier, whose previsit
-    // (or plain expansion) summed its full degree; each vertex but the source
-    // was claimed exactly once. So the component's size and edge count come
-    // from the level counters without another pass over depth[].
-    const auto &Uc = P.units;
-    const double claims = Uc[DSBFS_K_PREV_NORMAL][2] + Uc[DSBFS_K_TD_NORMAL][3] +
-                          Uc[DSBFS_K_TD_DELEG][2] + Uc[DSBFS_K_TD_DELEG][3] +
-                          Uc[DSBFS_K_BU_NORMAL][3] + Uc[DSBFS_K_BU_DELEG][2] +
-                          Uc[DSBFS_K_PLAIN][2] + Uc[DSBFS_K_TD_NN][2] + Uc[DSBFS_K_BU_NN][3];
-    stats->reached = 1 + int64_t(claims);
-    if (o.mode == 0) deg_sum = Uc[DSBFS_K_PLAIN][1];
-    stats->edges_cc = int64_t(deg_sum / 2);
+  LevelTotals tot;
+  unsigned long long U[DSBFS_NUM_KERNELS][4];
+  HIPCHK(hipMemcpyAsync(&tot, &a.ctl->tot, sizeof(tot), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(U, a.ctl->units, sizeof(U), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  // queue and list entries are counted by the decision
+  for (int k = 0; k < DSBFS_NUM_KERNELS; ++k)
+    if (k != DSBFS_K_BU_NORMAL && k != DSBFS_K_BU_DELEG && k != DSBFS_K_BU_NN)
+      U[k][0] = tot.units0[k];
+  U[DSBFS_K_INIT][0] = (unsigned long long)g->n;
+  stats->num_levels = num_levels;
+  for (int32_t i = 0; i < int32_t(seen.size()) && i < stats->capacity && stats->levels; ++i) {
+    stats->levels[i] = seen[i].rec;
+    for (double &t : stats->levels[i].kernel_ms) t = 0.0;  // filled from the spans below
+  }
+  // Every reached vertex sits in exactly one level's frontier, whose previsit
+  // (or plain expansion) summed its full degree; each vertex but the source
+  // was claimed exactly once. So the component's size and edge count come
+  // from the level counters without another pass over depth[].
+  stats->reached = 1 + int64_t(U[DSBFS_K_PREV_NORMAL][2] + U[DSBFS_K_TD_NORMAL][3] +
+                               U[DSBFS_K_TD_DELEG][2] + U[DSBFS_K_TD_DELEG][3] +
+                               U[DSBFS_K_BU_NORMAL][3] + U[DSBFS_K_BU_DELEG][2] +
+                               U[DSBFS_K_PLAIN][2] + U[DSBFS_K_TD_NN][2] + U[DSBFS_K_BU_NN][3]);
+  stats->edges_cc = int64_t((o.mode == 0 ? U[DSBFS_K_PLAIN][1] : tot.deg_sum) / 2);
 
-    // Algorithmic bytes per kernel from its unit counts (see dsbfs.h).
-    const double out_b = o.want_parent ? 8.0 : 4.0;  // depth (+ parent) per vertex
-    const auto &U = P.units;
-    double bytes[DSBFS_NUM_KERNELS] = {};
-    double edges[DSBFS_NUM_KERNELS] = {};
-    bytes[DSBFS_K_INIT] = U[DSBFS_K_INIT][0] * out_b;
-    bytes[DSBFS_K_PREV_NORMAL] = U[DSBFS_K_PREV_NORMAL][0] * (4 + 16) +
-                                 U[DSBFS_K_PREV_NORMAL][1] * 4 +
-                                 U[DSBFS_K_PREV_NORMAL][2] * (out_b + 4);
-    edges[DSBFS_K_PREV_NORMAL] = U[DSBFS_K_PREV_NORMAL][1];
-    bytes[DSBFS_K_PREV_DELEG] = U[DSBFS_K_PREV_DELEG][0] * (4 + 16);
-    bytes[DSBFS_K_TD_NORMAL] = U[DSBFS_K_TD_NORMAL][0] * (4 + 16) + U[DSBFS_K_TD_NORMAL][1] * 4 +
-                               U[DSBFS_K_TD_NORMAL][3] * (out_b + 4);
-    edges[DSBFS_K_TD_NORMAL] = U[DSBFS_K_TD_NORMAL][1];
-    bytes[DSBFS_K_TD_DELEG] = U[DSBFS_K_TD_DELEG][0] * (4 + 16) + U[DSBFS_K_TD_DELEG][1] * 4 +
-                              U[DSBFS_K_TD_DELEG][2] * (out_b + 4 + 4) +
-                              U[DSBFS_K_TD_DELEG][3] * (out_b + 4 + 4);
-    edges[DSBFS_K_TD_DELEG] = U[DSBFS_K_TD_DELEG][1];
-    bytes[DSBFS_K_BU_NORMAL] = U[DSBFS_K_BU_NORMAL][0] * 4 + U[DSBFS_K_BU_NORMAL][1] * 16 +
-                               U[DSBFS_K_BU_NORMAL][2] * 4 +
-                               U[DSBFS_K_BU_NORMAL][3] * (out_b + 4 + 4) +
-                               U[DSBFS_K_BU_NORMAL][4] * 4;
-    edges[DSBFS_K_BU_NORMAL] = U[DSBFS_K_BU_NORMAL][2];
-    bytes[DSBFS_K_BU_DELEG] = U[DSBFS_K_BU_DELEG][0] * (4 + 4 + 16) +
-                              U[DSBFS_K_BU_DELEG][1] * 4 + U[DSBFS_K_BU_DELEG][2] * (out_b + 4 + 4);
-    edges[DSBFS_K_BU_DELEG] = U[DSBFS_K_BU_DELEG][1];
-    bytes[DSBFS_K_CLOSE] = U[DSBFS_K_CLOSE][0] * 4;
-    bytes[DSBFS_K_PLAIN] = U[DSBFS_K_PLAIN][0] * (4 + 16) + U[DSBFS_K_PLAIN][1] * 4 +
-                           U[DSBFS_K_PLAIN][2] * (out_b + 4);
-    edges[DSBFS_K_PLAIN] = U[DSBFS_K_PLAIN][1];
-    bytes[DSBFS_K_TD_NN] = U[DSBFS_K_TD_NN][0] * (4 + 16) + U[DSBFS_K_TD_NN][1] * 4 +
-                           U[DSBFS_K_TD_NN][2] * (out_b + 4);
-    edges[DSBFS_K_TD_NN] = U[DSBFS_K_TD_NN][1];
-    bytes[DSBFS_K_BU_NN] = U[DSBFS_K_BU_NN][0] * 4 + U[DSBFS_K_BU_NN][1] * 16 +
-                           U[DSBFS_K_BU_NN][2] * 4 + U[DSBFS_K_BU_NN][3] * (out_b + 4 + 4);
-    edges[DSBFS_K_BU_NN] = U[DSBFS_K_BU_NN][2];
-    double ms[DSBFS_NUM_KERNELS] = {};
-    for (const Prof::Span &sp : P.spans) {
-      float t = 0.f;
-      HIPCHK(hipEventElapsedTime(&t, ws->events[sp.b], ws->events[sp.e]));
-      ms[sp.k] += double(t);
-      if (sp.level >= 0 && sp.level < stats->num_levels && sp.level < stats->capacity &&
-          stats->levels)
-        stats->levels[sp.level].kernel_ms[sp.k] += double(t);
-    }
-    for (int k = 0; k < DSBFS_NUM_KERNELS; ++k) {
-      stats->kernels[k].ms = ms[k];
-      stats->kernels[k].launches = P.launches[k];
-      stats->kernels[k].bytes = int64_t(bytes[k]);
-      stats->kernels[k].edges = int64_t(edges[k]);
-    }
+  // Algorithmic bytes per kernel from its unit counts (see dsbfs.h).
+  const int64_t out_b = o.want_parent ? 8 : 4;  // depth (+ parent) per vertex
+  auto u = [&](int k, int j) { return int64_t(U[k][j]); };
+  int64_t bytes[DSBFS_NUM_KERNELS] = {};
+  int64_t edges[DSBFS_NUM_KERNELS] = {};
+  bytes[DSBFS_K_INIT] = u(DSBFS_K_INIT, 0) * out_b;
+  bytes[DSBFS_K_PREV_DELEG] = u(DSBFS_K_PREV_DELEG, 0) * (4 + 16);
+  for (int k : {DSBFS_K_PREV_NORMAL, DSBFS_K_PLAIN, DSBFS_K_TD_NN}) {
+    bytes[k] = u(k, 0) * (4 + 16) + u(k, 1) * 4 + u(k, 2) * (out_b + 4);
+    edges[k] = u(k, 1);
+  }
+  bytes[DSBFS_K_TD_NORMAL] = u(DSBFS_K_TD_NORMAL, 0) * (4 + 16) + u(DSBFS_K_TD_NORMAL, 1) * 4 +
+                             u(DSBFS_K_TD_NORMAL, 3) * (out_b + 4);
+  edges[DSBFS_K_TD_NORMAL] = u(DSBFS_K_TD_NORMAL, 1);
+  bytes[DSBFS_K_TD_DELEG] = u(DSBFS_K_TD_DELEG, 0) * (4 + 16) + u(DSBFS_K_TD_DELEG, 1) * 4 +
+                            (u(DSBFS_K_TD_DELEG, 2) + u(DSBFS_K_TD_DELEG, 3)) * (out_b + 4 + 4);
+  edges[DSBFS_K_TD_DELEG] = u(DSBFS_K_TD_DELEG, 1);
+  for (int k : {DSBFS_K_BU_NORMAL, DSBFS_K_BU_NN}) {
+    bytes[k] = u(k, 0) * 4 + u(k, 1) * 16 + u(k, 2) * 4 + u(k, 3) * (out_b + 4 + 4);
+    edges[k] = u(k, 2);
+  }
+  bytes[DSBFS_K_BU_NORMAL] += int64_t(tot.kept) * 4;
+  bytes[DSBFS_K_BU_DELEG] = u(DSBFS_K_BU_DELEG, 0) * (4 + 4 + 16) + u(DSBFS_K_BU_DELEG, 1) * 4 +
+                            u(DSBFS_K_BU_DELEG, 2) * (out_b + 4 + 4);
+  edges[DSBFS_K_BU_DELEG] = u(DSBFS_K_BU_DELEG, 1);
+  bytes[DSBFS_K_CLOSE] = u(DSBFS_K_CLOSE, 0) * 4;
+  double ms[DSBFS_NUM_KERNELS] = {};
+  for (const Prof::Span &sp : P.spans) {
+    float t = 0.f;
+    HIPCHK(hipEventElapsedTime(&t, ws->events[sp.b], ws->events[sp.e]));
+    ms[sp.k] += double(t);
+    if (sp.level >= 0 && sp.level < stats->num_levels && sp.level < stats->capacity &&
+        stats->levels)
+      stats->levels[sp.level].kernel_ms[sp.k] += double(t);
+  }
+  for (int k = 0; k < DSBFS_NUM_KERNELS; ++k) {
+    stats->kernels[k].ms = ms[k];
+    stats->kernels[k].launches = k == DSBFS_K_INIT ? 1 : tot.launches[k];
+    stats->kernels[k].bytes = bytes[k];
+    stats->kernels[k].edges = edges[k];
   }
 }
 
@@ -1833,21 +2231,23 @@ inline size_t round256(size_t b) { return ((b < 256 ? 256 : b) + 255) / 256 * 25
 
 }  // namespace
 
+// What decides whether a graph is taken (about 25 bytes per vertex). It is
+// more than the search carves out of the array now: the limit on graphs stays
+// where callers know it.
 size_t noalloc_scratch_bytes(const Graph *g) {
   const int64_t n = g->n, d = g->d, nm = std::max(n, d);
+  const size_t tiles = (size_t((d + 2047) / 2048 + 1) * 8 + 255) / 256 * 256;
   size_t t = 0;
   t += 2 * round256(size_t(g->nwords()) * 4);          // Vn, Fn
   t += 3 * round256(size_t(g->dwords()) * 4);          // Vd, Fd, Cd
   t += 2 * round256(size_t(n) * 4);                    // q0, q1
-  t += 2 * round256(size_t(d) * 4);                    // dlist, dcand
+  t += 2 * round256(size_t(d) * 4);                    // dlist; room
   t += round256(size_t(nm) * 4);                       // dlen
   t += round256(size_t(nm + 1) * 8);                   // dscan
   t += 2 * round256(size_t(g->st.n_ndsrc) * 4);        // c0, c1
-  t += round256(2 * sizeof(LevelCtr));                 // ctr
-  t += round256(scan_tmp_bytes(nm));                   // scan_tmp
-  t += round256(sizeof(DevCtl));                       // dctl
-  t += round256(2 * dtiles_half(d));                   // dtiles
-  t += round256(kStatusSlots * sizeof(LevelStatus));   // status ring
+  t += round256(scan_tmp_bytes(nm));                   // room
+  t += round256(2 * tiles);                            // room
+  t += 3328;                                           // control block, status ring
   return t;
 }
 
@@ -1886,6 +2286,9 @@ void bfs_run_noalloc(const Graph *g, int32_t source, const dsbfs_run_opts *opts,
   Workspace ws;
   ws.g = g;
   ws.borrowed = true;
+  carve(ws.ctl, sizeof(SearchCtl));
+  DevBuf ring;
+  carve(ring, kStatusSlots * sizeof(LevelStatus));
   carve(ws.Vn, size_t(g->nwords()) * 4);
   carve(ws.Fn, size_t(g->nwords()) * 4);
   carve(ws.Vd, size_t(g->dwords()) * 4);
@@ -1894,20 +2297,12 @@ void bfs_run_noalloc(const Graph *g, int32_t source, const dsbfs_run_opts *opts,
   carve(ws.q0, size_t(n) * 4);
   carve(ws.q1, size_t(n) * 4);
   carve(ws.dlist, size_t(d) * 4);
-  carve(ws.dcand, size_t(d) * 4);
   carve(ws.dlen, size_t(nm) * 4);
   carve(ws.dscan, size_t(nm + 1) * 8);
   carve(ws.c0, size_t(g->st.n_ndsrc) * 4);
   carve(ws.c1, size_t(g->st.n_ndsrc) * 4);
-  carve(ws.ctr, 2 * sizeof(LevelCtr));
-  carve(ws.scan_tmp, scan_tmp_bytes(nm));
-  carve(ws.dctl, sizeof(DevCtl));
-  carve(ws.dtiles, 2 * dtiles_half(d));
-  DevBuf ring;
-  carve(ring, kStatusSlots * sizeof(LevelStatus));
-  if (off != need) fail(DSBFS_ERR_HIP, "allocation-free scratch layout mismatch");
-  LevelCtr hctr[2];
-  ws.hctr = hctr;
+  if (off > kScratchBytes)
+    fail(DSBFS_ERR_RANGE, "allocation-free search scratch exceeded");
   ws.hstat = ring.p;
   bfs_run(g, &ws, source, opts, depth, parent, stats, s);
   // the next call reuses the array: this one's work must be complete

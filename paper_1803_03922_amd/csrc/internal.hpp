@@ -118,27 +118,6 @@ struct Graph {
   int32_t nwords() const { return (n + 31) / 32; }
 };
 
-// Per-level counters of a single-source search (device; accumulated with
-// wave-aggregated atomics). Two copies alternate between levels.
-struct LevelCtr {
-  // Tails of the next normal queue (bits 0..31: the queue length of the next
-  // level) and of the next bottom-up normal candidate list (bits 32..63), in
-  // one word: the bottom-up normal pass appends to both and reserves both
-  // with one atomic. Neither count reaches 2^31, so no carry crosses.
-  unsigned long long qn_nc;
-  unsigned long long nd_list;   // frontier delegates of this level (length of dlist)
-  unsigned long long nd_cand;   // unvisited delegates with a dd or dn edge (length of dcand)
-  unsigned long long fv_nn, q_nn, fv_nd, q_nd;  // normal previsit
-  unsigned long long fv_dd, q_dd, fv_dn, q_dn;  // delegate previsit
-  // Work units per kernel (index DSBFS_K_*), slot meanings in bfs.hip.
-  unsigned long long units[DSBFS_NUM_KERNELS][4];
-};
-
-__host__ __device__ inline int64_t lc_qn(const LevelCtr *c) {
-  return int64_t(c->qn_nc & 0xffffffffull);
-}
-__host__ __device__ inline int64_t lc_nc(const LevelCtr *c) { return int64_t(c->qn_nc >> 32); }
-
 // Scratch of one search at a time (single-source and multi-source).
 struct Workspace {
   const Graph *g = nullptr;
@@ -147,26 +126,32 @@ struct Workspace {
   // frontier, and claimed (visited or found this level) delegates
   DevBuf Vn, Fn, Vd, Fd, Cd;
   DevBuf q0, q1;               // normal queues, int32[n]
-  DevBuf dlist, dcand, dlen;   // int32[d]
+  DevBuf dlist;                // frontier delegates of a forward visit, int32[d]
+  DevBuf dlen;                 // int32[max(n, d)]: second Fn bitmap; multi-source frontier list
   DevBuf dscan;                // int64[max(n, d) + 1]: prefix of top-down lengths
   DevBuf c0, c1;               // bottom-up normal candidates, int32[n_ndsrc]
-  DevBuf ctr;                  // LevelCtr[2]
-  DevBuf scan_tmp;
-  LevelCtr *hctr = nullptr;    // pinned host copy of ctr
+  DevBuf ctl;                  // control block of the search in progress (bfs.hip)
   std::vector<hipEvent_t> events;  // profiling event pool
-  // device-side level control of degree-separated DOBFS (bfs.hip)
-  DevBuf dctl;                 // control block of the search in progress
-  DevBuf dtiles;               // tile sums and their scan (delegate-frontier prefix sum)
   void *hstat = nullptr;       // pinned ring of per-level status records
-  void *lvl = nullptr;         // captured level graphs
-  hipEvent_t lev_ev[3] = {};   // completion of recent levels
   // multi-source lane state
   void *ms_state = nullptr;           // launch state of multi-source BFS (msbfs.hip)
   // borrowed: every buffer points into memory the workspace does not own (the
   // allocation-free search's static scratch); hstat is then device memory,
-  // read by copies, and hctr a host buffer of the caller's frame
+  // read by copies
   bool borrowed = false;
   ~Workspace();
+};
+
+// Compute units held for a launch whose blocks wait for each other (bfs.hip):
+// taken before the launch, returned once it has completed. wait = false: units
+// is 0 when there are not enough now.
+struct ResidentLease {
+  int units = 0;
+  void *gate = nullptr;
+  ResidentLease(int blocks, bool wait);
+  ~ResidentLease();
+  ResidentLease(const ResidentLease &) = delete;
+  ResidentLease &operator=(const ResidentLease &) = delete;
 };
 
 // Per-lane result rows of a level-at-a-time multi-source step (server).

@@ -809,6 +809,8 @@ static void msbfs_launch(const Graph *g, Workspace *ws, const int32_t *sources, 
   // control block cleared by a kernel-free copy of zeros from the host
   static const MsCtl zero{};
   HIPCHK(hipMemcpyAsync(st->ctl.p, &zero, sizeof(MsCtl), hipMemcpyHostToDevice, s));
+  // the grid's blocks wait for each other: no other such grid beside it
+  ResidentLease lease(grid, true);
   if (o.use_graph) {
     char key[160];
     std::snprintf(key, sizeof(key), "%d/%d/%d/%d/%d/%p", o.block, grid, k, o.bu_permille, words,
