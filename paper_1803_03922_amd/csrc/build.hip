@@ -39,44 +39,31 @@ __global__ void k_validate(const int32_t *src, const int32_t *dst, int64_t g, in
   }
 }
 
-// Both directions of every non-loop pair as 64-bit keys (u << B) | v.
-__global__ void k_pack(const int32_t *src, const int32_t *dst, int64_t g, int B, uint64_t *keys,
-                       unsigned long long *cursor) {
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  for (int64_t e0 = int64_t(blockIdx.x) * blockDim.x; e0 < g; e0 += stride) {
-    const int64_t e = e0 + threadIdx.x;
-    int32_t u = 0, v = 0;
-    bool keep = false;
-    if (e < g) {
-      u = src[e];
-      v = dst[e];
-      keep = u != v;
+// Both directions of every non-loop pair as 64-bit keys (u << B) | v, in any
+// order (they are sorted next). A block packs kPackItems pairs per thread and
+// reserves their places with one atomic: one per wave step, on one address,
+// took 12.6 ms for 67M pairs (12.6 ns each, one after the other). Bound by the
+// 24 bytes a pair moves: 0.5 ms.
+constexpr int kPackItems = 16;
+__global__ void __launch_bounds__(kBS) k_pack(const int32_t *src, const int32_t *dst, int64_t g,
+                                              int B, uint64_t *keys, unsigned long long *cursor) {
+  constexpr int64_t tile = int64_t(kBS) * kPackItems;
+  for (int64_t t0 = int64_t(blockIdx.x) * tile; t0 < g; t0 += int64_t(gridDim.x) * tile) {
+    const int64_t w0 = t0 + int64_t(threadIdx.x / kWave) * (kWave * kPackItems) + lane_id();
+    int32_t u[kPackItems], v[kPackItems];
+#pragma unroll
+    for (int i = 0; i < kPackItems; ++i) {
+      const int64_t e = w0 + i * kWave;
+      u[i] = e < g ? src[e] : 0;
+      v[i] = e < g ? dst[e] : 0;
     }
-    const int64_t pos = wave_append(keep, cursor);
-    if (keep) {
-      keys[2 * pos] = (uint64_t(uint32_t(u)) << B) | uint64_t(uint32_t(v));
-      keys[2 * pos + 1] = (uint64_t(uint32_t(v)) << B) | uint64_t(uint32_t(u));
-    }
+    pack_pairs<kPackItems>(u, v, B, keys, cursor);
   }
 }
 
-// poff[x] = index of the first key with row >= x, for x in [0, n]: between
-// consecutive keys j-1 and j every row in (row[j-1], row[j]] starts at j.
-__global__ void k_row_offsets(const uint64_t *keys, int64_t m, int B, int32_t n, int64_t *poff) {
-  for (int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; j <= m;
-       j += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t prev = j > 0 ? int64_t(keys[j - 1] >> B) : -1;
-    const int64_t cur = j < m ? int64_t(keys[j] >> B) : int64_t(n);
-    for (int64_t x = prev + 1; x <= cur; ++x) poff[x] = j;
-  }
-}
-
-__global__ void k_cols_and_degree(const uint64_t *keys, int64_t m, uint64_t vmask,
-                                  const int64_t *poff, int32_t n, int32_t *pcol, int32_t *deg) {
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  for (int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; j < m; j += stride)
-    pcol[j] = int32_t(keys[j] & vmask);
-  for (int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; v < n; v += stride)
+__global__ void k_degrees(const int64_t *poff, int32_t n, int32_t *deg) {
+  for (int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; v < n;
+       v += int64_t(gridDim.x) * blockDim.x)
     deg[v] = int32_t(poff[v + 1] - poff[v]);
 }
 
@@ -96,33 +83,6 @@ __global__ void k_did_scatter(const int32_t *vid_of, int32_t d, int32_t *did) {
   for (int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; k < d;
        k += int64_t(gridDim.x) * blockDim.x)
     did[vid_of[k]] = int32_t(k);
-}
-
-// cnt_del[u] = number of delegate neighbours of u. Edge-parallel over the
-// sorted keys; rows are contiguous, so a segmented wave scan by row folds a
-// hub's entries into one atomic per wave.
-__global__ void k_count_delegate_nbrs(const uint64_t *keys, int64_t m, int B, uint64_t vmask,
-                                      const int32_t *did, int32_t *cnt_del) {
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  const int l = lane_id();
-  for (int64_t j0 = int64_t(blockIdx.x) * blockDim.x; j0 < m; j0 += stride) {
-    const int64_t j = j0 + threadIdx.x;
-    int64_t u = -1 - l;  // distinct per inactive lane: never merges
-    int32_t c = 0;
-    if (j < m) {
-      const uint64_t k = keys[j];
-      u = int64_t(k >> B);
-      c = did[int32_t(k & vmask)] >= 0;
-    }
-    for (int o = 1; o < kWave; o <<= 1) {
-      const int64_t uo = __shfl_up(u, o, kWave);
-      const int32_t co = __shfl_up(c, o, kWave);
-      if (l >= o && uo == u) c += co;
-    }
-    const int64_t un = __shfl_down(u, 1, kWave);
-    const bool tail = (l == kWave - 1) || un != u;
-    if (j < m && tail && c) atomicAdd(&cnt_del[u], c);
-  }
 }
 
 __global__ void k_row_lengths(const int32_t *deg, const int32_t *did, const int32_t *vid_of,
@@ -188,84 +148,353 @@ __global__ void k_nn_fill(const int64_t *start, const int32_t *cnt, const uint64
   }
 }
 
-// Destination of row u in the new layout: (row offsets, columns, is delegate).
-struct RowDst {
-  uint64_t w;
-  int32_t *col;
-  bool del;
-};
-
-__device__ __forceinline__ RowDst row_dst(int32_t u, const int32_t *did, const uint64_t *noff,
-                                          int32_t *ncol, const uint64_t *doff, int32_t *dcol) {
-  const int32_t k = did[u];
-  if (k >= 0) return RowDst{doff[k], dcol, true};
-  return RowDst{noff[u], ncol, false};
+// ---------------------------------------------------------------------------
+// arranging the rows
+// ---------------------------------------------------------------------------
+// Degree bucket of a vertex on a log scale (8 buckets per power of two), so
+// that ordering by bucket orders neighbours by degree with a one-byte key.
+__host__ __device__ __forceinline__ uint32_t deg_bucket(int32_t deg) {
+  if (deg <= 1) return 0;
+#ifdef __HIP_DEVICE_COMPILE__
+  const uint32_t lg = 31u - __clz(uint32_t(deg));          // floor(log2)
+#else
+  const uint32_t lg = 31u - uint32_t(__builtin_clz(uint32_t(deg)));
+#endif
+  const uint32_t frac = lg >= 3 ? (uint32_t(deg) >> (lg - 3)) & 7u : (uint32_t(deg) << (3 - lg)) & 7u;
+  const uint32_t b = lg * 8u + frac;
+  return b > 254u ? 254u : b;
 }
 
-// Rows with at most kSmallRow entries: one thread walks the row in order.
-constexpr int kSmallRow = 64;
+// What the arrangement needs of a neighbour, in arrays that stay in the L2: a
+// byte per vertex with its degree bucket, plus one for delegates (degrees
+// above TH: delegate iff code > bucket(TH), bucket = code minus that one), and
+// per 32 vertices their delegate bits and the first one's delegate ID. The
+// degree and delegate ID arrays would be a line from beyond the L2 per entry
+// (16 MB each at 4M vertices): 3.3 ms for the dd keys of RMAT 22 alone.
+struct DelRank {
+  uint32_t bits;
+  int32_t base;
+};
 
-__global__ void k_split_small(const int64_t *poff, const int32_t *pcol, const int32_t *did,
-                              int32_t n, const uint64_t *noff, int32_t *ncol,
-                              const uint64_t *doff, int32_t *dcol) {
-  for (int64_t u = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; u < n;
-       u += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t b = poff[u], e = poff[u + 1];
-    if (e - b == 0 || e - b > kSmallRow) continue;
-    const RowDst r = row_dst(int32_t(u), did, noff, ncol, doff, dcol);
-    int64_t pa = row_start(r.w), pb = pa + row_first(r.w);
-    for (int64_t j = b; j < e; ++j) {
-      const int32_t v = pcol[j];
-      const int32_t kv = did[v];
-      const bool v_del = kv >= 0;
-      // first part: same class as the row for delegates (dd), opposite-of-delegate
-      // for normals (nn); columns of delegate neighbours are delegate IDs.
-      const bool first = r.del ? v_del : !v_del;
-      const int32_t val = v_del ? kv : v;
-      if (first) r.col[pa++] = val;
-      else r.col[pb++] = val;
+__global__ void k_codes(const int32_t *deg, const int32_t *did, int32_t n, int32_t th,
+                        uint8_t *code, DelRank *rank) {
+  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+  for (int64_t v0 = int64_t(blockIdx.x) * blockDim.x; v0 < n; v0 += stride) {
+    const int64_t v = v0 + threadIdx.x;
+    int32_t k = -1;
+    if (v < n) {
+      k = did[v];
+      code[v] = uint8_t(deg_bucket(deg[v]) + (deg[v] > th));
     }
+    const uint64_t m = __ballot(k >= 0);
+    const int l = lane_id();
+    const uint32_t bits = uint32_t(l < 32 ? m : m >> 32);
+    const int first = (l < 32 ? 0 : 32) + (bits ? __ffs(bits) - 1 : 0);
+    const int32_t base = __shfl(k, first, kWave);
+    if ((l & 31) == 0 && v < n) rank[v >> 5] = DelRank{bits, base};
   }
 }
 
-// Rows with more than kSmallRow entries: one wave per row, 64 entries per step,
-// order kept by ballot ranks.
-__global__ void k_split_large(const int32_t *rows, const int64_t *nrows, const int64_t *poff,
-                              const int32_t *pcol, const int32_t *did, const uint64_t *noff,
-                              int32_t *ncol, const uint64_t *doff, int32_t *dcol) {
-  const int64_t R = *nrows;
+struct Arrange {
+  const int64_t *poff;
+  const int32_t *pcol;     // rows of the plain CSR, ascending
+  const uint8_t *code;
+  const DelRank *rank;
+  const int32_t *deg, *did;
+  const int64_t *nstart, *dstart;
+  int32_t n;
+  int32_t bth;             // bucket of TH
+  int32_t *plain;          // plain rows by bucket, highest first (NULL: not wanted)
+  int32_t *ncol, *dcol;    // split rows
+  int32_t *cnt_del;        // delegate neighbours of each row
+
+  __device__ __forceinline__ bool is_del(uint32_t c) const { return int32_t(c) > bth; }
+  __device__ __forceinline__ int32_t del_id(int32_t v) const {
+    const DelRank r = rank[v >> 5];
+    return r.base + __popc(r.bits & ((1u << (v & 31)) - 1u));
+  }
+  // where row u's split entries go
+  __device__ __forceinline__ int32_t *split_row(int32_t u, bool &del) const {
+    const int32_t k = did[u];
+    del = k >= 0;
+    return del ? dcol + dstart[k] : ncol + nstart[u];
+  }
+  // order of an entry in the plain row: bucket, highest first
+  __device__ __forceinline__ uint32_t plain_key(uint32_t c) const {
+    return 255u - (c - (is_del(c) ? 1u : 0u));
+  }
+  // and in the split row: a delegate's row has its dd entries by bucket,
+  // highest first, then the dn entries; a normal row nn, then nd
+  __device__ __forceinline__ uint32_t split_key(uint32_t c, bool del) const {
+    return del ? (is_del(c) ? 255u - c : 255u) : (is_del(c) ? 1u : 0u);
+  }
+};
+
+// Rows with at most kShortRow entries. A wave takes 16 rows (or 8 at a time
+// when they are long), stages their entries in LDS and places each entry by
+// counting the entries of its row that go before it: plain by (bucket
+// descending, ID), dd by the same, dn and nn by ID, nd by (degree descending,
+// ID). Bound by the gathers of the code bytes; the walk over the row costs
+// len LDS reads per entry.
+constexpr int kShortRow = 64;
+constexpr int kShortCap = 512;  // entries a wave holds
+
+struct ShortWave {
+  int32_t col[kShortCap];
+  int32_t deg[kShortCap];
+  uint8_t code[kShortCap];
+  int32_t ex[kWave];    // exclusive prefix of the row lengths
+  int64_t beg[16];
+};
+
+__device__ __forceinline__ int owner_of(const int32_t *ex, int32_t e) {
+  int lo = 0;
+#pragma unroll
+  for (int step = 32; step > 0; step >>= 1)
+    if (ex[lo + step] <= e) lo += step;
+  return lo;
+}
+
+__global__ void __launch_bounds__(kBS) k_rows_short(Arrange a) {
+  __shared__ ShortWave s_w[kBS / kWave];
+  ShortWave &S = s_w[threadIdx.x / kWave];
   const int l = lane_id();
   const int64_t wid = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
   const int64_t nw = int64_t(gridDim.x) * blockDim.x / kWave;
-  for (int64_t i = wid; i < R; i += nw) {
-    const int32_t u = rows[i];
-    const int64_t b = poff[u], e = poff[u + 1];
-    const RowDst r = row_dst(u, did, noff, ncol, doff, dcol);
-    int64_t pa = row_start(r.w), pb = pa + row_first(r.w);
-    for (int64_t j0 = b; j0 < e; j0 += kWave) {
-      const int64_t j = j0 + l;
-      const bool ok = j < e;
-      int32_t v = 0, kv = -1;
-      if (ok) {
-        v = pcol[j];
-        kv = did[v];
+  for (int64_t v0 = wid * 16; v0 < a.n; v0 += nw * 16) {
+    int64_t b = 0;
+    int32_t all = 0;
+    bool mine = false;
+    if (l < 16 && v0 + l < a.n) {
+      b = a.poff[v0 + l];
+      all = int32_t(a.poff[v0 + l + 1] - b);
+      mine = all <= kShortRow;
+      if (!mine) all = 0;
+      if (mine && all == 0) a.cnt_del[v0 + l] = 0;
+    }
+    // 16 rows at once, or 8 and 8
+    const int32_t sum = lane_read(wave_incl_scan(all), kWave - 1);
+    if (sum == 0) continue;
+    for (int half = 0; half < (sum <= kShortCap ? 1 : 2); ++half) {
+      const bool take = sum <= kShortCap || l / 8 == half;
+      const int32_t len = take ? all : 0;
+      const int32_t incl = wave_incl_scan(len);
+      const int32_t T = lane_read(incl, kWave - 1);
+      wave_sync();
+      S.ex[l] = incl - len;
+      if (l < 16) S.beg[l] = b;
+      wave_sync();
+      for (int32_t e = l; e < T; e += kWave) {
+        const int o = owner_of(S.ex, e);
+        const int32_t v = a.pcol[S.beg[o] + (e - S.ex[o])];
+        const uint8_t c = a.code[v];
+        S.col[e] = v;
+        S.code[e] = c;
+        // exact degrees order the nd entries of normal rows
+        S.deg[e] = a.is_del(c) ? a.deg[v] : 0;
       }
-      const bool v_del = kv >= 0;
-      const bool first = r.del ? v_del : !v_del;
-      const uint64_t ma = __ballot(ok && first), mb = __ballot(ok && !first);
-      const int32_t val = v_del ? kv : v;
-      if (ok && first) r.col[pa + lanes_below(ma)] = val;
-      if (ok && !first) r.col[pb + lanes_below(mb)] = val;
-      pa += __popcll(ma);
-      pb += __popcll(mb);
+      wave_sync();
+      for (int32_t e = l; e < T; e += kWave) {
+        const int o = owner_of(S.ex, e);
+        const int32_t r0 = S.ex[o], r1 = o < kWave - 1 ? S.ex[o + 1] : T;
+        const uint32_t c = S.code[e];
+        const uint32_t pk = a.plain_key(c);
+        const int32_t dg = S.deg[e];
+        int32_t before = 0;   // entries of the plain row before this one
+        int32_t del = 0;      // delegate entries of the row
+        int32_t del_b = 0, del_d = 0;  // delegates before, by bucket / by degree
+        int32_t nor_b = 0;    // normals before, by ID
+        for (int32_t j = r0; j < r1; ++j) {
+          const uint32_t cj = S.code[j];
+          const uint32_t kj = a.plain_key(cj);
+          const bool dj = a.is_del(cj), ahead = j < e;
+          const int32_t gj = S.deg[j];
+          before += kj < pk || (kj == pk && ahead);
+          del += dj;
+          del_b += dj && (cj > c || (cj == c && ahead));
+          del_d += dj && (gj > dg || (gj == dg && ahead));
+          nor_b += !dj && ahead;
+        }
+        const int32_t v = S.col[e];
+        const int64_t u = v0 + o;
+        if (a.plain) a.plain[S.beg[o] + before] = v;
+        bool row_del;
+        int32_t *out = a.split_row(int32_t(u), row_del);
+        const bool is_del = a.is_del(c);
+        const int32_t len_o = r1 - r0;
+        int32_t pos;
+        if (row_del) pos = is_del ? del_b : del + nor_b;
+        else pos = is_del ? (len_o - del) + del_d : nor_b;
+        out[pos] = is_del ? a.del_id(v) : v;
+        if (e == r0) a.cnt_del[u] = del;
+      }
+      wave_sync();
     }
   }
 }
 
-__global__ void k_flag_large(const int64_t *poff, int32_t n, uint8_t *flag) {
-  for (int64_t u = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; u < n;
-       u += int64_t(gridDim.x) * blockDim.x)
-    flag[u] = poff[u + 1] - poff[u] > kSmallRow;
+// Longer rows: a stable counting sort by one-byte keys, for the plain row and
+// the split row together: counts, their prefix, then the entries 64 per wave
+// step, ranked inside the step by matching keys with ballots (their order, so
+// ascending IDs, is kept among equal keys). A wave per row up to kHugeRow
+// entries; past that a block of 16 waves per row. (Before: keys of 8 bytes
+// and four or five radix passes over all rows for each of the two orders.)
+constexpr int kHugeRow = 8192;
+
+// Lanes with the same key as this one, among `active`.
+__device__ __forceinline__ uint64_t match_key(uint32_t key, uint64_t active) {
+  uint64_t m = active;
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const bool bit = (key >> b) & 1u;
+    const uint64_t bal = __ballot(bit);
+    m &= bit ? bal : ~bal;
+  }
+  return m;
+}
+
+// Exclusive prefix of 256 counts by one wave, in place (4 counts a lane).
+__device__ __forceinline__ void prefix256(int32_t *cnt) {
+  const int l = lane_id();
+  int32_t c[4], t = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    c[i] = cnt[4 * l + i];
+    t += c[i];
+  }
+  int32_t run = wave_incl_scan(t) - t;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    cnt[4 * l + i] = run;
+    run += c[i];
+  }
+}
+
+__global__ void __launch_bounds__(kBS) k_rows_long(Arrange a, const int32_t *rows,
+                                                   const int64_t *nrows) {
+  __shared__ int32_t s_p[kBS / kWave][256], s_s[kBS / kWave][256];
+  int32_t *const cp = s_p[threadIdx.x / kWave], *const cs = s_s[threadIdx.x / kWave];
+  const int l = lane_id();
+  const int64_t wid = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
+  const int64_t nw = int64_t(gridDim.x) * blockDim.x / kWave;
+  const int64_t R = *nrows;
+  for (int64_t i = wid; i < R; i += nw) {
+    const int32_t u = rows[i];
+    const int64_t b = a.poff[u];
+    const int32_t len = int32_t(a.poff[u + 1] - b);
+    if (len > kHugeRow) continue;
+    bool del;
+    int32_t *const out = a.split_row(u, del);
+    wave_sync();
+    for (int k = l; k < 256; k += kWave) cp[k] = cs[k] = 0;
+    wave_sync();
+    int32_t ndel = 0;
+    for (int32_t j = l; j < len; j += kWave) {
+      const uint32_t c = a.code[a.pcol[b + j]];
+      ndel += a.is_del(c);
+      atomicAdd(&cp[a.plain_key(c)], 1);
+      atomicAdd(&cs[a.split_key(c, del)], 1);
+    }
+    ndel = wave_sum(ndel);
+    if (l == 0) a.cnt_del[u] = ndel;
+    wave_sync();
+    prefix256(cp);
+    prefix256(cs);
+    wave_sync();
+    for (int32_t j0 = 0; j0 < len; j0 += kWave) {
+      const bool ok = j0 + l < len;
+      const uint64_t act = __ballot(ok);
+      const int32_t v = ok ? a.pcol[b + j0 + l] : 0;
+      const uint32_t c = ok ? a.code[v] : 0;
+      const uint32_t ks = a.split_key(c, del);
+      const uint64_t ms = match_key(ks, act);
+      if (ok) out[cs[ks] + int32_t(lanes_below(ms))] = a.is_del(c) ? a.del_id(v) : v;
+      uint32_t kp = 0;
+      uint64_t mp = 0;
+      if (a.plain) {
+        kp = a.plain_key(c);
+        mp = match_key(kp, act);
+        if (ok) a.plain[b + cp[kp] + int32_t(lanes_below(mp))] = v;
+      }
+      wave_sync();
+      if (ok && lanes_below(ms) == 0) cs[ks] += __popcll(ms);
+      if (a.plain && ok && lanes_below(mp) == 0) cp[kp] += __popcll(mp);
+      wave_sync();
+    }
+  }
+}
+
+constexpr int kHugeBS = 1024, kHugeNW = kHugeBS / kWave;
+
+// One ordering of a huge row: counts per wave of each 1024-entry round, so that
+// entries of equal keys keep their order across the block's waves.
+template <class Key, class Put>
+__device__ void huge_order(int32_t len, int32_t (*wcnt)[256], int32_t *base, Key &&key,
+                           Put &&put) {
+  const int w = threadIdx.x / kWave, l = lane_id();
+  __syncthreads();
+  if (threadIdx.x < 256) base[threadIdx.x] = 0;
+  __syncthreads();
+  for (int32_t j = threadIdx.x; j < len; j += kHugeBS) atomicAdd(&base[key(j)], 1);
+  __syncthreads();
+  if (w == 0) prefix256(base);
+  __syncthreads();
+  for (int32_t j0 = 0; j0 < len; j0 += kHugeBS) {
+    const int32_t j = j0 + threadIdx.x;
+    const bool ok = j < len;
+    const uint32_t k = ok ? key(j) : 0u;
+    const uint64_t m = match_key(k, __ballot(ok));
+    for (int i = l; i < 256; i += kWave) wcnt[w][i] = 0;
+    wave_sync();
+    if (ok && lanes_below(m) == 0) wcnt[w][k] = __popcll(m);
+    __syncthreads();
+    if (threadIdx.x < 256) {
+      int32_t run = base[threadIdx.x];
+#pragma unroll
+      for (int i = 0; i < kHugeNW; ++i) {
+        const int32_t c = wcnt[i][threadIdx.x];
+        wcnt[i][threadIdx.x] = run;
+        run += c;
+      }
+      base[threadIdx.x] = run;
+    }
+    __syncthreads();
+    if (ok) put(j, wcnt[w][k] + int32_t(lanes_below(m)));
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(kHugeBS) k_rows_huge(Arrange a, const int32_t *rows,
+                                                       const int64_t *nrows) {
+  __shared__ int32_t wcnt[kHugeNW][256];
+  __shared__ int32_t base[256];
+  __shared__ int32_t ndel;
+  const int64_t R = *nrows;
+  for (int64_t i = blockIdx.x; i < R; i += gridDim.x) {
+    const int32_t u = rows[i];
+    const int64_t b = a.poff[u];
+    const int32_t len = int32_t(a.poff[u + 1] - b);
+    bool del;
+    int32_t *const out = a.split_row(u, del);
+    if (threadIdx.x == 0) ndel = 0;
+    __syncthreads();
+    int32_t nd = 0;
+    for (int32_t j = threadIdx.x; j < len; j += kHugeBS) nd += a.is_del(a.code[a.pcol[b + j]]);
+    nd = wave_sum(nd);
+    if (lane_id() == 0) atomicAdd(&ndel, nd);
+    __syncthreads();
+    if (threadIdx.x == 0) a.cnt_del[u] = ndel;
+    auto code = [&](int32_t j) { return uint32_t(a.code[a.pcol[b + j]]); };
+    huge_order(len, wcnt, base, [&](int32_t j) { return a.split_key(code(j), del); },
+               [&](int32_t j, int32_t pos) {
+                 const int32_t v = a.pcol[b + j];
+                 out[pos] = a.is_del(a.code[v]) ? a.del_id(v) : v;
+               });
+    if (a.plain)
+      huge_order(len, wcnt, base, [&](int32_t j) { return a.plain_key(code(j)); },
+                 [&](int32_t j, int32_t pos) { a.plain[b + pos] = a.pcol[b + j]; });
+    __syncthreads();
+  }
 }
 
 __global__ void k_flag_ndsrc(const int32_t *did, const int32_t *cnt_del, int32_t n, uint8_t *flag) {
@@ -341,93 +570,31 @@ __global__ void k_stats(const int32_t *deg, const int32_t *did, const int32_t *c
     }
     mx = dg > mx ? dg : mx;
   }
+  // one atomic a block and count (one a wave, on one line, took 1.6 ms at 4M vertices)
+  __shared__ unsigned long long sh[9];
+  if (threadIdx.x < 9) sh[threadIdx.x] = 0;
+  __syncthreads();
   for (int i = 0; i < 8; ++i) {
-    unsigned long long s = wave_sum(a[i]);
+    const unsigned long long s = wave_sum(a[i]);
     // out[7] is the maximum degree; the count of normals with an nn edge is out[8]
-    if (lane_id() == 0 && s) atomicAdd(&out[i < 7 ? i : 8], s);
+    if (lane_id() == 0 && s) atomicAdd(&sh[i < 7 ? i : 8], s);
   }
   for (int o = 32; o > 0; o >>= 1) {
     unsigned long long t = __shfl_xor(mx, o, kWave);
     mx = t > mx ? t : mx;
   }
-  if (lane_id() == 0) atomicMax(&out[7], mx);
+  if (lane_id() == 0) atomicMax(&sh[7], mx);
+  __syncthreads();
+  if (threadIdx.x < 9 && sh[threadIdx.x]) {
+    if (threadIdx.x == 7) atomicMax(&out[7], sh[7]);
+    else atomicAdd(&out[threadIdx.x], sh[threadIdx.x]);
+  }
 }
 
 int bits_for(int64_t n) {
   int B = 1;
   while ((int64_t(1) << B) < n) ++B;
   return B;
-}
-
-// Degree bucket of a vertex on a log scale (8 buckets per power of two), so
-// that sorting by bucket orders neighbours by degree with a short key.
-__device__ __forceinline__ uint32_t deg_bucket(int32_t deg) {
-  if (deg <= 1) return 0;
-  const uint32_t lg = 31u - __clz(uint32_t(deg));          // floor(log2)
-  const uint32_t frac = lg >= 3 ? (uint32_t(deg) >> (lg - 3)) & 7u : (uint32_t(deg) << (3 - lg)) & 7u;
-  const uint32_t b = lg * 8u + frac;
-  return b > 255u ? 255u : b;
-}
-
-// Keys of every dd entry: (row k, 255 - degree bucket of the neighbour,
-// neighbour delegate ID), so one radix sort orders each dd part by
-// neighbour degree, highest first (ties by ID). One wave per row.
-__global__ void k_dd_keys(const uint64_t *doff, const int32_t *dcol, const int64_t *ddpre,
-                          const int32_t *vid_of, const int32_t *deg, int32_t d, int Bd,
-                          uint64_t *keys) {
-  const int l = lane_id();
-  const int64_t wid = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
-  const int64_t nw = int64_t(gridDim.x) * blockDim.x / kWave;
-  for (int64_t k = wid; k < d; k += nw) {
-    const uint64_t w = doff[k];
-    const int64_t beg = row_start(w), len = row_first(w);
-    const int64_t out = ddpre[k];
-    for (int64_t j = l; j < len; j += kWave) {
-      const int32_t x = dcol[beg + j];
-      const uint64_t b = 255u - deg_bucket(deg[vid_of[x]]);
-      keys[out + j] = (uint64_t(k) << (Bd + 8)) | (b << Bd) | uint64_t(uint32_t(x));
-    }
-  }
-}
-
-// Writes the sorted dd entries back into their rows.
-__global__ void k_dd_back(const uint64_t *keys, int64_t e_dd, const uint64_t *doff,
-                          const int64_t *ddpre, int Bd, int32_t *dcol) {
-  const uint64_t xmask = (uint64_t(1) << Bd) - 1;
-  for (int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; j < e_dd;
-       j += int64_t(gridDim.x) * blockDim.x) {
-    const uint64_t key = keys[j];
-    const int64_t k = int64_t(key >> (Bd + 8));
-    dcol[row_start(doff[k]) + (j - ddpre[k])] = int32_t(key & xmask);
-  }
-}
-
-// Keys of every plain-CSR entry: (row, 255 - degree bucket of the
-// neighbour, position in the row). Rows are ascending by neighbour ID, so a
-// stable sort on the row and bucket bits orders each row by neighbour degree,
-// highest first, ties by ascending ID. One wave per row.
-__global__ void k_plain_keys(const int64_t *poff, const int32_t *pcol, const int32_t *deg,
-                             int32_t n, uint64_t *keys) {
-  const int l = lane_id();
-  const int64_t wid = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
-  const int64_t nw = int64_t(gridDim.x) * blockDim.x / kWave;
-  for (int64_t v = wid; v < n; v += nw) {
-    const int64_t beg = poff[v], len = poff[v + 1] - beg;
-    for (int64_t j = l; j < len; j += kWave) {
-      const uint64_t b = 255u - deg_bucket(deg[pcol[beg + j]]);
-      keys[beg + j] = (uint64_t(v) << 32) | (b << 24) | uint64_t(j);
-    }
-  }
-}
-
-// Rebuilds the columns in key order (each row keeps its range).
-__global__ void k_plain_back(const uint64_t *keys, int64_t m, const int64_t *poff,
-                             const int32_t *pcol, int32_t *out) {
-  for (int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < m;
-       e += int64_t(gridDim.x) * blockDim.x) {
-    const uint64_t key = keys[e];
-    out[e] = pcol[poff[int64_t(key >> 32)] + int64_t(key & 0xffffffu)];
-  }
 }
 
 // First entry of every dd part (its highest-degree neighbour) and that
@@ -444,15 +611,10 @@ __global__ void k_dd_first(const uint64_t *doff, const int32_t *dcol, const int3
   }
 }
 
-__global__ void k_dd_len(const uint64_t *doff, int32_t d, int32_t *len) {
-  for (int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; k < d;
-       k += int64_t(gridDim.x) * blockDim.x)
-    len[k] = int32_t(row_first(doff[k]));
-}
-
-// nd part of every normal row (at most a few dozen entries when TH is small):
-// insertion sort by neighbour degree, highest first, ties by delegate ID.
-// Parts longer than 64 entries keep ascending ID order.
+// nd parts of normal rows longer than kShortRow (TH above it; shorter rows are
+// ordered where they are arranged): insertion sort by neighbour degree,
+// highest first, ties by delegate ID. Parts longer than 64 entries keep
+// ascending ID order.
 __global__ void k_nd_sort(const uint64_t *noff, int32_t n, const int32_t *did, int32_t *ncol,
                           const int32_t *vid_of, const int32_t *deg) {
   for (int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; v < n;
@@ -460,7 +622,7 @@ __global__ void k_nd_sort(const uint64_t *noff, int32_t n, const int32_t *did, i
     if (did[v] >= 0) continue;
     const uint64_t w0 = noff[v], w1 = noff[v + 1];
     const int64_t b = row_start(w0) + row_first(w0), e = row_start(w1);
-    if (e - b < 2 || e - b > 64) continue;
+    if (e - row_start(w0) <= kShortRow || e - b < 2 || e - b > 64) continue;
     for (int64_t i = b + 1; i < e; ++i) {
       const int32_t x = ncol[i];
       const int32_t dx = deg[vid_of[x]];
@@ -558,35 +720,34 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
       M2 = rmat_pack_keys(rmat, B, keys.as<uint64_t>(), c, s);
     } else if (M2 > 0) {
       HIPCHK(hipMemsetAsync(c, 0, sizeof(unsigned long long), s));
-      hipLaunchKernelGGL(k_pack, dim3(grid_for(g, kBS, 8192)), dim3(kBS), 0, s, ds, dd, g, B,
-                         keys.as<uint64_t>(), c);
+      hipLaunchKernelGGL(k_pack, dim3(grid_for(g, kBS * kPackItems, 8192)), dim3(kBS), 0, s, ds,
+                         dd, g, B, keys.as<uint64_t>(), c);
       HIPCHK(hipGetLastError());
     }
     esrc.reset();
     edst.reset();
+    // 3. plain CSR and degrees: the sorted keys' distinct ones
     int64_t m = 0;
     {
       DevBuf tmp;
-      tmp.alloc(al, std::max(radix_tmp_bytes(M2), compact_tmp_bytes(M2)), s);
-      radix_sort_u64(keys.as<uint64_t>(), alt.as<uint64_t>(), M2, 2 * B, tmp.p, s);
+      tmp.alloc(al, std::max(radix_tmp_bytes(M2), unique_tmp_bytes(M2)), s);
+      if (radix_sort_u64_bits(keys.as<uint64_t>(), alt.as<uint64_t>(), M2, 0, 2 * B, tmp.p, s) !=
+          keys.as<uint64_t>())
+        std::swap(keys, alt);
+      alt.reset();
       int64_t *cnt = reinterpret_cast<int64_t *>(c + 2);
-      unique_sorted_u64(keys.as<uint64_t>(), M2, alt.as<uint64_t>(), cnt, tmp.p, s);
+      unique_count_u64(keys.as<uint64_t>(), M2, cnt, tmp.p, s);
       m = d2h_scalar(cnt, s);
+      G->m = m;
+      G->poff.alloc(al, size_t(n + 1) * 8, s);
+      G->pcol.alloc(al, size_t(m) * 4, s);
+      G->deg.alloc(al, size_t(n) * 4, s);
+      unique_to_csr(keys.as<uint64_t>(), M2, m, B, n, G->poff.as<int64_t>(),
+                    G->pcol.as<int32_t>(), tmp.p, s);
     }
     keys.reset();
-    G->m = m;
-    const uint64_t *uk = alt.as<uint64_t>();
-
-    // 3. plain CSR and degrees
-    G->poff.alloc(al, size_t(n + 1) * 8, s);
-    G->pcol.alloc(al, size_t(m) * 4, s);
-    G->deg.alloc(al, size_t(n) * 4, s);
-    hipLaunchKernelGGL(k_row_offsets, dim3(grid_for(m + 1, kBS, 16384)), dim3(kBS), 0, s, uk, m, B,
-                       n, G->poff.as<int64_t>());
-    HIPCHK(hipGetLastError());
-    hipLaunchKernelGGL(k_cols_and_degree, dim3(grid_for(std::max<int64_t>(m, n), kBS, 16384)),
-                       dim3(kBS), 0, s, uk, m, vmask, G->poff.as<int64_t>(), n,
-                       G->pcol.as<int32_t>(), G->deg.as<int32_t>());
+    hipLaunchKernelGGL(k_degrees, dim3(grid_for(n, kBS, 16384)), dim3(kBS), 0, s,
+                       G->poff.as<int64_t>(), n, G->deg.as<int32_t>());
     HIPCHK(hipGetLastError());
 
     // 4. degree separation: delegate iff degree > TH, IDs in ascending vertex ID
@@ -618,20 +779,80 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
       HIPCHK(hipGetLastError());
     }
 
-    // 5. delegate neighbours per row
-    DevBuf cnt_del;
+    // 5. columns into the split rows (and the plain rows by neighbour degree,
+    //    highest first: a bottom-up pass over them meets hubs first). dd parts
+    //    come by degree bucket, nd parts by degree; the four subgraphs do not
+    //    depend on the order.
+    DevBuf cnt_del, nstart, dstart;
     cnt_del.alloc(al, size_t(n) * 4, s);
-    HIPCHK(hipMemsetAsync(cnt_del.p, 0, size_t(n) * 4, s));
-    if (m > 0) {
-      hipLaunchKernelGGL(k_count_delegate_nbrs, dim3(grid_for(m, kBS, 16384)), dim3(kBS), 0, s,
-                         uk, m, B, vmask, G->did.as<int32_t>(), cnt_del.as<int32_t>());
+    nstart.alloc(al, size_t(n + 1) * 8, s);
+    dstart.alloc(al, size_t(d + 1) * 8, s);
+    {
+      DevBuf nlen, dlen, stmp;
+      nlen.alloc(al, size_t(n) * 4, s);
+      dlen.alloc(al, size_t(d) * 4, s);
+      stmp.alloc(al, scan_tmp_bytes(std::max<int64_t>(n, d)), s);
+      hipLaunchKernelGGL(k_row_lengths, dim3(grid_for(n, kBS, 8192)), dim3(kBS), 0, s,
+                         G->deg.as<int32_t>(), G->did.as<int32_t>(), G->vid_of.as<int32_t>(), n,
+                         int32_t(d), nlen.as<int32_t>(), dlen.as<int32_t>());
       HIPCHK(hipGetLastError());
+      scan_excl_i32_to_i64(nlen.as<int32_t>(), nstart.as<int64_t>(), n, stmp.p, s);
+      scan_excl_i32_to_i64(dlen.as<int32_t>(), dstart.as<int64_t>(), d, stmp.p, s);
     }
-    alt.reset();
+    const int64_t ncols = d2h_scalar(nstart.as<int64_t>() + n, s);
+    G->ncol.alloc(al, size_t(ncols) * 4, s);
+    G->dcol.alloc(al, size_t(m - ncols) * 4, s);
+    {
+      DevBuf code, rank, rows, sorted;
+      code.alloc(al, size_t(n), s);
+      rank.alloc(al, (size_t(n) + 31) / 32 * sizeof(DelRank), s);
+      if (o.keep_plain_csr) sorted.alloc(al, size_t(m) * 4, s);
+      hipLaunchKernelGGL(k_codes, dim3(grid_for(n, kBS, 8192)), dim3(kBS), 0, s,
+                         G->deg.as<int32_t>(), G->did.as<int32_t>(), n, o.threshold,
+                         code.as<uint8_t>(), rank.as<DelRank>());
+      HIPCHK(hipGetLastError());
+      Arrange a{};
+      a.poff = G->poff.as<int64_t>();
+      a.pcol = G->pcol.as<int32_t>();
+      a.code = code.as<uint8_t>();
+      a.rank = rank.as<DelRank>();
+      a.deg = G->deg.as<int32_t>();
+      a.did = G->did.as<int32_t>();
+      a.nstart = nstart.as<int64_t>();
+      a.dstart = dstart.as<int64_t>();
+      a.n = n;
+      a.bth = int32_t(deg_bucket(o.threshold));
+      a.plain = sorted.as<int32_t>();
+      a.ncol = G->ncol.as<int32_t>();
+      a.dcol = G->dcol.as<int32_t>();
+      a.cnt_del = cnt_del.as<int32_t>();
+      hipLaunchKernelGGL(k_rows_short, dim3(grid_for(n, 16 * kBS / kWave, 4096)), dim3(kBS), 0, s,
+                         a);
+      HIPCHK(hipGetLastError());
+      rows.alloc(al, size_t(n) * 4, s);
+      hipLaunchKernelGGL(k_flag_gt, dim3(grid_for(n, kBS, 8192)), dim3(kBS), 0, s,
+                         G->deg.as<int32_t>(), n, kShortRow, flag.as<uint8_t>());
+      HIPCHK(hipGetLastError());
+      compact_flags_u8(flag.as<uint8_t>(), n, rows.as<int32_t>(), cnt, tmp.p, s);
+      hipLaunchKernelGGL(k_rows_long, dim3(4096), dim3(kBS), 0, s, a, rows.as<int32_t>(), cnt);
+      HIPCHK(hipGetLastError());
+      hipLaunchKernelGGL(k_flag_gt, dim3(grid_for(n, kBS, 8192)), dim3(kBS), 0, s,
+                         G->deg.as<int32_t>(), n, kHugeRow, flag.as<uint8_t>());
+      HIPCHK(hipGetLastError());
+      compact_flags_u8(flag.as<uint8_t>(), n, rows.as<int32_t>(), cnt, tmp.p, s);
+      hipLaunchKernelGGL(k_rows_huge, dim3(512), dim3(kHugeBS), 0, s, a, rows.as<int32_t>(), cnt);
+      HIPCHK(hipGetLastError());
+      HIPCHK(hipStreamSynchronize(s));
+      if (o.keep_plain_csr) std::swap(G->pcol, sorted);
+    }
+    if (!o.keep_plain_csr) {
+      G->poff.reset();
+      G->pcol.reset();
+    }
 
-    // 6. statistics (needed for sizes and the packed-offset range check)
+    // 6. statistics and the packed-offset range check
     HIPCHK(hipMemsetAsync(c, 0, 9 * sizeof(unsigned long long), s));
-    hipLaunchKernelGGL(k_stats, dim3(grid_for(n, kBS, 4096)), dim3(kBS), 0, s,
+    hipLaunchKernelGGL(k_stats, dim3(grid_for(n, kBS, 1024)), dim3(kBS), 0, s,
                        G->deg.as<int32_t>(), G->did.as<int32_t>(), cnt_del.as<int32_t>(), n, c);
     HIPCHK(hipGetLastError());
     unsigned long long hs[9];
@@ -642,18 +863,6 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
 
     // 7. row offsets of the two row sets
     {
-      DevBuf nlen, dlen, nstart, dstart, stmp;
-      nlen.alloc(al, size_t(n) * 4, s);
-      dlen.alloc(al, size_t(d) * 4, s);
-      nstart.alloc(al, size_t(n + 1) * 8, s);
-      dstart.alloc(al, size_t(d + 1) * 8, s);
-      stmp.alloc(al, scan_tmp_bytes(std::max<int64_t>(n, d)), s);
-      hipLaunchKernelGGL(k_row_lengths, dim3(grid_for(n, kBS, 8192)), dim3(kBS), 0, s,
-                         G->deg.as<int32_t>(), G->did.as<int32_t>(), G->vid_of.as<int32_t>(), n,
-                         int32_t(d), nlen.as<int32_t>(), dlen.as<int32_t>());
-      HIPCHK(hipGetLastError());
-      scan_excl_i32_to_i64(nlen.as<int32_t>(), nstart.as<int64_t>(), n, stmp.p, s);
-      scan_excl_i32_to_i64(dlen.as<int32_t>(), dstart.as<int64_t>(), d, stmp.p, s);
       G->noff.alloc(al, size_t(n + 1) * 8, s);
       G->doff.alloc(al, size_t(d + 1) * 8, s);
       hipLaunchKernelGGL(k_pack_offsets, dim3(grid_for(n + 1, kBS, 8192)), dim3(kBS), 0, s,
@@ -668,31 +877,7 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
       HIPCHK(hipGetLastError());
     }
     const int64_t e_nn = hs[0], e_nd = hs[1], e_dn = hs[2], e_dd = hs[3];
-    G->ncol.alloc(al, size_t(e_nn + e_nd) * 4, s);
-    G->dcol.alloc(al, size_t(e_dn + e_dd) * 4, s);
-
-    // 8. scatter columns into the split rows
-    hipLaunchKernelGGL(k_split_small, dim3(grid_for(n, kBS, 16384)), dim3(kBS), 0, s,
-                       G->poff.as<int64_t>(), G->pcol.as<int32_t>(), G->did.as<int32_t>(), n,
-                       G->noff.as<uint64_t>(), G->ncol.as<int32_t>(), G->doff.as<uint64_t>(),
-                       G->dcol.as<int32_t>());
-    HIPCHK(hipGetLastError());
-    {
-      DevBuf rows;
-      rows.alloc(al, size_t(n) * 4, s);
-      hipLaunchKernelGGL(k_flag_large, dim3(grid_for(n, kBS, 8192)), dim3(kBS), 0, s,
-                         G->poff.as<int64_t>(), n, flag.as<uint8_t>());
-      HIPCHK(hipGetLastError());
-      compact_flags_u8(flag.as<uint8_t>(), n, rows.as<int32_t>(), cnt, tmp.p, s);
-      hipLaunchKernelGGL(k_split_large, dim3(2048), dim3(kBS), 0, s, rows.as<int32_t>(), cnt,
-                         G->poff.as<int64_t>(), G->pcol.as<int32_t>(), G->did.as<int32_t>(),
-                         G->noff.as<uint64_t>(), G->ncol.as<int32_t>(), G->doff.as<uint64_t>(),
-                         G->dcol.as<int32_t>());
-      HIPCHK(hipGetLastError());
-      HIPCHK(hipStreamSynchronize(s));
-    }
-
-    // 8a. compact copy of the nn parts (the forward nn visit's rows), while
+    // 8. compact copy of the nn parts (the forward nn visit's rows), while
     //     its 32-bit starts can address it
     if (e_nn < (int64_t(1) << 32) && !o.skip_nn_copy) {
       DevBuf cnt_nn, start, stmp;
@@ -714,40 +899,6 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
       HIPCHK(hipStreamSynchronize(s));
     }
 
-    // 8b. delegate-neighbour parts ordered by neighbour degree, highest first:
-    //     bottom-up scans meet frontier hubs early. (Order inside a part is
-    //     free; the four subgraphs are unchanged.)
-    if (d > 0 && e_dd > 1) {
-      const int Bd = bits_for(d);
-      DevBuf ddlen, ddpre, keys, alt2, stmp;
-      ddlen.alloc(al, size_t(d) * 4, s);
-      ddpre.alloc(al, size_t(d + 1) * 8, s);
-      stmp.alloc(al, scan_tmp_bytes(d), s);
-      hipLaunchKernelGGL(k_dd_len, dim3(grid_for(d, kBS, 4096)), dim3(kBS), 0, s,
-                         G->doff.as<uint64_t>(), int32_t(d), ddlen.as<int32_t>());
-      HIPCHK(hipGetLastError());
-      scan_excl_i32_to_i64(ddlen.as<int32_t>(), ddpre.as<int64_t>(), d, stmp.p, s);
-      keys.alloc(al, size_t(e_dd) * 8, s);
-      alt2.alloc(al, size_t(e_dd) * 8, s);
-      hipLaunchKernelGGL(k_dd_keys, dim3(4096), dim3(kBS), 0, s, G->doff.as<uint64_t>(),
-                         G->dcol.as<int32_t>(), ddpre.as<int64_t>(), G->vid_of.as<int32_t>(),
-                         G->deg.as<int32_t>(), int32_t(d), Bd, keys.as<uint64_t>());
-      HIPCHK(hipGetLastError());
-      {
-        DevBuf rtmp;
-        rtmp.alloc(al, radix_tmp_bytes(e_dd), s);
-        // keys are written row by row with IDs ascending inside a row, so a
-        // stable sort on the (row, bucket) fields alone keeps IDs ascending
-        // among equal buckets
-        radix_sort_u64_bits(keys.as<uint64_t>(), alt2.as<uint64_t>(), e_dd, Bd, 2 * Bd + 8,
-                            rtmp.p, s);
-      }
-      hipLaunchKernelGGL(k_dd_back, dim3(grid_for(e_dd, kBS, 16384)), dim3(kBS), 0, s,
-                         keys.as<uint64_t>(), e_dd, G->doff.as<uint64_t>(), ddpre.as<int64_t>(),
-                         Bd, G->dcol.as<int32_t>());
-      HIPCHK(hipGetLastError());
-      HIPCHK(hipStreamSynchronize(s));
-    }
     G->dd_first.alloc(al, size_t(d) * 8, s);
     if (d > 0) {
       hipLaunchKernelGGL(k_dd_first, dim3(grid_for(d, kBS, 4096)), dim3(kBS), 0, s,
@@ -755,7 +906,7 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
                          int32_t(d), G->dd_first.as<int32_t>());
       HIPCHK(hipGetLastError());
     }
-    if (d > 0 && e_nd > 1) {
+    if (d > 0 && e_nd > 1 && o.threshold > kShortRow) {
       hipLaunchKernelGGL(k_nd_sort, dim3(grid_for(n, kBS, 16384)), dim3(kBS), 0, s,
                          G->noff.as<uint64_t>(), n, G->did.as<int32_t>(), G->ncol.as<int32_t>(),
                          G->vid_of.as<int32_t>(), G->deg.as<int32_t>());
@@ -806,30 +957,6 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
                          G->vid_of.as<int32_t>(), G->deg.as<int32_t>(), cnt_del.as<int32_t>(),
                          int32_t(d), G->ddsrc_mask.as<uint32_t>(), G->dnsrc_mask.as<uint32_t>());
       HIPCHK(hipGetLastError());
-    }
-    if (!o.keep_plain_csr) {
-      G->poff.reset();
-      G->pcol.reset();
-    } else if (m > 1) {
-      // Plain rows by neighbour degree, highest first: a bottom-up pass over
-      // them (multi-source BFS, the query server) meets hubs first.
-      DevBuf keys, alt, rtmp, col2;
-      keys.alloc(al, size_t(m) * 8, s);
-      alt.alloc(al, size_t(m) * 8, s);
-      rtmp.alloc(al, radix_tmp_bytes(m), s);
-      hipLaunchKernelGGL(k_plain_keys, dim3(8192), dim3(kBS), 0, s, G->poff.as<int64_t>(),
-                         G->pcol.as<int32_t>(), G->deg.as<int32_t>(), n, keys.as<uint64_t>());
-      HIPCHK(hipGetLastError());
-      radix_sort_u64_bits(keys.as<uint64_t>(), alt.as<uint64_t>(), m, 24, 63, rtmp.p, s);
-      alt.reset();
-      rtmp.reset();
-      col2.alloc(al, size_t(m) * 4, s);
-      hipLaunchKernelGGL(k_plain_back, dim3(grid_for(m, kBS, 16384)), dim3(kBS), 0, s,
-                         keys.as<uint64_t>(), m, G->poff.as<int64_t>(), G->pcol.as<int32_t>(),
-                         col2.as<int32_t>());
-      HIPCHK(hipGetLastError());
-      HIPCHK(hipStreamSynchronize(s));
-      std::swap(G->pcol, col2);
     }
     HIPCHK(hipStreamSynchronize(s));
 

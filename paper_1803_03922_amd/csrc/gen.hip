@@ -94,22 +94,23 @@ __global__ void k_rmat_edges(RmatArgs a, int32_t *src, int32_t *dst) {
 }
 
 // Both directions of every edge that is not a self-loop, as (row << B) | col
-// keys, appended in wave order (the builder sorts them).
-__global__ void k_rmat_keys(RmatArgs a, int B, uint64_t *keys, unsigned long long *cursor) {
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  for (int64_t e0 = int64_t(blockIdx.x) * blockDim.x; e0 < a.g; e0 += stride) {
-    const int64_t e = e0 + threadIdx.x;
-    uint32_t u = 0, v = 0;
-    bool keep = false;
-    if (e < a.g) {
-      rmat_edge(a, e, u, v);
-      keep = u != v;
+// keys, in any order (the builder sorts them); a block reserves the places of
+// all its edges of a step with one atomic.
+constexpr int kGenItems = 8;
+__global__ void __launch_bounds__(256) k_rmat_keys(RmatArgs a, int B, uint64_t *keys,
+                                                   unsigned long long *cursor) {
+  const int64_t tile = int64_t(blockDim.x) * kGenItems;
+  for (int64_t t0 = int64_t(blockIdx.x) * tile; t0 < a.g; t0 += int64_t(gridDim.x) * tile) {
+    int32_t u[kGenItems], v[kGenItems];
+#pragma unroll
+    for (int i = 0; i < kGenItems; ++i) {
+      const int64_t e = t0 + int64_t(i) * blockDim.x + threadIdx.x;
+      uint32_t x = 0, y = 0;
+      if (e < a.g) rmat_edge(a, e, x, y);
+      u[i] = int32_t(x);
+      v[i] = int32_t(y);
     }
-    const int64_t pos = wave_append(keep, cursor);
-    if (keep) {
-      keys[2 * pos] = (uint64_t(u) << B) | uint64_t(v);
-      keys[2 * pos + 1] = (uint64_t(v) << B) | uint64_t(u);
-    }
+    pack_pairs<kGenItems>(u, v, B, keys, cursor);
   }
 }
 
@@ -148,7 +149,7 @@ int64_t rmat_pack_keys(const dsbfs_rmat_spec *sp, int B, uint64_t *keys, unsigne
   const RmatArgs a = rmat_args(sp);
   if (a.g == 0) return 0;
   HIPCHK(hipMemsetAsync(cursor, 0, sizeof(unsigned long long), s));
-  hipLaunchKernelGGL(k_rmat_keys, dim3(grid_for(a.g, 256, 65536)), dim3(256), 0, s, a, B, keys,
+  hipLaunchKernelGGL(k_rmat_keys, dim3(grid_for(a.g, 256 * kGenItems, 65536)), dim3(256), 0, s, a, B, keys,
                      cursor);
   HIPCHK(hipGetLastError());
   return 2 * int64_t(d2h_scalar(reinterpret_cast<const uint64_t *>(cursor), s));

@@ -469,6 +469,46 @@ __device__ __forceinline__ void block_add4(unsigned long long *dst, unsigned lon
 __device__ __forceinline__ int64_t row_start(uint64_t w) { return static_cast<int64_t>(w & kOffMask); }
 __device__ __forceinline__ int64_t row_first(uint64_t w) { return static_cast<int64_t>(w >> kOffShift); }
 
+// Appends both directions of up to N pairs per thread that are not loops as
+// keys (u << B) | v, with one atomic per block (block-uniform call). A pair
+// that is not there is given as a loop.
+template <int N>
+__device__ __forceinline__ void pack_pairs(const int32_t (&u)[N], const int32_t (&v)[N], int B,
+                                           uint64_t *keys, unsigned long long *cursor) {
+  __shared__ unsigned long long wbase[16];
+  const int w = threadIdx.x / kWave, nw = blockDim.x / kWave;
+  int total = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) total += __popcll(__ballot(u[i] != v[i]));
+  __syncthreads();
+  if (lane_id() == 0) wbase[w] = (unsigned long long)total;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long sum = 0;
+    for (int i = 0; i < nw; ++i) sum += wbase[i];
+    unsigned long long run = atomicAdd(cursor, sum);
+    for (int i = 0; i < nw; ++i) {
+      const unsigned long long t = wbase[i];
+      wbase[i] = run;
+      run += t;
+    }
+  }
+  __syncthreads();
+  unsigned long long pos = wbase[w];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const bool keep = u[i] != v[i];
+    const uint64_t m = __ballot(keep);
+    if (keep) {
+      const uint64_t a = uint64_t(uint32_t(u[i])), b = uint64_t(uint32_t(v[i]));
+      uint64_t *const to = keys + 2 * (pos + lanes_below(m));
+      to[0] = (a << B) | b;
+      to[1] = (b << B) | a;
+    }
+    pos += __popcll(m);
+  }
+}
+
 inline int grid_for(int64_t items, int per_block, int cap = 65536) {
   int64_t g = (items + per_block - 1) / per_block;
   if (g < 1) g = 1;
@@ -485,24 +525,27 @@ size_t scan_tmp_bytes(int64_t N);
 void scan_excl_i32_to_i64(const int32_t *in, int64_t *out, int64_t N, void *tmp, hipStream_t s);
 void scan_excl_i64(const int64_t *in, int64_t *out, int64_t N, void *tmp, hipStream_t s);
 
-// LSD radix sort of N uint64 keys over bits [0, key_bits). Result lands in
-// keys (alt is scratch of N keys). hist_tmp is radix_tmp_bytes(N) bytes.
+// Stable LSD radix sort of N uint64 keys on bits [lo_bit, hi_bit) (bits above
+// hi_bit are equal in all keys; keys already ordered below lo_bit keep that
+// order among equal sort fields). Returns the array that holds the result, keys
+// or alt (both of N keys). tmp: radix_tmp_bytes(N).
 size_t radix_tmp_bytes(int64_t N);
-void radix_sort_u64(uint64_t *keys, uint64_t *alt, int64_t N, int key_bits, void *hist_tmp,
-                    hipStream_t s);
-// Stable sort on bits [lo_bit, hi_bit) only (keys already ordered below lo_bit
-// keep that order among equal sort fields).
-void radix_sort_u64_bits(uint64_t *keys, uint64_t *alt, int64_t N, int lo_bit, int hi_bit,
-                         void *hist_tmp, hipStream_t s);
+uint64_t *radix_sort_u64_bits(uint64_t *keys, uint64_t *alt, int64_t N, int lo_bit, int hi_bit,
+                              void *tmp, hipStream_t s);
 
 // Order-preserving compaction of indices i in [0, N) with flag[i] != 0 into
 // out; *count (device) gets the number kept. tmp: compact_tmp_bytes(N).
 size_t compact_tmp_bytes(int64_t N);
 void compact_flags_u8(const uint8_t *flag, int64_t N, int32_t *out, int64_t *count, void *tmp,
                       hipStream_t s);
-// Keeps keys[i] where i == 0 or keys[i] != keys[i-1] (sorted input -> unique).
-void unique_sorted_u64(const uint64_t *keys, int64_t N, uint64_t *out, int64_t *count, void *tmp,
-                       hipStream_t s);
+// The distinct keys of a sorted array as CSR rows: key = (row << B) | column.
+// unique_count_u64 counts them (and leaves the tiles' prefix in tmp),
+// unique_to_csr, called next with the same tmp, writes their columns (col, m of
+// them) and the row offsets off[n + 1]. tmp: unique_tmp_bytes(N).
+size_t unique_tmp_bytes(int64_t N);
+void unique_count_u64(const uint64_t *keys, int64_t N, int64_t *count, void *tmp, hipStream_t s);
+void unique_to_csr(const uint64_t *keys, int64_t N, int64_t m, int B, int32_t n, int64_t *off,
+                   int32_t *col, void *tmp, hipStream_t s);
 
 // Host helpers.
 template <class T> T d2h_scalar(const T *dptr, hipStream_t s) {

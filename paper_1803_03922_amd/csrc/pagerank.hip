@@ -255,9 +255,9 @@ void pagerank_run(const Graph *g, double alpha, int32_t max_iter, double tol, do
       // alone leaves ties in ID order
       int db = 0;
       while ((int64_t(1) << db) <= g->st.max_degree) ++db;
-      radix_sort_u64_bits(keys.as<uint64_t>(), alt.as<uint64_t>(), d, 32, 32 + db, tmp.p, s);
-      hipLaunchKernelGGL(k_pr_ranks, dim3(G0), dim3(kPB), 0, s, keys.as<uint64_t>(), d,
-                         rank.as<int32_t>());
+      const uint64_t *sorted = radix_sort_u64_bits(keys.as<uint64_t>(), alt.as<uint64_t>(), d, 32,
+                                                   32 + db, tmp.p, s);
+      hipLaunchKernelGGL(k_pr_ranks, dim3(G0), dim3(kPB), 0, s, sorted, d, rank.as<int32_t>());
       HIPCHK(hipGetLastError());
       hipLaunchKernelGGL(k_pr_cols, dim3(grid_for(int64_t(d) * kWave, kPB, 8192)), dim3(kPB), 0,
                          s, g->doff.as<uint64_t>(), g->dcol.as<int32_t>(), rank.as<int32_t>(), d,

@@ -14,9 +14,12 @@ constexpr int kItems = 8;            // consecutive items per thread
 constexpr int64_t kTile = kBS * kItems;
 constexpr int kNW = kBS / kWave;
 
-constexpr int kRadixBS = 256;
-constexpr int kRadixRounds = 32;     // rounds of kRadixBS keys per tile
-constexpr int64_t kRadixTile = int64_t(kRadixBS) * kRadixRounds;
+constexpr int kRadixBS = 512;
+constexpr int kRadixNW = kRadixBS / kWave;
+constexpr int kRadixItems = 16;      // keys per thread
+constexpr int64_t kRadixTile = int64_t(kRadixBS) * kRadixItems;
+constexpr int kRadixBits = 9;        // digits of at most 9 bits
+constexpr int kRadixBins = 1 << kRadixBits;
 
 inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 inline int64_t ntiles(int64_t N, int64_t tile) { return (N + tile - 1) / tile; }
@@ -121,16 +124,6 @@ struct FlagOut {
   int32_t *out;
   __device__ void operator()(int64_t pos, int64_t i) const { out[pos] = static_cast<int32_t>(i); }
 };
-struct UniqPred {
-  const uint64_t *k;
-  __device__ bool operator()(int64_t i) const { return i == 0 || k[i] != k[i - 1]; }
-};
-struct UniqOut {
-  const uint64_t *k;
-  uint64_t *out;
-  __device__ void operator()(int64_t pos, int64_t i) const { out[pos] = k[i]; }
-};
-
 template <class P>
 __global__ void __launch_bounds__(kBS) k_compact_count(P pred, int64_t N, int64_t *bsum) {
   __shared__ int64_t sh[kNW + 1];
@@ -191,71 +184,173 @@ void compact_impl(P pred, O out, int64_t N, int64_t *count, void *tmp, hipStream
   HIPCHK(hipGetLastError());
 }
 
+// ---- distinct keys of a sorted array -> CSR ---------------------------------
+// Tiles of kUniqTile keys; a wave takes its keys 64 at a time, so that reads
+// and writes are coalesced and positions come from ballots.
+constexpr int kUniqItems = 16;
+constexpr int64_t kUniqTile = int64_t(kBS) * kUniqItems;
+
+__device__ __forceinline__ bool uniq_at(const uint64_t *keys, int64_t i, int64_t N, uint64_t &key,
+                                        uint64_t &prev) {
+  key = prev = 0;
+  if (i >= N) return false;
+  key = keys[i];
+  prev = i > 0 ? keys[i - 1] : ~key;
+  return key != prev;
+}
+
+__global__ void __launch_bounds__(kBS) k_uniq_count(const uint64_t *keys, int64_t N,
+                                                    int64_t *bsum) {
+  __shared__ int64_t sh[kNW + 1];
+  const int64_t w0 = int64_t(blockIdx.x) * kUniqTile +
+                     int64_t(threadIdx.x / kWave) * (kWave * kUniqItems) + lane_id();
+  int64_t c = 0;
+#pragma unroll
+  for (int k = 0; k < kUniqItems; ++k) {
+    uint64_t key, prev;
+    c += uniq_at(keys, w0 + int64_t(k) * kWave, N, key, prev);
+  }
+  c = block_sum(c, sh);
+  if (threadIdx.x == 0) bsum[blockIdx.x] = c;
+}
+
+// Columns of the distinct keys at their positions, and the offset of every row
+// that begins between a distinct key and the one before it (rows without a
+// key begin where the next one does).
+__global__ void __launch_bounds__(kBS) k_uniq_csr(const uint64_t *keys, int64_t N, int64_t m,
+                                                  int B, int32_t n, const int64_t *bscan,
+                                                  int64_t *off, int32_t *col) {
+  __shared__ int wtot[kNW];
+  const int w = threadIdx.x / kWave;
+  const uint64_t mask = (uint64_t(1) << B) - 1;
+  const int64_t w0 = int64_t(blockIdx.x) * kUniqTile + int64_t(w) * (kWave * kUniqItems) +
+                     lane_id();
+  uint64_t key[kUniqItems], prev[kUniqItems];
+  uint64_t bal[kUniqItems];
+  int tot = 0;
+#pragma unroll
+  for (int k = 0; k < kUniqItems; ++k) {
+    bal[k] = __ballot(uniq_at(keys, w0 + int64_t(k) * kWave, N, key[k], prev[k]));
+    tot += __popcll(bal[k]);
+  }
+  if (lane_id() == 0) wtot[w] = tot;
+  __syncthreads();
+  int64_t pos = bscan[blockIdx.x];
+  for (int i = 0; i < w; ++i) pos += wtot[i];
+#pragma unroll
+  for (int k = 0; k < kUniqItems; ++k) {
+    const int64_t i = w0 + int64_t(k) * kWave;
+    if ((bal[k] >> lane_id()) & 1ull) {
+      const int64_t p = pos + lanes_below(bal[k]);
+      col[p] = int32_t(key[k] & mask);
+      const int64_t row = int64_t(key[k] >> B), before = i > 0 ? int64_t(prev[k] >> B) : -1;
+      for (int64_t x = before + 1; x <= row; ++x) off[x] = p;
+    }
+    // rows after the last key
+    if (i == N - 1)
+      for (int64_t x = int64_t(key[k] >> B) + 1; x <= n; ++x) off[x] = m;
+    pos += __popcll(bal[k]);
+  }
+}
+
+__global__ void k_fill_i64(int64_t *p, int64_t N, int64_t v) {
+  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < N;
+       i += int64_t(gridDim.x) * blockDim.x)
+    p[i] = v;
+}
+
 // ---- radix sort -----------------------------------------------------------
 
 __global__ void __launch_bounds__(kRadixBS) k_radix_hist(const uint64_t *keys, int64_t N,
-                                                          int shift, int64_t nb,
-                                                          int64_t *ghist) {
-  __shared__ int hist[256];
+                                                          int shift, int bits, int64_t nb,
+                                                          int32_t *ghist) {
+  __shared__ int hist[kRadixBins];
+  const uint32_t dmask = (1u << bits) - 1u;
   hist[threadIdx.x] = 0;
   __syncthreads();
   const int64_t tile = int64_t(blockIdx.x) * kRadixTile;
-  for (int r = 0; r < kRadixRounds; ++r) {
-    int64_t i = tile + int64_t(r) * kRadixBS + threadIdx.x;
-    if (i < N) atomicAdd(&hist[(keys[i] >> shift) & 255u], 1);
+#pragma unroll
+  for (int r = 0; r < kRadixItems; ++r) {
+    const int64_t i = tile + int64_t(r) * kRadixBS + threadIdx.x;
+    if (i < N) atomicAdd(&hist[uint32_t(keys[i] >> shift) & dmask], 1);
   }
   __syncthreads();
-  ghist[int64_t(threadIdx.x) * nb + blockIdx.x] = hist[threadIdx.x];
+  if (threadIdx.x <= dmask) ghist[int64_t(threadIdx.x) * nb + blockIdx.x] = hist[threadIdx.x];
 }
 
-// Stable scatter of one tile: keys are taken in rounds of 256 (thread order =
-// key order); inside a wave, lanes with equal digits are matched with 8
-// ballots, so the rank of a key among equal digits of its wave is a popcount;
-// across waves and rounds the running per-digit offsets live in LDS.
+// Stable scatter of one tile of 8192 keys. Wave w holds the tile's keys
+// [1024 w, 1024 w + 1024), 64 at a time; lanes with equal digits are matched
+// with ballots, so a key's rank among the equal digits of its wave is a count
+// the wave keeps in LDS plus a popcount, with no block barrier between steps.
+// The keys then go to LDS in digit order and out from there: runs of the same
+// digit leave as whole lines (about 16 keys, 128 bytes, of random data), where
+// writing them one by one from registers kept 256 partly filled lines per
+// block open in the L2. 128M keys: 1.4 ms a pass of 8 bits before, 0.8 ms a
+// pass of 9 bits now (44 bits: five passes instead of six).
 __global__ void __launch_bounds__(kRadixBS) k_radix_scatter(const uint64_t *keys, uint64_t *out,
-                                                             int64_t N, int shift, int64_t nb,
-                                                             const int64_t *gscan) {
-  __shared__ int wcnt[kRadixBS / kWave][256];
-  __shared__ int64_t base[256];
-  __shared__ int rtot[256];
-  const int tid = threadIdx.x, w = tid / kWave;
-  base[tid] = gscan[int64_t(tid) * nb + blockIdx.x];
+                                                             int64_t N, int shift, int bits,
+                                                             int64_t nb, const int64_t *gscan) {
+  __shared__ uint64_t stage[kRadixTile];
+  __shared__ uint16_t wcnt[kRadixNW][kRadixBins];  // below 8192: two blocks fit a compute unit
+  __shared__ int64_t base[kRadixBins];  // where the tile's keys of a digit go, less their
+                                        // position in the tile's order
+  __shared__ int wsum[kRadixNW];
+  const int tid = threadIdx.x, w = tid / kWave, l = lane_id();
+  const uint32_t dmask = (1u << bits) - 1u;
   const int64_t tile = int64_t(blockIdx.x) * kRadixTile;
-  for (int r = 0; r < kRadixRounds; ++r) {
-    const int64_t rb = tile + int64_t(r) * kRadixBS;
-    if (rb >= N) break;  // uniform across the block
-    const int64_t i = rb + tid;
-    const bool active = i < N;
-    const uint64_t key = active ? keys[i] : 0;
-    const uint32_t dig = static_cast<uint32_t>((key >> shift) & 255u);
-    uint64_t m = __ballot(active);
+  const int64_t w0 = tile + int64_t(w) * (kWave * kRadixItems) + l;
+  uint64_t key[kRadixItems];
+  int rank[kRadixItems];
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
+  for (int r = 0; r < kRadixItems; ++r) {
+    const int64_t i = w0 + int64_t(r) * kWave;
+    key[r] = i < N ? keys[i] : 0;
+  }
+  for (int i = l; i < kRadixBins; i += kWave) wcnt[w][i] = 0;
+  wave_sync();
+#pragma unroll
+  for (int r = 0; r < kRadixItems; ++r) {
+    const bool ok = w0 + int64_t(r) * kWave < N;
+    const uint32_t dig = uint32_t(key[r] >> shift) & dmask;
+    uint64_t m = __ballot(ok);
+    for (int b = 0; b < bits; ++b) {
       const bool bit = (dig >> b) & 1u;
       const uint64_t bal = __ballot(bit);
       m &= bit ? bal : ~bal;
     }
-    const uint32_t rank = lanes_below(m);
+    const int below = int(lanes_below(m));
+    if (ok) rank[r] = wcnt[w][dig] + below;
+    wave_sync();
+    if (ok && below == 0) wcnt[w][dig] = uint16_t(wcnt[w][dig] + __popcll(m));
+    wave_sync();
+  }
+  __syncthreads();
+  // thread = digit: prefix over the waves, then over the digits
+  int total = 0;
 #pragma unroll
-    for (int k = 0; k < kRadixBS / kWave; ++k) wcnt[k][tid] = 0;
-    __syncthreads();
-    if (active && rank == 0) wcnt[w][dig] = __popcll(m);
-    __syncthreads();
-    {
-      int run = 0;
+  for (int k = 0; k < kRadixNW; ++k) {
+    const int c = wcnt[k][tid];
+    wcnt[k][tid] = uint16_t(total);
+    total += c;
+  }
+  const int incl = wave_incl_scan(total);
+  if (l == kWave - 1) wsum[w] = incl;
+  __syncthreads();
+  int first = incl - total;
+  for (int k = 0; k < w; ++k) first += wsum[k];
 #pragma unroll
-      for (int k = 0; k < kRadixBS / kWave; ++k) {
-        int c = wcnt[k][tid];
-        wcnt[k][tid] = run;
-        run += c;
-      }
-      rtot[tid] = run;
-    }
-    __syncthreads();
-    if (active) out[base[dig] + wcnt[w][dig] + rank] = key;
-    __syncthreads();
-    base[tid] += rtot[tid];
-    __syncthreads();
+  for (int k = 0; k < kRadixNW; ++k) wcnt[k][tid] = uint16_t(wcnt[k][tid] + first);
+  if (uint32_t(tid) <= dmask) base[tid] = gscan[int64_t(tid) * nb + blockIdx.x] - first;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kRadixItems; ++r)
+    if (w0 + int64_t(r) * kWave < N)
+      stage[wcnt[w][uint32_t(key[r] >> shift) & dmask] + rank[r]] = key[r];
+  __syncthreads();
+  const int cnt = int(min(kRadixTile, N - tile));
+  for (int i = tid; i < cnt; i += kRadixBS) {
+    const uint64_t k = stage[i];
+    out[base[uint32_t(k >> shift) & dmask] + i] = k;
   }
 }
 
@@ -281,47 +376,77 @@ void compact_flags_u8(const uint8_t *flag, int64_t N, int32_t *out, int64_t *cou
   compact_impl(FlagPred{flag}, FlagOut{out}, N, count, tmp, s);
 }
 
-void unique_sorted_u64(const uint64_t *keys, int64_t N, uint64_t *out, int64_t *count, void *tmp,
-                       hipStream_t s) {
-  compact_impl(UniqPred{keys}, UniqOut{keys, out}, N, count, tmp, s);
+size_t unique_tmp_bytes(int64_t N) {
+  const int64_t nb = ntiles(N, kUniqTile);
+  return align256(size_t(nb) * 8) + align256(size_t(nb + 1) * 8) + scan_tmp_bytes(nb);
+}
+
+void unique_count_u64(const uint64_t *keys, int64_t N, int64_t *count, void *tmp, hipStream_t s) {
+  if (N == 0) {
+    HIPCHK(hipMemsetAsync(count, 0, sizeof(int64_t), s));
+    return;
+  }
+  const int64_t nb = ntiles(N, kUniqTile);
+  char *t = static_cast<char *>(tmp);
+  int64_t *bsum = reinterpret_cast<int64_t *>(t);
+  t += align256(size_t(nb) * 8);
+  int64_t *bscan = reinterpret_cast<int64_t *>(t);
+  t += align256(size_t(nb + 1) * 8);
+  hipLaunchKernelGGL(k_uniq_count, dim3(unsigned(nb)), dim3(kBS), 0, s, keys, N, bsum);
+  HIPCHK(hipGetLastError());
+  scan_impl<int64_t>(bsum, bscan, nb, t, s);
+  HIPCHK(hipMemcpyAsync(count, bscan + nb, sizeof(int64_t), hipMemcpyDeviceToDevice, s));
+}
+
+void unique_to_csr(const uint64_t *keys, int64_t N, int64_t m, int B, int32_t n, int64_t *off,
+                   int32_t *col, void *tmp, hipStream_t s) {
+  if (N == 0) {
+    hipLaunchKernelGGL(k_fill_i64, dim3(grid_for(int64_t(n) + 1, 256, 4096)), dim3(256), 0, s, off,
+                       int64_t(n) + 1, int64_t(0));
+    HIPCHK(hipGetLastError());
+    return;
+  }
+  const int64_t nb = ntiles(N, kUniqTile);
+  const int64_t *bscan = reinterpret_cast<const int64_t *>(static_cast<char *>(tmp) +
+                                                           align256(size_t(nb) * 8));
+  hipLaunchKernelGGL(k_uniq_csr, dim3(unsigned(nb)), dim3(kBS), 0, s, keys, N, m, B, n, bscan, off,
+                     col);
+  HIPCHK(hipGetLastError());
 }
 
 size_t radix_tmp_bytes(int64_t N) {
   const int64_t nb = ntiles(N, kRadixTile);
-  const int64_t H = 256 * (nb > 0 ? nb : 1);
-  return align256(size_t(H) * 8) + align256(size_t(H + 1) * 8) + scan_tmp_bytes(H);
+  const int64_t H = kRadixBins * (nb > 0 ? nb : 1);
+  return align256(size_t(H) * 4) + align256(size_t(H + 1) * 8) + scan_tmp_bytes(H);
 }
 
-void radix_sort_u64(uint64_t *keys, uint64_t *alt, int64_t N, int key_bits, void *tmp,
-                    hipStream_t s) {
-  radix_sort_u64_bits(keys, alt, N, 0, key_bits, tmp, s);
-}
-
-void radix_sort_u64_bits(uint64_t *keys, uint64_t *alt, int64_t N, int lo_bit, int hi_bit,
-                         void *tmp, hipStream_t s) {
-  if (N <= 1 || hi_bit <= lo_bit) return;
+uint64_t *radix_sort_u64_bits(uint64_t *keys, uint64_t *alt, int64_t N, int lo_bit, int hi_bit,
+                              void *tmp, hipStream_t s) {
+  if (N <= 1 || hi_bit <= lo_bit) return keys;
   const int64_t nb = ntiles(N, kRadixTile);
-  const int64_t H = 256 * nb;
+  // the fewest passes of at most kRadixBits bits, of even widths
+  const int passes = (hi_bit - lo_bit + kRadixBits - 1) / kRadixBits;
+  const int width = (hi_bit - lo_bit + passes - 1) / passes;
+  const int64_t H = (int64_t(1) << width) * nb;
   char *t = static_cast<char *>(tmp);
-  int64_t *ghist = reinterpret_cast<int64_t *>(t);
-  t += align256(size_t(H) * 8);
+  int32_t *ghist = reinterpret_cast<int32_t *>(t);
+  t += align256(size_t(H) * 4);
   int64_t *gscan = reinterpret_cast<int64_t *>(t);
   t += align256(size_t(H + 1) * 8);
   uint64_t *src = keys, *dst = alt;
-  for (int shift = lo_bit; shift < hi_bit; shift += 8) {
-    hipLaunchKernelGGL(k_radix_hist, dim3(unsigned(nb)), dim3(kRadixBS), 0, s, src, N, shift, nb,
-                       ghist);
+  for (int shift = lo_bit; shift < hi_bit; shift += width) {
+    hipLaunchKernelGGL(k_radix_hist, dim3(unsigned(nb)), dim3(kRadixBS), 0, s, src, N, shift,
+                       width, nb, ghist);
     HIPCHK(hipGetLastError());
-    scan_impl<int64_t>(ghist, gscan, H, t, s);
+    scan_impl<int32_t>(ghist, gscan, H, t, s);
     hipLaunchKernelGGL(k_radix_scatter, dim3(unsigned(nb)), dim3(kRadixBS), 0, s, src, dst, N,
-                       shift, nb, gscan);
+                       shift, width, nb, gscan);
     HIPCHK(hipGetLastError());
     uint64_t *x = src;
     src = dst;
     dst = x;
   }
-  if (src != keys)
-    HIPCHK(hipMemcpyAsync(keys, src, size_t(N) * sizeof(uint64_t), hipMemcpyDeviceToDevice, s));
+  return src;
 }
 
 }  // namespace dsbfs
