@@ -22,31 +22,18 @@ namespace {
 
 constexpr int kBS = 256;
 
-__global__ void k_validate(const int32_t *src, const int32_t *dst, int64_t g, int32_t n,
-                           unsigned long long *ctr /* [0] bad, [1] non-loop */) {
-  unsigned long long bad = 0, keep = 0;
-  for (int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < g;
-       e += int64_t(gridDim.x) * blockDim.x) {
-    const int32_t u = src[e], v = dst[e];
-    if (u < 0 || u >= n || v < 0 || v >= n) ++bad;
-    else if (u != v) ++keep;
-  }
-  bad = wave_sum(bad);
-  keep = wave_sum(keep);
-  if (lane_id() == 0) {
-    if (bad) atomicAdd(&ctr[0], bad);
-    if (keep) atomicAdd(&ctr[1], keep);
-  }
-}
-
 // Both directions of every non-loop pair as 64-bit keys (u << B) | v, in any
 // order (they are sorted next). A block packs kPackItems pairs per thread and
 // reserves their places with one atomic: one per wave step, on one address,
 // took 12.6 ms for 67M pairs (12.6 ns each, one after the other). Bound by the
-// 24 bytes a pair moves: 0.5 ms.
+// 24 bytes a pair moves: 0.5 ms. Pairs with an endpoint outside [0, n) are
+// counted in *bad (the caller then discards the keys), which saves a pass over
+// the edge list before this one (0.45 ms).
 constexpr int kPackItems = 16;
 __global__ void __launch_bounds__(kBS) k_pack(const int32_t *src, const int32_t *dst, int64_t g,
-                                              int B, uint64_t *keys, unsigned long long *cursor) {
+                                              int32_t n, int B, uint64_t *keys,
+                                              unsigned long long *cursor,
+                                              unsigned long long *bad) {
   constexpr int64_t tile = int64_t(kBS) * kPackItems;
   for (int64_t t0 = int64_t(blockIdx.x) * tile; t0 < g; t0 += int64_t(gridDim.x) * tile) {
     const int64_t w0 = t0 + int64_t(threadIdx.x / kWave) * (kWave * kPackItems) + lane_id();
@@ -56,6 +43,13 @@ __global__ void __launch_bounds__(kBS) k_pack(const int32_t *src, const int32_t 
       const int64_t e = w0 + i * kWave;
       u[i] = e < g ? src[e] : 0;
       v[i] = e < g ? dst[e] : 0;
+      const bool out = u[i] < 0 || u[i] >= n || v[i] < 0 || v[i] >= n;
+      if (__ballot(out)) {
+        if (out) {
+          atomicAdd(bad, 1ull);
+          u[i] = v[i] = 0;
+        }
+      }
     }
     pack_pairs<kPackItems>(u, v, B, keys, cursor);
   }
@@ -389,11 +383,22 @@ __global__ void __launch_bounds__(kBS) k_rows_long(Arrange a, const int32_t *row
     for (int k = l; k < 256; k += kWave) cp[k] = cs[k] = 0;
     wave_sync();
     int32_t ndel = 0;
-    for (int32_t j = l; j < len; j += kWave) {
-      const uint32_t c = a.code[a.pcol[b + j]];
-      ndel += a.is_del(c);
-      atomicAdd(&cp[a.plain_key(c)], 1);
-      atomicAdd(&cs[a.split_key(c, del)], 1);
+    // four steps' loads together (a step alone is a chain of two gathers);
+    // slots past the row end load its last entry again
+    for (int32_t j0 = 0; j0 < len; j0 += 4 * kWave) {
+      int32_t v[4];
+      uint32_t c[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) v[x] = a.pcol[b + min(j0 + x * kWave + l, len - 1)];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) c[x] = a.code[v[x]];
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        if (j0 + x * kWave + l < len) {
+          ndel += a.is_del(c[x]);
+          if (a.plain) atomicAdd(&cp[a.plain_key(c[x])], 1);
+          atomicAdd(&cs[a.split_key(c[x], del)], 1);
+        }
     }
     ndel = wave_sum(ndel);
     if (l == 0) a.cnt_del[u] = ndel;
@@ -401,25 +406,37 @@ __global__ void __launch_bounds__(kBS) k_rows_long(Arrange a, const int32_t *row
     prefix256(cp);
     prefix256(cs);
     wave_sync();
-    for (int32_t j0 = 0; j0 < len; j0 += kWave) {
-      const bool ok = j0 + l < len;
-      const uint64_t act = __ballot(ok);
-      const int32_t v = ok ? a.pcol[b + j0 + l] : 0;
-      const uint32_t c = ok ? a.code[v] : 0;
-      const uint32_t ks = a.split_key(c, del);
-      const uint64_t ms = match_key(ks, act);
-      if (ok) out[cs[ks] + int32_t(lanes_below(ms))] = a.is_del(c) ? a.del_id(v) : v;
-      uint32_t kp = 0;
-      uint64_t mp = 0;
-      if (a.plain) {
-        kp = a.plain_key(c);
-        mp = match_key(kp, act);
-        if (ok) a.plain[b + cp[kp] + int32_t(lanes_below(mp))] = v;
+    for (int32_t j0 = 0; j0 < len; j0 += 4 * kWave) {
+      int32_t v4[4], id4[4];
+      uint32_t c4[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) v4[x] = a.pcol[b + min(j0 + x * kWave + l, len - 1)];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        c4[x] = a.code[v4[x]];
+        const int32_t id = a.del_id(v4[x]);
+        id4[x] = a.is_del(c4[x]) ? id : v4[x];
       }
-      wave_sync();
-      if (ok && lanes_below(ms) == 0) cs[ks] += __popcll(ms);
-      if (a.plain && ok && lanes_below(mp) == 0) cp[kp] += __popcll(mp);
-      wave_sync();
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const bool ok = j0 + x * kWave + l < len;
+        const uint64_t act = __ballot(ok);
+        if (act == 0) break;
+        const uint32_t ks = a.split_key(c4[x], del);
+        const uint64_t ms = match_key(ks, act);
+        if (ok) out[cs[ks] + int32_t(lanes_below(ms))] = id4[x];
+        uint32_t kp = 0;
+        uint64_t mp = 0;
+        if (a.plain) {
+          kp = a.plain_key(c4[x]);
+          mp = match_key(kp, act);
+          if (ok) a.plain[b + cp[kp] + int32_t(lanes_below(mp))] = v4[x];
+        }
+        wave_sync();
+        if (ok && lanes_below(ms) == 0) cs[ks] += __popcll(ms);
+        if (a.plain && ok && lanes_below(mp) == 0) cp[kp] += __popcll(mp);
+        wave_sync();
+      }
     }
   }
 }
@@ -683,7 +700,7 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
     const int B = bits_for(n);
     const uint64_t vmask = (uint64_t(1) << B) - 1;
 
-    // 1. edges on the device, validated (or generated: step 2)
+    // 1. edges on the device (or generated: step 2)
     DevBuf esrc, edst;
     const int32_t *ds = src, *dd = dst;
     if (!rmat && !o.edges_on_device && g > 0) {
@@ -698,19 +715,7 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
     ctr.alloc(al, 16 * sizeof(unsigned long long), s);
     HIPCHK(hipMemsetAsync(ctr.p, 0, 16 * sizeof(unsigned long long), s));
     unsigned long long *c = ctr.as<unsigned long long>();
-    int64_t M2 = 2 * g;   // upper bound for the generator (self-loops are dropped)
-    if (!rmat) {
-      if (g > 0) {
-        hipLaunchKernelGGL(k_validate, dim3(grid_for(g, kBS, 8192)), dim3(kBS), 0, s, ds, dd, g,
-                           n, c);
-        HIPCHK(hipGetLastError());
-      }
-      unsigned long long hc[2];
-      HIPCHK(hipMemcpyAsync(hc, c, sizeof(hc), hipMemcpyDeviceToHost, s));
-      HIPCHK(hipStreamSynchronize(s));
-      if (hc[0]) fail(DSBFS_ERR_INVALID_ARG, "edge endpoint outside [0, num_vertices)");
-      M2 = 2 * int64_t(hc[1]);
-    }
+    int64_t M2 = 2 * g;   // upper bound (self-loops are dropped)
 
     // 2. symmetrize into keys, sort, de-duplicate
     DevBuf keys, alt;
@@ -718,11 +723,15 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
     alt.alloc(al, size_t(M2) * 8, s);
     if (rmat) {
       M2 = rmat_pack_keys(rmat, B, keys.as<uint64_t>(), c, s);
-    } else if (M2 > 0) {
-      HIPCHK(hipMemsetAsync(c, 0, sizeof(unsigned long long), s));
+    } else if (g > 0) {
       hipLaunchKernelGGL(k_pack, dim3(grid_for(g, kBS * kPackItems, 8192)), dim3(kBS), 0, s, ds,
-                         dd, g, B, keys.as<uint64_t>(), c);
+                         dd, g, n, B, keys.as<uint64_t>(), c, c + 1);
       HIPCHK(hipGetLastError());
+      unsigned long long hc[2];
+      HIPCHK(hipMemcpyAsync(hc, c, sizeof(hc), hipMemcpyDeviceToHost, s));
+      HIPCHK(hipStreamSynchronize(s));
+      if (hc[1]) fail(DSBFS_ERR_INVALID_ARG, "edge endpoint outside [0, num_vertices)");
+      M2 = 2 * int64_t(hc[0]);
     }
     esrc.reset();
     edst.reset();
