@@ -145,20 +145,6 @@ __global__ void k_nn_fill(const int64_t *start, const int32_t *cnt, const uint64
 // ---------------------------------------------------------------------------
 // arranging the rows
 // ---------------------------------------------------------------------------
-// Degree bucket of a vertex on a log scale (8 buckets per power of two), so
-// that ordering by bucket orders neighbours by degree with a one-byte key.
-__host__ __device__ __forceinline__ uint32_t deg_bucket(int32_t deg) {
-  if (deg <= 1) return 0;
-#ifdef __HIP_DEVICE_COMPILE__
-  const uint32_t lg = 31u - __clz(uint32_t(deg));          // floor(log2)
-#else
-  const uint32_t lg = 31u - uint32_t(__builtin_clz(uint32_t(deg)));
-#endif
-  const uint32_t frac = lg >= 3 ? (uint32_t(deg) >> (lg - 3)) & 7u : (uint32_t(deg) << (3 - lg)) & 7u;
-  const uint32_t b = lg * 8u + frac;
-  return b > 254u ? 254u : b;
-}
-
 // What the arrangement needs of a neighbour, in arrays that stay in the L2: a
 // byte per vertex with its degree bucket, plus one for delegates (degrees
 // above TH: delegate iff code > bucket(TH), bucket = code minus that one), and

@@ -108,11 +108,13 @@ struct Graph {
   DevBuf nnoff, nncol;
   DevBuf poff, pcol;  // plain CSR: int64 offsets [n+1], int32 columns [m]
   // PageRank's gather-friendly copy, built by its first call and kept with
-  // the graph: pr_rank[k] = rank of delegate k by descending degree (ties by
-  // ID), and pr_col = dcol with every dd entry replaced by that rank, so the
-  // contributions of the most-gathered delegates sit together (int32 [d],
-  // int32 [e_dd + e_dn]).
-  mutable DevBuf pr_rank, pr_col;
+  // the graph: pr_rank[k] = rank of delegate k by descending degree bucket
+  // (ties by ID), pr_order its inverse, pr_lead the leading ranks whose rows a
+  // block pulls, and pr_col = dcol with every dd entry replaced by that rank,
+  // so the contributions of the most-gathered delegates sit together (int32
+  // [d], [d], [e_dd + e_dn]).
+  mutable DevBuf pr_rank, pr_order, pr_col;
+  mutable int32_t pr_lead = 0;
   mutable std::mutex pr_mu;
   int32_t dwords() const { return (d + 31) / 32; }
   int32_t nwords() const { return (n + 31) / 32; }
@@ -507,6 +509,20 @@ __device__ __forceinline__ void pack_pairs(const int32_t (&u)[N], const int32_t 
     }
     pos += __popcll(m);
   }
+}
+
+// Degree bucket of a vertex on a log scale (8 buckets per power of two), so
+// that ordering by bucket orders neighbours by degree with a one-byte key.
+__host__ __device__ __forceinline__ uint32_t deg_bucket(int32_t deg) {
+  if (deg <= 1) return 0;
+#ifdef __HIP_DEVICE_COMPILE__
+  const uint32_t lg = 31u - __clz(uint32_t(deg));          // floor(log2)
+#else
+  const uint32_t lg = 31u - uint32_t(__builtin_clz(uint32_t(deg)));
+#endif
+  const uint32_t frac = lg >= 3 ? (uint32_t(deg) >> (lg - 3)) & 7u : (uint32_t(deg) << (3 - lg)) & 7u;
+  const uint32_t b = lg * 8u + frac;
+  return b > 254u ? 254u : b;
 }
 
 inline int grid_for(int64_t items, int per_block, int cap = 65536) {
