@@ -243,6 +243,53 @@ __device__ __forceinline__ LaneSet<W> front_of(const LaneSet<W> *fcur, const Lan
   return c >= nlim ? hcur[c - nlim] : fcur[c];
 }
 
+// Lanes that a hub's row [p, p1) brings, by one wave: 64 entries, then 256 at a
+// time, until `want` is covered. Each lane ORs the sets it reads; the wave's OR
+// and the coverage test come once a step, so four column loads and four sets
+// are in flight (most rows of the heavy level are read to the end; one step of
+// 64 and a wave OR at a time is a chain of two round trips per 64 entries).
+// Slots past the end read the last entry again, which an OR does not notice.
+constexpr int kHubSteps = 4;
+template <int W>
+__device__ __forceinline__ LaneSet<W> hub_scan(const int32_t *col, int64_t p, int64_t p1,
+                                               const LaneSet<W> *fcur, const LaneSet<W> *hcur,
+                                               int32_t nlim, const LaneSet<W> &want,
+                                               unsigned long long &edges) {
+  const int l = lane_id();
+  LaneSet<W> acc{};
+  bool first = true;
+  while (p < p1) {
+    LaneSet<W> y;
+    if (first) {
+      y = front_of<W>(fcur, hcur, nlim, col[min(p + l, p1 - 1)]);
+    } else {
+      int32_t c[kHubSteps];
+#pragma unroll
+      for (int u = 0; u < kHubSteps; ++u) c[u] = col[min(p + u * kWave + l, p1 - 1)];
+      LaneSet<W> z[kHubSteps];
+#pragma unroll
+      for (int u = 0; u < kHubSteps; ++u) z[u] = front_of<W>(fcur, hcur, nlim, c[u]);
+      y = z[0];
+#pragma unroll
+      for (int u = 1; u < kHubSteps; ++u)
+#pragma unroll
+        for (int x = 0; x < W; ++x) y.w[x] |= z[u].w[x];
+    }
+    const int64_t step = first ? kWave : kHubSteps * kWave;
+    bool done = true;
+#pragma unroll
+    for (int x = 0; x < W; ++x) {
+      acc.w[x] |= wave_or(y.w[x]);
+      done = done && (acc.w[x] & want.w[x]) == want.w[x];
+    }
+    if (l == 0) edges += uint64_t(min(step, p1 - p));
+    if (done) break;
+    p += step;
+    first = false;
+  }
+  return acc;
+}
+
 template <int W>
 __device__ LaneSet<W> bu_wave(const int64_t *off, const int32_t *col, const LaneSet<W> *fcur,
                               const LaneSet<W> *hcur, int32_t nlim, int64_t w,
@@ -524,9 +571,10 @@ __global__ void __launch_bounds__(1024) k_msbfs(MsArgs a) {
         }
         // hubs, 64 per wave step: each lane screens one and closes it if it
         // wants nothing (most hubs in late levels); the wave then scans the
-        // rows of the others one at a time
-        for (int64_t h0 = wid * kWave; h0 < a.nhubs; h0 += nwaves * kWave) {
-          const int64_t hl = h0 + l;
+        // rows of the others one at a time. Hubs are listed by degree, so a
+        // wave takes every nwaves-th one: each gets rows of all lengths.
+        for (int64_t h0 = wid; h0 < a.nhubs; h0 += nwaves * kWave) {
+          const int64_t hl = h0 + l * nwaves;
           bool need = false;
           if (hl < a.nhubs) {
             const int32_t wl = a.hubs[hl];
@@ -541,27 +589,14 @@ __global__ void __launch_bounds__(1024) k_msbfs(MsArgs a) {
             }
           }
           for (uint64_t todo = __ballot(need); todo; todo &= todo - 1) {
-            const int64_t h = h0 + __builtin_ctzll(todo);
+            const int64_t h = h0 + __builtin_ctzll(todo) * nwaves;
             const int32_t w = a.hubs[h];
             const LaneSet<W> s0 = seen[w];
-            LaneSet<W> want, acc{};
+            LaneSet<W> want;
 #pragma unroll
             for (int x = 0; x < W; ++x) want.w[x] = ~s0.w[x] & live.w[x];
-            {
-              const int64_t p1 = a.off[w + 1];
-              for (int64_t p = a.off[w]; p < p1; p += kWave) {
-                LaneSet<W> y{};
-                if (p + l < p1) y = front_of<W>(fcur, hcur, nlim, a.col2[p + l]);
-                bool done = true;
-#pragma unroll
-                for (int x = 0; x < W; ++x) {
-                  acc.w[x] |= wave_or(y.w[x]);
-                  done = done && (acc.w[x] & want.w[x]) == want.w[x];
-                }
-                if (l == 0) edges += uint64_t(min<int64_t>(kWave, p1 - p));
-                if (done) break;
-              }
-            }
+            const LaneSet<W> acc = hub_scan<W>(a.col2, a.off[w], a.off[w + 1], fcur, hcur, nlim,
+                                               want, edges);
             LaneSet<W> nw;
 #pragma unroll
             for (int x = 0; x < W; ++x) nw.w[x] = acc.w[x] & want.w[x];
@@ -634,6 +669,22 @@ __global__ void k_flag_hub(const int64_t *off, int32_t n, uint8_t *flag) {
   for (int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; v < n;
        v += int64_t(gridDim.x) * blockDim.x)
     flag[v] = off[v + 1] - off[v] > kHub;
+}
+
+// Sort keys of the hubs: (255 - degree bucket) above the vertex.
+__global__ void k_hub_keys(const int32_t *hubs, int64_t nhubs, const int32_t *deg,
+                           uint64_t *keys) {
+  for (int64_t h = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; h < nhubs;
+       h += int64_t(gridDim.x) * blockDim.x) {
+    const int32_t v = hubs[h];
+    keys[h] = (uint64_t(255u - deg_bucket(deg[v])) << 32) | uint64_t(uint32_t(v));
+  }
+}
+
+__global__ void k_hub_list(const uint64_t *keys, int64_t nhubs, int32_t *hubs) {
+  for (int64_t h = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; h < nhubs;
+       h += int64_t(gridDim.x) * blockDim.x)
+    hubs[h] = int32_t(uint32_t(keys[h]));
 }
 
 int device_cus() {
@@ -719,6 +770,38 @@ void msbfs_release(Workspace *ws) {
   ws->ms_state = nullptr;
 }
 
+// The vertices whose rows a whole wave scans in bottom-up levels (once per
+// workspace), by degree bucket, highest first, ties by ID. That is the order of
+// the entries of every plain row too: the hub frontier sets a row reads lie in
+// ascending order, those read most share lines and stay in the L2.
+static void hub_list(const Graph *g, MsState *st, hipStream_t s) {
+  if (st->nhubs >= 0) return;
+  const Alloc *al = &g->al;
+  DevBuf flag, tmp, cnt;
+  flag.alloc(al, size_t(g->n), s);
+  tmp.alloc(al, std::max(compact_tmp_bytes(g->n), radix_tmp_bytes(g->n)), s);
+  cnt.alloc(al, 8, s);
+  st->hubs.alloc(al, size_t(g->n) * 4, s);
+  hipLaunchKernelGGL(k_flag_hub, dim3(grid_for(g->n, 256, 8192)), dim3(256), 0, s,
+                     g->poff.as<int64_t>(), g->n, flag.as<uint8_t>());
+  HIPCHK(hipGetLastError());
+  compact_flags_u8(flag.as<uint8_t>(), g->n, st->hubs.as<int32_t>(), cnt.as<int64_t>(), tmp.p, s);
+  const int64_t nh = d2h_scalar(cnt.as<int64_t>(), s);
+  if (nh > 0) {
+    DevBuf keys, alt;
+    keys.alloc(al, size_t(nh) * 8, s);
+    alt.alloc(al, size_t(nh) * 8, s);
+    const dim3 G(grid_for(nh, 256, 8192)), B(256);
+    hipLaunchKernelGGL(k_hub_keys, G, B, 0, s, st->hubs.as<int32_t>(), nh, g->deg.as<int32_t>(),
+                       keys.as<uint64_t>());
+    const uint64_t *sorted = radix_sort_u64_bits(keys.as<uint64_t>(), alt.as<uint64_t>(), nh, 32,
+                                                 40, tmp.p, s);
+    hipLaunchKernelGGL(k_hub_list, G, B, 0, s, sorted, nh, st->hubs.as<int32_t>());
+    HIPCHK(hipGetLastError());
+  }
+  st->nhubs = nh;
+}
+
 static void msbfs_launch(const Graph *g, Workspace *ws, const int32_t *sources, int32_t k,
                          const dsbfs_ms_opts &o, int32_t *depth, hipStream_t s,
                          unsigned long long *levels_out, unsigned long long *edges_out) {
@@ -733,20 +816,7 @@ static void msbfs_launch(const Graph *g, Workspace *ws, const int32_t *sources, 
   MsState *st = reinterpret_cast<MsState *>(ws->ms_state);
   const Alloc *al = &g->al;
   if (!st->ctl.p) st->ctl.alloc(al, sizeof(MsCtl), s);
-  if (st->nhubs < 0) {
-    // vertices whose rows a whole wave scans in bottom-up levels
-    DevBuf flag, tmp, cnt;
-    flag.alloc(al, size_t(g->n), s);
-    tmp.alloc(al, compact_tmp_bytes(g->n), s);
-    cnt.alloc(al, 8, s);
-    st->hubs.alloc(al, size_t(g->n) * 4, s);
-    hipLaunchKernelGGL(k_flag_hub, dim3(grid_for(g->n, 256, 8192)), dim3(256), 0, s,
-                       g->poff.as<int64_t>(), g->n, flag.as<uint8_t>());
-    HIPCHK(hipGetLastError());
-    compact_flags_u8(flag.as<uint8_t>(), g->n, st->hubs.as<int32_t>(), cnt.as<int64_t>(), tmp.p,
-                     s);
-    st->nhubs = d2h_scalar(cnt.as<int64_t>(), s);
-  }
+  hub_list(g, st, s);
   // hub frontier cache: the remapped columns once per graph (while hub slot
   // numbers n + h fit int32)
   if (st->nhubs > 0 && !st->col2.p && int64_t(g->n) + st->nhubs < int64_t(INT32_MAX)) {
@@ -1194,9 +1264,10 @@ __global__ void __launch_bounds__(256) k_lv_bu(MsLevel a) {
   }
   const int64_t wid = tid / kWave, nwaves = nthreads / kWave;
   // hubs, 64 per wave step: lanes close those that want nothing, the wave
-  // scans the rows of the others one at a time
-  for (int64_t h0 = wid * kWave; h0 < a.nhubs; h0 += nwaves * kWave) {
-    const int64_t hl = h0 + l;
+  // scans the rows of the others one at a time (every nwaves-th hub: they are
+  // listed by degree)
+  for (int64_t h0 = wid; h0 < a.nhubs; h0 += nwaves * kWave) {
+    const int64_t hl = h0 + l * nwaves;
     bool need = false;
     if (hl < a.nhubs) {
       const int32_t wl = a.hubs[hl];
@@ -1204,21 +1275,15 @@ __global__ void __launch_bounds__(256) k_lv_bu(MsLevel a) {
       if (!need) a.fnext[wl] = 0;
     }
     for (uint64_t todo = __ballot(need); todo; todo &= todo - 1) {
-      const int32_t w = a.hubs[h0 + __builtin_ctzll(todo)];
+      const int32_t w = a.hubs[h0 + __builtin_ctzll(todo) * nwaves];
       const uint64_t s0 = a.seen[w];
       const uint64_t want = ~s0 & a.live;
-      uint64_t nw = 0;
-      {
-        const int64_t p1 = a.off[w + 1];
-        uint64_t acc = 0;
-        for (int64_t p = a.off[w]; p < p1; p += kWave) {
-          const uint64_t x = p + l < p1 ? a.fcur[a.col[p + l]] : 0ull;
-          acc |= wave_or(x);
-          if (l == 0) edges += uint64_t(min<int64_t>(kWave, p1 - p));
-          if ((acc & want) == want) break;
-        }
-        nw = acc & want;
-      }
+      const uint64_t nw =
+          hub_scan<1>(a.col, a.off[w], a.off[w + 1],
+                      reinterpret_cast<const LaneSet<1> *>(a.fcur), nullptr, INT32_MAX,
+                      LaneSet<1>{{want}}, edges)
+              .w[0] &
+          want;
       if (l == 0) {
         if (nw) a.seen[w] = s0 | nw;
         a.fnext[w] = nw;
@@ -1311,19 +1376,7 @@ void ms_level_prepare(const Graph *g, Workspace *ws, hipStream_t s) {
   if (!ws->ms_state) ws->ms_state = new MsState();
   MsState *st = reinterpret_cast<MsState *>(ws->ms_state);
   const Alloc *al = &g->al;
-  if (st->nhubs < 0) {
-    DevBuf flag, tmp, cnt;
-    flag.alloc(al, size_t(g->n), s);
-    tmp.alloc(al, compact_tmp_bytes(g->n), s);
-    cnt.alloc(al, 8, s);
-    st->hubs.alloc(al, size_t(g->n) * 4, s);
-    hipLaunchKernelGGL(k_flag_hub, dim3(grid_for(g->n, 256, 8192)), dim3(256), 0, s,
-                       g->poff.as<int64_t>(), g->n, flag.as<uint8_t>());
-    HIPCHK(hipGetLastError());
-    compact_flags_u8(flag.as<uint8_t>(), g->n, st->hubs.as<int32_t>(), cnt.as<int64_t>(), tmp.p,
-                     s);
-    st->nhubs = d2h_scalar(cnt.as<int64_t>(), s);
-  }
+  hub_list(g, st, s);
   const int64_t n = g->n;
   if (!st->lvring.p) st->lvring.alloc(al, size_t(kRing) * size_t(n) * 8, s);
   if (!st->lvseen.p) st->lvseen.alloc(al, size_t(n) * 8, s);
