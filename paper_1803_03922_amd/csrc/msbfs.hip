@@ -243,51 +243,140 @@ __device__ __forceinline__ LaneSet<W> front_of(const LaneSet<W> *fcur, const Lan
   return c >= nlim ? hcur[c - nlim] : fcur[c];
 }
 
-// Lanes that a hub's row [p, p1) brings, by one wave: 64 entries, then 256 at a
-// time, until `want` is covered. Each lane ORs the sets it reads; the wave's OR
-// and the coverage test come once a step, so four column loads and four sets
-// are in flight (most rows of the heavy level are read to the end; one step of
-// 64 and a wave OR at a time is a chain of two round trips per 64 entries).
-// Slots past the end read the last entry again, which an OR does not notice.
+// ORs into acc the lanes that entries [p, min(p + 64 kHubSteps, p1)) of a hub's
+// row bring, by one wave: four column loads, then four sets in flight per lane,
+// one wave OR for the step. Slots past the end read the last entry again,
+// which an OR does not notice.
 constexpr int kHubSteps = 4;
+constexpr int64_t kHubStep = kHubSteps * kWave;
 template <int W>
-__device__ __forceinline__ LaneSet<W> hub_scan(const int32_t *col, int64_t p, int64_t p1,
-                                               const LaneSet<W> *fcur, const LaneSet<W> *hcur,
-                                               int32_t nlim, const LaneSet<W> &want,
-                                               unsigned long long &edges) {
+__device__ __forceinline__ void hub_step(const int32_t *col, int64_t p, int64_t p1,
+                                         const LaneSet<W> *fcur, const LaneSet<W> *hcur,
+                                         int32_t nlim, LaneSet<W> &acc) {
   const int l = lane_id();
-  LaneSet<W> acc{};
-  bool first = true;
-  while (p < p1) {
-    LaneSet<W> y;
-    if (first) {
-      y = front_of<W>(fcur, hcur, nlim, col[min(p + l, p1 - 1)]);
-    } else {
-      int32_t c[kHubSteps];
+  int32_t c[kHubSteps];
 #pragma unroll
-      for (int u = 0; u < kHubSteps; ++u) c[u] = col[min(p + u * kWave + l, p1 - 1)];
-      LaneSet<W> z[kHubSteps];
+  for (int u = 0; u < kHubSteps; ++u) c[u] = col[min(p + u * kWave + l, p1 - 1)];
+  LaneSet<W> z[kHubSteps];
 #pragma unroll
-      for (int u = 0; u < kHubSteps; ++u) z[u] = front_of<W>(fcur, hcur, nlim, c[u]);
-      y = z[0];
+  for (int u = 0; u < kHubSteps; ++u) z[u] = front_of<W>(fcur, hcur, nlim, c[u]);
 #pragma unroll
-      for (int u = 1; u < kHubSteps; ++u)
+  for (int u = 1; u < kHubSteps; ++u)
 #pragma unroll
-        for (int x = 0; x < W; ++x) y.w[x] |= z[u].w[x];
+    for (int x = 0; x < W; ++x) z[0].w[x] |= z[u].w[x];
+#pragma unroll
+  for (int x = 0; x < W; ++x) acc.w[x] |= wave_or_all(z[0].w[x]);
+}
+
+template <int W>
+__device__ __forceinline__ bool lanes_covered(const LaneSet<W> &acc, const LaneSet<W> &want) {
+  bool done = true;
+#pragma unroll
+  for (int x = 0; x < W; ++x) done = done && (acc.w[x] & want.w[x]) == want.w[x];
+  return done;
+}
+
+// The hubs' part of a bottom-up level (whole block). 64 hubs per wave step:
+// each lane screens one and closes it if it wants nothing (most hubs in late
+// levels); the wave then scans the rows of the others one at a time, 64
+// entries, then 256 a step, until the wanted lanes are covered. Hubs are
+// listed by degree and dealt out to the blocks one by one, so every wave gets
+// rows of all lengths. A row that is not covered after kHubWave entries is put
+// aside (in the wave's LDS rows) and scanned by all waves of the block
+// together: one wave alone took 60 us of a 70 us level for the longest row of
+// RMAT 20, the grid waiting for it.
+//   get(h, want): hub h's vertex, and the lanes it wants; close(h, w, nw):
+//   hub h, vertex w, first reached by lanes nw (one thread).
+constexpr int64_t kHubWave = kWave + 4 * kHubStep;
+template <int W, int NW, class Get, class Close>
+__device__ void hub_pass(BuRows<W> (&rows)[NW], unsigned long long *s_or, int *s_cnt,
+                         const int64_t *off, const int32_t *col, int64_t nhubs,
+                         const LaneSet<W> *fcur, const LaneSet<W> *hcur, int32_t nlim,
+                         unsigned long long &edges, Get &&get, Close &&close) {
+  const int l = lane_id(), wv = threadIdx.x / kWave, nwb = blockDim.x / kWave;
+  BuRows<W> &mine = rows[wv];
+  const int64_t nwaves = int64_t(gridDim.x) * nwb;
+  int aside = 0;  // rows put aside by this wave
+  for (int64_t h0 = int64_t(wv) * gridDim.x + blockIdx.x; h0 < nhubs; h0 += nwaves * kWave) {
+    const int64_t hl = h0 + l * nwaves;
+    bool need = false;
+    if (hl < nhubs) {
+      LaneSet<W> want;
+      const int32_t w = get(hl, want);
+      need = lanes_any(want);
+      if (!need) close(hl, w, LaneSet<W>{});
     }
-    const int64_t step = first ? kWave : kHubSteps * kWave;
-    bool done = true;
+    for (uint64_t todo = __ballot(need); todo; todo &= todo - 1) {
+      const int64_t h = h0 + __builtin_ctzll(todo) * nwaves;
+      LaneSet<W> want;
+      const int32_t w = get(h, want);
+      int64_t p = off[w];
+      const int64_t p0 = p, p1 = off[w + 1];
+      LaneSet<W> acc;
+      {
+        const LaneSet<W> y = front_of<W>(fcur, hcur, nlim, col[min(p + l, p1 - 1)]);
 #pragma unroll
-    for (int x = 0; x < W; ++x) {
-      acc.w[x] |= wave_or(y.w[x]);
-      done = done && (acc.w[x] & want.w[x]) == want.w[x];
+        for (int x = 0; x < W; ++x) acc.w[x] = wave_or_all(y.w[x]);
+        p += kWave;
+      }
+      const int64_t stop = aside < kWave ? min(p1, p0 + kHubWave) : p1;
+      bool done = lanes_covered(acc, want);
+      for (; !done && p < stop; p += kHubStep) {
+        hub_step<W>(col, p, p1, fcur, hcur, nlim, acc);
+        done = lanes_covered(acc, want);
+      }
+      if (l == 0) edges += uint64_t(min(p, p1) - p0);
+      if (!done && p < p1) {
+        if (l == 0) {
+          mine.beg[aside] = h;
+          mine.want[aside] = acc;
+        }
+        ++aside;
+      } else if (l == 0) {
+#pragma unroll
+        for (int x = 0; x < W; ++x) acc.w[x] &= want.w[x];
+        close(h, w, acc);
+      }
     }
-    if (l == 0) edges += uint64_t(min(step, p1 - p));
-    if (done) break;
-    p += step;
-    first = false;
   }
-  return acc;
+  if (l == 0) s_cnt[wv] = aside;
+  __syncthreads();
+  for (int v = 0; v < nwb; ++v) {
+    const int cnt = s_cnt[v];
+    for (int i = 0; i < cnt; ++i) {
+      const int64_t h = rows[v].beg[i];
+      LaneSet<W> want, acc = rows[v].want[i];
+      const int32_t w = get(h, want);
+      if (threadIdx.x < W) s_or[threadIdx.x] = acc.w[threadIdx.x];
+      __syncthreads();
+      const int64_t p1 = off[w + 1];
+      bool done = false;
+      for (int64_t p = off[w] + kHubWave; !done && p < p1; p += nwb * kHubStep) {
+        const int64_t pw = p + wv * kHubStep;
+        if (pw < p1) {
+          LaneSet<W> y{};
+          hub_step<W>(col, pw, p1, fcur, hcur, nlim, y);
+          if (l == 0) {
+            edges += uint64_t(min(kHubStep, p1 - pw));
+#pragma unroll
+            for (int x = 0; x < W; ++x)
+              if (y.w[x]) atomicOr(&s_or[x], (unsigned long long)y.w[x]);
+          }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int x = 0; x < W; ++x) acc.w[x] = s_or[x];
+        done = lanes_covered(acc, want);
+        __syncthreads();
+      }
+      if (threadIdx.x == 0) {
+#pragma unroll
+        for (int x = 0; x < W; ++x) acc.w[x] &= want.w[x];
+        close(h, w, acc);
+      }
+    }
+  }
+  __syncthreads();
 }
 
 template <int W>
@@ -356,6 +445,8 @@ __global__ void __launch_bounds__(1024) k_msbfs(MsArgs a) {
     int64_t win[16][kWave + 1];
   } s_u;
   __shared__ unsigned long long sh[16];
+  __shared__ unsigned long long s_or[W];
+  __shared__ int s_cnt[16];
   constexpr int kLanes = 64 * W;
   const int32_t n = a.n;
   LaneSet<W> *const seen = static_cast<LaneSet<W> *>(a.seen);
@@ -569,43 +660,21 @@ __global__ void __launch_bounds__(1024) k_msbfs(MsArgs a) {
             for (int x = 0; x < W; ++x) lor.w[x] |= nw.w[x];
           }
         }
-        // hubs, 64 per wave step: each lane screens one and closes it if it
-        // wants nothing (most hubs in late levels); the wave then scans the
-        // rows of the others one at a time. Hubs are listed by degree, so a
-        // wave takes every nwaves-th one: each gets rows of all lengths.
-        for (int64_t h0 = wid; h0 < a.nhubs; h0 += nwaves * kWave) {
-          const int64_t hl = h0 + l * nwaves;
-          bool need = false;
-          if (hl < a.nhubs) {
-            const int32_t wl = a.hubs[hl];
-            const LaneSet<W> sl = seen[wl];
-            LaneSet<W> wantl;
+        hub_pass<W>(
+            s_u.rows, s_or, s_cnt, a.off, a.col2, a.nhubs, fcur, hcur, nlim, edges,
+            [&](int64_t h, LaneSet<W> &want) {
+              const int32_t w = a.hubs[h];
+              const LaneSet<W> sv = seen[w];
 #pragma unroll
-            for (int x = 0; x < W; ++x) wantl.w[x] = ~sl.w[x] & live.w[x];
-            need = lanes_any(wantl);
-            if (!need) {
-              fnext[wl] = LaneSet<W>{};
-              if (hot) hnext[hl] = LaneSet<W>{};
-            }
-          }
-          for (uint64_t todo = __ballot(need); todo; todo &= todo - 1) {
-            const int64_t h = h0 + __builtin_ctzll(todo) * nwaves;
-            const int32_t w = a.hubs[h];
-            const LaneSet<W> s0 = seen[w];
-            LaneSet<W> want;
-#pragma unroll
-            for (int x = 0; x < W; ++x) want.w[x] = ~s0.w[x] & live.w[x];
-            const LaneSet<W> acc = hub_scan<W>(a.col2, a.off[w], a.off[w + 1], fcur, hcur, nlim,
-                                               want, edges);
-            LaneSet<W> nw;
-#pragma unroll
-            for (int x = 0; x < W; ++x) nw.w[x] = acc.w[x] & want.w[x];
-            if (l == 0) {
+              for (int x = 0; x < W; ++x) want.w[x] = ~sv.w[x] & live.w[x];
+              return w;
+            },
+            [&](int64_t h, int32_t w, const LaneSet<W> &nw) {
               const bool any = lanes_any(nw);
               if (any) {
-                LaneSet<W> s1;
+                LaneSet<W> s1 = seen[w];
 #pragma unroll
-                for (int x = 0; x < W; ++x) s1.w[x] = s0.w[x] | nw.w[x];
+                for (int x = 0; x < W; ++x) s1.w[x] |= nw.w[x];
                 seen[w] = s1;
               }
               fnext[w] = nw;
@@ -613,9 +682,7 @@ __global__ void __launch_bounds__(1024) k_msbfs(MsArgs a) {
               act += any;
 #pragma unroll
               for (int x = 0; x < W; ++x) lor.w[x] |= nw.w[x];
-            }
-          }
-        }
+            });
       }
       const unsigned long long bact = block_sum_u64(act, sh);
       if (threadIdx.x == 0 && bact) atomicAdd(&a.ctl->active[(L + 1) % 3], bact);
@@ -1233,10 +1300,12 @@ __global__ void k_lv_td_close(MsLevel a) {
 
 __global__ void __launch_bounds__(256) k_lv_bu(MsLevel a) {
   __shared__ BuRows<1> s_rows[4];
+  __shared__ unsigned long long s_or[1];
+  __shared__ int s_cnt[4];
   const int64_t nthreads = int64_t(gridDim.x) * blockDim.x;
   const int64_t tid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   const int64_t iters = (int64_t(a.n) + nthreads - 1) / nthreads;
-  const int l = lane_id(), wv = threadIdx.x / kWave;
+  const int wv = threadIdx.x / kWave;
   unsigned long long act = 0, edges = 0;
   uint64_t lor = 0;
   for (int64_t it = 0; it < iters; ++it) {
@@ -1262,36 +1331,20 @@ __global__ void __launch_bounds__(256) k_lv_bu(MsLevel a) {
       lor |= nw;
     }
   }
-  const int64_t wid = tid / kWave, nwaves = nthreads / kWave;
-  // hubs, 64 per wave step: lanes close those that want nothing, the wave
-  // scans the rows of the others one at a time (every nwaves-th hub: they are
-  // listed by degree)
-  for (int64_t h0 = wid; h0 < a.nhubs; h0 += nwaves * kWave) {
-    const int64_t hl = h0 + l * nwaves;
-    bool need = false;
-    if (hl < a.nhubs) {
-      const int32_t wl = a.hubs[hl];
-      need = (~a.seen[wl] & a.live) != 0;
-      if (!need) a.fnext[wl] = 0;
-    }
-    for (uint64_t todo = __ballot(need); todo; todo &= todo - 1) {
-      const int32_t w = a.hubs[h0 + __builtin_ctzll(todo) * nwaves];
-      const uint64_t s0 = a.seen[w];
-      const uint64_t want = ~s0 & a.live;
-      const uint64_t nw =
-          hub_scan<1>(a.col, a.off[w], a.off[w + 1],
-                      reinterpret_cast<const LaneSet<1> *>(a.fcur), nullptr, INT32_MAX,
-                      LaneSet<1>{{want}}, edges)
-              .w[0] &
-          want;
-      if (l == 0) {
-        if (nw) a.seen[w] = s0 | nw;
-        a.fnext[w] = nw;
-        act += nw != 0;
-        lor |= nw;
-      }
-    }
-  }
+  hub_pass<1>(
+      s_rows, s_or, s_cnt, a.off, a.col, a.nhubs, reinterpret_cast<const LaneSet<1> *>(a.fcur),
+      nullptr, INT32_MAX, edges,
+      [&](int64_t h, LaneSet<1> &want) {
+        const int32_t w = a.hubs[h];
+        want.w[0] = ~a.seen[w] & a.live;
+        return w;
+      },
+      [&](int64_t, int32_t w, const LaneSet<1> &nw) {
+        if (nw.w[0]) a.seen[w] |= nw.w[0];
+        a.fnext[w] = nw.w[0];
+        act += nw.w[0] != 0;
+        lor |= nw.w[0];
+      });
   lv_flush(a, act, lor, edges);
 }
 
