@@ -58,14 +58,9 @@ constexpr int kSegs = 256;  // segments of a forward list (one block each)
 // ctr[(L + 2) % 3] and clears ctr[(L + 1) % 3].
 //
 // Sums are kept in kCtrCopies parts, each word on a 128-byte line of its own:
-// device-scope atomics on one line are served one after the other (12.6 ns
-// each), and 2048 blocks adding four counts to one line at the end of a large
-// level cost it about 100 us. A block adds to part blockIdx % kCtrCopies.
+// 2048 blocks adding four counts to one line at the end of a large level cost
+// it about 100 us. A block adds to part blockIdx % kCtrCopies.
 constexpr int kCtrCopies = 8;
-struct alignas(128) CtrLine {
-  unsigned long long v;
-  unsigned long long pad[15];
-};
 enum { kFvNn, kQNn, kFvNd, kQNd, kFdn, kFvDd, kQDd, kFvDn, kQDn, kPrevSums,
        kClDn = kPrevSums,  // delegates with a dn edge claimed by this level
        kNumSums };

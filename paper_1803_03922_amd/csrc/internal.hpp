@@ -156,10 +156,25 @@ struct ResidentLease {
   ResidentLease &operator=(const ResidentLease &) = delete;
 };
 
+// A counter on a 128-byte line of its own: device-scope atomics on one line are
+// served one after the other, 12.6 ns each.
+struct alignas(128) CtrLine {
+  unsigned long long v;
+  unsigned long long pad[15];
+};
+
 // Per-lane result rows of a level-at-a-time multi-source step (server).
 // Sources of the lanes admitted at one level (by value: no copy per level).
 struct SeedList {
   int32_t src[64];
+};
+
+// Control block of one level of the server's batches (device; two alternate):
+// the next frontier's size and lanes, in parts that the reader sums, and the
+// length of a top-down level's list.
+constexpr int kLvParts = 16;
+struct LvCtl {
+  CtrLine active[kLvParts], alive[kLvParts], td_count;
 };
 
 // Rows written by one flush of the server's level ring (see k_lv_flush).

@@ -1133,21 +1133,30 @@ struct MsLevel {
   int64_t *tdscan;
   const int32_t *hubs;
   int64_t nhubs;
-  unsigned long long *ctl;  // [0] active, [1] alive, [2] td_count, [3] edges
+  LvCtl *ctl;
   uint64_t live;
 };
 
 namespace {
 
-__device__ __forceinline__ void lv_flush(const MsLevel &a, unsigned long long act, uint64_t lor,
-                                         unsigned long long edges) {
+// Adds a block's counts to the level's control block (block-uniform): summed in
+// LDS first, then one atomic each into the block's part. One atomic a wave on
+// one line (8192 waves, three words) had been 0.3 ms of every bottom-up level.
+__device__ __forceinline__ void lv_flush(const MsLevel &a, unsigned long long act, uint64_t lor) {
+  __shared__ unsigned long long s_act, s_lor;
+  if (threadIdx.x == 0) s_act = s_lor = 0;
+  __syncthreads();
   act = wave_sum(act);
-  edges = wave_sum(edges);
   lor = wave_or_all(lor);
-  if (lane_id() == 0) {
-    if (act) atomicAdd(&a.ctl[0], act);
-    if (lor) atomicOr(&a.ctl[1], (unsigned long long)lor);
-    if (edges) atomicAdd(&a.ctl[3], edges);
+  if (lane_id() == 0 && act) {
+    atomicAdd(&s_act, act);
+    atomicOr(&s_lor, (unsigned long long)lor);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && s_act) {
+    const int part = blockIdx.x % kLvParts;
+    atomicAdd(&a.ctl->active[part].v, s_act);
+    atomicOr(&a.ctl->alive[part].v, s_lor);
   }
 }
 
@@ -1175,23 +1184,32 @@ __global__ void k_lv_seed(MsLevel a, uint64_t mask, SeedList src) {
 }
 
 // Also, when publish is set (once per level, after the level's kernels):
-// block 0 copies the level's control block to host_ctl (pinned host memory,
-// read by the host once the stream passes this kernel) and clears
-// next_ctl, the control block of the next level.
+// block 0 sums the level's control block into host_ctl (size of the next
+// frontier, its lanes; pinned host memory, read by the host once the stream
+// passes this kernel) and clears next_ctl, the control block of the next level.
 // Writes the result rows of a set of lanes from ring levels [f.jlo, f.jhi]
 // (fewer than kRing): depth j - start[i] where lane i's bit is in level j's
 // mask and f.valid[j - jlo] admits lane i (levels before a lane's start or
 // already written are excluded), and, when `final`, -1 where the lane never
 // arrived. final: the set is f.lanes minus the lanes still alive after the
 // level just run (ctl[1]), i.e. the lanes that completed; else f.lanes.
-__global__ void k_lv_flush(MsLevel a, LaneFlush f, unsigned long long *next_ctl,
+__global__ void k_lv_flush(MsLevel a, LaneFlush f, LvCtl *next_ctl,
                            unsigned long long *host_ctl) {
-  if (host_ctl && blockIdx.x == 0 && threadIdx.x < 4) {
-    host_ctl[threadIdx.x] = a.ctl[threadIdx.x];
-    next_ctl[threadIdx.x] = 0;
-  }
   uint64_t set = f.lanes;
-  if (f.final) set &= ~a.ctl[1];
+  if (f.final) {
+    const int l = lane_id();
+    const uint64_t alive = wave_or_all(l < kLvParts ? a.ctl->alive[l].v : 0ull);
+    set &= ~alive;
+    if (host_ctl && blockIdx.x == 0 && threadIdx.x < kWave) {
+      const unsigned long long act = wave_sum(l < kLvParts ? a.ctl->active[l].v : 0ull);
+      if (l == 0) {
+        host_ctl[0] = act;
+        host_ctl[1] = alive;
+        next_ctl->td_count.v = 0;
+      }
+      if (l < kLvParts) next_ctl->active[l].v = next_ctl->alive[l].v = 0;
+    }
+  }
   if (!set) return;
   const int64_t nthreads = int64_t(gridDim.x) * blockDim.x;
   const int64_t tid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -1234,14 +1252,14 @@ __global__ void k_lv_td_list(MsLevel a) {
     const int64_t v = v0 + threadIdx.x;
     const bool f = v < a.n && a.fcur[v] != 0;
     if (v < a.n) a.fnext[v] = 0;
-    const int64_t pos = wave_append(f, &a.ctl[2]);
+    const int64_t pos = wave_append(f, &a.ctl->td_count.v);
     if (f) a.tdlist[pos] = int32_t(v);
   }
 }
 
 __global__ void __launch_bounds__(1024) k_lv_td_scan(MsLevel a) {
   __shared__ unsigned long long sh[16];
-  const int64_t cnt = int64_t(a.ctl[2]);
+  const int64_t cnt = int64_t(a.ctl->td_count.v);
   unsigned long long carry = 0;
   for (int64_t i0 = 0; i0 < cnt; i0 += blockDim.x) {
     const int64_t i = i0 + threadIdx.x;
@@ -1266,9 +1284,8 @@ __global__ void __launch_bounds__(1024) k_lv_td_scan(MsLevel a) {
 }
 
 __global__ void k_lv_td_expand(MsLevel a) {
-  const int64_t cnt = int64_t(a.ctl[2]);
+  const int64_t cnt = int64_t(a.ctl->td_count.v);
   const int64_t E = a.tdscan[cnt];
-  unsigned long long edges = 0;
   for (int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < E;
        e += int64_t(gridDim.x) * blockDim.x) {
     int64_t lo = 0, hi = cnt - 1;
@@ -1279,13 +1296,11 @@ __global__ void k_lv_td_expand(MsLevel a) {
     }
     const int32_t v = a.tdlist[lo];
     const int32_t w = a.col[a.off[v] + (e - a.tdscan[lo])];
-    ++edges;
     // lanes already in next (a possibly stale read: the atomic decides) need
     // no atomic
     const uint64_t m = a.fcur[v] & ~a.seen[w] & ~a.fnext[w];
     if (m) atomicOr(reinterpret_cast<unsigned long long *>(&a.fnext[w]), m);
   }
-  lv_flush(a, 0, 0, edges);
 }
 
 // Close of a top-down level: fold next into seen (the scatter only set lanes
@@ -1307,7 +1322,7 @@ __global__ void k_lv_td_close(MsLevel a) {
       }
     }
   }
-  lv_flush(a, act, lor, 0);
+  lv_flush(a, act, lor);
 }
 
 __global__ void __launch_bounds__(256) k_lv_bu(MsLevel a) {
@@ -1357,7 +1372,7 @@ __global__ void __launch_bounds__(256) k_lv_bu(MsLevel a) {
         act += nw.w[0] != 0;
         lor |= nw.w[0];
       });
-  lv_flush(a, act, lor, edges);
+  lv_flush(a, act, lor);
 }
 
 }  // namespace
@@ -1365,9 +1380,9 @@ __global__ void __launch_bounds__(256) k_lv_bu(MsLevel a) {
 // Host side of one level for the server. ws must have 64 lanes. `live` are
 // the lanes with a non-empty frontier; L is the level (ring slot L is its
 // frontier, slot L + 1 receives the next). After the call (asynchronous on s)
-// ctl[0] holds the next frontier's vertex count, ctl[1] its lanes. Returns
+// ctl holds the next frontier's vertex count and lanes. Returns
 // the direction used (0 top-down, 1 up).
-static MsLevel level_args(const Graph *g, Workspace *ws, int32_t L, unsigned long long *ctl) {
+static MsLevel level_args(const Graph *g, Workspace *ws, int32_t L, LvCtl *ctl) {
   MsState *st = reinterpret_cast<MsState *>(ws->ms_state);
   MsLevel a{};
   a.off = g->poff.as<int64_t>();
@@ -1386,7 +1401,7 @@ static MsLevel level_args(const Graph *g, Workspace *ws, int32_t L, unsigned lon
 }
 
 int ms_level(const Graph *g, Workspace *ws, uint64_t live, int64_t active, int32_t bu_permille,
-             int32_t L, unsigned long long *ctl, hipStream_t s) {
+             int32_t L, LvCtl *ctl, hipStream_t s) {
   MsLevel a = level_args(g, ws, L, ctl);
   a.live = live;
   const int SG = device_cus() * 8;
@@ -1408,8 +1423,8 @@ int ms_level(const Graph *g, Workspace *ws, uint64_t live, int64_t active, int32
 // Writes result rows from the level ring (k_lv_flush); ctl is the level's
 // control block (read for `final`). With host_ctl, also publishes ctl there
 // and clears next_ctl (see k_lv_flush).
-void ms_level_flush(const Graph *g, Workspace *ws, const LaneFlush &f, unsigned long long *ctl,
-                    unsigned long long *next_ctl, unsigned long long *host_ctl, hipStream_t s) {
+void ms_level_flush(const Graph *g, Workspace *ws, const LaneFlush &f, LvCtl *ctl,
+                    LvCtl *next_ctl, unsigned long long *host_ctl, hipStream_t s) {
   if (f.jhi - f.jlo >= kRing || f.jhi < f.jlo)
     fail(DSBFS_ERR_DEVICE, "server level flush window outside the ring");
   MsLevel a = level_args(g, ws, f.jhi, ctl);

@@ -49,9 +49,9 @@
 namespace dsbfs {
 
 int ms_level(const Graph *g, Workspace *ws, uint64_t live, int64_t active, int32_t bu_permille,
-             int32_t L, unsigned long long *ctl, hipStream_t s);
-void ms_level_flush(const Graph *g, Workspace *ws, const LaneFlush &f, unsigned long long *ctl,
-                    unsigned long long *next_ctl, unsigned long long *host_ctl, hipStream_t s);
+             int32_t L, LvCtl *ctl, hipStream_t s);
+void ms_level_flush(const Graph *g, Workspace *ws, const LaneFlush &f, LvCtl *ctl, LvCtl *next_ctl,
+                    unsigned long long *host_ctl, hipStream_t s);
 int ms_level_ring();
 size_t ms_state_bytes(const Workspace *ws);
 void ms_level_prepare(const Graph *g, Workspace *ws, hipStream_t s);
@@ -118,9 +118,10 @@ struct Cohort {
   int64_t active = 0;
   int32_t L = 0;
   int32_t batch_start = 0;  // level at which the running batch began
-  // control blocks of the levels, alternating by level parity (4 words each),
+  // control blocks of the levels, alternating by level parity,
   // and the host copy of the last finished level's
-  unsigned long long *ctl_dev = nullptr, *ctl_host = nullptr;
+  LvCtl *ctl_dev = nullptr;
+  unsigned long long *ctl_host = nullptr;
   SeedList seeds{};  // sources of the lanes admitted for the next level
   bool launched = false;
 };
@@ -482,8 +483,8 @@ struct Server {
   // Enqueues one multi-source level of cohort c of G on its stream, then the
   // rows of the lanes it completes.
   void launch_level(GState *G, Cohort &c) {
-    unsigned long long *const ctl = c.ctl_dev + 4 * (c.L & 1);
-    unsigned long long *const next_ctl = c.ctl_dev + 4 * ((c.L + 1) & 1);
+    LvCtl *const ctl = c.ctl_dev + (c.L & 1);
+    LvCtl *const next_ctl = c.ctl_dev + ((c.L + 1) & 1);
     HIPCHK(hipEventRecord(c.ev0, c.stream));
     // this level's next frontier overwrites ring level L + 1 - ring: lanes
     // whose rows still need it are written up to level L first
@@ -714,8 +715,8 @@ void cohort_init(Cohort &c, Graph *g, bool batched) {
   HIPCHK(hipEventCreate(&c.ev0));
   c.ws = workspace_create(g, 64);
   if (batched) ms_level_prepare(g, c.ws, c.stream);
-  HIPCHK(hipMalloc(reinterpret_cast<void **>(&c.ctl_dev), 8 * sizeof(unsigned long long)));
-  HIPCHK(hipMemsetAsync(c.ctl_dev, 0, 8 * sizeof(unsigned long long), c.stream));
+  HIPCHK(hipMalloc(reinterpret_cast<void **>(&c.ctl_dev), 2 * sizeof(LvCtl)));
+  HIPCHK(hipMemsetAsync(c.ctl_dev, 0, 2 * sizeof(LvCtl), c.stream));
   HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&c.ctl_host), 4 * sizeof(unsigned long long),
                        hipHostMallocDefault));
   HIPCHK(hipStreamSynchronize(c.stream));
