@@ -44,14 +44,25 @@ struct alignas(128) BarSlot {
 // A batch runs 64 x W sources as the bits of W 64-bit words per vertex.
 constexpr int kMaxWords = 4;
 
+// A part of a level's counts, on a line of its own: vertices with a non-empty
+// next mask, lanes with a non-empty next frontier. A block adds to one part,
+// once; one atomic per wave and lane word on one line (16K of them at 256
+// lanes, 12.6 ns each) had the grid waiting 60 us (64 lanes) to 0.2 ms (256)
+// at the end of every level.
+constexpr int kMsParts = 8;
+struct alignas(128) MsPart {
+  unsigned long long active;
+  unsigned long long alive[kMaxWords];
+  unsigned long long pad[11];
+};
+
 struct MsCtl {
   BarSlot grp[kBarGroups];     // arrivals per block group (monotonic)
   BarSlot top;                 // groups complete (monotonic)
   unsigned int err;            // 1: a barrier wait timed out
   unsigned int pad;
   unsigned long long td_count;   // frontier vertices listed for a top-down level
-  unsigned long long active[3];  // vertices with a non-empty next mask, per level (rolling)
-  unsigned long long alive[3][kMaxWords];  // lanes with a non-empty next frontier (rolling)
+  MsPart part[3][kMsParts];      // per level (rolling): the next frontier, in parts
   unsigned long long levels;     // levels run, summed over batches
   unsigned long long edges;      // adjacency entries read, summed over batches
 };
@@ -234,8 +245,6 @@ __device__ void flush_depth(const MsArgs &a, int64_t row0, const uint64_t *mask,
 }
 
 constexpr int kHub = 64;
-
-__device__ __forceinline__ uint64_t wave_or(uint64_t x) { return wave_or_all(x); }
 
 // LDS rows of one wave for the bottom-up walk (64 vertices).
 template <int W>
@@ -495,11 +504,8 @@ __global__ void __launch_bounds__(1024) k_msbfs(MsArgs a) {
     }
     if (hot)
       for (int64_t h = tid; h < a.nhubs; h += nthreads) hot[h] = LaneSet<W>{};
-    if (blockIdx.x == 0 && threadIdx.x < 3) {
-      a.ctl->active[threadIdx.x] = 0;
-#pragma unroll
-      for (int x = 0; x < kMaxWords; ++x) a.ctl->alive[threadIdx.x][x] = 0;
-    }
+    if (blockIdx.x == 0 && threadIdx.x < 3 * kMsParts)
+      a.ctl->part[threadIdx.x / kMsParts][threadIdx.x % kMsParts] = MsPart{};
     if (!grid_sync(a.ctl, a.timeout_ticks)) return;
     // seed the sources of this batch (duplicates share a vertex: OR the lanes)
     if (tid < lanes) {
@@ -533,11 +539,8 @@ __global__ void __launch_bounds__(1024) k_msbfs(MsArgs a) {
       LaneSet<W> *const hnext = hot ? hot + ((L + 1) & 1) * a.nhubs : nullptr;
       // the rolling count slot level L + 1 adds into; every block read it
       // (for level L - 2) before the barrier that ended level L - 1
-      if (blockIdx.x == 0 && threadIdx.x == 0) {
-        a.ctl->active[(L + 2) % 3] = 0;
-#pragma unroll
-        for (int x = 0; x < W; ++x) a.ctl->alive[(L + 2) % 3][x] = 0;
-      }
+      if (blockIdx.x == 0 && threadIdx.x < kMsParts)
+        a.ctl->part[(L + 2) % 3][threadIdx.x] = MsPart{};
       unsigned long long act = 0;
       LaneSet<W> lor{};
       if (active <= a.bu_threshold) {
@@ -702,19 +705,30 @@ __global__ void __launch_bounds__(1024) k_msbfs(MsArgs a) {
             });
       }
       const unsigned long long bact = block_sum_u64(act, sh);
-      if (threadIdx.x == 0 && bact) atomicAdd(&a.ctl->active[(L + 1) % 3], bact);
+      if (threadIdx.x < W) s_or[threadIdx.x] = 0;
+      __syncthreads();
 #pragma unroll
       for (int x = 0; x < W; ++x) {
-        const uint64_t o = wave_or(lor.w[x]);
-        if (l == 0 && o) atomicOr(&a.ctl->alive[(L + 1) % 3][x], (unsigned long long)o);
+        const uint64_t o = wave_or_all(lor.w[x]);
+        if (l == 0 && o) atomicOr(&s_or[x], (unsigned long long)o);
+      }
+      __syncthreads();
+      if (bact) {
+        MsPart &p = a.ctl->part[(L + 1) % 3][blockIdx.x % kMsParts];
+        if (threadIdx.x == 0) atomicAdd(&p.active, bact);
+        if (threadIdx.x < W && s_or[threadIdx.x])
+          atomicOr(&p.alive[threadIdx.x], s_or[threadIdx.x]);
       }
       if (!grid_sync(a.ctl, a.timeout_ticks)) return;
-      active = int64_t(__hip_atomic_load(&a.ctl->active[(L + 1) % 3], __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT));
+      // the parts, one a lane; every wave sums them for itself
+      const MsPart &p = a.ctl->part[(L + 1) % 3][l % kMsParts];
+      auto part = [&](const unsigned long long *q) {
+        return l < kMsParts ? __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                            : 0ull;
+      };
+      active = int64_t(wave_sum(part(&p.active)));
 #pragma unroll
-      for (int x = 0; x < W; ++x)
-        live.w[x] = __hip_atomic_load(&a.ctl->alive[(L + 1) % 3][x], __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_AGENT);
+      for (int x = 0; x < W; ++x) live.w[x] = wave_or_all(part(&p.alive[x]));
       if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&a.ctl->levels, 1ull);
       if (active == 0) break;
       // a top-down level L + 1 ORs into slot L + 2, which must start at zero
