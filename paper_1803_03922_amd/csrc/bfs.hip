@@ -165,6 +165,13 @@ struct Search {
   double f0[4], f1[4];
   uint64_t forced_seed;
   int32_t forced, nn_do;
+  // Output of delegates and of bottom-up claims by a dense pass at the end
+  // (k_output), from arrays by delegate and by position of the nd source list.
+  int32_t compact;
+  int2 *dout;
+  int32_t *ppar;
+  uint8_t *plev;
+  const RankDir *drank, *nrank;
   int32_t count;  // statistics are wanted: keep work units and every workload sum
   int32_t source, mode;
 
@@ -174,6 +181,20 @@ struct Search {
   __device__ __forceinline__ void put(int32_t v, int32_t p, int32_t dep) const {
     depth[v] = dep;
     if (parent) parent[v] = p;
+  }
+  // a delegate claimed
+  __device__ __forceinline__ void put_deleg(int32_t k, int32_t p, int32_t dep) const {
+    if (compact) dout[k] = int2{p, dep + 1};
+    else put(vid_of[k], p, dep);
+  }
+  // position pos of the nd source list (vertex v) claimed bottom-up
+  __device__ __forceinline__ void put_pos(int32_t pos, int32_t v, int32_t p, int32_t dep) const {
+    if (compact && dep < 256) {
+      plev[pos] = uint8_t(dep);
+      if (parent) ppar[pos] = p;
+    } else {
+      put(v, p, dep);
+    }
   }
 };
 
@@ -407,18 +428,26 @@ __device__ bool grid_sync(GridBar &b, unsigned long long epoch, int *ok) {
 // ---------------------------------------------------------------------------
 // init
 // ---------------------------------------------------------------------------
-// Fills the outputs, clears bitmaps and the control block, and seeds the
-// source: a delegate is claimed (the first previsit moves it to the frontier
-// mask), a normal vertex enters the queue. The counters of "level -1" hold the
-// level-0 queue length. Bound by the output fill: 6.5 TB/s at 67M vertices.
+// Clears bitmaps and the control block, fills the outputs (or, in compact
+// mode, clears what the output pass reads) and seeds the source: a delegate is
+// claimed (the first previsit moves it to the frontier mask), a normal vertex
+// enters the queue. The counters of "level -1" hold the level-0 queue length.
+// Bound by the output fill: 6.5 TB/s at 67M vertices.
 __global__ void k_init(Search a, LevelState init) {
   const int64_t stride = int64_t(gridDim.x) * blockDim.x;
   const int64_t t0 = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   const int32_t s = a.source;
   const int32_t k = a.mode == 1 ? a.did[s] : -1;
-  for (int64_t v = t0; v < a.n; v += stride) {
-    a.depth[v] = v == s ? 0 : -1;
-    if (a.parent) a.parent[v] = v == s ? s : -1;
+  if (a.compact) {
+    for (int64_t i = t0; i < a.d; i += stride) a.dout[i] = i == k ? int2{s, 1} : int2{-1, 0};
+    for (int64_t i = t0; i < (a.n_ndsrc + 3) / 4; i += stride)
+      reinterpret_cast<uint32_t *>(a.plev)[i] = 0;
+    if (k < 0 && t0 == 0) a.put(s, s, 0);
+  } else {
+    for (int64_t v = t0; v < a.n; v += stride) {
+      a.depth[v] = v == s ? 0 : -1;
+      if (a.parent) a.parent[v] = v == s ? s : -1;
+    }
   }
   for (int64_t w = t0; w < a.nwords; w += stride) {
     a.Vn[w] = k < 0 && w == (s >> 5) ? 1u << (s & 31) : 0u;
@@ -440,6 +469,60 @@ __global__ void k_init(Search a, LevelState init) {
       before.qn_nc.v = k < 0 ? 1u : 0u;
       before.sum[kClDn][0].v = k >= 0 && bit_test(a.dnm, uint32_t(k)) ? 1u : 0u;
       if (k < 0) a.Q0[0] = s;
+    }
+  }
+}
+
+// Compact mode's output: every vertex once, in order, so that depth and parent
+// leave as whole lines. A delegate's come from dout, a normal vertex claimed
+// bottom-up has its depth at its position of the nd source list, an unvisited
+// one gets -1, and a normal vertex claimed top-down was written by its claim.
+// Storing each claim where it belongs had the heavy level of RMAT 26 make 16.5M
+// write requests of a few bytes, 26 G/s (its delegates alone 7.8M), which
+// bound it; the arrays here take 3M, and this pass writes 8 bytes a vertex at
+// the rate of a copy, in place of the fill before the search.
+constexpr int kOutUnroll = 4;
+__global__ void __launch_bounds__(256) k_output(Search a) {
+  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+  for (int64_t v0 = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; v0 < a.n;
+       v0 += stride * kOutUnroll) {
+    RankDir dr[kOutUnroll], nr[kOutUnroll];
+    uint32_t vis[kOutUnroll];
+#pragma unroll
+    for (int u = 0; u < kOutUnroll; ++u) {
+      const int64_t w = min(v0 + u * stride, int64_t(a.n) - 1) >> 5;
+      dr[u] = a.drank[w];
+      nr[u] = a.nrank[w];
+      vis[u] = a.Vn[w];
+    }
+    int32_t dep[kOutUnroll], par[kOutUnroll];
+    bool put[kOutUnroll];
+#pragma unroll
+    for (int u = 0; u < kOutUnroll; ++u) {
+      const int64_t v = v0 + u * stride;
+      dep[u] = par[u] = -1;
+      put[u] = v < a.n;
+      if (!put[u]) continue;
+      if (dr[u].has(int32_t(v))) {
+        const int2 o = a.dout[dr[u].rank(int32_t(v))];
+        dep[u] = o.y - 1;
+        par[u] = o.y ? o.x : -1;
+      } else if ((vis[u] >> (v & 31)) & 1u) {
+        put[u] = false;
+        if (nr[u].has(int32_t(v))) {
+          const int32_t pos = nr[u].rank(int32_t(v));
+          dep[u] = a.plev[pos];
+          if (a.parent) par[u] = a.ppar[pos];
+          put[u] = dep[u] != 0;
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kOutUnroll; ++u) {
+      const int64_t v = v0 + u * stride;
+      if (!put[u]) continue;
+      __builtin_nontemporal_store(dep[u], a.depth + v);
+      if (a.parent) __builtin_nontemporal_store(par[u], a.parent + v);
     }
   }
 }
@@ -739,7 +822,7 @@ __device__ __forceinline__ void expand_step(const Search &a, const WaveRows &R,
       if (to_normal) {
         a.put(v[u], R.aux[o[u]], dep);
       } else {
-        a.put(a.vid_of[v[u]], R.aux[o[u]], dep);
+        a.put_deleg(v[u], R.aux[o[u]], dep);
         with_dn += bit_test(a.dnm, uint32_t(v[u]));
       }
     }
@@ -1026,7 +1109,7 @@ __device__ __forceinline__ void list_step(const Search &a, const WaveRows &R, in
     const bool want = ok[u] && !((wd[u] >> (x[u] & 31)) & 1u);
     if (__ballot(want && dd[u])) {
       if (wave_bit_claim(a.Cd, uint32_t(x[u]), ok[u] && dd[u], want && dd[u])) {
-        a.put(a.vid_of[x[u]], R.aux[o[u]], dep);
+        a.put_deleg(x[u], R.aux[o[u]], dep);
         with_dn += bit_test(a.dnm, uint32_t(x[u]));
         ++cl_d;
       }
@@ -1346,7 +1429,7 @@ template <int NW> __device__ void bu_normal(const Search &a, Scratch<NW> &S, int
     const bool won = ok && found;
     wave_bit_set(a.Vn, uint32_t(v), ok, won);
     if (won) {
-      a.put(v, hit0 >= 0 ? pk0 : a.vid_of[a.nds_col[beg + (fe - (incl - len))]], L + 1);
+      a.put_pos(pos, v, hit0 >= 0 ? pk0 : a.vid_of[a.nds_col[beg + (fe - (incl - len))]], L + 1);
       ++claimed;
     }
     qa.push(won, v);
@@ -1403,7 +1486,7 @@ template <int NW> __device__ void bu_deleg(const Search &a, Scratch<NW> &S, int 
     for (int32_t i0 = 0; i0 < total; i0 += kWave) {
       const int32_t i = i0 + l;
       const bool ok = i < total;
-      int32_t k = 0, len = 0, vk = 0, px = 0;
+      int32_t k = 0, len = 0, px = 0;
       int64_t p = 0, mid = 0, hit = -1;
       int wo = 0, bit = 0;
       if (ok) {
@@ -1411,8 +1494,7 @@ template <int NW> __device__ void bu_deleg(const Search &a, Scratch<NW> &S, int 
         bit = nth_bit(uint32_t(wbits[wo]), i - wpre[wo]);
         k = int32_t((w0 + wo) * 32 + bit);
         const uint64_t x0 = a.doff[k], x1 = a.doff[k + 1];
-        vk = a.vid_of[k];             // fetched beside the row bounds,
-        const int2 f = a.dd_first[k];  // as is the dense first dd entry
+        const int2 f = a.dd_first[k];  // fetched beside the row bounds
         const int64_t beg = row_start(x0);
         mid = beg + row_first(x0);
         p = dd_bu ? beg : mid;
@@ -1453,7 +1535,7 @@ template <int NW> __device__ void bu_deleg(const Search &a, Scratch<NW> &S, int 
           const int32_t x = a.dcol[hit];
           par = hit < mid ? a.vid_of[x] : x;
         }
-        a.put(vk, par, L + 1);
+        a.put_deleg(k, par, L + 1);
         ++claimed;
       }
     }
@@ -1762,6 +1844,9 @@ Workspace *workspace_create(const Graph *g, int32_t max_lanes) {
     ws->c0.alloc(al, size_t(g->st.n_ndsrc) * 4, s);
     ws->c1.alloc(al, size_t(g->st.n_ndsrc) * 4, s);
     ws->ctl.alloc(al, sizeof(SearchCtl), s);
+    ws->ppar.alloc(al, size_t(g->st.n_ndsrc) * 4, s);
+    ws->plev.alloc(al, (size_t(g->st.n_ndsrc) + 3) / 4 * 4, s);
+    ws->dout.alloc(al, size_t(d) * 8, s);
     HIPCHK(hipHostMalloc(&ws->hstat, kStatusSlots * sizeof(LevelStatus), hipHostMallocDefault));
     std::memset(ws->hstat, 0, kStatusSlots * sizeof(LevelStatus));
     return ws;
@@ -1912,6 +1997,11 @@ Search search_args(const Graph *g, Workspace *ws, const dsbfs_run_opts &o, int32
   a.C1 = ws->c1.as<int32_t>();
   a.dlist = ws->dlist.as<int32_t>();
   a.dscan = ws->dscan.as<int64_t>();
+  a.dout = ws->dout.as<int2>();
+  a.ppar = ws->ppar.as<int32_t>();
+  a.plev = ws->plev.as<uint8_t>();
+  a.drank = g->drank.as<RankDir>();
+  a.nrank = g->nrank.as<RankDir>();
   a.ctl = ws->ctl.as<SearchCtl>();
   a.hs = static_cast<LevelStatus *>(ws->hstat);
   for (int k = 0; k < 3; ++k) {
@@ -2013,9 +2103,17 @@ void launch_init(const Search &a, const LevelState &st, hipStream_t s) {
   HIPCHK(hipGetLastError());
 }
 
+void launch_output(const Search &a, hipStream_t s) {
+  if (!a.compact) return;
+  hipLaunchKernelGGL(k_output, dim3(grid_for(a.n, 256 * kOutUnroll, 8192)), dim3(256), 0, s, a);
+  HIPCHK(hipGetLastError());
+}
+
 // Level by level; seen gets the records of the levels with a frontier.
-void run_levels(const Graph *g, Workspace *ws, const Search &a, const dsbfs_run_opts &o, Prof &P,
+void run_levels(const Graph *g, Workspace *ws, Search a, const dsbfs_run_opts &o, Prof &P,
                 std::vector<LevelStatus> &seen, hipStream_t s) {
+  // (the allocation-free search's scratch has no room for the arrays)
+  a.compact = o.mode == 1 && !ws->borrowed;
   LevelStatus *hs = static_cast<LevelStatus *>(ws->hstat);
   if (!ws->borrowed)
     for (int i = 0; i < kStatusSlots; ++i) hs[i].seq = 0;
@@ -2047,6 +2145,8 @@ void run_levels(const Graph *g, Workspace *ws, const Search &a, const dsbfs_run_
       if (st.done) break;
       seen.push_back(st);
     }
+    P.timed(DSBFS_K_INIT, -1, [&] { launch_output(a, s); });
+    HIPCHK(hipStreamSynchronize(s));
     return;
   }
   // The host stays one level ahead and stops once a level reports an empty
@@ -2066,6 +2166,7 @@ void run_levels(const Graph *g, Workspace *ws, const Search &a, const dsbfs_run_
     if (monotone && o.mode == 1 && st.rec.dir[0] == 1 && st.rec.dir[1] == 1)
       skip = st.rec.dir[2] == 1 ? 1 : 2;
   }
+  launch_output(a, s);
   // the level behind the last one is still queued: the workspace is free for
   // a search on another stream only after it
   HIPCHK(hipStreamSynchronize(s));

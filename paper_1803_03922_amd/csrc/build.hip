@@ -148,16 +148,10 @@ __global__ void k_nn_fill(const int64_t *start, const int32_t *cnt, const uint64
 // What the arrangement needs of a neighbour, in arrays that stay in the L2: a
 // byte per vertex with its degree bucket, plus one for delegates (degrees
 // above TH: delegate iff code > bucket(TH), bucket = code minus that one), and
-// per 32 vertices their delegate bits and the first one's delegate ID. The
-// degree and delegate ID arrays would be a line from beyond the L2 per entry
+// the delegates' rank directory for their IDs. The degree and delegate ID arrays would be a line from beyond the L2 per entry
 // (16 MB each at 4M vertices): 3.3 ms for the dd keys of RMAT 22 alone.
-struct DelRank {
-  uint32_t bits;
-  int32_t base;
-};
-
 __global__ void k_codes(const int32_t *deg, const int32_t *did, int32_t n, int32_t th,
-                        uint8_t *code, DelRank *rank) {
+                        uint8_t *code, RankDir *rank) {
   const int64_t stride = int64_t(gridDim.x) * blockDim.x;
   for (int64_t v0 = int64_t(blockIdx.x) * blockDim.x; v0 < n; v0 += stride) {
     const int64_t v = v0 + threadIdx.x;
@@ -171,7 +165,7 @@ __global__ void k_codes(const int32_t *deg, const int32_t *did, int32_t n, int32
     const uint32_t bits = uint32_t(l < 32 ? m : m >> 32);
     const int first = (l < 32 ? 0 : 32) + (bits ? __ffs(bits) - 1 : 0);
     const int32_t base = __shfl(k, first, kWave);
-    if ((l & 31) == 0 && v < n) rank[v >> 5] = DelRank{bits, base};
+    if ((l & 31) == 0 && v < n) rank[v >> 5] = RankDir{bits, base};
   }
 }
 
@@ -179,7 +173,7 @@ struct Arrange {
   const int64_t *poff;
   const int32_t *pcol;     // rows of the plain CSR, ascending
   const uint8_t *code;
-  const DelRank *rank;
+  const RankDir *rank;
   const int32_t *deg, *did;
   const int64_t *nstart, *dstart;
   int32_t n;
@@ -190,8 +184,7 @@ struct Arrange {
 
   __device__ __forceinline__ bool is_del(uint32_t c) const { return int32_t(c) > bth; }
   __device__ __forceinline__ int32_t del_id(int32_t v) const {
-    const DelRank r = rank[v >> 5];
-    return r.base + __popc(r.bits & ((1u << (v & 31)) - 1u));
+    return rank[v >> 5].rank(v);
   }
   // where row u's split entries go
   __device__ __forceinline__ int32_t *split_row(int32_t u, bool &del) const {
@@ -532,6 +525,16 @@ __global__ void k_source_masks(const int32_t *vid_of, const int32_t *deg, const 
   }
 }
 
+// Rank directory of the nd source list (cleared before).
+__global__ void k_nd_rank(const int32_t *ndsrc, int64_t cnt, RankDir *rank) {
+  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < cnt;
+       i += int64_t(gridDim.x) * blockDim.x) {
+    const int32_t v = ndsrc[i];
+    if (i == 0 || (ndsrc[i - 1] >> 5) != (v >> 5)) rank[v >> 5].base = int32_t(i);
+    atomicOr(&rank[v >> 5].bits, 1u << (v & 31));
+  }
+}
+
 __global__ void k_nds_len(const int32_t *ndsrc, int64_t cnt, const int32_t *cnt_del,
                           int32_t *len) {
   for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < cnt;
@@ -798,19 +801,19 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
     G->ncol.alloc(al, size_t(ncols) * 4, s);
     G->dcol.alloc(al, size_t(m - ncols) * 4, s);
     {
-      DevBuf code, rank, rows, sorted;
+      DevBuf code, rows, sorted;
       code.alloc(al, size_t(n), s);
-      rank.alloc(al, (size_t(n) + 31) / 32 * sizeof(DelRank), s);
+      G->drank.alloc(al, size_t(G->nwords()) * sizeof(RankDir), s);
       if (o.keep_plain_csr) sorted.alloc(al, size_t(m) * 4, s);
       hipLaunchKernelGGL(k_codes, dim3(grid_for(n, kBS, 8192)), dim3(kBS), 0, s,
                          G->deg.as<int32_t>(), G->did.as<int32_t>(), n, o.threshold,
-                         code.as<uint8_t>(), rank.as<DelRank>());
+                         code.as<uint8_t>(), G->drank.as<RankDir>());
       HIPCHK(hipGetLastError());
       Arrange a{};
       a.poff = G->poff.as<int64_t>();
       a.pcol = G->pcol.as<int32_t>();
       a.code = code.as<uint8_t>();
-      a.rank = rank.as<DelRank>();
+      a.rank = G->drank.as<RankDir>();
       a.deg = G->deg.as<int32_t>();
       a.did = G->did.as<int32_t>();
       a.nstart = nstart.as<int64_t>();
@@ -928,7 +931,11 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
       G->nds_off.alloc(al, size_t(nsrc + 1) * 8, s);
       G->nds_col.alloc(al, size_t(e_nd) * 4, s);
       G->nds_first.alloc(al, size_t(nsrc) * 8, s);
+      G->nrank.alloc(al, size_t(G->nwords()) * sizeof(RankDir), s);
+      HIPCHK(hipMemsetAsync(G->nrank.p, 0, size_t(G->nwords()) * sizeof(RankDir), s));
       if (nsrc > 0) {
+        hipLaunchKernelGGL(k_nd_rank, dim3(grid_for(nsrc, kBS, 8192)), dim3(kBS), 0, s,
+                           G->ndsrc.as<int32_t>(), nsrc, G->nrank.as<RankDir>());
         hipLaunchKernelGGL(k_nds_len, dim3(grid_for(nsrc, kBS, 8192)), dim3(kBS), 0, s,
                            G->ndsrc.as<int32_t>(), nsrc, cnt_del.as<int32_t>(),
                            len.as<int32_t>());

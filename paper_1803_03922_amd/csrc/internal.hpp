@@ -81,6 +81,17 @@ struct DevBuf {
 // ---------------------------------------------------------------------------
 constexpr uint16_t kLenWide = 0xFFFF;
 
+// Directory of a set of vertices, one entry per 32: their bits, and the rank
+// (position among all of the set, ascending) of the first of them.
+struct RankDir {
+  uint32_t bits;
+  int32_t base;
+  __host__ __device__ bool has(int32_t v) const { return (bits >> (v & 31)) & 1u; }
+  __device__ int32_t rank(int32_t v) const {
+    return base + __popc(bits & ((1u << (v & 31)) - 1u));
+  }
+};
+
 struct Graph {
   Alloc al;
   hipStream_t stream = nullptr;
@@ -98,6 +109,9 @@ struct Graph {
   // delegate), kLenWide when either is 255 or more (read noff instead); the
   // normal previsit reads these 2 bytes instead of two 8-byte row offsets
   DevBuf nlen;
+  // ranks of the delegates (their IDs) and of the nd source list (positions),
+  // RankDir [ceil(n / 32)]
+  DevBuf drank, nrank;
   DevBuf nnsrc;     // normal vertices with a normal neighbour, ascending (nn_do bottom-up)
   // nn parts again, concatenated in vertex order (int32 [e_nn] vertex IDs),
   // and the start of each vertex's part (uint32 [n]): a forward nn visit
@@ -132,6 +146,11 @@ struct Workspace {
   DevBuf dlen;                 // int32[max(n, d)]: second Fn bitmap; multi-source frontier list
   DevBuf dscan;                // int64[max(n, d) + 1]: prefix of top-down lengths
   DevBuf c0, c1;               // bottom-up normal candidates, int32[n_ndsrc]
+  // what bottom-up visits and delegate claims find, until a dense pass at the
+  // end of the search writes it out (bfs.hip): per position of the nd source
+  // list parent (int32) and depth (uint8, 0: none), per delegate (parent,
+  // depth + 1)
+  DevBuf ppar, plev, dout;
   DevBuf ctl;                  // control block of the search in progress (bfs.hip)
   std::vector<hipEvent_t> events;  // profiling event pool
   void *hstat = nullptr;       // pinned ring of per-level status records

@@ -80,7 +80,7 @@ size_t graph_footprint(const Graph *g) {
          buf_bytes(g->ddsrc_mask) + buf_bytes(g->dnsrc_mask) + buf_bytes(g->nds_off) +
          buf_bytes(g->nds_col) + buf_bytes(g->nds_first) + buf_bytes(g->dd_first) +
          buf_bytes(g->nlen) + buf_bytes(g->nnsrc) + buf_bytes(g->nnoff) + buf_bytes(g->nncol) +
-         buf_bytes(g->pr_rank) + buf_bytes(g->pr_order) + buf_bytes(g->pr_col) +
+         buf_bytes(g->drank) + buf_bytes(g->nrank) + buf_bytes(g->pr_rank) + buf_bytes(g->pr_order) + buf_bytes(g->pr_col) +
          buf_bytes(g->poff) +
          buf_bytes(g->pcol);
 }
@@ -89,7 +89,8 @@ size_t workspace_footprint(const Workspace *w) {
   return buf_bytes(w->Vn) + buf_bytes(w->Fn) + buf_bytes(w->Vd) + buf_bytes(w->Fd) +
          buf_bytes(w->Cd) + buf_bytes(w->q0) + buf_bytes(w->q1) + buf_bytes(w->dlist) +
          buf_bytes(w->dlen) + buf_bytes(w->dscan) + buf_bytes(w->c0) + buf_bytes(w->c1) +
-         buf_bytes(w->ctl) + ms_state_bytes(w);
+         buf_bytes(w->ctl) + buf_bytes(w->ppar) + buf_bytes(w->plev) + buf_bytes(w->dout) +
+         ms_state_bytes(w);
 }
 
 enum QState { Q_PENDING = 0, Q_RUNNING = 1, Q_DONE = 2, Q_RELEASED = 3 };
@@ -170,7 +171,7 @@ void ema(double &avg, double x) { avg = avg > 0 ? 0.75 * avg + 0.25 * x : x; }
 std::vector<DevBuf *> graph_bufs(Graph *g) {
   return {&g->deg, &g->did, &g->vid_of, &g->noff, &g->ncol, &g->doff, &g->dcol, &g->ndsrc,
           &g->ddsrc_mask, &g->dnsrc_mask, &g->nds_off, &g->nds_col, &g->nds_first, &g->dd_first,
-          &g->nlen, &g->nnsrc, &g->nnoff, &g->nncol, &g->pr_rank, &g->pr_order, &g->pr_col, &g->poff,
+          &g->nlen, &g->nnsrc, &g->nnoff, &g->nncol, &g->drank, &g->nrank, &g->pr_rank, &g->pr_order, &g->pr_col, &g->poff,
           &g->pcol};
 }
 
