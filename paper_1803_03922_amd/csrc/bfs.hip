@@ -479,50 +479,65 @@ __global__ void k_init(Search a, LevelState init) {
 // one gets -1, and a normal vertex claimed top-down was written by its claim.
 // Storing each claim where it belongs had the heavy level of RMAT 26 make 16.5M
 // write requests of a few bytes, 26 G/s (its delegates alone 7.8M), which
-// bound it; the arrays here take 3M, and this pass writes 8 bytes a vertex at
-// the rate of a copy, in place of the fill before the search.
-constexpr int kOutUnroll = 4;
-__global__ void __launch_bounds__(256) k_output(Search a) {
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  for (int64_t v0 = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; v0 < a.n;
-       v0 += stride * kOutUnroll) {
-    RankDir dr[kOutUnroll], nr[kOutUnroll];
-    uint32_t vis[kOutUnroll];
+// bound it; the arrays here take 3M, and this pass writes 8 bytes a vertex in
+// place of the fill before the search.
+//
+// A thread has kOutRow vertices in a row: one directory entry of each kind
+// and one word of visited bits for all of them, entries of the arrays that
+// follow each other, and one 16-byte store where all are put (the caller's
+// arrays may begin at any int32: then, and beside vertices that a claim wrote,
+// one store each). Loads have no branches (a lane with nothing to read takes
+// entry 0), so that all are in flight at once. RMAT 26, 537 MB out: 244 us; with
+// a vertex a thread, four apart, 292 us, and with the loads behind branches, a
+// chain of round trips, 310 us. The stores alone take 100 us; each of the three
+// gathers adds 35 to 48 us.
+constexpr int kOutRow = 4;
+template <bool VEC> __global__ void __launch_bounds__(256) k_output(Search a) {
+  const int64_t stride = int64_t(gridDim.x) * blockDim.x * kOutRow;
+  for (int64_t v0 = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) * kOutRow; v0 < a.n;
+       v0 += stride) {
+    const RankDir dr = a.drank[v0 >> 5], nr = a.nrank[v0 >> 5];
+    const uint32_t vis = a.Vn[v0 >> 5];
+    int32_t k[kOutRow], pos[kOutRow];
+    bool is_d[kOutRow], is_n[kOutRow], seen[kOutRow];
 #pragma unroll
-    for (int u = 0; u < kOutUnroll; ++u) {
-      const int64_t w = min(v0 + u * stride, int64_t(a.n) - 1) >> 5;
-      dr[u] = a.drank[w];
-      nr[u] = a.nrank[w];
-      vis[u] = a.Vn[w];
+    for (int u = 0; u < kOutRow; ++u) {
+      const int32_t v = int32_t(v0) + u;
+      is_d[u] = dr.has(v);
+      seen[u] = (vis >> (v & 31)) & 1u;
+      is_n[u] = !is_d[u] && seen[u] && nr.has(v);
+      k[u] = is_d[u] ? dr.rank(v) : 0;
+      pos[u] = is_n[u] ? nr.rank(v) : 0;
     }
-    int32_t dep[kOutUnroll], par[kOutUnroll];
-    bool put[kOutUnroll];
+    int2 o[kOutRow];
+    int32_t lev[kOutRow], pp[kOutRow];
 #pragma unroll
-    for (int u = 0; u < kOutUnroll; ++u) {
-      const int64_t v = v0 + u * stride;
-      dep[u] = par[u] = -1;
-      put[u] = v < a.n;
-      if (!put[u]) continue;
-      if (dr[u].has(int32_t(v))) {
-        const int2 o = a.dout[dr[u].rank(int32_t(v))];
-        dep[u] = o.y - 1;
-        par[u] = o.y ? o.x : -1;
-      } else if ((vis[u] >> (v & 31)) & 1u) {
-        put[u] = false;
-        if (nr[u].has(int32_t(v))) {
-          const int32_t pos = nr[u].rank(int32_t(v));
-          dep[u] = a.plev[pos];
-          if (a.parent) par[u] = a.ppar[pos];
-          put[u] = dep[u] != 0;
-        }
-      }
+    for (int u = 0; u < kOutRow; ++u) {
+      o[u] = a.dout[k[u]];
+      lev[u] = a.plev[pos[u]];
+      pp[u] = a.parent ? a.ppar[pos[u]] : 0;
+    }
+    int32_t dep[kOutRow], par[kOutRow];
+    bool put[kOutRow], all = VEC;
+#pragma unroll
+    for (int u = 0; u < kOutRow; ++u) {
+      dep[u] = is_d[u] ? o[u].y - 1 : (is_n[u] ? lev[u] : -1);
+      par[u] = is_d[u] ? (o[u].y ? o[u].x : -1) : (is_n[u] ? pp[u] : -1);
+      // a visited normal vertex without a depth here was written by its claim
+      put[u] = v0 + u < a.n && (is_d[u] || !seen[u] || (is_n[u] && lev[u] != 0));
+      all = all && put[u];
+    }
+    if (all) {
+      *reinterpret_cast<int4 *>(a.depth + v0) = int4{dep[0], dep[1], dep[2], dep[3]};
+      if (a.parent)
+        *reinterpret_cast<int4 *>(a.parent + v0) = int4{par[0], par[1], par[2], par[3]};
+      continue;
     }
 #pragma unroll
-    for (int u = 0; u < kOutUnroll; ++u) {
-      const int64_t v = v0 + u * stride;
+    for (int u = 0; u < kOutRow; ++u) {
       if (!put[u]) continue;
-      __builtin_nontemporal_store(dep[u], a.depth + v);
-      if (a.parent) __builtin_nontemporal_store(par[u], a.parent + v);
+      a.depth[v0 + u] = dep[u];
+      if (a.parent) a.parent[v0 + u] = par[u];
     }
   }
 }
@@ -2105,7 +2120,12 @@ void launch_init(const Search &a, const LevelState &st, hipStream_t s) {
 
 void launch_output(const Search &a, hipStream_t s) {
   if (!a.compact) return;
-  hipLaunchKernelGGL(k_output, dim3(grid_for(a.n, 256 * kOutUnroll, 8192)), dim3(256), 0, s, a);
+  const dim3 grid(grid_for(a.n, 256 * kOutRow, 65536)), block(256);
+  const bool vec = (uintptr_t(a.depth) | uintptr_t(a.parent)) % 16 == 0;
+  if (vec)
+    hipLaunchKernelGGL(k_output<true>, grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL(k_output<false>, grid, block, 0, s, a);
   HIPCHK(hipGetLastError());
 }
 
