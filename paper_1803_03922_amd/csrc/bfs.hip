@@ -161,6 +161,7 @@ struct Search {
   int64_t *dscan;
   SearchCtl *ctl;
   LevelStatus *hs;
+  double nn_mean;  // nn edges per normal vertex
   // options
   double f0[4], f1[4];
   uint64_t forced_seed;
@@ -867,6 +868,129 @@ __device__ __forceinline__ void expand_rows(const Search &a, WaveRows &R, const 
     expand_step<to_normal, 1>(a, R, col, e0, T, dep, qa, claimed, with_dn);
 }
 
+// A heavy level's nn visit: every edge to a vertex that no earlier level
+// claimed stores its row's vertex there, and settle() collects what was
+// stored. Atomics bound such a level otherwise: 26 G/s on this card whatever
+// they touch (random 4-byte stores 80 G/s), and as a wave's cached bitmap words
+// do not show the other chiplets' claims, nearly every edge to a vertex
+// unvisited at the level's start needs one.
+// ER 2^22 of mean degree 16: its two heavy levels 685 and 501 us before, 270 and
+// 370 with 20 each for settle(); the second is bound by 51M bit tests (200 G/s)
+// and gains from rows read in order.
+template <int U>
+__device__ __forceinline__ void scatter_step(const Search &a, const WaveRows &R,
+                                             const int32_t *col, int32_t e0, int32_t T,
+                                             int32_t dep) {
+  const int l = lane_id();
+  int32_t v[U];
+  int o[U];
+  uint32_t wd[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int32_t e = min(e0 + u * kWave + l, T - 1);
+    o[u] = owner64(R.excl, e);
+    v[u] = col[R.beg[o[u]] + (e - R.excl[o[u]])];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) wd[u] = a.Vn[uint32_t(v[u]) >> 5];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    // (the lanes past the end repeat the last edge)
+    if ((wd[u] >> (v[u] & 31)) & 1u) continue;
+    if (a.parent) a.parent[v[u]] = R.aux[o[u]];
+    else a.depth[v[u]] = dep;
+  }
+}
+
+__device__ __forceinline__ void scatter_rows(const Search &a, WaveRows &R, const int32_t *col,
+                                             int32_t u, int32_t len, int64_t beg, int32_t dep,
+                                             uint32_t &edges) {
+  const int l = lane_id();
+  const int32_t incl = wave_incl_scan(len);
+  const int32_t T = lane_read(incl, kWave - 1);
+  if (T == 0) return;
+  wave_sync();
+  R.excl[l] = incl - len;
+  R.aux[l] = u;
+  R.beg[l] = beg;
+  wave_sync();
+  if (l == 0) edges += uint32_t(T);
+  int32_t e0 = 0;
+  for (; T - e0 > 2 * kWave; e0 += 4 * kWave) scatter_step<4>(a, R, col, e0, T, dep);
+  for (; e0 < T; e0 += kWave) scatter_step<1>(a, R, col, e0, T, dep);
+}
+
+// Claims what the scatter of level L stored: the normal vertices whose parent
+// (or depth, where the caller wants no parents) is set and that no level has
+// claimed yet. A wave has a contiguous share of the vertices, 64 groups of 64
+// at a time, and the block reserves room for all its claims of a round with one
+// atomic (a buffer per wave had 10K atomics on the tail, 115 us at 3.2M claims;
+// now 20). The next level reads the rows in near-ascending order, too. Runs
+// beside the delegate list, which reads nothing of it.
+template <int NW> __device__ void settle(const Search &a, Scratch<NW> &S, int L) {
+  constexpr int U = 4;
+  const int l = lane_id(), nw = blockDim.x / kWave;
+  const int64_t nwaves = int64_t(gridDim.x) * nw;
+  const int64_t wid = int64_t(blockIdx.x) * nw + threadIdx.x / kWave;
+  const int64_t groups = (int64_t(a.n) + kWave - 1) / kWave;
+  const int64_t per = (groups + nwaves - 1) / nwaves;
+  const int64_t gb = min(wid * per, groups), ge = min(gb + per, groups);
+  const int32_t *const set = a.parent ? a.parent : a.depth;
+  int32_t *const out = a.q((L + 1) & 1);
+  uint32_t claimed = 0;
+  for (int64_t r0 = 0; r0 < per; r0 += kWave) {
+    unsigned long long mine = 0;  // lane i: the claims of group gb + r0 + i
+    const int64_t re = min(ge, gb + r0 + kWave);
+    for (int64_t g0 = gb + r0; g0 < re; g0 += U) {
+      int32_t x[U];
+      uint32_t vis[U], dl[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t v = min((g0 + u) * kWave + l, int64_t(a.n) - 1);
+        x[u] = set[v];
+        vis[u] = a.Vn[v >> 5];
+        dl[u] = a.drank[v >> 5].bits;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t v = (g0 + u) * kWave + l;
+        const bool won =
+            g0 + u < re && v < a.n && x[u] != -1 && !(((vis[u] | dl[u]) >> (v & 31)) & 1u);
+        const unsigned long long m = __ballot(won);
+        const uint32_t half = uint32_t(l < 32 ? m : m >> 32);
+        if ((l & 31) == 0 && half) a.Vn[v >> 5] = vis[u] | half;
+        if (won && a.parent) a.depth[v] = L + 1;
+        if (l == int(g0 + u - gb - r0)) mine = m;
+      }
+    }
+    const int32_t c = __popcll(mine);
+    claimed += c;
+    const int32_t incl = wave_incl_scan(c);
+    if (l == kWave - 1) S.sh[threadIdx.x / kWave] = incl;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int64_t all = 0;
+      for (int w = 0; w < nw; ++w) {
+        const int64_t k = S.sh[w];
+        S.sh[w] = all;
+        all += k;
+      }
+      S.qbase = all ? atomicAdd(&a.ctl->ctr[L % 3].qn_nc.v, (unsigned long long)all) & 0xffffffffull
+                    : 0ull;
+    }
+    __syncthreads();
+    const int64_t to = int64_t(S.qbase) + S.sh[threadIdx.x / kWave];
+    for (int g = 0; gb + r0 + g < re; ++g) {
+      const unsigned long long m = lane_read(mine, g);
+      const int32_t at = lane_read(incl - c, g);
+      if ((m >> l) & 1ull)
+        out[to + at + int(lanes_below(m))] = int32_t((gb + r0 + g) * kWave + l);
+    }
+    __syncthreads();
+  }
+  count_units(a, S, DSBFS_K_PREV_NORMAL, 0, 0, claimed, 0);
+}
+
 // The nn part of row u: its length and, when `start` is set, where it begins
 // (in the compact nn copy if there is one, else in the full rows).
 __device__ __forceinline__ void nn_part(const Search &a, int32_t u, bool start, int32_t &nn,
@@ -889,7 +1013,9 @@ __device__ __forceinline__ void nn_part(const Search &a, int32_t u, bool start, 
 // One pass over the normal queue: previsit (nn/nd workloads and counts of the
 // frontier, normal frontier bitmap Fn) fused with the nn top-down visit. With
 // nn under the direction decision (nn_do) it only counts and marks.
-template <int NW> __device__ void prev_normal(const Search &a, Scratch<NW> &S, int L) {
+// scatter: the visit of a heavy level (settle() follows).
+template <int NW>
+__device__ void prev_normal(const Search &a, Scratch<NW> &S, int L, bool scatter) {
   const int64_t qn = S.qn;
   if (int64_t(blockIdx.x) * blockDim.x >= qn) return;
   const int mark = S.mark, expand = !a.nn_do;
@@ -915,7 +1041,9 @@ template <int NW> __device__ void prev_normal(const Search &a, Scratch<NW> &S, i
     }
     // queues filled by the bottom-up pass are in ascending order: mark word by word
     if (mark) wave_bit_set(Fn, uint32_t(u), i < qn, true);
-    if (expand)
+    if (scatter)
+      scatter_rows(a, R, a.nnoff ? a.nncol : a.ncol, u, nn, beg, L + 1, edges);
+    else if (expand)
       expand_rows<true>(a, R, a.nnoff ? a.nncol : a.ncol, u, nn, beg, L + 1, qa, edges, claimed,
                         none);
   }
@@ -937,8 +1065,9 @@ template <int NW> __device__ void prev_normal(const Search &a, Scratch<NW> &S, i
 // one does not wait for the marking of the other) and the counters of level
 // L + 1.
 enum { kDeleg = 1, kNormal = 2, kClear = 4, kNn = 8, kCommit = 16 };
-template <int NW, int parts> __device__ __forceinline__ void previsit(const Search &a,
-                                                                      Scratch<NW> &S, int L) {
+template <int NW, int parts>
+__device__ __forceinline__ void previsit(const Search &a, Scratch<NW> &S, int L,
+                                         bool scatter = false) {
   if (parts & kClear) {
     if (S.st.marked) {
       uint32_t *const F = a.fn((L + 1) & 1);
@@ -949,7 +1078,7 @@ template <int NW, int parts> __device__ __forceinline__ void previsit(const Sear
     ctr_clear(a.ctl->ctr[(L + 1) % 3]);
   }
   if (parts & kDeleg) prev_deleg(a, S);
-  if (parts & kNormal) prev_normal(a, S, L);
+  if (parts & kNormal) prev_normal(a, S, L, scatter);
   if (parts & (kDeleg | kNormal)) red_flush(S, a.ctl->ctr[L % 3], 0, kPrevSums);
 }
 
@@ -1724,6 +1853,7 @@ __global__ void __launch_bounds__(kBS, 8) k_plain_expand(Search a, int L) {
 // search's state by itself, so a level needs no other exchange than its
 // counters.
 constexpr int kWideNW = 16;
+constexpr double kHeavyEdges = 1 << 18;
 
 // How block 0 left: 1 done, -1 a barrier wait exceeded its bound.
 __device__ __forceinline__ void one_launch_end(const Search &a, int levels, bool ok) {
@@ -1737,7 +1867,20 @@ __device__ __forceinline__ void one_launch_end(const Search &a, int levels, bool
   }
 }
 
-__global__ void __launch_bounds__(1024) k_search(Search a) {
+// Whether a level's nn visit scatters (scatter_step): its edges to unvisited
+// vertices, as the mean nn row and the share of normals left predict them, are
+// at least n / 16 + 2^18. settle() reads and writes about 12 bytes a vertex and
+// costs a barrier, 8 us and 7 per million vertices; an edge saves an atomic for
+// a store, 26 us per million. ER 2^22 with n / 4, n / 16, n / 16 + 2^18, n / 16 +
+// 2^20: 1448, 1409, 1412, 1485 us (1812 without); the smaller lines without the
+// constant cost searches of 2^17 vertices 3%.
+__device__ __forceinline__ bool heavy_level(const Search &a, int64_t qn, int64_t left) {
+  const double n = a.n;
+  return double(qn) * a.nn_mean * double(left) >= n * (n / 16 + kHeavyEdges);
+}
+
+// HEAVY: levels may scatter (heavy_graph()).
+template <bool HEAVY> __global__ void __launch_bounds__(1024) k_search(Search a) {
   __shared__ Scratch<kWideNW> S;
   GridBar &bar = a.ctl->bar;
   unsigned long long ep = 0;
@@ -1745,17 +1888,21 @@ __global__ void __launch_bounds__(1024) k_search(Search a) {
   units_open(a, S);
   int L = 0;
   bool ok = true;
+  int64_t left = a.n - a.d;  // normals in no frontier so far
   for (;; ++L) {
     level_open(a, S, L);
-    previsit<kWideNW, kDeleg | kNormal | kClear>(a, S, L);
+    left -= S.qn;
+    const bool heavy = HEAVY && heavy_level(a, S.qn, left);
+    previsit<kWideNW, kDeleg | kNormal | kClear>(a, S, L, heavy);
     if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
     level_plan(a, S, L);
     if (a.count && blockIdx.x == 0 && threadIdx.x == 0)
       account_level(a, S.st, S.ns, S.now, S.qn, S.nc_prev, S.plan, a.ctl->tot);
     if (S.ns.done) break;
     const Plan &p = S.plan;
-    if (p.dd_td || p.dn_td) {
-      list_deleg(a, S);
+    if (heavy) settle(a, S, L);
+    if (p.dd_td || p.dn_td) list_deleg(a, S);
+    if (heavy || p.dd_td || p.dn_td) {
       if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
     }
     if (p.dd_td || p.dn_td || p.nd_td || p.nn_td) {
@@ -1822,6 +1969,15 @@ int stride_grid() { return 256 * 8; }
 struct OneLaunch {
   int blocks, threads;
 };
+
+// Whether the search's levels may scatter: nn rows long enough for it to pay,
+// a graph in which some level can pass heavy_level (qn * left is at most
+// n^2 / 4), and nn outside the direction decision. The other searches run the
+// kernel without that code, which costs them 1.5 to 3% (more registers and
+// instructions at every level).
+bool heavy_graph(const Search &a) {
+  return !a.nn_do && a.nn_mean >= 4 && a.nn_mean * a.n / 4 >= a.n / 16.0 + kHeavyEdges;
+}
 
 OneLaunch one_launch_shape(const Graph *g, int mode) {
   const int64_t w = int64_t(g->n) * (mode == 0 ? 4 : 1);
@@ -2019,6 +2175,7 @@ Search search_args(const Graph *g, Workspace *ws, const dsbfs_run_opts &o, int32
   a.nrank = g->nrank.as<RankDir>();
   a.ctl = ws->ctl.as<SearchCtl>();
   a.hs = static_cast<LevelStatus *>(ws->hstat);
+  a.nn_mean = double(g->st.e_nn) / double(std::max(g->n - g->d, 1));
   for (int k = 0; k < 3; ++k) {
     a.f0[k] = o.factor0[k];
     a.f1[k] = o.factor1[k];
@@ -2201,8 +2358,10 @@ bool run_one_launch(const Graph *g, Workspace *ws, Search a, const OneLaunch &sh
   LevelStatus *hs = static_cast<LevelStatus *>(ws->hstat);
   if (!ws->borrowed) hs->seq = 0;
   launch_init(a, first_state(g), s);
-  if (a.mode == 1)
-    hipLaunchKernelGGL(k_search, dim3(shape.blocks), dim3(shape.threads), 0, s, a);
+  if (a.mode == 1 && heavy_graph(a))
+    hipLaunchKernelGGL(k_search<true>, dim3(shape.blocks), dim3(shape.threads), 0, s, a);
+  else if (a.mode == 1)
+    hipLaunchKernelGGL(k_search<false>, dim3(shape.blocks), dim3(shape.threads), 0, s, a);
   else
     hipLaunchKernelGGL(k_plain_search, dim3(shape.blocks), dim3(shape.threads), 0, s, a);
   HIPCHK(hipGetLastError());
