@@ -732,9 +732,9 @@ __device__ __forceinline__ void level_plan(const Search &a, Scratch<NW> &S, int 
 // ---------------------------------------------------------------------------
 // Mask words of one wave step of the delegate passes: a power of two, small
 // enough that every wave of the grid has a step when there are that many words.
-__device__ __forceinline__ int mask_step(int32_t words, int64_t nwaves) {
+__device__ __forceinline__ int mask_step(int32_t words, int64_t nwaves, int least = 2) {
   int c = kWave;
-  while (c > 2 && int64_t(words) < c * nwaves) c >>= 1;
+  while (c > least && int64_t(words) < c * nwaves) c >>= 1;
   return c;
 }
 
@@ -1587,14 +1587,17 @@ template <int NW> __device__ void bu_normal(const Search &a, Scratch<NW> &S, int
 }
 
 // Bottom-up dd and/or nd (destination: delegates): unclaimed delegates with
-// an edge in a subgraph scanned bottom-up this level. A wave takes a few mask
-// words and enumerates their candidates 64 at a time, one per lane, so no
+// an edge in a subgraph scanned bottom-up this level. A wave takes a few bytes
+// of the masks and enumerates their candidates 64 at a time, one per lane, so no
 // candidate list is written. Each lane first tests the first entry of its
 // scanned range (dd parts start with their highest-degree neighbour, the
 // likeliest to be in the frontier); the rows that miss are then walked
 // together. dd entries are tested against Fd, dn entries against the normal
-// frontier bitmap Fn. The words are this wave's alone: claims are collected in
-// LDS and the word stored once.
+// frontier bitmap Fn. The bytes are this wave's alone: claims are collected in
+// LDS and the byte stored once. Bytes, not words, so that few delegates still
+// spread over the waves: a wave walks its candidates' rows in a chain of steps
+// (a search of 2^12 vertices: 43 of its 127 us with 64 delegates a wave,
+// 14 of 95 with eight).
 template <int NW> __device__ void bu_deleg(const Search &a, Scratch<NW> &S, int L,
                                            uint32_t &with_dn) {
   const int dd_bu = S.plan.dd_bu, nd_bu = S.plan.nd_bu;
@@ -1602,7 +1605,11 @@ template <int NW> __device__ void bu_deleg(const Search &a, Scratch<NW> &S, int 
   const int l = lane_id();
   const int64_t nwaves = int64_t(gridDim.x) * (blockDim.x / kWave);
   const int64_t wid = int64_t(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave;
-  const int cw = min(mask_step(a.dwords, nwaves), 16);
+  const int32_t dbytes = a.dwords * 4;
+  const int cw = mask_step(dbytes, nwaves, 1);
+  uint8_t *const Cd = reinterpret_cast<uint8_t *>(a.Cd);
+  const uint8_t *const ddm = reinterpret_cast<const uint8_t *>(a.ddm);
+  const uint8_t *const dnms = reinterpret_cast<const uint8_t *>(a.dnm);
   WaveRows &R = S.w[threadIdx.x / kWave];
   // this wave's part of the append buffers: mask words and their prefix, and
   // the bits claimed
@@ -1610,13 +1617,13 @@ template <int NW> __device__ void bu_deleg(const Search &a, Scratch<NW> &S, int 
   int32_t *const wbits = wpre + kWave;
   unsigned int *const wgot = reinterpret_cast<unsigned int *>(wpre + 2 * kWave);
   uint32_t cands = 0, edges = 0, claimed = 0;
-  for (int64_t w0 = wid * cw; w0 < a.dwords; w0 += nwaves * cw) {
+  for (int64_t w0 = wid * cw; w0 < dbytes; w0 += nwaves * cw) {
     const int64_t w = w0 + l;
     uint32_t c = 0, cd = 0, dnm = 0;
-    if (l < cw && w < a.dwords) {
-      cd = a.Cd[w];
-      dnm = a.dnm[w];
-      c = ~cd & ((dd_bu ? a.ddm[w] : 0u) | (nd_bu ? dnm : 0u));
+    if (l < cw && w < dbytes) {
+      cd = Cd[w];
+      dnm = dnms[w];
+      c = ~cd & ((dd_bu ? ddm[w] : 0u) | (nd_bu ? dnm : 0u));
     }
     const int32_t pc = __popc(c);
     const int32_t pincl = wave_incl_scan(pc);
@@ -1636,7 +1643,7 @@ template <int NW> __device__ void bu_deleg(const Search &a, Scratch<NW> &S, int 
       if (ok) {
         wo = owner64(wpre, i);
         bit = nth_bit(uint32_t(wbits[wo]), i - wpre[wo]);
-        k = int32_t((w0 + wo) * 32 + bit);
+        k = int32_t((w0 + wo) * 8 + bit);
         const uint64_t x0 = a.doff[k], x1 = a.doff[k + 1];
         const int2 f = a.dd_first[k];  // fetched beside the row bounds
         const int64_t beg = row_start(x0);
@@ -1686,7 +1693,7 @@ template <int NW> __device__ void bu_deleg(const Search &a, Scratch<NW> &S, int 
     wave_sync();
     const uint32_t got = wgot[l];
     if (got) {
-      a.Cd[w] = cd | got;
+      Cd[w] = uint8_t(cd | got);
       with_dn += __popc(got & dnm);
     }
   }
