@@ -162,6 +162,7 @@ struct Search {
   SearchCtl *ctl;
   LevelStatus *hs;
   double nn_mean;  // nn edges per normal vertex
+  int32_t nn_rows;  // rows of about 256 nn edges together, a power of two up to 64
   // options
   double f0[4], f1[4];
   uint64_t forced_seed;
@@ -361,6 +362,29 @@ struct WaveAppend {
     cnt = 0;
   }
 };
+
+// What the block's waves have left in their buffers, with one atomic (a flush
+// per wave had up to 8192 of them wait on the tail at a level's end: RMAT 22
+// 402 -> 381 us, RMAT 26 2340 -> 2230).
+template <int NW> __device__ __forceinline__ void flush_block(Scratch<NW> &S, WaveAppend &qa) {
+  const int nw = blockDim.x / kWave, w = threadIdx.x / kWave;
+  if (lane_id() == 0) S.sh[w] = qa.cnt;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int64_t all = 0;
+    for (int i = 0; i < nw; ++i) {
+      const int64_t c = S.sh[i];
+      S.sh[i] = all;
+      all += c;
+    }
+    S.qbase = all ? atomicAdd(qa.gcount, (unsigned long long)all) & 0xffffffffull : 0ull;
+  }
+  __syncthreads();
+  const int64_t to = int64_t(S.qbase) + S.sh[w];
+  for (int i = lane_id(); i < qa.cnt; i += kWave) qa.gout[to + i] = qa.buf[i];
+  qa.cnt = 0;
+  __syncthreads();
+}
 
 // The block's two append buffers as one buffer per wave.
 template <int NW>
@@ -732,7 +756,7 @@ __device__ __forceinline__ void level_plan(const Search &a, Scratch<NW> &S, int 
 // ---------------------------------------------------------------------------
 // Mask words of one wave step of the delegate passes: a power of two, small
 // enough that every wave of the grid has a step when there are that many words.
-__device__ __forceinline__ int mask_step(int32_t words, int64_t nwaves, int least = 2) {
+__device__ __forceinline__ int mask_step(int32_t words, int64_t nwaves, int least) {
   int c = kWave;
   while (c > least && int64_t(words) < c * nwaves) c >>= 1;
   return c;
@@ -752,7 +776,7 @@ template <int NW> __device__ void prev_deleg(const Search &a, Scratch<NW> &S) {
   const int l = lane_id();
   const int64_t nwaves = int64_t(gridDim.x) * (blockDim.x / kWave);
   const int64_t wid = int64_t(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave;
-  const int cw = mask_step(a.dwords, nwaves);
+  const int cw = mask_step(a.dwords, nwaves, 2);
   WaveRows &R = S.w[threadIdx.x / kWave];
   uint32_t cnt = 0, q_dd = 0, q_dn = 0;
   unsigned long long fv_dd = 0, fv_dn = 0;
@@ -991,6 +1015,31 @@ template <int NW> __device__ void settle(const Search &a, Scratch<NW> &S, int L)
   count_units(a, S, DSBFS_K_PREV_NORMAL, 0, 0, claimed, 0);
 }
 
+// A wave's rows of a queue of q entries: as few a step as give every wave of the
+// grid one, but no fewer than nn_rows and no more than 64, dealt out over the
+// blocks. A wave expands its rows in a chain of steps: with 64 rows of 16 edges
+// a wave, the waves in blocks in a row, a level of 3170 rows took 67 us, now 20
+// (ER 2^22, 1199 -> 1100 us; RMAT 22, nearly all rows in full steps, gains 3%
+// from the dealing alone). Rows of one edge or two are not spread: it would
+// only add atomics to Fn. A queue short enough for 256 blocks is left to those:
+// a block that claims costs an atomic on the queue's tail.
+struct QueueShare {
+  int64_t first, stride;
+  int rows;
+  // the whole block has none
+  __device__ __forceinline__ bool none(int64_t q) const {
+    return rows == 0 || int64_t(blockIdx.x) * rows >= q;
+  }
+};
+__device__ __forceinline__ QueueShare queue_share(const Search &a, int64_t q) {
+  const int nw = blockDim.x / kWave;
+  const int64_t grid =
+      q <= 256 * int64_t(blockDim.x) ? min(int64_t(gridDim.x), int64_t(256)) : int64_t(gridDim.x);
+  const int rows = mask_step(int32_t(q), grid * nw, a.nn_rows);
+  if (blockIdx.x >= grid) return {q, 0, 0};
+  return {(int64_t(threadIdx.x / kWave) * grid + blockIdx.x) * rows, grid * nw * rows, rows};
+}
+
 // The nn part of row u: its length and, when `start` is set, where it begins
 // (in the compact nn copy if there is one, else in the full rows).
 __device__ __forceinline__ void nn_part(const Search &a, int32_t u, bool start, int32_t &nn,
@@ -1017,7 +1066,8 @@ __device__ __forceinline__ void nn_part(const Search &a, int32_t u, bool start, 
 template <int NW>
 __device__ void prev_normal(const Search &a, Scratch<NW> &S, int L, bool scatter) {
   const int64_t qn = S.qn;
-  if (int64_t(blockIdx.x) * blockDim.x >= qn) return;
+  const QueueShare sh = queue_share(a, qn);
+  if (sh.none(qn)) return;
   const int mark = S.mark, expand = !a.nn_do;
   const int32_t *const Q = a.q(L & 1);
   uint32_t *const Fn = a.fn(L & 1);
@@ -1025,12 +1075,12 @@ __device__ void prev_normal(const Search &a, Scratch<NW> &S, int L, bool scatter
   WaveAppend qa = wave_append_buf(S, &a.ctl->ctr[L % 3].qn_nc.v, a.q((L + 1) & 1));
   uint32_t q_nn = 0, q_nd = 0, edges = 0, claimed = 0, none = 0;
   unsigned long long fv_nn = 0, fv_nd = 0;
-  for (int64_t b0 = int64_t(blockIdx.x) * blockDim.x; b0 < qn;
-       b0 += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t i = b0 + threadIdx.x;
+  for (int64_t i0 = sh.first; i0 < qn; i0 += sh.stride) {
+    const int64_t i = i0 + lane_id();
+    const bool ok = lane_id() < sh.rows && i < qn;
     int32_t u = 0, nn = 0;
     int64_t beg = 0;
-    if (i < qn) {
+    if (ok) {
       int64_t nd = 0;
       u = Q[i];
       nn_part(a, u, expand, nn, nd, beg);
@@ -1040,14 +1090,16 @@ __device__ void prev_normal(const Search &a, Scratch<NW> &S, int L, bool scatter
       q_nd += nd > 0;
     }
     // queues filled by the bottom-up pass are in ascending order: mark word by word
-    if (mark) wave_bit_set(Fn, uint32_t(u), i < qn, true);
+    if (mark) wave_bit_set(Fn, uint32_t(u), ok, true);
     if (scatter)
       scatter_rows(a, R, a.nnoff ? a.nncol : a.ncol, u, nn, beg, L + 1, edges);
     else if (expand)
       expand_rows<true>(a, R, a.nnoff ? a.nncol : a.ncol, u, nn, beg, L + 1, qa, edges, claimed,
                         none);
   }
-  qa.flush();
+  // (few waves: their atomics are done before the block's waves have met)
+  if (qn > 256 * sh.rows) flush_block(S, qa);
+  else qa.flush();
   block_acc(&S.red[kQNd], q_nd);
   // the other sums only where a decision or the statistics read them
   if (a.count || a.forced != 0 || S.st.dir[2] == 0 || a.f1[2] != 0.0)
@@ -1371,18 +1423,21 @@ __device__ void td_normal(const Search &a, Scratch<NW> &S, int L, uint32_t &with
   const int64_t qn = S.plan.qn;
   const int nd_td = (parts & kNormal) && S.plan.nd_td, nn_td = (parts & kNn) && S.plan.nn_td;
   if (!nd_td && !nn_td) return;
+  const QueueShare sh = queue_share(a, qn);
+  if (sh.none(qn)) return;
+  const int l = lane_id();
   const int32_t *const Q = a.q(L & 1);
   WaveRows &R = S.w[threadIdx.x / kWave];
   WaveAppend qa = wave_append_buf(S, &a.ctl->ctr[L % 3].qn_nc.v, a.q((L + 1) & 1));
   uint32_t nd_e = 0, nd_c = 0, nn_e = 0, nn_c = 0, none = 0;
-  for (int64_t b0 = int64_t(blockIdx.x) * blockDim.x; b0 < qn;
-       b0 += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t i = b0 + threadIdx.x;
-    const int32_t u = i < qn ? Q[i] : 0;
+  for (int64_t i0 = sh.first; i0 < qn; i0 += sh.stride) {
+    const int64_t i = i0 + l;
+    const bool ok = l < sh.rows && i < qn;
+    const int32_t u = ok ? Q[i] : 0;
     if (nd_td) {
       int32_t len = 0;
       int64_t beg = 0;
-      if (i < qn) {
+      if (ok) {
         const uint64_t w0 = a.noff[u], w1 = a.noff[u + 1];
         beg = row_start(w0) + row_first(w0);
         len = int32_t(row_start(w1) - beg);
@@ -1392,7 +1447,7 @@ __device__ void td_normal(const Search &a, Scratch<NW> &S, int L, uint32_t &with
     if (nn_td) {
       int32_t nn = 0;
       int64_t nd = 0, beg = 0;
-      if (i < qn) nn_part(a, u, true, nn, nd, beg);
+      if (ok) nn_part(a, u, true, nn, nd, beg);
       expand_rows<true>(a, R, a.nnoff ? a.nncol : a.ncol, u, nn, beg, L + 1, qa, nn_e, nn_c,
                         none);
     }
@@ -2183,6 +2238,8 @@ Search search_args(const Graph *g, Workspace *ws, const dsbfs_run_opts &o, int32
   a.ctl = ws->ctl.as<SearchCtl>();
   a.hs = static_cast<LevelStatus *>(ws->hstat);
   a.nn_mean = double(g->st.e_nn) / double(std::max(g->n - g->d, 1));
+  a.nn_rows = kWave;
+  while (a.nn_rows > 1 && a.nn_mean * (a.nn_rows / 2) >= 4 * kWave) a.nn_rows >>= 1;
   for (int k = 0; k < 3; ++k) {
     a.f0[k] = o.factor0[k];
     a.f1[k] = o.factor1[k];
