@@ -2015,19 +2015,24 @@ __global__ void __launch_bounds__(1024) k_plain_search(Search a) {
 int stride_grid() { return 256 * 8; }
 
 // Shape of a one-launch search (blocks = 0: level by level instead). A barrier
-// costs more the more blocks there are, a level's work less, so the grid grows
-// with the graph; plain top-down searches read every edge, about four times
-// the work per vertex. Measured (us a search, RMAT edge factor 16, parents;
-// 32x256 / 64x256 / 64x512 / 128x512 / 256x512 / 256x1024 / level by level):
-//   n = 2^12   152 /  155 /  159 / 169 / 190 / 200 / 225
-//   n = 2^16   141 /  133 /  135 / 142 / 166 / 184 / 203
-//   n = 2^18   371 /  272 /  220 / 221 / 249 / 266 / 290
-//   n = 2^20   597 /  386 /  296 / 259 / 278 / 306 / 366
-//   n = 2^22  2027 / 1115 /  718 / 490 / 421 / 437 / 501
-//   n = 2^23  4484 / 2375 / 1468 / 914 / 695 / 654 / 733
-//   n = 2^26     - /    - /    - /   - / 3102 / 2628 / 2535
-// plain, n = 2^16  264 / 206 / 181 / 186 / 224 / 292 / 284
-// plain, n = 2^20 3728 / 2058 / 1457 / 1030 / 903 / 943 / 957
+// costs more the more blocks there are, a level's work less the more waves, so
+// the grid grows with the graph. Measured (us a search, RMAT edge factor 16,
+// parents; 32x256 / 64x256 / 64x512 / 128x512 / 128x1024 / 256x512 / 256x1024 /
+// level by level):
+//   n = 2^12   125 /  127 /  128 / 136 / 143 / 154 / 162 / 188
+//   n = 2^14   118 /  117 /  118 / 128 / 135 / 148 / 155 / 187
+//   n = 2^15   141 /  133 /  130 / 136 / 144 / 158 / 167 / 192
+//   n = 2^17   170 /  151 /  143 / 148 / 155 / 169 / 179 / 212
+//   n = 2^18   491 /  349 /  279 / 250 / 231 / 246 / 246 / 297
+//   n = 2^20   594 /  389 /  301 / 260 / 261 / 271 / 282 / 357
+//   n = 2^21  1023 /  605 /  425 / 328 / 294 / 304 / 300 / 379
+//   n = 2^22  1857 / 1020 /  643 / 429 / 354 / 353 / 329 / 398
+//   n = 2^23  4431 / 2310 / 1386 / 831 / 613 / 583 / 488 / 527
+//   n = 2^24  9663 / 4999 / 2909 / 1695 / 1252 / 1144 / 908 / 854
+// ER, mean degree 16, n = 2^20  1453 / 843 / 618 / 444 / 424 / 393 / 396 / 748
+// Plain top-down searches read every edge, about four times the work a vertex:
+//   n = 2^16  264 / 206 / 181 / 186 / - / 224 / 292 / 284
+//   n = 2^20 3728 / 2058 / 1457 / 1030 / - / 903 / 943 / 957
 struct OneLaunch {
   int blocks, threads;
 };
@@ -2042,13 +2047,20 @@ bool heavy_graph(const Search &a) {
 }
 
 OneLaunch one_launch_shape(const Graph *g, int mode) {
-  const int64_t w = int64_t(g->n) * (mode == 0 ? 4 : 1);
-  if (w <= (1 << 15)) return {32, 256};
-  if (w <= (1 << 17)) return {64, 256};
-  if (w <= 3 << 17) return {64, 512};
-  if (w <= 3 << 19) return {128, 512};
-  if (w <= 3 << 21) return {256, 512};
-  if (w <= 3 << 22) return {256, 1024};
+  const int64_t n = g->n;
+  if (mode == 0) {
+    if (n <= 1 << 13) return {32, 256};
+    if (n <= 1 << 15) return {64, 256};
+    if (n <= 3 << 15) return {64, 512};
+    if (n <= 3 << 17) return {128, 512};
+    if (n <= 3 << 19) return {256, 512};
+    if (n <= 3 << 20) return {256, 1024};
+    return {0, 0};
+  }
+  if (n <= 1 << 14) return {32, 256};
+  if (n <= 3 << 16) return {64, 512};
+  if (n <= 3 << 20) return {128, 1024};
+  if (n <= 3 << 22) return {256, 1024};
   return {0, 0};
 }
 
