@@ -115,10 +115,10 @@ def copy_peak(torch, nbytes=4 << 30, reps=10):
 VISIT_KERNEL = {"init": "init", "normal_frontier": "prev_normal", "delegate_previsit": "prev_deleg",
                 "nd_forward": "td_normal", "deleg_forward": "td_deleg",
                 "dn_backward": "bu_normal", "deleg_backward": "bu_deleg"}
-KERNEL_SYMBOL = {"prev_normal": "k_normal_level", "td_normal": "k_td_nd",
-                 "bu_normal": "k_bu_normal", "bu_deleg": "k_bu_deleg", "td_deleg": "k_td_deleg",
-                 "prev_deleg": "k_prev_deleg", "close": "k_close", "init": "k_init",
-                 "plain": "k_plain_expand"}
+KERNEL_SYMBOL = {"prev_normal": "k_previsit_normal", "td_normal": "k_forward_normal",
+                 "bu_normal": "k_backward_normal", "bu_deleg": "k_backward_deleg",
+                 "td_deleg": "k_forward_deleg", "prev_deleg": "k_previsit_deleg",
+                 "close": "k_previsit_clear", "init": "k_init", "plain": "k_plain_expand"}
 
 
 def main():
@@ -702,8 +702,8 @@ def bench_batched(args, torch, dsbfs, inputs):
     d1 = torch.empty(n, dtype=torch.int32, device="cuda")
     o1 = dsbfs.run_opts(want_parent=False)
     # edges of each source's component from an untimed search with
-    # statistics; the timed single searches run without them (captured level
-    # graphs), as in the single-source bench
+    # statistics; the timed single searches run without them, as in the
+    # single-source bench
     ecc = {}
     for s in set(sources.tolist()):
         ecc[s] = dsbfs.bfs(g, ws, s, d1, None, opts=o1, want_stats=True)["edges_cc"]

@@ -166,7 +166,7 @@ enum {
   DSBFS_K_TD_DELEG = 4,    /* top-down dd and/or dn from the delegate frontier */
   DSBFS_K_BU_NORMAL = 5,   /* bottom-up dn over the nd source list */
   DSBFS_K_BU_DELEG = 6,    /* bottom-up dd and/or nd over unvisited delegates */
-  DSBFS_K_CLOSE = 7,       /* level close */
+  DSBFS_K_CLOSE = 7,       /* clearing of the frontier bitmap of the level before */
   DSBFS_K_PLAIN = 8,       /* mode 0: length, scan and expansion of one level */
   DSBFS_K_TD_NN = 9,       /* nn_do: top-down nn from the normal queue */
   DSBFS_K_BU_NN = 10,      /* nn_do: bottom-up nn over normals with an nn edge */
@@ -339,11 +339,12 @@ dsbfs_status dsbfs_bfs(const dsbfs_graph *g, dsbfs_workspace *ws, int32_t source
  * dsbfs_bfs, with the search's scratch memory taken from one static device
  * array per GPU of 64 MiB (held from the library's load until the process
  * ends). A graph needing more (about 26 MB at RMAT scale 20; roughly 25 bytes
- * per vertex) is refused with RANGE before any device work. Levels run as
- * direct launches, and the call returns after its work on `stream` has
- * completed; calls on one device are serialized by a lock, so they never
- * overlap, and each call starts from a cleared state (the array keeps the
- * previous call's contents, which the search overwrites before reading).
+ * per vertex) is refused with RANGE before any device work. The search runs
+ * in one launch where the GPU has room for it (level by level otherwise), and
+ * the call returns after its work on `stream` has completed; calls on one
+ * device are serialized by a lock, so they never overlap, and each call starts
+ * from a cleared state (the array keeps the previous call's contents, which
+ * the search overwrites before reading).
  * opts->profile must be 0 (timing events are not created).
  * Errors: as dsbfs_bfs; RANGE (graph too large for the scratch array);
  * INVALID_ARG (profile = 1).
