@@ -19,7 +19,9 @@
 // launch nor a barrier.
 // Exactly-once discovery comes from atomic test-and-set on the claimed
 // bitmaps (normals: Vn; delegates: Cd = visited or found this level), so
-// queues hold no duplicates and depth/parent are written once per vertex.
+// queues hold no duplicates and depth/parent are written once per vertex. (The
+// heavy nn visits of long normal rows store first and claim afterwards, one
+// thread a vertex: scatter_step, settle.)
 //
 // Mode 0 is plain top-down BFS over the plain CSR (the paper's "BFS" beside
 // "DOBFS", Section VI-C): a list phase (degrees of the queue's rows) and an
@@ -1910,7 +1912,7 @@ __global__ void __launch_bounds__(kBS, 8) k_plain_expand(Search a, int L) {
 // ---------------------------------------------------------------------------
 // For graphs whose levels are a few microseconds of work: a kernel boundary
 // costs 4.5 us (12 kernels and a 13 us graph hand-over per level before:
-// search_rmat22's 642 us were 380 us of dispatch), a grid barrier of 64 wide
+// of the 642 us of an RMAT 22 search 380 were dispatch), a grid barrier of 64 wide
 // blocks 2.5 us and there are two or three per level. Every block follows the
 // search's state by itself, so a level needs no other exchange than its
 // counters.
