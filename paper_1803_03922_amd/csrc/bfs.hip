@@ -1635,8 +1635,7 @@ template <int NW> __device__ void bu_normal(const Search &a, Scratch<NW> &S, int
     }
     qa.push(won, v);
     ca.push(ok && !visited && !found, pos);
-    __syncthreads();
-    if (S.qcount > cap - int(blockDim.x) || S.ccount > cap - int(blockDim.x)) flush_pair(qa, ca);
+    flush_pair_if_full(qa, ca, int(blockDim.x));
   }
   flush_pair(qa, ca);
   // units: list entries read, unvisited scanned, edges inspected, claimed

@@ -477,6 +477,18 @@ __device__ inline void flush_pair(BlockAppend &q, BlockAppend &c) {
   __syncthreads();
 }
 
+// Writes both buffers out once one may not hold another step's entries (at
+// most `margin`). Block-uniform: the decision is read between two barriers,
+// where no push can change the counts. With the first alone, a wave could push
+// its next step's entries before another had read the counts of this one: the
+// two then parted at the barriers of flush_pair, and entries were lost.
+__device__ inline void flush_pair_if_full(BlockAppend &q, BlockAppend &c, int margin) {
+  __syncthreads();
+  const bool full = *q.count > q.cap - margin || *c.count > c.cap - margin;
+  __syncthreads();
+  if (full) flush_pair(q, c);
+}
+
 // Sums four per-thread counts over the block and adds them to dst[0..3] with
 // one global atomic each (block-uniform call; sh holds 4 * waves entries).
 __device__ __forceinline__ void block_add4(unsigned long long *dst, unsigned long long a,
