@@ -283,7 +283,6 @@ __global__ void __launch_bounds__(kDB) k_pr_deleg(PrStep a, const uint64_t *doff
     const int64_t b = row_start(w0), mid = b + row_first(w0), e = row_start(w1);
     const double s = wave_sum_f64(pr_pull<kPrUnroll>(
         a, pcol, b + int64_t(w) * (kPrUnroll * kWave) + l, mid, e, kDW * kPrUnroll * kWave));
-    __syncthreads();
     if (l == 0) sh[w] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -291,6 +290,9 @@ __global__ void __launch_bounds__(kDB) k_pr_deleg(PrStep a, const uint64_t *doff
       for (int i = 0; i < kDW; ++i) t += sh[i];
       pr_deleg_done(a, k, r, vid_of[k], e - b, base + a.alpha * t, delta);
     }
+    // before anything else is written to sh: the next row's sums, or, where no
+    // row is left for this block, those of block_add_f64
+    __syncthreads();
   }
   const int64_t nw = int64_t(gridDim.x) * kDW;
   for (int64_t r = lead + int64_t(blockIdx.x) * kDW + w; r < a.d; r += nw) {
