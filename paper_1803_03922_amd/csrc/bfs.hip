@@ -2127,12 +2127,17 @@ void run_opts_default(dsbfs_run_opts *o) { *o = default_opts(); }
 // persistent multi-source kernel) may not be resident in part beside each
 // other: two such grids could hold the compute units each needs to complete.
 // Each takes its blocks' worth of compute units from its device's gate before
-// the launch and returns them once the launch has completed.
+// the launch and returns them once the launch has completed. Callers that wait
+// (batches) are served in order of arrival, and while one does, a caller that
+// can do without (a search, which then goes level by level) takes no units:
+// searches that overlap each other would keep a batch from the whole chip for
+// as long as they go on.
 namespace {
 struct ResidentGate {
   std::mutex mu;
   std::condition_variable cv;
   int used = 0;
+  uint64_t next = 0, serving = 0;  // tickets of the callers that wait
 };
 ResidentGate &resident_gate() {
   static ResidentGate gates[64];
@@ -2148,8 +2153,14 @@ ResidentLease::ResidentLease(int blocks, bool wait) {
   ResidentGate &g = resident_gate();
   std::unique_lock<std::mutex> lk(g.mu);
   const int want = std::min(blocks, kGateUnits);
-  if (wait) g.cv.wait(lk, [&] { return g.used + want <= kGateUnits; });
-  if (g.used + want > kGateUnits) return;
+  if (wait) {
+    const uint64_t ticket = g.next++;
+    g.cv.wait(lk, [&] { return g.serving == ticket && g.used + want <= kGateUnits; });
+    ++g.serving;
+    g.cv.notify_all();  // the next in line may fit beside this one
+  } else if (g.serving != g.next || g.used + want > kGateUnits) {
+    return;
+  }
   g.used += want;
   units = want;
   gate = &g;

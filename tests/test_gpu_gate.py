@@ -1,0 +1,91 @@
+"""Searches and batches that want the compute units at the same time: a batch
+(whose grid needs all of them) is served beside searches that never pause."""
+import threading
+import time
+
+import numpy as np
+import pytest
+
+from gpu_helpers import lib, log, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+
+class _Setup:
+    def __init__(self, inputs_mod, oracle_mod, scale=18, k=6):
+        self.d = lib()
+        self.torch = torch_cuda()
+        self.n = 1 << scale
+        src, dst = inputs_mod.rmat_edges(scale)
+        self.g = self.d.Graph(src, dst, self.n, threshold=32)
+        O = oracle_mod.Graph(src, dst, self.n)
+        self.sources = inputs_mod.pick_sources(src, dst, self.n, k, seed=11).tolist()
+        self.want = {s: O.bfs(s, want_parent=False)[0] for s in self.sources}
+
+    def batch(self, ws, depth, stream):
+        self.d.msbfs(self.g, ws, self.sources, depth, stream=stream.cuda_stream)
+
+    def rows_right(self, depth):
+        got = depth.cpu().numpy()
+        return all(np.array_equal(got[i], self.want[s]) for i, s in enumerate(self.sources))
+
+
+def test_batches_are_served_beside_searches_without_pause(inputs_mod, oracle_mod):
+    """Two threads whose searches last a quarter of a second (a path: a barrier
+    or two for each of 30000 levels) and follow one another without a pause, so
+    that compute units are taken at nearly every moment, and two threads with
+    batches. The searches go on until every batch has returned, or until a limit
+    that only batches never served would reach."""
+    T = _Setup(inputs_mod, oracle_mod, scale=14)
+    d, torch, limit, n = T.d, T.torch, 12.0, 30000
+    v = np.arange(n - 1, dtype=np.int32)
+    path = d.Graph(v, v + 1, n, threshold=32, keep_plain_csr=False)
+    batches_done, errors, bad, count = threading.Event(), [], [], [0, 0]
+    t0 = time.monotonic()
+
+    def searches(k):
+        try:
+            stream, ws = torch.cuda.Stream(), d.Workspace(path)
+            depth = torch.empty(n, dtype=torch.int32, device="cuda")
+            time.sleep(0.1 * k)
+            while not batches_done.is_set() and time.monotonic() - t0 < limit:
+                d.bfs(path, ws, 0, depth, None, opts=d.run_opts(want_parent=False),
+                      stream=stream.cuda_stream)
+                count[k] += 1
+            if not np.array_equal(depth.cpu().numpy(), np.arange(n)):
+                bad.append(k)
+        except Exception as e:
+            errors.append(e)
+
+    def batches():
+        try:
+            stream, ws = torch.cuda.Stream(), d.Workspace(T.g, max_lanes=64)
+            depth = torch.empty((len(T.sources), T.n), dtype=torch.int32, device="cuda")
+            for i in range(3):
+                T.batch(ws, depth, stream)
+                if not T.rows_right(depth):
+                    bad.append(("batch", i))
+        except Exception as e:
+            errors.append(e)
+
+    searchers = [threading.Thread(target=searches, args=(k,)) for k in range(2)]
+    for t in searchers:
+        t.start()
+    while min(count) < 2 and not errors:  # both are at it, their first calls behind them
+        time.sleep(0.01)
+    start = time.monotonic()
+    batchers = [threading.Thread(target=batches) for _ in range(2)]
+    for t in batchers:
+        t.start()
+    for t in batchers:
+        t.join()
+    took = time.monotonic() - start
+    batches_done.set()
+    for t in searchers:
+        t.join()
+    log(f"6 batches beside {sum(count)} searches in {took:.2f} s")
+    assert not errors, errors
+    assert not bad, bad
+    assert took < limit / 2, f"batches took {took:.1f} s: served only once the searches had ended"
+    path.destroy()
+    T.g.destroy()
