@@ -465,8 +465,7 @@ __device__ LaneSet<W> bu_wave(const int64_t *off, const int32_t *col, const Lane
 
 constexpr int kTdBuf = 4096;
 
-template <int W>
-__global__ void __launch_bounds__(1024) k_msbfs(MsArgs a) {
+template <int W> __device__ __forceinline__ void run_batches(const MsArgs &a) {
   // per wave: bottom-up rows, or a top-down level's window of the degree scan
   __shared__ union {
     BuRows<W> rows[16];
@@ -774,6 +773,19 @@ __global__ void __launch_bounds__(1024) k_msbfs(MsArgs a) {
   }
   const unsigned long long be = block_sum_u64(edges, sh);
   if (threadIdx.x == 0 && be) atomicAdd(&a.ctl->edges, be);
+}
+
+template <int W> __global__ void __launch_bounds__(1024) k_msbfs(MsArgs a) { run_batches<W>(a); }
+
+// One word: 112 registers instead of 128 (the attribute counts half of the
+// unified file). At 128 a block of 1024 threads takes a compute unit's whole
+// register file and starts only once nothing else runs there: a batch beside
+// another stream's kernel waited for its end, however few waves that had. At 96
+// (amdgpu_waves_per_eu) a batch takes 10 us more. The wider batches need 128.
+template <>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_num_vgpr(56)))
+k_msbfs<1>(MsArgs a) {
+  run_batches<1>(a);
 }
 
 __global__ void k_hub_index(const int32_t *hubs, int64_t nhubs, int32_t *hub_idx) {

@@ -89,3 +89,41 @@ def test_batches_are_served_beside_searches_without_pause(inputs_mod, oracle_mod
     assert took < limit / 2, f"batches took {took:.1f} s: served only once the searches had ended"
     path.destroy()
     T.g.destroy()
+
+
+def _sleep(T, stream, seconds):
+    """Puts a kernel of one wave on stream that runs for about `seconds`; the event
+    recorded after it."""
+    torch = T.torch
+    with torch.cuda.stream(stream):
+        e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        torch.cuda._sleep(1_000_000)
+        e0.record()
+        torch.cuda._sleep(100_000_000)
+        e1.record()
+        e1.synchronize()
+        torch.cuda._sleep(int(100_000_000 * seconds * 1e3 / e0.elapsed_time(e1)))
+        ended = torch.cuda.Event()
+        ended.record()
+    return ended
+
+
+def test_batch_beside_another_streams_kernel(inputs_mod, oracle_mod):
+    """A batch of one word starts while another stream's kernel of a single wave
+    runs: its blocks leave that wave's compute unit room."""
+    T = _Setup(inputs_mod, oracle_mod, scale=14)
+    torch = T.torch
+    ws = T.d.Workspace(T.g, max_lanes=64)
+    rows = torch.empty((len(T.sources), T.n), dtype=torch.int32, device="cuda")
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    T.batch(ws, rows, two)  # what only a first call does
+    ended = _sleep(T, one, 0.5)
+    rows.fill_(7)
+    t0 = time.monotonic()
+    T.batch(ws, rows, two)
+    took = time.monotonic() - t0
+    asleep = not ended.query()
+    log(f"batch beside another stream's kernel: {took * 1e3:.1f} ms")
+    assert T.rows_right(rows)
+    assert asleep, f"the batch returned only after the other stream's kernel ({took:.2f} s)"
+    T.g.destroy()
