@@ -2441,6 +2441,7 @@ void run_levels(const Graph *g, Workspace *ws, Search a, const dsbfs_run_opts &o
 // workspace is then to be initialized again).
 bool run_one_launch(const Graph *g, Workspace *ws, Search a, const OneLaunch &shape,
                     hipStream_t s, int32_t *levels) {
+  stream_drain(s);
   ResidentLease lease(shape.blocks, false);
   if (!lease.units) return false;
   LevelStatus *hs = static_cast<LevelStatus *>(ws->hstat);

@@ -987,6 +987,8 @@ static void msbfs_launch(const Graph *g, Workspace *ws, const int32_t *sources, 
     }
     st->graphs.clear();
   }
+  // before the units are taken below (the copies that follow are short)
+  stream_drain(s);
   HIPCHK(hipMemcpyAsync(st->srcs.p, sources, size_t(k) * 4, hipMemcpyHostToDevice, s));
   const void *kern = ms_kernel(words);
   int occ = 0;

@@ -1,5 +1,7 @@
 """Searches and batches that want the compute units at the same time: a batch
-(whose grid needs all of them) is served beside searches that never pause."""
+(whose grid needs all of them) is served beside searches that never pause, and
+beside kernels of other streams; nobody waits for work that another caller's
+stream still has to do first."""
 import threading
 import time
 
@@ -21,6 +23,10 @@ class _Setup:
         O = oracle_mod.Graph(src, dst, self.n)
         self.sources = inputs_mod.pick_sources(src, dst, self.n, k, seed=11).tolist()
         self.want = {s: O.bfs(s, want_parent=False)[0] for s in self.sources}
+
+    def search(self, ws, depth, stream, s):
+        self.d.bfs(self.g, ws, s, depth, None, opts=self.d.run_opts(want_parent=False),
+                   stream=stream.cuda_stream)
 
     def batch(self, ws, depth, stream):
         self.d.msbfs(self.g, ws, self.sources, depth, stream=stream.cuda_stream)
@@ -125,5 +131,49 @@ def test_batch_beside_another_streams_kernel(inputs_mod, oracle_mod):
     asleep = not ended.query()
     log(f"batch beside another stream's kernel: {took * 1e3:.1f} ms")
     assert T.rows_right(rows)
+    assert asleep, f"the batch returned only after the other stream's kernel ({took:.2f} s)"
+    T.g.destroy()
+
+
+@pytest.mark.parametrize("queued", ["search", "batch"])
+def test_no_wait_for_earlier_work_of_another_stream(inputs_mod, oracle_mod, queued):
+    """A call queued behind a long kernel of its own stream does not keep a batch
+    on another stream waiting until that kernel has ended."""
+    T = _Setup(inputs_mod, oracle_mod, scale=16)
+    d, torch = T.d, T.torch
+    ws, wb, wc = d.Workspace(T.g), *(d.Workspace(T.g, max_lanes=64) for _ in range(2))
+    depth = torch.empty(T.n, dtype=torch.int32, device="cuda")
+    rows, rows_c = (torch.empty((len(T.sources), T.n), dtype=torch.int32, device="cuda")
+                    for _ in range(2))
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    T.search(ws, depth, one, T.sources[0])  # what only first calls do
+    T.batch(wc, rows_c, one)
+    T.batch(wb, rows, two)
+    rows.fill_(7)
+    torch.cuda.synchronize()
+    ended = _sleep(T, one, 0.7)
+    errors = []
+
+    def behind():
+        try:
+            if queued == "search":
+                T.search(ws, depth, one, T.sources[1])
+            else:
+                T.batch(wc, rows_c, one)
+        except Exception as e:
+            errors.append(e)
+
+    t = threading.Thread(target=behind)
+    t.start()
+    time.sleep(0.1)
+    t0 = time.monotonic()
+    T.batch(wb, rows, two)
+    took = time.monotonic() - t0
+    asleep = not ended.query()
+    t.join()
+    log(f"batch beside a {queued} behind a long kernel: {took * 1e3:.1f} ms")
+    assert not errors, errors
+    assert T.rows_right(rows) and T.rows_right(rows_c)
+    assert np.array_equal(depth.cpu().numpy(), T.want[T.sources[int(queued == "search")]])
     assert asleep, f"the batch returned only after the other stream's kernel ({took:.2f} s)"
     T.g.destroy()
