@@ -294,6 +294,15 @@ dsbfs_status dsbfs_server_destroy(dsbfs_server *s) {
 
 int64_t dsbfs_now_ns(void) { return now_ns(); }
 
+// Not part of the interface (dsbfs.h does not declare it): lets a test have a
+// workspace's one-launch searches give up at their first wait (ticks = -1; 0 sets
+// the usual bound again). Returns how many searches it will run level by level
+// before it tries one launch again.
+int32_t dsbfs_test_barrier_bound(dsbfs_workspace *ws, int64_t ticks) {
+  ws->w->bar_ticks = ticks;
+  return ws->w->back.skip;
+}
+
 const char *dsbfs_status_str(dsbfs_status st) {
   switch (st) {
     case DSBFS_OK: return "ok";

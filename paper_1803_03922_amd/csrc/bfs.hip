@@ -122,9 +122,11 @@ constexpr int kStatusSlots = 4;
 // Grid barrier: arrivals per group of blocks, groups complete, and one release
 // word per group, each on its own 128-byte line.
 constexpr int kBarGroups = 8;
+constexpr int kMaxOneLaunch = 256;  // blocks of a one-launch search at most
 struct GridBar {
   CtrLine arrive[kBarGroups], top, release[kBarGroups];
   CtrLine err;  // 1: a wait exceeded its bound; every block leaves
+  uint32_t started[kMaxOneLaunch];  // 1: the block runs
 };
 
 // Control block of a search (device memory).
@@ -178,6 +180,7 @@ struct Search {
   const RankDir *drank, *nrank;
   int32_t count;  // statistics are wanted: keep work units and every workload sum
   int32_t source, mode;
+  long long bar_ticks;  // bound of a wait of the grid barrier
 
   __device__ __forceinline__ uint32_t *fn(int p) const { return p ? Fn1 : Fn0; }
   __device__ __forceinline__ int32_t *q(int p) const { return p ? Q1 : Q0; }
@@ -408,10 +411,28 @@ __device__ __forceinline__ WaveAppend wave_append_buf(Scratch<NW> &S, unsigned l
 // 5.2 for 256, 9 for 512: the fences of each block are served one after the
 // other, which is why a one-launch search runs few, wide blocks.
 // A wait is bounded: past the bound every block leaves (returns false) and the
-// host runs the search level by level instead.
-constexpr long long kBarTicks = 20000000;  // 0.2 s of the 100 MHz wall clock
+// host runs the search level by level instead. Blocks that do not run yet (other
+// kernels hold their compute units, and may for long) are not waited for as blocks
+// at work are: the widest shape's blocks of 1024 threads with 128 registers need
+// every compute unit to themselves, and beside a long one-wave kernel such a
+// search lost the whole bound, then 0.2 s. (Held at 112 registers they would fit
+// beside it, at 2 to 5% of every search.)
+constexpr long long kStartTicks = 200000;     // 2 ms of the 100 MHz wall clock
+constexpr long long kBarTicks = 2000000000;   // 20 s
 
-__device__ bool grid_sync(GridBar &b, unsigned long long epoch, int *ok) {
+// Tells the others that this block runs (a store: a count on one line is 2 us).
+__device__ __forceinline__ void grid_start(GridBar &b) {
+  if (threadIdx.x == 0)
+    __hip_atomic_store(&b.started[blockIdx.x], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ bool grid_started(const GridBar &b) {
+  for (unsigned i = 0; i < gridDim.x; ++i)
+    if (!__hip_atomic_load(&b.started[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return false;
+  return true;
+}
+
+__device__ bool grid_sync(GridBar &b, unsigned long long epoch, int *ok, long long bound) {
   __syncthreads();
   if (threadIdx.x == 0) {
     const unsigned G = gridDim.x, grp = blockIdx.x % kBarGroups;
@@ -432,13 +453,18 @@ __device__ bool grid_sync(GridBar &b, unsigned long long epoch, int *ok) {
       }
     }
     const long long t0 = wall_clock64();
+    long long limit = min(bound, kStartTicks);
     int good = 1;
     while (ctr_load(&b.release[grp].v) < epoch) {
       if (ctr_load(&b.err.v)) {
         good = 0;
         break;
       }
-      if (wall_clock64() - t0 > kBarTicks) {
+      if (wall_clock64() - t0 > limit) {
+        if (limit < bound && grid_started(b)) {
+          limit = bound;
+          continue;
+        }
         __hip_atomic_store(&b.err.v, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         good = 0;
         break;
@@ -1947,6 +1973,7 @@ template <bool HEAVY> __global__ void __launch_bounds__(1024) k_search(Search a)
   __shared__ Scratch<kWideNW> S;
   GridBar &bar = a.ctl->bar;
   unsigned long long ep = 0;
+  grid_start(bar);
   if (threadIdx.x == 0) S.st = a.ctl->st[0];
   units_open(a, S);
   int L = 0;
@@ -1957,7 +1984,7 @@ template <bool HEAVY> __global__ void __launch_bounds__(1024) k_search(Search a)
     left -= S.qn;
     const bool heavy = HEAVY && heavy_level(a, S.qn, left);
     previsit<kWideNW, kDeleg | kNormal | kClear>(a, S, L, heavy);
-    if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+    if (!(ok = grid_sync(bar, ++ep, &S.ok, a.bar_ticks))) break;
     level_plan(a, S, L);
     if (a.count && blockIdx.x == 0 && threadIdx.x == 0)
       account_level(a, S.st, S.ns, S.now, S.qn, S.nc_prev, S.plan, a.ctl->tot);
@@ -1966,19 +1993,19 @@ template <bool HEAVY> __global__ void __launch_bounds__(1024) k_search(Search a)
     if (heavy) settle(a, S, L);
     if (p.dd_td || p.dn_td) list_deleg(a, S);
     if (heavy || p.dd_td || p.dn_td) {
-      if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+      if (!(ok = grid_sync(bar, ++ep, &S.ok, a.bar_ticks))) break;
     }
     if (p.dd_td || p.dn_td || p.nd_td || p.nn_td) {
       forward<kWideNW, kDeleg | kNormal | kNn>(a, S, L);
-      if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+      if (!(ok = grid_sync(bar, ++ep, &S.ok, a.bar_ticks))) break;
     }
     if (p.nn_bu) {
       bu_nn(a, S, L);
-      if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+      if (!(ok = grid_sync(bar, ++ep, &S.ok, a.bar_ticks))) break;
     }
     if (p.dn_bu || p.dd_bu || p.nd_bu) {
       backward<kWideNW, kDeleg | kNormal>(a, S, L);
-      if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+      if (!(ok = grid_sync(bar, ++ep, &S.ok, a.bar_ticks))) break;
     }
     __syncthreads();
     if (threadIdx.x == 0) S.st = S.ns;
@@ -1992,6 +2019,7 @@ __global__ void __launch_bounds__(1024) k_plain_search(Search a) {
   __shared__ Scratch<kWideNW> S;
   GridBar &bar = a.ctl->bar;
   unsigned long long ep = 0;
+  grid_start(bar);
   units_open(a, S);
   int L = 0;
   bool ok = true;
@@ -2003,10 +2031,10 @@ __global__ void __launch_bounds__(1024) k_plain_search(Search a) {
       ++a.ctl->tot.launches[DSBFS_K_PLAIN];
     }
     list_plain(a, S, L);
-    if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+    if (!(ok = grid_sync(bar, ++ep, &S.ok, a.bar_ticks))) break;
     uint32_t none = 0;
     expand_list<true>(a, S, L, none);
-    if (!(ok = grid_sync(bar, ++ep, &S.ok))) break;
+    if (!(ok = grid_sync(bar, ++ep, &S.ok, a.bar_ticks))) break;
   }
   units_close(a, S);
   one_launch_end(a, L, ok);
@@ -2276,6 +2304,7 @@ Search search_args(const Graph *g, Workspace *ws, const dsbfs_run_opts &o, int32
   a.count = count;
   a.source = source;
   a.mode = o.mode;
+  a.bar_ticks = ws->bar_ticks ? ws->bar_ticks : kBarTicks;
   return a;
 }
 
@@ -2438,9 +2467,17 @@ void run_levels(const Graph *g, Workspace *ws, Search a, const dsbfs_run_opts &o
 }
 
 // The whole search in one launch; false if its grid could not run (its
-// workspace is then to be initialized again).
+// workspace is then to be initialized again). After a launch that gave up on a
+// wait, the workspace's next searches go level by level without trying, 16 at
+// first and four times as many after every further one in a row: what the wait
+// cost is spread over them while whatever holds the compute units stays.
 bool run_one_launch(const Graph *g, Workspace *ws, Search a, const OneLaunch &shape,
                     hipStream_t s, int32_t *levels) {
+  Backoff &back = ws->back;
+  if (back.skip > 0) {
+    --back.skip;
+    return false;
+  }
   stream_drain(s);
   ResidentLease lease(shape.blocks, false);
   if (!lease.units) return false;
@@ -2460,7 +2497,13 @@ bool run_one_launch(const Graph *g, Workspace *ws, Search a, const OneLaunch &sh
   HIPCHK(hipStreamSynchronize(s));
   if (!ws->borrowed) st = *hs;
   *levels = st.level;
-  return st.seq == 1;
+  if (st.seq == 1) {
+    back = Backoff{};
+    return true;
+  }
+  back.len = back.len ? std::min(4 * back.len, 4096) : 16;
+  back.skip = back.len;
+  return false;
 }
 
 }  // namespace
@@ -2584,6 +2627,7 @@ constexpr int kMaxDevices = 64;
 struct ScratchSlot {
   std::mutex mu;         // one search at a time per device
   void *ptr = nullptr;   // device address of `scratch` on this device
+  Backoff back;          // of the searches in it, as a workspace's
 };
 
 ScratchSlot &scratch_slot(int dev) {
@@ -2668,7 +2712,9 @@ void bfs_run_noalloc(const Graph *g, int32_t source, const dsbfs_run_opts *opts,
   if (off > kScratchBytes)
     fail(DSBFS_ERR_RANGE, "allocation-free search scratch exceeded");
   ws.hstat = ring.p;
+  ws.back = sl.back;
   bfs_run(g, &ws, source, opts, depth, parent, stats, s);
+  sl.back = ws.back;
   // the next call reuses the array: this one's work must be complete
   HIPCHK(hipStreamSynchronize(s));
 }

@@ -134,6 +134,12 @@ struct Graph {
   int32_t nwords() const { return (n + 31) / 32; }
 };
 
+// Searches that do not try a single launch after one that had to give up.
+struct Backoff {
+  int skip = 0;  // of them left
+  int len = 0;   // how many the last one set
+};
+
 // Scratch of one search at a time (single-source and multi-source).
 struct Workspace {
   const Graph *g = nullptr;
@@ -154,6 +160,8 @@ struct Workspace {
   DevBuf ctl;                  // control block of the search in progress (bfs.hip)
   std::vector<hipEvent_t> events;  // profiling event pool
   void *hstat = nullptr;       // pinned ring of per-level status records
+  Backoff back;
+  int64_t bar_ticks = 0;       // bound of a one-launch search's waits; 0: the usual one
   // multi-source lane state
   void *ms_state = nullptr;           // launch state of multi-source BFS (msbfs.hip)
   // borrowed: every buffer points into memory the workspace does not own (the
