@@ -2164,7 +2164,7 @@ namespace {
 struct ResidentGate {
   std::mutex mu;
   std::condition_variable cv;
-  int used = 0;
+  int units = 0, used = 0;         // compute units of the device, and those taken
   uint64_t next = 0, serving = 0;  // tickets of the callers that wait
 };
 ResidentGate &resident_gate() {
@@ -2172,21 +2172,26 @@ ResidentGate &resident_gate() {
   int dev = 0;
   HIPCHK(hipGetDevice(&dev));
   if (dev < 0 || dev >= 64) fail(DSBFS_ERR_INVALID_ARG, "device index out of range");
-  return gates[dev];
+  ResidentGate &g = gates[dev];
+  std::lock_guard<std::mutex> lk(g.mu);
+  if (!g.units)
+    HIPCHK(hipDeviceGetAttribute(&g.units, hipDeviceAttributeMultiprocessorCount, dev));
+  return g;
 }
-constexpr int kGateUnits = 256;  // compute units
 }  // namespace
 
+// More blocks than compute units are either several to a unit by the launch's own
+// occupancy check (the batches' kernel, wait = true) or too many.
 ResidentLease::ResidentLease(int blocks, bool wait) {
   ResidentGate &g = resident_gate();
   std::unique_lock<std::mutex> lk(g.mu);
-  const int want = std::min(blocks, kGateUnits);
+  const int want = wait ? std::min(blocks, g.units) : blocks;
   if (wait) {
     const uint64_t ticket = g.next++;
-    g.cv.wait(lk, [&] { return g.serving == ticket && g.used + want <= kGateUnits; });
+    g.cv.wait(lk, [&] { return g.serving == ticket && g.used + want <= g.units; });
     ++g.serving;
     g.cv.notify_all();  // the next in line may fit beside this one
-  } else if (g.serving != g.next || g.used + want > kGateUnits) {
+  } else if (g.serving != g.next || g.used + want > g.units) {
     return;
   }
   g.used += want;
