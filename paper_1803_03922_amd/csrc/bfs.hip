@@ -2622,8 +2622,13 @@ void bfs_run(const Graph *g, Workspace *ws, int32_t source, const dsbfs_run_opts
 // load until the process ends; host code never uses the array's name as an
 // address, only the device address hipGetSymbolAddress returns for the
 // current device.
+// What grows with the graph has kScratchBytes; the control block and the status
+// ring, of fixed size, lie behind it.
 constexpr size_t kScratchBytes = size_t(64) << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+constexpr size_t round256(size_t b) { return ((b < 256 ? 256 : b) + 255) / 256 * 256; }
+constexpr size_t kFixedBytes =
+    round256(sizeof(SearchCtl)) + round256(kStatusSlots * sizeof(LevelStatus));
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kFixedBytes];
 
 namespace {
 
@@ -2640,12 +2645,11 @@ ScratchSlot &scratch_slot(int dev) {
   return slots[dev];
 }
 
-inline size_t round256(size_t b) { return ((b < 256 ? 256 : b) + 255) / 256 * 256; }
-
 }  // namespace
 
 // What decides whether a graph is taken (about 25 bytes per vertex). It is
-// more than the search carves out of the array now: the limit on graphs stays
+// more than the search carves out of kScratchBytes now (every part carved below
+// is a term here; those marked "room" have no part): the limit on graphs stays
 // where callers know it.
 size_t noalloc_scratch_bytes(const Graph *g) {
   const int64_t n = g->n, d = g->d, nm = std::max(n, d);
@@ -2660,7 +2664,7 @@ size_t noalloc_scratch_bytes(const Graph *g) {
   t += 2 * round256(size_t(g->st.n_ndsrc) * 4);        // c0, c1
   t += round256(scan_tmp_bytes(nm));                   // room
   t += round256(2 * tiles);                            // room
-  t += 3328;                                           // control block, status ring
+  t += 3328;                                           // room
   return t;
 }
 
@@ -2687,7 +2691,7 @@ void bfs_run_noalloc(const Graph *g, int32_t source, const dsbfs_run_opts *opts,
     sl.ptr = ptr;
   }
   char *base = static_cast<char *>(sl.ptr);
-  size_t off = 0;
+  size_t off = kScratchBytes;  // the fixed parts first, then the others from 0
   auto carve = [&](DevBuf &b, size_t bytes) {
     b.p = base + off;
     b.bytes = round256(bytes);
@@ -2702,6 +2706,7 @@ void bfs_run_noalloc(const Graph *g, int32_t source, const dsbfs_run_opts *opts,
   carve(ws.ctl, sizeof(SearchCtl));
   DevBuf ring;
   carve(ring, kStatusSlots * sizeof(LevelStatus));
+  off = 0;
   carve(ws.Vn, size_t(g->nwords()) * 4);
   carve(ws.Fn, size_t(g->nwords()) * 4);
   carve(ws.Vd, size_t(g->dwords()) * 4);
