@@ -2095,6 +2095,43 @@ OneLaunch one_launch_shape(const Graph *g, int mode) {
 
 }  // namespace
 
+// Where the dense output's arrays lie: in the part of dscan that a degree-separated
+// search leaves unused, then behind the bitmap in dlen, which may grow to 4 n
+// bytes for it (and 4 KB, for the smallest graphs' lines). Every graph with d <= n / 2 has room: 16 d bytes of
+// dscan's 8 n, then 5 bytes a position (at most n - d) in the 8 (n - 2 d) left there
+// and dlen's 3.9 n. Arrays of their own took 5 bytes a position and 8 a delegate
+// of every workspace. Graphs with more delegates than normals write depths and
+// parents where they belong as they go: consecutive delegates are near-consecutive
+// vertices there, which is what the arrays are for.
+static void place_output(Workspace *ws, const Alloc *al, hipStream_t s) {
+  const Graph *g = ws->g;
+  const size_t n = size_t(g->n), d = size_t(g->d), nds = size_t(g->st.n_ndsrc);
+  struct Room {
+    size_t at, end;
+    bool take(size_t bytes, size_t &where) {
+      const size_t b = (at + 255) / 256 * 256;
+      if (b + bytes > end) return false;
+      where = b;
+      at = b + bytes;
+      return true;
+    }
+  };
+  const size_t fn = size_t(g->nwords()) * 4;
+  Room scan{d * 8, (n + 1) * 8}, len{fn, n * 4 + 4096};
+  const size_t size[3] = {std::max<size_t>(d, 1) * 8, std::max<size_t>(nds, 1) * 4,
+                          (std::max<size_t>(nds, 1) + 3) / 4 * 4};
+  size_t at[3];
+  bool in_scan[3], fits = true;
+  for (int i = 0; i < 3 && fits; ++i) {
+    in_scan[i] = scan.take(size[i], at[i]);
+    fits = in_scan[i] || len.take(size[i], at[i]);
+  }
+  ws->dlen.alloc(al, fits ? len.at : fn, s);
+  if (!fits) return;
+  void **const to[3] = {&ws->dout, &ws->ppar, &ws->plev};
+  for (int i = 0; i < 3; ++i) *to[i] = (in_scan[i] ? ws->dscan : ws->dlen).as<char>() + at[i];
+}
+
 Workspace *workspace_create(const Graph *g, int32_t max_lanes) {
   if (max_lanes != 0 && max_lanes != 64)
     fail(DSBFS_ERR_INVALID_ARG, "max_lanes must be 0 or 64");
@@ -2113,14 +2150,11 @@ Workspace *workspace_create(const Graph *g, int32_t max_lanes) {
     ws->q0.alloc(al, size_t(n) * 4, s);
     ws->q1.alloc(al, size_t(n) * 4, s);
     ws->dlist.alloc(al, size_t(d) * 4, s);
-    ws->dlen.alloc(al, size_t(std::max(n, d)) * 4, s);
     ws->dscan.alloc(al, size_t(std::max(n, d) + 1) * 8, s);
     ws->c0.alloc(al, size_t(g->st.n_ndsrc) * 4, s);
     ws->c1.alloc(al, size_t(g->st.n_ndsrc) * 4, s);
     ws->ctl.alloc(al, sizeof(SearchCtl), s);
-    ws->ppar.alloc(al, size_t(g->st.n_ndsrc) * 4, s);
-    ws->plev.alloc(al, (size_t(g->st.n_ndsrc) + 3) / 4 * 4, s);
-    ws->dout.alloc(al, size_t(d) * 8, s);
+    place_output(ws, al, s);
     HIPCHK(hipHostMalloc(&ws->hstat, kStatusSlots * sizeof(LevelStatus), hipHostMallocDefault));
     std::memset(ws->hstat, 0, kStatusSlots * sizeof(LevelStatus));
     return ws;
@@ -2274,8 +2308,7 @@ Search search_args(const Graph *g, Workspace *ws, const dsbfs_run_opts &o, int32
   a.depth = depth;
   a.parent = parent;
   a.Vn = ws->Vn.as<uint32_t>();
-  // two normal frontier bitmaps alternate by level; the second lies in dlen,
-  // which single-source searches do not use otherwise
+  // two normal frontier bitmaps alternate by level
   a.Fn0 = ws->Fn.as<uint32_t>();
   a.Fn1 = ws->dlen.as<uint32_t>();
   a.Vd = ws->Vd.as<uint32_t>();
@@ -2287,9 +2320,9 @@ Search search_args(const Graph *g, Workspace *ws, const dsbfs_run_opts &o, int32
   a.C1 = ws->c1.as<int32_t>();
   a.dlist = ws->dlist.as<int32_t>();
   a.dscan = ws->dscan.as<int64_t>();
-  a.dout = ws->dout.as<int2>();
-  a.ppar = ws->ppar.as<int32_t>();
-  a.plev = ws->plev.as<uint8_t>();
+  a.dout = static_cast<int2 *>(ws->dout);
+  a.ppar = static_cast<int32_t *>(ws->ppar);
+  a.plev = static_cast<uint8_t *>(ws->plev);
   a.drank = g->drank.as<RankDir>();
   a.nrank = g->nrank.as<RankDir>();
   a.ctl = ws->ctl.as<SearchCtl>();
@@ -2412,7 +2445,7 @@ void launch_output(const Search &a, hipStream_t s) {
 void run_levels(const Graph *g, Workspace *ws, Search a, const dsbfs_run_opts &o, Prof &P,
                 std::vector<LevelStatus> &seen, hipStream_t s) {
   // (the allocation-free search's scratch has no room for the arrays)
-  a.compact = o.mode == 1 && !ws->borrowed;
+  a.compact = o.mode == 1 && ws->dout;
   LevelStatus *hs = static_cast<LevelStatus *>(ws->hstat);
   if (!ws->borrowed)
     for (int i = 0; i < kStatusSlots; ++i) hs[i].seq = 0;
@@ -2659,7 +2692,7 @@ size_t noalloc_scratch_bytes(const Graph *g) {
   t += 3 * round256(size_t(g->dwords()) * 4);          // Vd, Fd, Cd
   t += 2 * round256(size_t(n) * 4);                    // q0, q1
   t += 2 * round256(size_t(d) * 4);                    // dlist; room
-  t += round256(size_t(nm) * 4);                       // dlen
+  t += round256(size_t(nm) * 4);                       // dlen, and room
   t += round256(size_t(nm + 1) * 8);                   // dscan
   t += 2 * round256(size_t(g->st.n_ndsrc) * 4);        // c0, c1
   t += round256(scan_tmp_bytes(nm));                   // room
@@ -2715,7 +2748,7 @@ void bfs_run_noalloc(const Graph *g, int32_t source, const dsbfs_run_opts *opts,
   carve(ws.q0, size_t(n) * 4);
   carve(ws.q1, size_t(n) * 4);
   carve(ws.dlist, size_t(d) * 4);
-  carve(ws.dlen, size_t(nm) * 4);
+  carve(ws.dlen, size_t(g->nwords()) * 4);
   carve(ws.dscan, size_t(nm + 1) * 8);
   carve(ws.c0, size_t(g->st.n_ndsrc) * 4);
   carve(ws.c1, size_t(g->st.n_ndsrc) * 4);

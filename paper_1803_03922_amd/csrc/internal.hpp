@@ -149,14 +149,16 @@ struct Workspace {
   DevBuf Vn, Fn, Vd, Fd, Cd;
   DevBuf q0, q1;               // normal queues, int32[n]
   DevBuf dlist;                // frontier delegates of a forward visit, int32[d]
-  DevBuf dlen;                 // int32[max(n, d)]: second Fn bitmap; multi-source frontier list
+  DevBuf dlen;                 // second Fn bitmap
   DevBuf dscan;                // int64[max(n, d) + 1]: prefix of top-down lengths
   DevBuf c0, c1;               // bottom-up normal candidates, int32[n_ndsrc]
   // what bottom-up visits and delegate claims find, until a dense pass at the
   // end of the search writes it out (bfs.hip): per position of the nd source
   // list parent (int32) and depth (uint8, 0: none), per delegate (parent,
-  // depth + 1)
-  DevBuf ppar, plev, dout;
+  // depth + 1). They lie in dscan, of which a degree-separated search uses d
+  // entries, and behind dlen's bitmap; NULL where they do not fit there
+  // (place_output).
+  void *ppar = nullptr, *plev = nullptr, *dout = nullptr;
   DevBuf ctl;                  // control block of the search in progress (bfs.hip)
   std::vector<hipEvent_t> events;  // profiling event pool
   void *hstat = nullptr;       // pinned ring of per-level status records

@@ -1006,7 +1006,7 @@ static void msbfs_launch(const Graph *g, Workspace *ws, const int32_t *sources, 
   a.depth = depth;
   a.seen = st->seen.p;
   a.ring = st->ring.p;
-  a.tdlist = ws->dlen.as<int32_t>();    // int32[max(n, d)]
+  a.tdlist = ws->q0.as<int32_t>();      // int32[n]
   a.tdscan = ws->dscan.as<int64_t>();   // int64[max(n, d) + 1]
   a.hubs = st->hubs.as<int32_t>();
   a.nhubs = st->nhubs;
@@ -1449,7 +1449,7 @@ static MsLevel level_args(const Graph *g, Workspace *ws, int32_t L, LvCtl *ctl) 
   a.ring = st->lvring.as<uint64_t>();
   a.fcur = a.ring + int64_t(L & (kRing - 1)) * g->n;
   a.fnext = a.ring + int64_t((L + 1) & (kRing - 1)) * g->n;
-  a.tdlist = ws->dlen.as<int32_t>();
+  a.tdlist = ws->q0.as<int32_t>();
   a.tdscan = ws->dscan.as<int64_t>();
   a.hubs = st->hubs.as<int32_t>();
   a.nhubs = st->nhubs;

@@ -89,8 +89,7 @@ size_t workspace_footprint(const Workspace *w) {
   return buf_bytes(w->Vn) + buf_bytes(w->Fn) + buf_bytes(w->Vd) + buf_bytes(w->Fd) +
          buf_bytes(w->Cd) + buf_bytes(w->q0) + buf_bytes(w->q1) + buf_bytes(w->dlist) +
          buf_bytes(w->dlen) + buf_bytes(w->dscan) + buf_bytes(w->c0) + buf_bytes(w->c1) +
-         buf_bytes(w->ctl) + buf_bytes(w->ppar) + buf_bytes(w->plev) + buf_bytes(w->dout) +
-         ms_state_bytes(w);
+         buf_bytes(w->ctl) + ms_state_bytes(w);
 }
 
 enum QState { Q_PENDING = 0, Q_RUNNING = 1, Q_DONE = 2, Q_RELEASED = 3 };
