@@ -873,6 +873,10 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
                          G->deg.as<int32_t>(), G->did.as<int32_t>(), cnt_del.as<int32_t>(), n,
                          G->nlen.as<uint16_t>());
       HIPCHK(hipGetLastError());
+      // (the copy below is the largest a build of few edges ever is)
+      nstart.reset();
+      dstart.reset();
+      flag.reset();
     }
     const int64_t e_nn = hs[0], e_nd = hs[1], e_dn = hs[2], e_dd = hs[3];
     // 8. compact copy of the nn parts (the forward nn visit's rows), while
@@ -912,6 +916,7 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
     }
 
     // 9. source list of nd, source masks of dd and dn
+    flag.alloc(al, size_t(n), s);
     hipLaunchKernelGGL(k_flag_ndsrc, dim3(grid_for(n, kBS, 8192)), dim3(kBS), 0, s,
                        G->did.as<int32_t>(), cnt_del.as<int32_t>(), n, flag.as<uint8_t>());
     HIPCHK(hipGetLastError());

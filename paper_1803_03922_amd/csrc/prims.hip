@@ -64,8 +64,9 @@ __global__ void __launch_bounds__(kBS) k_scan_reduce(const T *in, int64_t N, int
   if (threadIdx.x == 0) bsum[blockIdx.x] = s;
 }
 
-template <class T>
-__global__ void __launch_bounds__(kBS) k_scan_down(const T *in, int64_t *out, int64_t N,
+// (in and out may be one array: a block reads its tile before it writes it)
+template <class T, class O>
+__global__ void __launch_bounds__(kBS) k_scan_down(const T *in, O *out, int64_t N,
                                                     const int64_t *bscan) {
   __shared__ int64_t sh[kNW + 1];
   const int64_t base = int64_t(blockIdx.x) * kTile + int64_t(threadIdx.x) * kItems;
@@ -82,21 +83,21 @@ __global__ void __launch_bounds__(kBS) k_scan_down(const T *in, int64_t *out, in
   pre += boff;
 #pragma unroll
   for (int k = 0; k < kItems; ++k) {
-    if (base + k < N) out[base + k] = pre;
+    if (base + k < N) out[base + k] = O(pre);
     pre += static_cast<int64_t>(v[k]);
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[N] = boff + total;
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[N] = O(boff + total);
 }
 
-template <class T>
-void scan_impl(const T *in, int64_t *out, int64_t N, void *tmp, hipStream_t s) {
+template <class T, class O = int64_t>
+void scan_impl(const T *in, O *out, int64_t N, void *tmp, hipStream_t s) {
   const int64_t nb = ntiles(N, kTile);
   if (N == 0) {
-    HIPCHK(hipMemsetAsync(out, 0, sizeof(int64_t), s));
+    HIPCHK(hipMemsetAsync(out, 0, sizeof(O), s));
     return;
   }
   if (nb == 1) {
-    hipLaunchKernelGGL(k_scan_down<T>, dim3(1), dim3(kBS), 0, s, in, out, N,
+    hipLaunchKernelGGL((k_scan_down<T, O>), dim3(1), dim3(kBS), 0, s, in, out, N,
                        static_cast<const int64_t *>(nullptr));
     HIPCHK(hipGetLastError());
     return;
@@ -109,7 +110,7 @@ void scan_impl(const T *in, int64_t *out, int64_t N, void *tmp, hipStream_t s) {
   hipLaunchKernelGGL(k_scan_reduce<T>, dim3(unsigned(nb)), dim3(kBS), 0, s, in, N, bsum);
   HIPCHK(hipGetLastError());
   scan_impl<int64_t>(bsum, bscan, nb, t, s);
-  hipLaunchKernelGGL(k_scan_down<T>, dim3(unsigned(nb)), dim3(kBS), 0, s, in, out, N,
+  hipLaunchKernelGGL((k_scan_down<T, O>), dim3(unsigned(nb)), dim3(kBS), 0, s, in, out, N,
                      static_cast<const int64_t *>(bscan));
   HIPCHK(hipGetLastError());
 }
@@ -263,8 +264,8 @@ __global__ void k_fill_i64(int64_t *p, int64_t N, int64_t v) {
 
 __global__ void __launch_bounds__(kRadixBS) k_radix_hist(const uint64_t *keys, int64_t N,
                                                           int shift, int bits, int64_t nb,
-                                                          int32_t *ghist) {
-  __shared__ int hist[kRadixBins];
+                                                          uint32_t *ghist) {
+  __shared__ uint32_t hist[kRadixBins];
   const uint32_t dmask = (1u << bits) - 1u;
   hist[threadIdx.x] = 0;
   __syncthreads();
@@ -272,7 +273,7 @@ __global__ void __launch_bounds__(kRadixBS) k_radix_hist(const uint64_t *keys, i
 #pragma unroll
   for (int r = 0; r < kRadixItems; ++r) {
     const int64_t i = tile + int64_t(r) * kRadixBS + threadIdx.x;
-    if (i < N) atomicAdd(&hist[uint32_t(keys[i] >> shift) & dmask], 1);
+    if (i < N) atomicAdd(&hist[uint32_t(keys[i] >> shift) & dmask], 1u);
   }
   __syncthreads();
   if (threadIdx.x <= dmask) ghist[int64_t(threadIdx.x) * nb + blockIdx.x] = hist[threadIdx.x];
@@ -287,9 +288,10 @@ __global__ void __launch_bounds__(kRadixBS) k_radix_hist(const uint64_t *keys, i
 // writing them one by one from registers kept 256 partly filled lines per
 // block open in the L2. 128M keys: 1.4 ms a pass of 8 bits before, 0.8 ms a
 // pass of 9 bits now (44 bits: five passes instead of six).
+template <class O>
 __global__ void __launch_bounds__(kRadixBS) k_radix_scatter(const uint64_t *keys, uint64_t *out,
                                                              int64_t N, int shift, int bits,
-                                                             int64_t nb, const int64_t *gscan) {
+                                                             int64_t nb, const O *gscan) {
   __shared__ uint64_t stage[kRadixTile];
   __shared__ uint16_t wcnt[kRadixNW][kRadixBins];  // below 8192: two blocks fit a compute unit
   __shared__ int64_t base[kRadixBins];  // where the tile's keys of a digit go, less their
@@ -340,7 +342,7 @@ __global__ void __launch_bounds__(kRadixBS) k_radix_scatter(const uint64_t *keys
   for (int k = 0; k < w; ++k) first += wsum[k];
 #pragma unroll
   for (int k = 0; k < kRadixNW; ++k) wcnt[k][tid] = uint16_t(wcnt[k][tid] + first);
-  if (uint32_t(tid) <= dmask) base[tid] = gscan[int64_t(tid) * nb + blockIdx.x] - first;
+  if (uint32_t(tid) <= dmask) base[tid] = int64_t(gscan[int64_t(tid) * nb + blockIdx.x]) - first;
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < kRadixItems; ++r)
@@ -414,10 +416,17 @@ void unique_to_csr(const uint64_t *keys, int64_t N, int64_t m, int B, int32_t n,
   HIPCHK(hipGetLastError());
 }
 
+// Up to this many keys their places fit 32 bits, and the counts are scanned where
+// they are: 0.25 bytes of scratch a key instead of 0.75 (the 512 digits of a pass
+// took a build that just fitted 1.5% over its limit).
+constexpr int64_t kRadix32 = UINT32_MAX;
+
 size_t radix_tmp_bytes(int64_t N) {
   const int64_t nb = ntiles(N, kRadixTile);
   const int64_t H = kRadixBins * (nb > 0 ? nb : 1);
-  return align256(size_t(H) * 4) + align256(size_t(H + 1) * 8) + scan_tmp_bytes(H);
+  return (N <= kRadix32 ? align256(size_t(H + 1) * 4)
+                        : align256(size_t(H) * 4) + align256(size_t(H + 1) * 8)) +
+         scan_tmp_bytes(H);
 }
 
 uint64_t *radix_sort_u64_bits(uint64_t *keys, uint64_t *alt, int64_t N, int lo_bit, int hi_bit,
@@ -429,18 +438,24 @@ uint64_t *radix_sort_u64_bits(uint64_t *keys, uint64_t *alt, int64_t N, int lo_b
   const int width = (hi_bit - lo_bit + passes - 1) / passes;
   const int64_t H = (int64_t(1) << width) * nb;
   char *t = static_cast<char *>(tmp);
-  int32_t *ghist = reinterpret_cast<int32_t *>(t);
-  t += align256(size_t(H) * 4);
+  uint32_t *ghist = reinterpret_cast<uint32_t *>(t);
+  t += align256(size_t(N <= kRadix32 ? H + 1 : H) * 4);
   int64_t *gscan = reinterpret_cast<int64_t *>(t);
-  t += align256(size_t(H + 1) * 8);
+  if (N > kRadix32) t += align256(size_t(H + 1) * 8);
   uint64_t *src = keys, *dst = alt;
   for (int shift = lo_bit; shift < hi_bit; shift += width) {
     hipLaunchKernelGGL(k_radix_hist, dim3(unsigned(nb)), dim3(kRadixBS), 0, s, src, N, shift,
                        width, nb, ghist);
     HIPCHK(hipGetLastError());
-    scan_impl<int32_t>(ghist, gscan, H, t, s);
-    hipLaunchKernelGGL(k_radix_scatter, dim3(unsigned(nb)), dim3(kRadixBS), 0, s, src, dst, N,
-                       shift, width, nb, gscan);
+    if (N <= kRadix32) {
+      scan_impl(ghist, ghist, H, t, s);
+      hipLaunchKernelGGL(k_radix_scatter<uint32_t>, dim3(unsigned(nb)), dim3(kRadixBS), 0, s, src,
+                         dst, N, shift, width, nb, ghist);
+    } else {
+      scan_impl(ghist, gscan, H, t, s);
+      hipLaunchKernelGGL(k_radix_scatter<int64_t>, dim3(unsigned(nb)), dim3(kRadixBS), 0, s, src,
+                         dst, N, shift, width, nb, gscan);
+    }
     HIPCHK(hipGetLastError());
     uint64_t *x = src;
     src = dst;
