@@ -22,18 +22,51 @@ namespace {
 
 constexpr int kBS = 256;
 
+// Pairs with an endpoint outside [0, n) (ctr[0]) and, of the others, those that
+// are not loops (ctr[1]), which is what the keys need room for: room for every
+// pair would be four times a list's own size too much where most are loops. One
+// pass over the list, both counts with one atomic a block.
+constexpr int kPackItems = 16;
+__global__ void __launch_bounds__(kBS) k_count_pairs(const int32_t *src, const int32_t *dst,
+                                                     int64_t g, int32_t n,
+                                                     unsigned long long *ctr) {
+  constexpr int64_t tile = int64_t(kBS) * kPackItems;
+  __shared__ unsigned long long sh[2];
+  if (threadIdx.x < 2) sh[threadIdx.x] = 0;
+  __syncthreads();
+  unsigned long long bad = 0, keep = 0;
+  for (int64_t t0 = int64_t(blockIdx.x) * tile; t0 < g; t0 += int64_t(gridDim.x) * tile) {
+    int32_t u[kPackItems], v[kPackItems];
+#pragma unroll
+    for (int i = 0; i < kPackItems; ++i) {
+      const int64_t e = t0 + i * kBS + threadIdx.x;
+      u[i] = e < g ? src[e] : 0;
+      v[i] = e < g ? dst[e] : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < kPackItems; ++i) {
+      const bool out = uint32_t(u[i]) >= uint32_t(n) || uint32_t(v[i]) >= uint32_t(n);
+      bad += out;
+      keep += !out && u[i] != v[i];
+    }
+  }
+  bad = wave_sum(bad);
+  keep = wave_sum(keep);
+  if (lane_id() == 0) {
+    if (bad) atomicAdd(&sh[0], bad);
+    if (keep) atomicAdd(&sh[1], keep);
+  }
+  __syncthreads();
+  if (threadIdx.x < 2 && sh[threadIdx.x]) atomicAdd(&ctr[threadIdx.x], sh[threadIdx.x]);
+}
+
 // Both directions of every non-loop pair as 64-bit keys (u << B) | v, in any
 // order (they are sorted next). A block packs kPackItems pairs per thread and
 // reserves their places with one atomic: one per wave step, on one address,
 // took 12.6 ms for 67M pairs (12.6 ns each, one after the other). Bound by the
-// 24 bytes a pair moves: 0.5 ms. Pairs with an endpoint outside [0, n) are
-// counted in *bad (the caller then discards the keys), which saves a pass over
-// the edge list before this one (0.45 ms).
-constexpr int kPackItems = 16;
+// 24 bytes a pair moves: 0.5 ms.
 __global__ void __launch_bounds__(kBS) k_pack(const int32_t *src, const int32_t *dst, int64_t g,
-                                              int32_t n, int B, uint64_t *keys,
-                                              unsigned long long *cursor,
-                                              unsigned long long *bad) {
+                                              int B, uint64_t *keys, unsigned long long *cursor) {
   constexpr int64_t tile = int64_t(kBS) * kPackItems;
   for (int64_t t0 = int64_t(blockIdx.x) * tile; t0 < g; t0 += int64_t(gridDim.x) * tile) {
     const int64_t w0 = t0 + int64_t(threadIdx.x / kWave) * (kWave * kPackItems) + lane_id();
@@ -43,13 +76,6 @@ __global__ void __launch_bounds__(kBS) k_pack(const int32_t *src, const int32_t 
       const int64_t e = w0 + i * kWave;
       u[i] = e < g ? src[e] : 0;
       v[i] = e < g ? dst[e] : 0;
-      const bool out = u[i] < 0 || u[i] >= n || v[i] < 0 || v[i] >= n;
-      if (__ballot(out)) {
-        if (out) {
-          atomicAdd(bad, 1ull);
-          u[i] = v[i] = 0;
-        }
-      }
     }
     pack_pairs<kPackItems>(u, v, B, keys, cursor);
   }
@@ -689,7 +715,7 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
     const int B = bits_for(n);
     const uint64_t vmask = (uint64_t(1) << B) - 1;
 
-    // 1. edges on the device (or generated: step 2)
+    // 1. edges on the device, checked and counted (or generated: step 2)
     DevBuf esrc, edst;
     const int32_t *ds = src, *dd = dst;
     if (!rmat && !o.edges_on_device && g > 0) {
@@ -704,7 +730,17 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
     ctr.alloc(al, 16 * sizeof(unsigned long long), s);
     HIPCHK(hipMemsetAsync(ctr.p, 0, 16 * sizeof(unsigned long long), s));
     unsigned long long *c = ctr.as<unsigned long long>();
-    int64_t M2 = 2 * g;   // upper bound (self-loops are dropped)
+    int64_t M2 = 2 * g;   // upper bound for the generator (self-loops are dropped)
+    if (!rmat && g > 0) {
+      hipLaunchKernelGGL(k_count_pairs, dim3(grid_for(g, kBS * kPackItems, 2048)), dim3(kBS), 0, s,
+                         ds, dd, g, n, c);
+      HIPCHK(hipGetLastError());
+      unsigned long long hc[2];
+      HIPCHK(hipMemcpyAsync(hc, c, sizeof(hc), hipMemcpyDeviceToHost, s));
+      HIPCHK(hipStreamSynchronize(s));
+      if (hc[0]) fail(DSBFS_ERR_INVALID_ARG, "edge endpoint outside [0, num_vertices)");
+      M2 = 2 * int64_t(hc[1]);
+    }
 
     // 2. symmetrize into keys, sort, de-duplicate
     DevBuf keys, alt;
@@ -712,15 +748,10 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
     alt.alloc(al, size_t(M2) * 8, s);
     if (rmat) {
       M2 = rmat_pack_keys(rmat, B, keys.as<uint64_t>(), c, s);
-    } else if (g > 0) {
+    } else if (M2 > 0) {
       hipLaunchKernelGGL(k_pack, dim3(grid_for(g, kBS * kPackItems, 8192)), dim3(kBS), 0, s, ds,
-                         dd, g, n, B, keys.as<uint64_t>(), c, c + 1);
+                         dd, g, B, keys.as<uint64_t>(), c);
       HIPCHK(hipGetLastError());
-      unsigned long long hc[2];
-      HIPCHK(hipMemcpyAsync(hc, c, sizeof(hc), hipMemcpyDeviceToHost, s));
-      HIPCHK(hipStreamSynchronize(s));
-      if (hc[1]) fail(DSBFS_ERR_INVALID_ARG, "edge endpoint outside [0, num_vertices)");
-      M2 = 2 * int64_t(hc[0]);
     }
     esrc.reset();
     edst.reset();

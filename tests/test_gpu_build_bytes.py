@@ -1,5 +1,6 @@
 """The most device memory a build holds at a time, through an allocator that
-counts: few edges on many vertices, many edges; from the host and on the device, with and
+counts: edge lists that are mostly loops (which the keys need no room for), few
+edges on many vertices, many edges; from the host and on the device, with and
 without the plain rows. The limits are what builds held at most before the
 builder packed its pairs in blocks."""
 import numpy as np
@@ -40,12 +41,18 @@ def _edges(kind):
         return (rng.integers(0, N, 100, dtype=np.int32) for _ in range(2))
     u = rng.integers(0, N, 8 * N, dtype=np.int32)
     v = rng.integers(0, N, 8 * N, dtype=np.int32)
+    if kind == "loops":
+        v[:8 * N * 15 // 16] = u[:8 * N * 15 // 16]
+    elif kind == "only loops":
+        v = u.copy()
     return u, v
 
 
 # bytes a vertex
 @pytest.mark.parametrize("kind,plain,device,limit", [
     ("few", False, False, 47.1), ("few", True, True, 47.1),
+    ("loops", False, False, 80.2), ("loops", False, True, 59.1), ("loops", True, True, 66.1),
+    ("only loops", True, False, 64.2), ("only loops", True, True, 47.1),
     ("edges", False, True, 264.1), ("edges", True, False, 495.1)])
 def test_build_peak(oracle_mod, kind, plain, device, limit):
     d, torch = lib(), torch_cuda()
@@ -57,5 +64,13 @@ def test_build_peak(oracle_mod, kind, plain, device, limit):
     O = oracle_mod.Graph(src, dst, N)
     np.testing.assert_array_equal(g.export(0, np.int32), O.degrees())
     assert a.peak <= limit * N
+    # an endpoint outside the range is refused before the keys are allocated
+    bad = dst.copy()
+    bad[len(bad) // 2] = N
+    b = _Peak()
+    with pytest.raises(d.DsbfsError) as e:
+        d.Graph(to(src), to(bad), N, threshold=32, keep_plain_csr=plain, allocator=b)
+    assert e.value.status == d.ERR_INVALID_ARG
+    assert not b.live and b.peak <= (0 if device else 8 * len(src)) + 4096
     g.destroy()
     assert not a.live
