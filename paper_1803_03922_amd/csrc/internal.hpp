@@ -122,12 +122,12 @@ struct Graph {
   DevBuf nnoff, nncol;
   DevBuf poff, pcol;  // plain CSR: int64 offsets [n+1], int32 columns [m]
   // PageRank's gather-friendly copy, built by its first call and kept with
-  // the graph: pr_rank[k] = rank of delegate k by descending degree bucket
-  // (ties by ID), pr_order its inverse, pr_lead the leading ranks whose rows a
-  // block pulls, and pr_col = dcol with every dd entry replaced by that rank,
-  // so the contributions of the most-gathered delegates sit together (int32
-  // [d], [d], [e_dd + e_dn]).
-  mutable DevBuf pr_rank, pr_order, pr_col;
+  // the graph: pr_order = the delegates by descending degree bucket (ties by
+  // ID), pr_lead the leading ones whose rows a block pulls, and pr_col = dcol
+  // with every dd entry replaced by its rank in that order, so the
+  // contributions of the most-gathered delegates sit together (int32 [d],
+  // [e_dd + e_dn]).
+  mutable DevBuf pr_order, pr_col;
   mutable int32_t pr_lead = 0;
   mutable std::mutex pr_mu;
   int32_t dwords() const { return (d + 31) / 32; }

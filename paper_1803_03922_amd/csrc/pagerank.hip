@@ -15,8 +15,7 @@
 // row), and the pull over delegate rows (dd part from the delegate array, dn
 // part from the normal array; a wave per row, a block per long row). Each pull
 // also writes its vertex's contribution to the next step (a row's length is
-// its degree), into the other of two sets of arrays, so no kernel reads the
-// ranks back; the ranks themselves are written by the last two steps only
+// its degree), into the other of two arrays, so no kernel reads the ranks back; the ranks themselves are written by the last two steps only
 // (the last one's L1 change needs the one before), or by every step when a
 // tolerance asks for the change of each. Row sums run in a fixed order; the
 // dangling mass and the L1 change are summed with atomics, whose order can
@@ -129,8 +128,9 @@ __global__ void __launch_bounds__(kPB) k_pr_cols(const uint64_t *doff, const int
 
 // Contributions of every vertex at rank x0, and the dangling mass.
 __global__ void __launch_bounds__(kPB) k_pr_first(double x0, const int32_t *deg,
-                                                  const int32_t *did, const int32_t *rank,
-                                                  int32_t n, double *cn, double *cd, double *cdr,
+                                                  const int32_t *did, const int32_t *vid_of,
+                                                  const int32_t *order, int32_t n, int32_t d,
+                                                  double *cn, double *cd, double *cdr,
                                                   PrAcc *acc) {
   __shared__ double sh[kPB / kWave];
   double dang = 0.0;
@@ -139,16 +139,14 @@ __global__ void __launch_bounds__(kPB) k_pr_first(double x0, const int32_t *deg,
     const int64_t v = v0 + threadIdx.x;
     if (v < n) {
       const int32_t dg = deg[v];
-      const double c = dg > 0 ? x0 / double(dg) : 0.0;
       if (dg == 0) dang += x0;
-      const int32_t k = did[v];
-      if (k >= 0) {
-        cd[k] = c;
-        cdr[rank[k]] = c;
-      } else {
-        cn[v] = c;
-      }
+      if (did[v] < 0) cn[v] = dg > 0 ? x0 / double(dg) : 0.0;
     }
+  }
+  for (int64_t r = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; r < d;
+       r += int64_t(gridDim.x) * blockDim.x) {
+    const int32_t k = order[r];
+    cd[k] = cdr[r] = x0 / double(deg[vid_of[k]]);  // a delegate has neighbours
   }
   block_add_f64(&acc->part[blockIdx.x % kAccParts].dangling, dang, sh);
 }
@@ -157,8 +155,11 @@ __global__ void __launch_bounds__(kPB) k_pr_first(double x0, const int32_t *deg,
 struct PrStep {
   int32_t n, d;
   double alpha;
-  const double *cn, *cd, *cdr;  // contributions: normals, delegates by ID and by rank
-  double *cn1, *cd1, *cdr1;     // those of the next step
+  // contributions: normals, delegates by ID and by rank; and those of the next
+  // step (cd is written by the delegate pull, which does not read it, after the
+  // normal pull has)
+  const double *cn, *cdr;
+  double *cd, *cn1, *cdr1;
   const PrAcc *in;              // dangling mass of r
   PrAcc *out;                   // L1 change, dangling mass of r'
   PrAcc *clear;                 // the next step's `out`
@@ -188,6 +189,7 @@ constexpr int kPrRowUnroll = 4;
 __global__ void __launch_bounds__(kPB) k_pr_normal(PrStep a, const uint64_t *noff,
                                                    const int32_t *ncol, const int32_t *did) {
   __shared__ double sh[kPB / kWave];
+  const double *const cd = a.cd;
   const double base = pr_base(a);
   double delta = 0.0, dang = 0.0;
   pr_clear(a.clear);
@@ -206,7 +208,7 @@ __global__ void __launch_bounds__(kPB) k_pr_normal(PrStep a, const uint64_t *nof
 #pragma unroll
         for (int u = 0; u < kPrRowUnroll; ++u) {
           const int64_t j = i0 + u;
-          const double g = ((j < e ? j : e - 1) < mid ? a.cn : a.cd)[c[u]];
+          const double g = ((j < e ? j : e - 1) < mid ? a.cn : cd)[c[u]];
           y[u] = j < e ? g : 0.0;
         }
 #pragma unroll
@@ -257,7 +259,7 @@ __device__ __forceinline__ void pr_deleg_done(const PrStep &a, int32_t k, int64_
                                               int64_t deg, double x, double &delta) {
   pr_rank(a, v, x, delta);
   const double c = x / double(deg);  // a delegate has more than TH >= 0 neighbours
-  a.cd1[k] = c;
+  a.cd[k] = c;
   a.cdr1[r] = c;
 }
 
@@ -348,18 +350,18 @@ void pagerank_run(const Graph *g, double alpha, int32_t max_iter, double tol, do
                          pcol.as<int32_t>());
       HIPCHK(hipGetLastError());
       g->pr_lead = d2h_scalar(lead.as<int32_t>(), s);
-      g->pr_rank = std::move(rank);
       g->pr_order = std::move(order);
       g->pr_col = std::move(pcol);
     }
   }
-  // two sets of contributions, alternating by step
-  DevBuf cn[2], cd[2], cdr[2], acc;
+  // contributions; those that a pull reads while it writes the next step's are
+  // kept twice, alternating by step
+  DevBuf cn[2], cd, cdr[2], acc;
   for (int i = 0; i < 2; ++i) {
     cn[i].alloc(al, size_t(n) * 8, s);
-    cd[i].alloc(al, size_t(std::max(d, 1)) * 8, s);
     cdr[i].alloc(al, size_t(std::max(d, 1)) * 8, s);
   }
+  cd.alloc(al, size_t(std::max(d, 1)) * 8, s);
   // accumulators: step i reads the dangling mass of A[i % 3] and adds into
   // A[(i + 1) % 3]; the third is cleared meanwhile
   acc.alloc(al, 3 * sizeof(PrAcc), s);
@@ -373,8 +375,9 @@ void pagerank_run(const Graph *g, double alpha, int32_t max_iter, double tol, do
   double dl = 0.0;
   if (max_iter > 0) {
     hipLaunchKernelGGL(k_pr_first, dim3(G1), dim3(kPB), 0, s, 1.0 / double(n),
-                       g->deg.as<int32_t>(), g->did.as<int32_t>(), g->pr_rank.as<int32_t>(), n,
-                       cn[0].as<double>(), cd[0].as<double>(), cdr[0].as<double>(), A);
+                       g->deg.as<int32_t>(), g->did.as<int32_t>(), g->vid_of.as<int32_t>(),
+                       g->pr_order.as<int32_t>(), n, d, cn[0].as<double>(), cd.as<double>(),
+                       cdr[0].as<double>(), A);
     HIPCHK(hipGetLastError());
   }
   for (; it < max_iter; ++it) {
@@ -385,10 +388,9 @@ void pagerank_run(const Graph *g, double alpha, int32_t max_iter, double tol, do
     a.d = d;
     a.alpha = alpha;
     a.cn = cn[p].as<double>();
-    a.cd = cd[p].as<double>();
+    a.cd = cd.as<double>();
     a.cdr = cdr[p].as<double>();
     a.cn1 = cn[q].as<double>();
-    a.cd1 = cd[q].as<double>();
     a.cdr1 = cdr[q].as<double>();
     a.in = A + it % 3;
     a.out = A + (it + 1) % 3;
