@@ -2062,6 +2062,18 @@ int stride_grid() { return 256 * 8; }
 // Plain top-down searches read every edge, about four times the work a vertex:
 //   n = 2^16  264 / 206 / 181 / 186 / - / 224 / 292 / 284
 //   n = 2^20 3728 / 2058 / 1457 / 1030 / - / 903 / 943 / 957
+// Denser graphs take the shape of a larger one (m directed edges; the same columns):
+//   plain, n = 2^14, m = 23M   949 /  534 /  359 /  289 / 289 / 330 / 371 / 316
+//   plain, ER 2^14, m = 106M  4423 / 2257 / 1248 /  711 / 506 / 481 / 404 / 346
+//   plain, ER 2^18, m = 134M  6126 / 3133 / 1875 / 1025 / 979 / 650 / 684 / 750
+// where all of them are read, that is in plain searches and in those that stay
+// top-down; a direction-optimized search of a graph with hubs reads few of them,
+// however many there are, but one of a uniform graph scans long rows before it
+// meets its frontier:
+//   RMAT 2^14, m = 23M          93 /   91 /   93 /  102 / 108 / 118 / 126 / 161
+//   ER 2^14, m = 32M          1208 /  673 /  387 /  240 / 165 / 169 / 179 / 205
+//   ER 2^16, m = 132M         5525 / 2837 / 1504 /  807 / 473 / 456 / 290 / 243
+//   ER 2^20, m = 134M        14180 / 7145 / 3972 / 2081 / 1270 / 1138 / 746 / 671
 struct OneLaunch {
   int blocks, threads;
 };
@@ -2075,22 +2087,37 @@ bool heavy_graph(const Search &a) {
   return !a.nn_do && a.nn_mean >= 4 && a.nn_mean * a.n / 4 >= a.n / 16.0 + kHeavyEdges;
 }
 
-OneLaunch one_launch_shape(const Graph *g, int mode) {
-  const int64_t n = g->n;
-  if (mode == 0) {
-    if (n <= 1 << 13) return {32, 256};
-    if (n <= 1 << 15) return {64, 256};
-    if (n <= 3 << 15) return {64, 512};
-    if (n <= 3 << 17) return {128, 512};
-    if (n <= 3 << 19) return {256, 512};
-    if (n <= 3 << 20) return {256, 1024};
-    return {0, 0};
-  }
-  if (n <= 1 << 14) return {32, 256};
-  if (n <= 3 << 16) return {64, 512};
-  if (n <= 3 << 20) return {128, 1024};
-  if (n <= 3 << 22) return {256, 1024};
+// w: vertices of a graph of edge factor 16 with about as much work.
+OneLaunch plain_shape(int64_t n, int64_t w) {
+  if (w <= 1 << 13) return {32, 256};
+  if (w <= 1 << 15) return {64, 256};
+  if (w <= 3 << 15) return {64, 512};
+  if (w <= 3 << 17) return {128, 512};
+  // (many edges of many vertices: 650 and 684 us at 2^18 and 134M, 1101 and 1170 at 2^20)
+  if (w <= 3 << 19 || (n >= 1 << 17 && n <= 3 << 19)) return {256, 512};
+  if (n <= 3 << 20) return {256, 1024};
   return {0, 0};
+}
+
+OneLaunch one_launch_shape(int64_t n, int64_t m, int64_t max_degree, const dsbfs_run_opts &o) {
+  // (below 2^20 edges the columns differ by less than runs do)
+  const bool dense = m > 1 << 20;
+  const OneLaunch plain = plain_shape(n, dense ? std::max(n, m / 64) : n);
+  if (o.mode == 0) return plain;
+  // uniform: the largest degree is 1.1 to 1.3 times the mean in ER graphs, 2.9 times
+  // and more in the densest RMAT ones (where a source sees most of the graph at once
+  // there is nothing to scan: ER 2^12 with 15M edges 67 us in 32 blocks, 84 in 128)
+  const bool uniform = dense && max_degree * n <= 2 * m && 2 * max_degree <= n;
+  const int64_t w = uniform ? std::max(n, m / 32) : n;
+  OneLaunch r{256, 1024};
+  if (n > 3 << 22) return {0, 0};
+  if (w <= 1 << 14) r = {32, 256};
+  else if (w <= 3 << 16) r = {64, 512};
+  else if (w <= 3 << 20) r = {128, 1024};
+  // a search that stays top-down, by its schedule or its factor
+  const bool forward = o.forced == 1 || (o.forced == 0 && o.factor0[0] >= 1.0);
+  if (forward && dense && plain.blocks * plain.threads > r.blocks * r.threads) r = plain;
+  return r;
 }
 
 }  // namespace
@@ -2569,7 +2596,7 @@ void bfs_run(const Graph *g, Workspace *ws, int32_t source, const dsbfs_run_opts
   int32_t num_levels = 0;
   // One launch unless the caller wants a record per level.
   const bool records = stats && stats->levels && stats->capacity > 0;
-  const OneLaunch shape = one_launch_shape(g, o.mode);
+  const OneLaunch shape = one_launch_shape(g->n, g->m, g->st.max_degree, o);
   if (!(shape.blocks && !P.on && !records &&
         run_one_launch(g, ws, a, shape, s, &num_levels))) {
     run_levels(g, ws, a, o, P, seen, s);
