@@ -713,7 +713,6 @@ Graph *graph_create(const int32_t *src, const int32_t *dst, int64_t g, int32_t n
     G->TH = o.threshold;
     const Alloc *al = &G->al;
     const int B = bits_for(n);
-    const uint64_t vmask = (uint64_t(1) << B) - 1;
 
     // 1. edges on the device, checked and counted (or generated: step 2)
     DevBuf esrc, edst;

@@ -194,7 +194,6 @@ struct alignas(128) CtrLine {
   unsigned long long pad[15];
 };
 
-// Per-lane result rows of a level-at-a-time multi-source step (server).
 // Sources of the lanes admitted at one level (by value: no copy per level).
 struct SeedList {
   int32_t src[64];
@@ -317,14 +316,6 @@ __device__ __forceinline__ int64_t wave_append(bool want, unsigned long long *co
 __device__ __forceinline__ bool bit_test(const uint32_t *bm, uint32_t v) {
   return (bm[v >> 5] >> (v & 31)) & 1u;
 }
-// Test-and-set: true iff this call changed the bit from 0 to 1. The test before
-// the atomic is a plain cached read: a stale word can only lack a bit (bits
-// are set, never cleared, while a kernel claims), and then the atomic decides.
-__device__ __forceinline__ bool bit_claim(uint32_t *bm, uint32_t v) {
-  const uint32_t b = 1u << (v & 31);
-  if (bm[v >> 5] & b) return false;
-  return !(atomicOr(&bm[v >> 5], b) & b);
-}
 
 // Wave-cooperative bitmap update for lanes whose bits tend to share words
 // (vertices visited in ascending order). Adjacent lanes with the same word
@@ -445,23 +436,6 @@ struct BlockAppend {
       if (over) gout[b + lanes_below(mo)] = v;
     }
   }
-  // Block-uniform: writes the buffer out if it holds more than cap - margin.
-  __device__ void maybe_flush(int margin) {
-    __syncthreads();
-    if (*count > cap - margin) flush();
-  }
-  // Block-uniform.
-  __device__ void flush() {
-    __syncthreads();
-    const int c = min(*count, cap);
-    if (threadIdx.x == 0) *base = c ? reserve((unsigned long long)c) : 0ull;
-    __syncthreads();
-    const unsigned long long b = *base;
-    for (int i = threadIdx.x; i < c; i += blockDim.x) gout[b + i] = buf[i];
-    __syncthreads();
-    if (threadIdx.x == 0) *count = 0;
-    __syncthreads();
-  }
 };
 
 // Writes out two append buffers that count in the two halves of one word
@@ -499,31 +473,6 @@ __device__ inline void flush_pair_if_full(BlockAppend &q, BlockAppend &c, int ma
   const bool full = *q.count > q.cap - margin || *c.count > c.cap - margin;
   __syncthreads();
   if (full) flush_pair(q, c);
-}
-
-// Sums four per-thread counts over the block and adds them to dst[0..3] with
-// one global atomic each (block-uniform call; sh holds 4 * waves entries).
-__device__ __forceinline__ void block_add4(unsigned long long *dst, unsigned long long a,
-                                           unsigned long long b, unsigned long long c,
-                                           unsigned long long d, unsigned long long *sh) {
-  const int w = threadIdx.x / kWave, nw = blockDim.x / kWave;
-  a = wave_sum(a);
-  b = wave_sum(b);
-  c = wave_sum(c);
-  d = wave_sum(d);
-  if (lane_id() == 0) {
-    sh[w] = a;
-    sh[nw + w] = b;
-    sh[2 * nw + w] = c;
-    sh[3 * nw + w] = d;
-  }
-  __syncthreads();
-  if (threadIdx.x < 4) {
-    unsigned long long t = 0;
-    for (int i = 0; i < nw; ++i) t += sh[threadIdx.x * nw + i];
-    if (t) atomicAdd(&dst[threadIdx.x], t);
-  }
-  __syncthreads();
 }
 
 __device__ __forceinline__ int64_t row_start(uint64_t w) { return static_cast<int64_t>(w & kOffMask); }
@@ -597,7 +546,6 @@ inline int grid_for(int64_t items, int per_block, int cap = 65536) {
 // of scan_tmp_bytes(N) bytes.
 size_t scan_tmp_bytes(int64_t N);
 void scan_excl_i32_to_i64(const int32_t *in, int64_t *out, int64_t N, void *tmp, hipStream_t s);
-void scan_excl_i64(const int64_t *in, int64_t *out, int64_t N, void *tmp, hipStream_t s);
 
 // Stable LSD radix sort of N uint64 keys on bits [lo_bit, hi_bit) (bits above
 // hi_bit are equal in all keys; keys already ordered below lo_bit keep that

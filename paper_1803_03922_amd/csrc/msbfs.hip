@@ -1240,16 +1240,16 @@ __global__ void k_lv_seed(MsLevel a, uint64_t mask, SeedList src) {
   }
 }
 
-// Also, when publish is set (once per level, after the level's kernels):
-// block 0 sums the level's control block into host_ctl (size of the next
-// frontier, its lanes; pinned host memory, read by the host once the stream
-// passes this kernel) and clears next_ctl, the control block of the next level.
 // Writes the result rows of a set of lanes from ring levels [f.jlo, f.jhi]
 // (fewer than kRing): depth j - start[i] where lane i's bit is in level j's
 // mask and f.valid[j - jlo] admits lane i (levels before a lane's start or
 // already written are excluded), and, when `final`, -1 where the lane never
 // arrived. final: the set is f.lanes minus the lanes still alive after the
-// level just run (ctl[1]), i.e. the lanes that completed; else f.lanes.
+// level just run, i.e. the lanes that completed; else f.lanes. With host_ctl
+// (once per level, after the level's kernels) block 0 also sums the level's
+// control block into it (size of the next frontier, its lanes; pinned host
+// memory, read by the host once the stream passes this kernel) and clears
+// next_ctl, the control block of the next level.
 __global__ void k_lv_flush(MsLevel a, LaneFlush f, LvCtl *next_ctl,
                            unsigned long long *host_ctl) {
   uint64_t set = f.lanes;

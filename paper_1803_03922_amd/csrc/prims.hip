@@ -2,7 +2,8 @@
 // exclusive scan, order-preserving compaction and LSD radix sort of 64-bit
 // keys. Tiles are wave64-native: block-level scans are built from wave
 // shuffles plus one LDS slot per wave, and the radix scatter ranks keys inside
-// a wave by digit matching with 8 ballots (stable, no LDS key staging).
+// a wave by digit matching with a ballot a bit (stable) and stages the keys in
+// LDS.
 #include "internal.hpp"
 
 namespace dsbfs {
@@ -366,9 +367,6 @@ size_t scan_tmp_bytes(int64_t N) {
 
 void scan_excl_i32_to_i64(const int32_t *in, int64_t *out, int64_t N, void *tmp, hipStream_t s) {
   scan_impl<int32_t>(in, out, N, tmp, s);
-}
-void scan_excl_i64(const int64_t *in, int64_t *out, int64_t N, void *tmp, hipStream_t s) {
-  scan_impl<int64_t>(in, out, N, tmp, s);
 }
 
 size_t compact_tmp_bytes(int64_t N) { return scan_tmp_bytes(N); }
