@@ -937,6 +937,9 @@ static void hub_list(const Graph *g, MsState *st, hipStream_t s) {
                                                  40, tmp.p, s);
     hipLaunchKernelGGL(k_hub_list, G, B, 0, s, sorted, nh, st->hubs.as<int32_t>());
     HIPCHK(hipGetLastError());
+    // a call that fails after this one's list leaves it to a next one, which may
+    // come on another stream
+    HIPCHK(hipStreamSynchronize(s));
   }
   st->nhubs = nh;
 }
