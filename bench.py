@@ -115,10 +115,12 @@ def copy_peak(torch, nbytes=4 << 30, reps=10):
 VISIT_KERNEL = {"init": "init", "normal_frontier": "prev_normal", "delegate_previsit": "prev_deleg",
                 "nd_forward": "td_normal", "deleg_forward": "td_deleg",
                 "dn_backward": "bu_normal", "deleg_backward": "bu_deleg"}
-KERNEL_SYMBOL = {"prev_normal": "k_previsit_normal", "td_normal": "k_forward_normal",
-                 "bu_normal": "k_backward_normal", "bu_deleg": "k_backward_deleg",
-                 "td_deleg": "k_forward_deleg", "prev_deleg": "k_previsit_deleg",
-                 "close": "k_previsit_clear", "init": "k_init", "plain": "k_plain_expand"}
+# and the kernels that run them in a profiled search (bits of `parts` in bfs.hip)
+KERNEL_SYMBOL = {"prev_normal": "k_previsit<2>", "prev_deleg": "k_previsit<1>",
+                 "close": "k_previsit<4>", "td_normal": "k_forward<2>", "td_deleg": "k_forward<1>",
+                 "td_nn": "k_forward<8>", "bu_normal": "k_backward<2>",
+                 "bu_deleg": "k_backward<17>", "bu_nn": "k_bu_nn", "init": "k_init",
+                 "plain": "k_plain_expand"}
 
 
 def main():
@@ -252,7 +254,7 @@ def main():
     tiny = [int(s) for s in sources.tolist() if edges_cc[s] * 1000 < max(edges_cc.values())]
 
     # Kernel breakdown: the model sources again with every kernel timed by HIP
-    # events on the search's stream (direct launches instead of graphs).
+    # events on the search's stream (a kernel per visit).
     msrc = sources.tolist()[:args.model_sources]
     kern, ptimes, gpu_levels = {}, [], {}
     for s in msrc:
@@ -271,7 +273,7 @@ def main():
     def time_factors(f0, nn=None):
         o3 = dsbfs.run_opts(want_parent=parent is not None, factor0=f0, nn_do=nn is not None,
                             factor_nn=nn)
-        # untimed: a change of nn_do captures new level graphs on the host
+        # untimed: the first search of these options loads their kernels
         timed(g, ws, int(sources[0]), o3)
         tt, rr = [], []
         for i in range(args.factor_steps):
@@ -297,7 +299,7 @@ def main():
     depth_only = None
     if parent is not None and args.depth_only:
         o_np = dsbfs.run_opts(mode=mode, want_parent=False)
-        timed(g, ws, int(sources[0]), o_np)   # untimed: captures the depth-only level graphs
+        timed(g, ws, int(sources[0]), o_np)   # untimed
         tt, rr = [], []
         for s in sources.tolist():
             ms, _ = timed(g, ws, s, o_np)
