@@ -299,6 +299,7 @@ int64_t dsbfs_now_ns(void) { return now_ns(); }
 // the usual bound again). Returns how many searches it will run level by level
 // before it tries one launch again.
 int32_t dsbfs_test_barrier_bound(dsbfs_workspace *ws, int64_t ticks) {
+  if (!ws) return -1;
   ws->w->bar_ticks = ticks;
   return ws->w->back.skip;
 }

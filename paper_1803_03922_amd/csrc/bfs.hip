@@ -2471,7 +2471,7 @@ void launch_output(const Search &a, hipStream_t s) {
 // Level by level; seen gets the records of the levels with a frontier.
 void run_levels(const Graph *g, Workspace *ws, Search a, const dsbfs_run_opts &o, Prof &P,
                 std::vector<LevelStatus> &seen, hipStream_t s) {
-  // (the allocation-free search's scratch has no room for the arrays)
+  // (no arrays: the allocation-free search, graphs with many delegates)
   a.compact = o.mode == 1 && ws->dout;
   LevelStatus *hs = static_cast<LevelStatus *>(ws->hstat);
   if (!ws->borrowed)

@@ -174,8 +174,9 @@ __global__ void k_nn_fill(const int64_t *start, const int32_t *cnt, const uint64
 // What the arrangement needs of a neighbour, in arrays that stay in the L2: a
 // byte per vertex with its degree bucket, plus one for delegates (degrees
 // above TH: delegate iff code > bucket(TH), bucket = code minus that one), and
-// the delegates' rank directory for their IDs. The degree and delegate ID arrays would be a line from beyond the L2 per entry
-// (16 MB each at 4M vertices): 3.3 ms for the dd keys of RMAT 22 alone.
+// the delegates' rank directory for their IDs. The degree and delegate ID
+// arrays would be a line from beyond the L2 per entry (16 MB each at 4M
+// vertices): 3.3 ms for the dd keys of RMAT 22 alone.
 __global__ void k_codes(const int32_t *deg, const int32_t *did, int32_t n, int32_t th,
                         uint8_t *code, RankDir *rank) {
   const int64_t stride = int64_t(gridDim.x) * blockDim.x;

@@ -149,8 +149,8 @@ int64_t rmat_pack_keys(const dsbfs_rmat_spec *sp, int B, uint64_t *keys, unsigne
   const RmatArgs a = rmat_args(sp);
   if (a.g == 0) return 0;
   HIPCHK(hipMemsetAsync(cursor, 0, sizeof(unsigned long long), s));
-  hipLaunchKernelGGL(k_rmat_keys, dim3(grid_for(a.g, 256 * kGenItems, 65536)), dim3(256), 0, s, a, B, keys,
-                     cursor);
+  hipLaunchKernelGGL(k_rmat_keys, dim3(grid_for(a.g, 256 * kGenItems, 65536)), dim3(256), 0, s, a,
+                     B, keys, cursor);
   HIPCHK(hipGetLastError());
   return 2 * int64_t(d2h_scalar(reinterpret_cast<const uint64_t *>(cursor), s));
 }
