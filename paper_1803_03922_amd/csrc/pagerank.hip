@@ -15,11 +15,12 @@
 // row), and the pull over delegate rows (dd part from the delegate array, dn
 // part from the normal array; a wave per row, a block per long row). Each pull
 // also writes its vertex's contribution to the next step (a row's length is
-// its degree), into the other of two arrays, so no kernel reads the ranks back; the ranks themselves are written by the last two steps only
-// (the last one's L1 change needs the one before), or by every step when a
-// tolerance asks for the change of each. Row sums run in a fixed order; the
-// dangling mass and the L1 change are summed with atomics, whose order can
-// move the last bits between runs.
+// its degree), into the other of two arrays, so no kernel reads the ranks back;
+// the ranks themselves are written by the last two steps only (the last one's
+// L1 change needs the one before), or by every step when a tolerance asks for
+// the change of each. Row sums run in a fixed order; the dangling mass and the
+// L1 change are summed with atomics, whose order can move the last bits between
+// runs.
 //
 // The dd part is 90% of the edges at RMAT 26, and on scale-free graphs most
 // of its gathers land on the few highest-degree delegates, which delegate IDs
