@@ -23,6 +23,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cstdio>
+#include <exception>
 #include <fstream>
 #include <map>
 #include <sstream>
@@ -909,6 +910,16 @@ void msbfs_release(Workspace *ws) {
   ws->ms_state = nullptr;
 }
 
+// A call that fails leaves what it has set up (hub list, columns with hub slots) to
+// a next one, which may come on another stream: complete.
+struct DrainOnFailure {
+  hipStream_t s;
+  const int before = std::uncaught_exceptions();
+  ~DrainOnFailure() {
+    if (std::uncaught_exceptions() > before) (void)hipStreamSynchronize(s);
+  }
+};
+
 // The vertices whose rows a whole wave scans in bottom-up levels (once per
 // workspace), by degree bucket, highest first, ties by ID. That is the order of
 // the entries of every plain row too: the hub frontier sets a row reads lie in
@@ -937,9 +948,6 @@ static void hub_list(const Graph *g, MsState *st, hipStream_t s) {
                                                  40, tmp.p, s);
     hipLaunchKernelGGL(k_hub_list, G, B, 0, s, sorted, nh, st->hubs.as<int32_t>());
     HIPCHK(hipGetLastError());
-    // a call that fails after this one's list leaves it to a next one, which may
-    // come on another stream
-    HIPCHK(hipStreamSynchronize(s));
   }
   st->nhubs = nh;
 }
@@ -957,6 +965,10 @@ static void msbfs_launch(const Graph *g, Workspace *ws, const int32_t *sources, 
   if (!ws->ms_state) ws->ms_state = new MsState();
   MsState *st = reinterpret_cast<MsState *>(ws->ms_state);
   const Alloc *al = &g->al;
+  // before the units are taken below (what this call queues itself is short, and a
+  // first call's part of it runs beside the host's)
+  stream_drain(s);
+  const DrainOnFailure drain{s};
   if (!st->ctl.p) st->ctl.alloc(al, sizeof(MsCtl), s);
   hub_list(g, st, s);
   // hub frontier cache: the remapped columns once per graph (while hub slot
@@ -990,8 +1002,6 @@ static void msbfs_launch(const Graph *g, Workspace *ws, const int32_t *sources, 
     }
     st->graphs.clear();
   }
-  // before the units are taken below (the copies that follow are short)
-  stream_drain(s);
   HIPCHK(hipMemcpyAsync(st->srcs.p, sources, size_t(k) * 4, hipMemcpyHostToDevice, s));
   const void *kern = ms_kernel(words);
   int occ = 0;
@@ -1516,6 +1526,7 @@ void ms_level_prepare(const Graph *g, Workspace *ws, hipStream_t s) {
   if (!ws->ms_state) ws->ms_state = new MsState();
   MsState *st = reinterpret_cast<MsState *>(ws->ms_state);
   const Alloc *al = &g->al;
+  const DrainOnFailure drain{s};
   hub_list(g, st, s);
   const int64_t n = g->n;
   if (!st->lvring.p) st->lvring.alloc(al, size_t(kRing) * size_t(n) * 8, s);
