@@ -324,7 +324,8 @@ dsbfs_status dsbfs_workspace_destroy(dsbfs_workspace *ws);
  * Section IV: per level, previsit of the normal queue and of the delegate
  * frontier mask, the direction decision of Section IV-B for dd, dn and nd
  * (nn always forward), then the visits. opts NULL = defaults. stats may be
- * NULL; when given, the call synchronizes the stream and fills it.
+ * NULL. The call returns once the search has completed on `stream`; searches on
+ * different workspaces may run at once, from different threads and streams.
  * Errors: INVALID_ARG (source outside [0, n), null depth, mode 0 without a
  * plain CSR, parent NULL while want_parent), HIP, DEVICE.
  */
@@ -396,7 +397,11 @@ typedef struct dsbfs_ms_opts {
  * device int32[k][n] array: row i gets the hop distances from sources[i]
  * (-1 unreachable), exactly as k single-source searches would. Uses the plain
  * CSR (graph built with keep_plain_csr = 1). opts NULL = tuned/cached
- * defaults. Errors: INVALID_ARG, HIP, DEVICE (persistent-grid barrier failure).
+ * defaults. The call returns once its launch has completed on `stream`. The
+ * launch needs every compute unit: calls on one device run one after the other,
+ * in order of arrival, and each waits for searches that hold compute units when
+ * it comes (later ones do without until it has run).
+ * Errors: INVALID_ARG, HIP, DEVICE (persistent-grid barrier failure).
  */
 dsbfs_status dsbfs_msbfs(const dsbfs_graph *g, dsbfs_workspace *ws, const int32_t *sources,
                          int32_t k, const dsbfs_ms_opts *opts, int32_t *depth, void *stream);
