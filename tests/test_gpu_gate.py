@@ -17,6 +17,7 @@ class _Setup:
     def __init__(self, inputs_mod, oracle_mod, scale=18, k=6):
         self.d = lib()
         self.torch = torch_cuda()
+        self.probe = self.torch.zeros(1, device="cuda")
         self.n = 1 << scale
         src, dst = inputs_mod.rmat_edges(scale)
         self.g = self.d.Graph(src, dst, self.n, threshold=32)
@@ -118,6 +119,27 @@ def _sleep(T, stream, seconds):
     return ended
 
 
+def _beside(T, ended):
+    """A stream whose kernels run beside the one that `ended` comes after. (The
+    runtime has four hardware queues, and streams that share one wait for each
+    other, which no library call on them can change.)"""
+    torch = T.torch
+    for _ in range(8):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            T.probe.add_(1)
+            done = torch.cuda.Event()
+            done.record()
+        until = time.monotonic() + 0.05
+        while time.monotonic() < until and not done.query():
+            time.sleep(0.001)
+        if done.query():
+            assert not ended.query()
+            return stream
+        log("a stream shares the long kernel's hardware queue")
+    pytest.fail("no stream runs beside the long kernel")
+
+
 def test_batch_beside_another_streams_kernel(inputs_mod, oracle_mod):
     """A batch of one word starts while another stream's kernel of a single wave
     runs: its blocks leave that wave's compute unit room."""
@@ -125,10 +147,12 @@ def test_batch_beside_another_streams_kernel(inputs_mod, oracle_mod):
     torch = T.torch
     ws = T.d.Workspace(T.g, max_lanes=64)
     rows = torch.empty((len(T.sources), T.n), dtype=torch.int32, device="cuda")
-    one, two = torch.cuda.Stream(), torch.cuda.Stream()
-    T.batch(ws, rows, two)  # what only a first call does
-    ended = _sleep(T, one, 0.5)
+    one = torch.cuda.Stream()
+    T.batch(ws, rows, one)  # what only a first call does
     rows.fill_(7)
+    torch.cuda.synchronize()
+    ended = _sleep(T, one, 0.7)
+    two = _beside(T, ended)
     t0 = time.monotonic()
     T.batch(ws, rows, two)
     took = time.monotonic() - t0
@@ -149,13 +173,14 @@ def test_no_wait_for_earlier_work_of_another_stream(inputs_mod, oracle_mod, queu
     depth = torch.empty(T.n, dtype=torch.int32, device="cuda")
     rows, rows_c = (torch.empty((len(T.sources), T.n), dtype=torch.int32, device="cuda")
                     for _ in range(2))
-    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    one = torch.cuda.Stream()
     T.search(ws, depth, one, T.sources[0])  # what only first calls do
     T.batch(wc, rows_c, one)
-    T.batch(wb, rows, two)
+    T.batch(wb, rows, one)
     rows.fill_(7)
     torch.cuda.synchronize()
-    ended = _sleep(T, one, 0.7)
+    ended = _sleep(T, one, 0.9)
+    two = _beside(T, ended)
     errors = []
 
     def behind():

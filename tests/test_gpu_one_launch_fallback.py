@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 from gpu_helpers import lib, log, torch_cuda
-from test_gpu_gate import _sleep
+from test_gpu_gate import _beside, _sleep
 
 pytestmark = pytest.mark.gpu
 
@@ -81,22 +81,26 @@ def test_search_beside_another_streams_kernel(oracle_mod):
     g = d.Graph(src, dst, n, threshold=32, keep_plain_csr=False)
     ws = d.Workspace(g)
     depth = torch.empty(n, dtype=torch.int32, device="cuda")
-    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    one = torch.cuda.Stream()
     o = d.run_opts(want_parent=False)
-    d.bfs(g, ws, 5, depth, None, opts=o, stream=two.cuda_stream)
+    d.bfs(g, ws, 5, depth, None, opts=o, stream=one.cuda_stream)
 
     class T:
         pass
-    T.torch = torch
-    ended = _sleep(T, one, 1.2)
+    T.torch, T.probe = torch, torch.zeros(1, device="cuda")
+    torch.cuda.synchronize()
+    ended = _sleep(T, one, 1.5)
+    two = _beside(T, ended)
     times = []
     for _ in range(4):
-        depth.fill_(7)
-        torch.cuda.current_stream().synchronize()
+        with torch.cuda.stream(two):
+            depth.fill_(7)
+        two.synchronize()
         t0 = time.monotonic()
         d.bfs(g, ws, 5, depth, None, opts=o, stream=two.cuda_stream)
         times.append(round((time.monotonic() - t0) * 1e3, 2))
-        got = depth.cpu().numpy()
+        with torch.cuda.stream(two):
+            got = depth.cpu().numpy()
         np.testing.assert_array_equal(got, want)
     asleep = not ended.query()
     log(f"searches beside another stream's kernel: {times} ms")
