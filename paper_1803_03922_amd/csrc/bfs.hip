@@ -2684,12 +2684,13 @@ void bfs_run(const Graph *g, Workspace *ws, int32_t source, const dsbfs_run_opts
 // address, only the device address hipGetSymbolAddress returns for the
 // current device.
 // What grows with the graph has kScratchBytes; the control block and the status
-// ring, of fixed size, lie behind it.
+// ring, of fixed size, lie before it (behind it, 64 MB from all else that a search
+// reads, they cost it 2 us).
 constexpr size_t kScratchBytes = size_t(64) << 20;
 constexpr size_t round256(size_t b) { return ((b < 256 ? 256 : b) + 255) / 256 * 256; }
 constexpr size_t kFixedBytes =
     round256(sizeof(SearchCtl)) + round256(kStatusSlots * sizeof(LevelStatus));
-static __device__ __align__(256) unsigned char scratch[kScratchBytes + kFixedBytes];
+static __device__ __align__(256) unsigned char scratch[kFixedBytes + kScratchBytes];
 
 namespace {
 
@@ -2752,7 +2753,7 @@ void bfs_run_noalloc(const Graph *g, int32_t source, const dsbfs_run_opts *opts,
     sl.ptr = ptr;
   }
   char *base = static_cast<char *>(sl.ptr);
-  size_t off = kScratchBytes;  // the fixed parts first, then the others from 0
+  size_t off = 0;
   auto carve = [&](DevBuf &b, size_t bytes) {
     b.p = base + off;
     b.bytes = round256(bytes);
@@ -2767,7 +2768,6 @@ void bfs_run_noalloc(const Graph *g, int32_t source, const dsbfs_run_opts *opts,
   carve(ws.ctl, sizeof(SearchCtl));
   DevBuf ring;
   carve(ring, kStatusSlots * sizeof(LevelStatus));
-  off = 0;
   carve(ws.Vn, size_t(g->nwords()) * 4);
   carve(ws.Fn, size_t(g->nwords()) * 4);
   carve(ws.Vd, size_t(g->dwords()) * 4);
@@ -2780,7 +2780,7 @@ void bfs_run_noalloc(const Graph *g, int32_t source, const dsbfs_run_opts *opts,
   carve(ws.dscan, size_t(nm + 1) * 8);
   carve(ws.c0, size_t(g->st.n_ndsrc) * 4);
   carve(ws.c1, size_t(g->st.n_ndsrc) * 4);
-  if (off > kScratchBytes)
+  if (off > kFixedBytes + kScratchBytes)
     fail(DSBFS_ERR_RANGE, "allocation-free search scratch exceeded");
   ws.hstat = ring.p;
   ws.back = sl.back;
