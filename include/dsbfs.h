@@ -400,7 +400,8 @@ typedef struct dsbfs_ms_opts {
  * defaults. The call returns once its launch has completed on `stream`. The
  * launch needs every compute unit: calls on one device run one after the other,
  * in order of arrival, and each waits for searches that hold compute units when
- * it comes (later ones do without until it has run).
+ * it comes, at most some 250 levels of each (later ones do without until it has
+ * run).
  * Errors: INVALID_ARG, HIP, DEVICE (persistent-grid barrier failure).
  */
 dsbfs_status dsbfs_msbfs(const dsbfs_graph *g, dsbfs_workspace *ws, const int32_t *sources,

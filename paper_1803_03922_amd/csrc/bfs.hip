@@ -36,6 +36,7 @@
 #include <cmath>
 #include <condition_variable>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <string>
 
@@ -140,6 +141,8 @@ struct SearchCtl {
   int32_t seg_cnt[kSegs];   // its entries
   int32_t levels;           // one launch: levels with a non-empty frontier
   int32_t pad;
+  int64_t left;             // where a further launch goes on from (with st[0]):
+                            // normals in no frontier so far
 };
 
 // Arguments of every kernel of a search.
@@ -181,12 +184,15 @@ struct Search {
   int32_t count;  // statistics are wanted: keep work units and every workload sum
   int32_t source, mode;
   long long bar_ticks;  // bound of a wait of the grid barrier
+  // one launch: its first level (a multiple of 6: levels are counted from 0 in each
+  // launch, and buffers alternate by level parity and level % 3)
+  int32_t level0;
 
   __device__ __forceinline__ uint32_t *fn(int p) const { return p ? Fn1 : Fn0; }
   __device__ __forceinline__ int32_t *q(int p) const { return p ? Q1 : Q0; }
   __device__ __forceinline__ int32_t *cand(int p) const { return p ? C1 : C0; }
   __device__ __forceinline__ void put(int32_t v, int32_t p, int32_t dep) const {
-    depth[v] = dep;
+    depth[v] = dep + level0;
     if (parent) parent[v] = p;
   }
   // a delegate claimed
@@ -950,7 +956,7 @@ __device__ __forceinline__ void scatter_step(const Search &a, const WaveRows &R,
     // (the lanes past the end repeat the last edge)
     if ((wd[u] >> (v[u] & 31)) & 1u) continue;
     if (a.parent) a.parent[v[u]] = R.aux[o[u]];
-    else a.depth[v[u]] = dep;
+    else a.depth[v[u]] = dep + a.level0;
   }
 }
 
@@ -1011,7 +1017,7 @@ template <int NW> __device__ void settle(const Search &a, Scratch<NW> &S, int L)
         const unsigned long long m = __ballot(won);
         const uint32_t half = uint32_t(l < 32 ? m : m >> 32);
         if ((l & 31) == 0 && half) a.Vn[v >> 5] = vis[u] | half;
-        if (won && a.parent) a.depth[v] = L + 1;
+        if (won && a.parent) a.depth[v] = L + 1 + a.level0;
         if (l == int(g0 + u - gb - r0)) mine = m;
       }
     }
@@ -1944,15 +1950,24 @@ __global__ void __launch_bounds__(kBS, 8) k_plain_expand(Search a, int L) {
 constexpr int kWideNW = 16;
 constexpr double kHeavyEdges = 1 << 18;
 
-// How block 0 left: 1 done, -1 a barrier wait exceeded its bound.
-__device__ __forceinline__ void one_launch_end(const Search &a, int levels, bool ok) {
+// A launch ends after this many levels, and the host launches the next: between
+// them a batch that waits for compute units gets them. A path of 30000 vertices
+// kept one waiting for a quarter of a second. Most graphs have fewer levels; a
+// launch more is some 15 us after 2 ms.
+constexpr int kLaunchLevels = 252;
+static_assert(kLaunchLevels % 6 == 0, "see Search::level0");
+
+// How block 0 left: kDone, kGaveUp where a barrier wait exceeded its bound, kGoOn
+// with levels left.
+enum { kDone = 1, kGoOn = 2, kGaveUp = -1 };
+__device__ __forceinline__ void one_launch_end(const Search &a, int how, int levels) {
   if (blockIdx.x != 0) return;
   __syncthreads();
   if (threadIdx.x == 0) {
     a.ctl->levels = levels;
     a.hs->level = levels;
     __threadfence_system();
-    __hip_atomic_store(&a.hs->seq, ok ? 1 : -1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&a.hs->seq, how, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -1972,14 +1987,15 @@ __device__ __forceinline__ bool heavy_level(const Search &a, int64_t qn, int64_t
 template <bool HEAVY> __global__ void __launch_bounds__(1024) k_search(Search a) {
   __shared__ Scratch<kWideNW> S;
   GridBar &bar = a.ctl->bar;
-  unsigned long long ep = 0;
   grid_start(bar);
   if (threadIdx.x == 0) S.st = a.ctl->st[0];
   units_open(a, S);
+  unsigned long long ep = 0;
   int L = 0;
   bool ok = true;
-  int64_t left = a.n - a.d;  // normals in no frontier so far
-  for (;; ++L) {
+  // normals in no frontier so far
+  int64_t left = HEAVY && a.level0 > 0 ? a.ctl->left : int64_t(a.n) - a.d;
+  for (; L < kLaunchLevels; ++L) {
     level_open(a, S, L);
     left -= S.qn;
     const bool heavy = HEAVY && heavy_level(a, S.qn, left);
@@ -2012,18 +2028,23 @@ template <bool HEAVY> __global__ void __launch_bounds__(1024) k_search(Search a)
     __syncthreads();
   }
   units_close(a, S);
-  one_launch_end(a, L, ok);
+  const bool more = ok && L == kLaunchLevels;
+  if (more && blockIdx.x == 0 && threadIdx.x == 0) {
+    a.ctl->st[0] = S.st;
+    a.ctl->left = left;
+  }
+  one_launch_end(a, more ? kGoOn : ok ? kDone : kGaveUp, a.level0 + L);
 }
 
 __global__ void __launch_bounds__(1024) k_plain_search(Search a) {
   __shared__ Scratch<kWideNW> S;
   GridBar &bar = a.ctl->bar;
-  unsigned long long ep = 0;
   grid_start(bar);
+  unsigned long long ep = 0;
   units_open(a, S);
   int L = 0;
   bool ok = true;
-  for (;; ++L) {
+  for (; L < kLaunchLevels; ++L) {
     if (!plain_open(a, S, L)) break;
     ctr_clear(a.ctl->ctr[(L + 1) % 3]);
     if (a.count && blockIdx.x == 0 && threadIdx.x == 0) {
@@ -2037,7 +2058,13 @@ __global__ void __launch_bounds__(1024) k_plain_search(Search a) {
     if (!(ok = grid_sync(bar, ++ep, &S.ok, a.bar_ticks))) break;
   }
   units_close(a, S);
-  one_launch_end(a, L, ok);
+  one_launch_end(a, !ok ? kGaveUp : L == kLaunchLevels ? kGoOn : kDone, a.level0 + L);
+}
+
+// Before a launch that goes on: the barrier as at the first one's start.
+__global__ void k_clear_bar(GridBar *bar) {
+  uint32_t *const w = reinterpret_cast<uint32_t *>(bar);
+  for (int i = threadIdx.x; i < int(sizeof(GridBar) / 4); i += blockDim.x) w[i] = 0;
 }
 
 // Number of resident waves worth of blocks for grid-stride kernels.
@@ -2259,6 +2286,12 @@ ResidentLease::ResidentLease(int blocks, bool wait) {
   g.used += want;
   units = want;
   gate = &g;
+}
+
+bool ResidentLease::wanted() const {
+  ResidentGate &g = *static_cast<ResidentGate *>(gate);
+  std::lock_guard<std::mutex> lk(g.mu);
+  return g.serving != g.next;
 }
 
 ResidentLease::~ResidentLease() {
@@ -2532,8 +2565,8 @@ void run_levels(const Graph *g, Workspace *ws, Search a, const dsbfs_run_opts &o
   HIPCHK(hipStreamSynchronize(s));
 }
 
-// The whole search in one launch; false if its grid could not run (its
-// workspace is then to be initialized again). After a launch that gave up on a
+// The whole search in one launch (deep ones in several, see kLaunchLevels); false
+// if a grid could not run (its workspace is then to be initialized again). After a launch that gave up on a
 // wait, the workspace's next searches go level by level without trying, 16 at
 // first and four times as many after every further one in a row: what the wait
 // cost is spread over them while whatever holds the compute units stays.
@@ -2545,25 +2578,35 @@ bool run_one_launch(const Graph *g, Workspace *ws, Search a, const OneLaunch &sh
     return false;
   }
   stream_drain(s);
-  ResidentLease lease(shape.blocks, false);
-  if (!lease.units) return false;
+  auto lease = std::make_unique<ResidentLease>(shape.blocks, false);
+  if (!lease->units) return false;
   LevelStatus *hs = static_cast<LevelStatus *>(ws->hstat);
-  if (!ws->borrowed) hs->seq = 0;
   launch_init(a, first_state(g), s);
-  if (a.mode == 1 && heavy_graph(a))
-    hipLaunchKernelGGL(k_search<true>, dim3(shape.blocks), dim3(shape.threads), 0, s, a);
-  else if (a.mode == 1)
-    hipLaunchKernelGGL(k_search<false>, dim3(shape.blocks), dim3(shape.threads), 0, s, a);
-  else
-    hipLaunchKernelGGL(k_plain_search, dim3(shape.blocks), dim3(shape.threads), 0, s, a);
-  HIPCHK(hipGetLastError());
   LevelStatus st;
-  if (ws->borrowed)
-    HIPCHK(hipMemcpyAsync(&st, hs, sizeof(LevelStatus), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
-  if (!ws->borrowed) st = *hs;
+  for (;;) {
+    if (!ws->borrowed) hs->seq = 0;
+    if (a.mode == 1 && heavy_graph(a))
+      hipLaunchKernelGGL(k_search<true>, dim3(shape.blocks), dim3(shape.threads), 0, s, a);
+    else if (a.mode == 1)
+      hipLaunchKernelGGL(k_search<false>, dim3(shape.blocks), dim3(shape.threads), 0, s, a);
+    else
+      hipLaunchKernelGGL(k_plain_search, dim3(shape.blocks), dim3(shape.threads), 0, s, a);
+    HIPCHK(hipGetLastError());
+    if (ws->borrowed)
+      HIPCHK(hipMemcpyAsync(&st, hs, sizeof(LevelStatus), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    if (!ws->borrowed) st = *hs;
+    if (st.seq != kGoOn) break;
+    a.level0 = st.level;
+    hipLaunchKernelGGL(k_clear_bar, dim3(1), dim3(kBS), 0, s, &a.ctl->bar);
+    if (lease->wanted()) {
+      // behind those that wait now
+      lease.reset();
+      lease = std::make_unique<ResidentLease>(shape.blocks, true);
+    }
+  }
   *levels = st.level;
-  if (st.seq == 1) {
+  if (st.seq == kDone) {
     back = Backoff{};
     return true;
   }

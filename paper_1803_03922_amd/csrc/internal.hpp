@@ -183,6 +183,7 @@ struct ResidentLease {
   void *gate = nullptr;
   ResidentLease(int blocks, bool wait);
   ~ResidentLease();
+  bool wanted() const;  // others wait for units
   ResidentLease(const ResidentLease &) = delete;
   ResidentLease &operator=(const ResidentLease &) = delete;
 };

@@ -25,6 +25,7 @@ struct ResidentLease {
   void *gate = nullptr;
   ResidentLease(int blocks, bool wait);
   ~ResidentLease();
+  bool wanted() const;
 };
 #include "gate.inc"
 
@@ -44,6 +45,7 @@ int main() {
     a.reset();
     L b = take(u / 2, false), c = take(u - u / 2, false);
     CHECK(b->units && c->units && take(1, false)->units == 0);
+    CHECK(!b->wanted() && !c->wanted());
     // two that wait (several blocks a unit): served in order, and none that does
     // not wait goes before them, though units are free meanwhile
     std::vector<int> order;
@@ -60,6 +62,7 @@ int main() {
       while (waiting <= i) std::this_thread::yield();
       std::this_thread::sleep_for(std::chrono::milliseconds(50));
     }
+    CHECK(b->wanted() && c->wanted());
     c.reset();
     CHECK(take(1, false)->units == 0);
     b.reset();
